@@ -190,6 +190,14 @@ struct EpiSiluMul {
 // rotary embedding on q and k heads (pairs (c, c + dh/2)), q -> [M][nq], k/v -> caches.
 // row_sp[row] = (sequence, absolute position) of the row, position -1 if its sequence does not fit the
 // cache (written by k_row_positions before the GEMM).
+// own * cos -+ partner * sin (lower / upper half of the head), with the fused operation spelled out: left to the
+// compiler's choice it differs between the two epilogues below, and with it the last bit of a row's q and K between
+// the tiles that a call's row count selects.
+__device__ __forceinline__ float rotated(float own, float partner, float2 cs, bool lo)
+{
+    const float y = partner * cs.y;
+    return __builtin_fmaf(own, cs.x, lo ? -y : y);
+}
 template <int TN> struct AuxRope { float2 t0[TN], t1[TN]; int2 sp0, sp1; };
 
 template <int DHT>                                      // head size: 64 or 128
@@ -248,8 +256,8 @@ struct EpiQkvRope {
                 const bool lo = ((32 * j) & (dh - 1)) < half;                 // the same for every c < 32
                 const int jp = lo ? j + half / 32 : j - half / 32;            // tile of the partner column
                 const float y0 = v0[jp], y1 = v1[jp];
-                o0 = lo ? (o0 * x.t0[j].x - y0 * x.t0[j].y) : (o0 * x.t0[j].x + y0 * x.t0[j].y);
-                o1 = lo ? (o1 * x.t1[j].x - y1 * x.t1[j].y) : (o1 * x.t1[j].x + y1 * x.t1[j].y);
+                o0 = rotated(o0, y0, x.t0[j], lo);
+                o1 = rotated(o1, y1, x.t1[j], lo);
             }
             const int hj = (32 * j) / dh;                // head inside the tile of column 32*j + c
             const int64_t off = (seg == 0) ? 32 * j : (int64_t)hj * hstep + 32 * j;
@@ -361,8 +369,8 @@ struct EpiQkvRopeTile {
                         const int dd = (cj0 & (half - 1)) / 32;
                         const float y0 = acc[i][jp][r], y1 = acc[i][jp][r + 1];
                         const float2 a0 = cs[n % 3][e][dd], a1 = cs[n % 3][e + 1][dd];
-                        o0 = lo ? (o0 * a0.x - y0 * a0.y) : (o0 * a0.x + y0 * a0.y);
-                        o1 = lo ? (o1 * a1.x - y1 * a1.y) : (o1 * a1.x + y1 * a1.y);
+                        o0 = rotated(o0, y0, a0, lo);
+                        o1 = rotated(o1, y1, a1, lo);
                     }
                     // the neighbour's values of both rows (lanes c ^ 1); even columns store (own, neighbour's) of the
                     // first row, odd columns (neighbour's, own) of the second
@@ -818,6 +826,120 @@ k_gemm_mfma(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t M, int
 }
 
 // ------------------------------------------------------------------------------------------------
+// The same product with smaller tiles, for row counts whose 256 x 256 tiles would leave CUs idle. ST LDS stages filled
+// by LDS-direct loads. AHEAD (one workgroup per CU): the fragments of slice kt + 1 are read while slice kt is multiplied
+// and ST slices are in flight, so a step is bound by the CU's load path (about 85 GB/s whatever the tile: 0.19 us per
+// slice of a 64 x 64 tile, 0.39 us of 128 x 128). Without AHEAD two workgroups share a CU (two stages of a 128 x 128
+// tile each) and hide each other's barriers and LDS reads. Every output is the chain of 32x32x16 MFMAs over k that
+// k_gemm_mfma runs, so the tile does not show in the results (bit for bit).
+// ------------------------------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, int ST, class Epi>
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
+k_gemm_tile(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t m_first, int64_t M, int Nv, int K, int tiles_m,
+            int tiles_n, Epi epi)
+{
+    constexpr int NWN = BN / WN, NT = (BM / WM) * NWN * 64;
+    constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int RPP = NT / 8, AP = BM / RPP, BP = BN / RPP;      // rows per pass of the workgroup's loads, passes
+    constexpr uint32_t SB = (BM + BN) * 128;                       // bytes of a stage
+    static_assert(BM % RPP == 0 && BN % RPP == 0 && RPP % 16 == 0, "tile / thread mismatch");
+    static_assert(ST >= 2 && (AP + BP) * (ST - 1) < 64, "vmcnt counts the loads in flight");
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / NWN, wn = wave - wm * NWN;
+    // XCD-aware tile mapping as in k_gemm_mfma
+    const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) / 8;
+    const int lin = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (lin >= n_tiles) return;
+    const int group_sz = GROUP_M * tiles_n, grp = lin / group_sz, in_grp = lin - grp * group_sz;
+    const int rows_here = (tiles_m - grp * GROUP_M) < GROUP_M ? (tiles_m - grp * GROUP_M) : GROUP_M;
+    const int64_t m0 = m_first + (int64_t)(grp * GROUP_M + in_grp % rows_here) * BM;
+    const int n0 = (in_grp / rows_here) * BN;
+
+    const int chunk = tid & 7, rip = tid >> 3;
+    const uint32_t sw = (uint32_t)((chunk ^ SOL_SWZ(rip)) * 8);
+    const bf16_t *a_base = A + m0 * lda;
+    uint32_t a_off[AP];
+#pragma unroll
+    for (int p = 0; p < AP; ++p) {
+        int64_t rl = p * RPP + rip;
+        if (m0 + rl >= M) rl = M - 1 - m0;                 // ragged last tile: re-read the last row, never stored
+        a_off[p] = ((uint32_t)(rl * lda) + sw) * 2u;
+    }
+    const bf16_t *b_base[BP];
+#pragma unroll
+    for (int p = 0; p < BP; ++p) b_base[p] = bmap.row(n0 + p * RPP + wave * 8);   // a wave's 8 rows lie in one weight matrix
+    const uint32_t b_off = ((uint32_t)(rip & 7) * (uint32_t)bmap.ld + sw) * 2u;
+
+    const int KT = K / BK;                                 // even (K is a multiple of 128)
+    auto request = [&](int kt, uint32_t stage) {
+        const int koff = (kt < KT ? kt : KT - 1) * BK;     // past the end: the last slice again, never multiplied
+#pragma unroll
+        for (int p = 0; p < AP; ++p) dtl16(a_base + koff, a_off[p], stage + (uint32_t)(p * RPP * 128 + wave * 1024));
+#pragma unroll
+        for (int p = 0; p < BP; ++p) dtl16(b_base[p] + koff, b_off, stage + (uint32_t)((BM + p * RPP) * 128 + wave * 1024));
+    };
+    const int frow = lane & 31, fk = lane >> 5, fsw = SOL_SWZ(frow);
+    const int a_frag = (wm * WM + frow) * 128, b_frag = (BM + wn * WN + frow) * 128;
+    auto fragments = [&](bf16x8_t (&fa)[4][TM], bf16x8_t (&fb)[4][TN], uint32_t stage) {
+        const unsigned char *const st = lds + stage;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const int coff = ((kk * 2 + fk) ^ fsw) << 4;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                fa[kk][i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(st + a_frag + i * 32 * 128 + coff));
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                fb[kk][j] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(st + b_frag + j * 32 * 128 + coff));
+        }
+    };
+    floatx16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    auto multiply = [&](const bf16x8_t (&fa)[4][TM], const bf16x8_t (&fb)[4][TN]) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fb[kk][j], acc[i][j], 0, 0, 0);
+    };
+    // All but the N youngest slices that this wave requested have landed and its fragment reads are over; so for all waves.
+#define SOL_TILE_SYNC(N) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"((AP + BP) * (N)) : "memory")
+#pragma unroll
+    for (int s = 0; s < ST; ++s) request(s, s * SB);
+    bf16x8_t fa0[4][TM], fb0[4][TN], fa1[4][TM], fb1[4][TN];
+    uint32_t cur = 0, nxt = SB;                            // the stages of slices kt and kt + 1
+    SOL_TILE_SYNC(ST - 1);
+    fragments(fa0, fb0, 0);
+    for (int kt = 0; kt < KT; kt += 2) {
+        SOL_TILE_SYNC(ST - 2);                             // slice kt + 1 is there, the stage of slice kt is read out
+        request(kt + ST, cur);
+        fragments(fa1, fb1, nxt);
+        multiply(fa0, fb0);
+        cur = nxt; nxt = nxt + SB == ST * SB ? 0 : nxt + SB;
+        SOL_TILE_SYNC(ST - 2);
+        request(kt + 1 + ST, cur);
+        fragments(fa0, fb0, nxt);
+        multiply(fa1, fb1);
+        cur = nxt; nxt = nxt + SB == ST * SB ? 0 : nxt + SB;
+    }
+#undef SOL_TILE_SYNC
+    vm_wait<0>();                                           // no LDS-direct load outlives its workgroup
+    const int64_t row_w = m0 + wm * WM + 4 * (lane >> 5);
+    if (m0 + BM <= M) gemm_epilogue<true, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
+    else gemm_epilogue<false, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
+}
+
+// ------------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------------
 // compute units of the current device (one persistent workgroup each), 0 if the query fails
@@ -876,7 +998,110 @@ static bool launch_mfma(const bf16_t *A, int64_t lda, const BMap &bmap, int64_t 
 // The q/k/v epilogue needs a whole head (up to 128 columns) inside one wave tile.
 constexpr int SOL_WN = 128;
 #define SOL_TILE 256, 256, 128, SOL_WN
-#define SOL_TILE_QKV 256, 256, 128, SOL_WN
+
+// How the rows of a product are dealt to tiles. Per round of one workgroup on every CU, a 256 x 256 tile per CU costs
+// 1; a grid of one smaller tile per CU at most costs, relative to that (K = 2048 .. 14336, 80 .. 2048 rows, the
+// projections of the 1B and 8B shapes; what a round takes hardly depends on how many CUs it fills):
+//   64 x 64: 0.23   128 x 64: 0.36   128 x 128: 0.5   128 x 256: 0.75
+// (down projection of the 1B shape, 256 x 256 -> rule: 333 rows 122 -> 28 us, 1024 rows 123 -> 43, 2048 rows 125 -> 69.)
+// So a call takes the smallest tile of which every CU gets at most one; with more rows than that, whole rounds of
+// 256 x 256 tiles first and the smaller tile for the rest where that ends sooner than a last round that is nearly
+// empty. The tile does not show in the results.
+struct GemmPlan {
+    int64_t big;                 // rows [0, big) in 256 x 256 tiles (all rows, or a multiple of 256)
+    int small;                   // the others: 0 = 64 x 64, 1 = 128 x 64, 2 = 128 x 128, 3 = 128 x 256
+};
+static double small_tile_cost(int64_t rows, int N, int cus, int &cfg)
+{
+    static const int bm[4] = {64, 128, 128, 128}, bn[4] = {64, 64, 128, 256};
+    static const double cost[4] = {0.23, 0.36, 0.5, 0.75};
+    for (cfg = 0; cfg < 4; ++cfg)
+        if ((rows + bm[cfg] - 1) / bm[cfg] * (N / bn[cfg]) <= cus) return cost[cfg];
+    return 1e9;
+}
+static GemmPlan plan_gemm(int64_t M, int N)
+{
+    const int cus = device_cus() > 0 ? device_cus() : 256;
+    const int64_t tn = N / 256, whole = M / 256;           // tile columns, whole tile rows
+    const double launch = 0.05;                            // one more kernel
+    GemmPlan best{M, 0};
+    double best_cost = (double)(((M + 255) / 256 * tn + cus - 1) / cus);
+    const int64_t rounds = whole * tn / cus;               // whole rounds of whole tiles
+    const int64_t cand[3] = {0, rounds > 0 ? rounds * cus / tn : 0, whole};
+    for (int64_t r : cand) {
+        if (r * 256 >= M) continue;
+        int cfg;
+        const double c = (double)((r * tn + cus - 1) / cus) + small_tile_cost(M - r * 256, N, cus, cfg) + (r > 0 ? launch : 0.0);
+        if (c < best_cost) { best_cost = c; best = GemmPlan{r * 256, cfg}; }
+    }
+    return best;
+}
+
+template <int BM, int BN, int WM, int WN, int ST, class Epi>
+static bool launch_tile(const bf16_t *A, int64_t lda, const BMap &bmap, int64_t m_first, int64_t M, int Nv, int K,
+                        const Epi &epi, hipStream_t st)
+{
+    constexpr size_t lds = (size_t)ST * (BM + BN) * 128;
+    auto kern = k_gemm_tile<BM, BN, WM, WN, ST, Epi>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess) return false;
+        attr_done = true;
+    }
+    const int tiles_m = (int)((M - m_first + BM - 1) / BM), tiles_n = Nv / BN, per_xcd = (tiles_m * tiles_n + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3((BM / WM) * (BN / WN) * 64), lds, st, A, lda, bmap, m_first, M, Nv, K,
+                       tiles_m, tiles_n, epi);
+    return true;
+}
+
+// Rows [m_first, M) in tiles of configuration cfg (GemmPlan::small). WN: columns an epilogue needs in one wave tile.
+template <int WN, class Epi>
+static bool launch_small(int cfg, const bf16_t *A, int64_t lda, const BMap &bmap, int64_t m_first, int64_t M, int Nv, int K,
+                         const Epi &epi, hipStream_t st)
+{
+    if (Nv % 256 || K % (2 * BK) || K < 2 * BK) return false;
+    if constexpr (WN == 128) {                               // a head of 128 in one wave tile: no 64-column tiles
+        if (cfg <= 1) return launch_tile<64, 128, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        if (cfg == 2) return launch_tile<128, 128, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        return launch_tile<128, 256, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+    } else {
+        if (cfg == 0) return launch_tile<64, 64, 32, WN, 4>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        if (cfg == 1) return launch_tile<128, 64, 32, WN, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        if (cfg == 2) return launch_tile<128, 128, 32, 64, 4>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        return launch_tile<128, 256, 64, 64, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+    }
+}
+
+template <int DHT>
+static bool launch_qkv_rope(const bf16_t *h, const BMap &bm, bf16_t *q, bf16_t *kc, bf16_t *vc, const float2 *rope,
+                            const int32_t *pos0, int n_seq, int T, int L_max, int crows, int Hq, int Hkv, int d, int *flags,
+                            int2 *row_sp, hipStream_t st)
+{
+    const int64_t M = (int64_t)n_seq * T;
+    const int N = (Hq + 2 * Hkv) * DHT;
+    const GemmPlan plan = plan_gemm(M, N);
+    // whole tiles of at most two sequences each: positions by arithmetic (the epilogue's 32-bit byte offsets span two
+    // cache slabs, 128 rows of q, and the cos / sin table); it runs unless k_row_positions has flagged a sequence, in
+    // which case the general kernel behind it does
+    const bool tiles = plan.big > 0 && plan.big % 256 == 0 && T >= 128 && (int64_t)(Hkv + 1) * crows * DHT * 2 < (1ll << 31) &&
+                       (int64_t)L_max * DHT * 4 < (1ll << 31);
+    const bool sure = pos0 == nullptr && T <= L_max;          // every sequence starts at 0 and fits: nothing to flag
+    int *gate = sure ? nullptr : flags;
+    if (!(tiles && sure && plan.big == M))                    // the rows' (sequence, position) table, and the flags
+        hipLaunchKernelGGL(k_row_positions, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, pos0, M, T, L_max, row_sp, flags);
+    if (tiles) {
+        EpiQkvRopeTile<DHT> te{q, kc, vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
+        if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, te, st)) return false;
+    }
+    if (plan.big > 0 && !(tiles && sure)) {
+        EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
+        if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, epi, st)) return false;
+    }
+    if (plan.big == M) return true;
+    EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, nullptr};
+    return launch_small<DHT>(plan.small, h, d, bm, plan.big, M, N, d, epi, st);
+}
 
 bool launch_gemm_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
                           const float2 *rope, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh,
@@ -884,80 +1109,74 @@ bool launch_gemm_qkv_rope(const void *h, const void *wq, const void *wk, const v
 {
     const int nq = Hq * dh, nkv = Hkv * dh;
     if ((dh != 64 && dh != 128) || nq % 256 || nkv % 256) return false;      // heads must not straddle wave tiles
-    const int crows = cache_rows > 0 ? cache_rows : L_max;                    // rows of a (sequence, KV head) in the caches
-    const int64_t M = (int64_t)n_seq * T;
-    if (M <= 0) return true;
+    if ((int64_t)n_seq * T <= 0) return true;
     if (d % (2 * BK) || d < 2 * BK) return false;
+    const int crows = cache_rows > 0 ? cache_rows : L_max;                    // rows of a (sequence, KV head) in the caches
     BMap bm{};
     bm.base[0] = (const bf16_t *)wq; bm.base[1] = (const bf16_t *)wk; bm.base[2] = (const bf16_t *)wv;
     bm.seg_end[0] = nq; bm.seg_end[1] = nq + nkv; bm.seg_end[2] = nq + 2 * nkv;
     bm.mode = 0; bm.half = 0; bm.ld = d;
-    int2 *row_sp = (int2 *)row_sp_ws;
-    // whole tiles of at most two sequences each: positions by arithmetic (the epilogue's 32-bit byte offsets span two
-    // cache slabs, 128 rows of q, and the cos / sin table); it runs unless k_row_positions has flagged a sequence, in
-    // which case the general kernel behind it does
-    const bool tiles = M % 256 == 0 && T >= 128 && (int64_t)(Hkv + 1) * crows * dh * 2 < (1ll << 31) &&
-                       (int64_t)L_max * dh * 4 < (1ll << 31);
-    const bool sure = pos0 == nullptr && T <= L_max;          // every sequence starts at 0 and fits: nothing to flag
-    int *gate = sure ? nullptr : flags;
-    if (!(tiles && sure))                                     // the rows' (sequence, position) table, and the flags
-        hipLaunchKernelGGL(k_row_positions, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, pos0, M, T, L_max, row_sp, flags);
-    if (dh == 64) {
-        if (tiles) {
-            EpiQkvRopeTile<64> te{(bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
-            if (!launch_mfma<SOL_TILE_QKV>((const bf16_t *)h, d, bm, M, nq + 2 * nkv, d, te, st)) return false;
-            if (sure) return true;
-        }
-        EpiQkvRope<64> epi{(bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
-        return launch_mfma<SOL_TILE_QKV>((const bf16_t *)h, d, bm, M, nq + 2 * nkv, d, epi, st);
-    }
-    if (tiles) {
-        EpiQkvRopeTile<128> te{(bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
-        if (!launch_mfma<SOL_TILE_QKV>((const bf16_t *)h, d, bm, M, nq + 2 * nkv, d, te, st)) return false;
-        if (sure) return true;
-    }
-    EpiQkvRope<128> epi{(bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
-    return launch_mfma<SOL_TILE_QKV>((const bf16_t *)h, d, bm, M, nq + 2 * nkv, d, epi, st);
+    auto *const go = dh == 64 ? launch_qkv_rope<64> : launch_qkv_rope<128>;
+    return go((const bf16_t *)h, bm, (bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, pos0, n_seq, T, L_max, crows, Hq, Hkv, d,
+              flags, (int2 *)row_sp_ws, st);
+}
+
+static BMap plain_map(const void *w, int N, int K)
+{
+    BMap bm{};
+    bm.base[0] = (const bf16_t *)w; bm.seg_end[0] = bm.seg_end[1] = bm.seg_end[2] = N; bm.mode = 0; bm.ld = K;
+    return bm;
+}
+
+// A product over plain weight rows: `big` of the plan with epilogue eb where that part is whole tiles, else e.
+template <class EpiBig, class Epi>
+static bool launch_planned(const void *a, const void *w, int64_t M, int N, int K, const EpiBig &eb, const Epi &e, hipStream_t st)
+{
+    if (M <= 0) return true;
+    if (N % 256 || K % (2 * BK) || K < 2 * BK) return false;
+    const BMap bm = plain_map(w, N, K);
+    const GemmPlan plan = plan_gemm(M, N);
+    if (plan.big > 0 && !(plan.big % 256 == 0 ? launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, plan.big, N, K, eb, st)
+                                              : launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, plan.big, N, K, e, st)))
+        return false;
+    return plan.big == M || launch_small<32>(plan.small, (const bf16_t *)a, K, bm, plan.big, M, N, K, e, st);
 }
 
 bool launch_gemm_resid_f32(const void *a, const void *w, const void *resid, float *out, int64_t M, int N, int K,
                            hipStream_t st)
 {
-    BMap bm{};
-    bm.base[0] = (const bf16_t *)w; bm.seg_end[0] = bm.seg_end[1] = bm.seg_end[2] = N; bm.mode = 0; bm.ld = K;
-    if (M % 256 == 0) {                                   // whole tiles
-        EpiResidF32Tile te{(const bf16_t *)resid, out, N};
-        return launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, M, N, K, te, st);
-    }
-    EpiResidF32 epi{(const bf16_t *)resid, out, N};
-    return launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, M, N, K, epi, st);
+    const EpiResidF32Tile te{(const bf16_t *)resid, out, N};
+    const EpiResidF32 epi{(const bf16_t *)resid, out, N};
+    return launch_planned(a, w, M, N, K, te, epi, st);
 }
 
 bool launch_gemm_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int64_t M, int dff, int d,
                              hipStream_t st)
 {
-    if (dff % (SOL_WN / 2)) return false;
+    const int N = 2 * dff;
+    if (M <= 0) return true;
+    if (dff % (SOL_WN / 2) || N % 256 || d % (2 * BK) || d < 2 * BK) return false;
     BMap bm{};
-    bm.base[0] = (const bf16_t *)wg; bm.base[1] = (const bf16_t *)wu; bm.mode = 1; bm.half = SOL_WN / 2; bm.ld = d;
-    EpiSiluMul epi{(bf16_t *)a, dff};
-    return launch_mfma<SOL_TILE>((const bf16_t *)h, d, bm, M, 2 * dff, d, epi, st);
+    bm.base[0] = (const bf16_t *)wg; bm.base[1] = (const bf16_t *)wu; bm.mode = 1; bm.ld = d;
+    const EpiSiluMul epi{(bf16_t *)a, dff};
+    const GemmPlan plan = plan_gemm(M, N);
+    bm.half = SOL_WN / 2;                                     // gate / up interleaved in halves of a wave tile's columns
+    if (plan.big > 0 && !launch_mfma<SOL_TILE>((const bf16_t *)h, d, bm, plan.big, N, d, epi, st)) return false;
+    bm.half = 32;
+    return plan.big == M || launch_small<64>(plan.small, (const bf16_t *)h, d, bm, plan.big, M, N, d, epi, st);
 }
 
 bool launch_gemm_resid_out(const void *a, const void *w, const float *x2, void *out, int64_t M, int N, int K,
                            hipStream_t st)
 {
-    BMap bm{};
-    bm.base[0] = (const bf16_t *)w; bm.seg_end[0] = bm.seg_end[1] = bm.seg_end[2] = N; bm.mode = 0; bm.ld = K;
-    EpiResidOut epi{x2, (bf16_t *)out, N};
-    return launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, M, N, K, epi, st);
+    const EpiResidOut epi{x2, (bf16_t *)out, N};
+    return launch_planned(a, w, M, N, K, epi, epi, st);
 }
 
 bool launch_gemm_f32(const void *a, const void *w, float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st)
 {
-    BMap bm{};
-    bm.base[0] = (const bf16_t *)w; bm.seg_end[0] = bm.seg_end[1] = bm.seg_end[2] = N; bm.mode = 0; bm.ld = K;
-    EpiStoreF32 epi{C, ldc};
-    return launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, M, N, K, epi, st);
+    const EpiStoreF32 epi{C, ldc};
+    return launch_planned(a, w, M, N, K, epi, epi, st);
 }
 
 
@@ -981,9 +1200,8 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
     hipLaunchKernelGGL(k_row_targets, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, targets, M, G, T,
                        broadcast_g ? 1 : 0, V, row_tgt, flags);
     if (Mp > M) launch_fill_i32((int32_t *)((bf16_t *)hf + M * K), 0, (Mp - M) * K / 2, st);   // K is even
-    BMap bt{};
-    bt.base[0] = (const bf16_t *)hf; bt.seg_end[0] = bt.seg_end[1] = bt.seg_end[2] = (int)Mp; bt.mode = 0; bt.ld = K;
-    EpiNllCols epc{part, Mp};
+    const BMap bt = plain_map(hf, (int)Mp, K);
+        EpiNllCols epc{part, Mp};
     if (!launch_mfma<SOL_TILE>((const bf16_t *)lm_head, K, bt, V, (int)Mp, K, epc, st)) return false;
     hipLaunchKernelGGL(k_target_logit, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const bf16_t *)hf,
                        (const bf16_t *)lm_head, row_tgt, M, K, tgt_logit);
