@@ -943,7 +943,7 @@ k_gemm_tile(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t m_firs
 // launchers
 // ------------------------------------------------------------------------------------------------
 // compute units of the current device (one persistent workgroup each), 0 if the query fails
-static int device_cus()
+int device_cus()
 {
     static int cus[64] = {};
     int dev = 0;

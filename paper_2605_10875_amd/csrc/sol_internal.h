@@ -85,6 +85,13 @@ void launch_test_quant(const float *z, int rows, int n, const int32_t *bits, int
 void launch_gemm_generic(const void *A, int a_dtype, int64_t lda, const void *W, int w_dtype, int64_t ldw,
                          float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st);
 
+// The same for fp32 operands and up to three stacked weight matrices [n][ldw] (unused ones: nullptr, 0) side by side in
+// C's columns, on the fp32 matrix instructions. False (nothing launched): K no multiple of 32, rows not 16-byte aligned.
+bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w0, int n0, const float *w1, int n1, const float *w2, int n2,
+                         int64_t ldw, float *C, int64_t ldc, int64_t M, int K, hipStream_t st);
+// compute units of the current device, 0 if the query fails
+int device_cus();
+
 // ---- bf16 MFMA GEMMs with fused epilogues (sol_gemm_mfma.hip) -----------------------------------
 // Each returns false (and launches nothing) if the shape is outside what the tile configuration
 // covers; the caller then takes the generic path for that stage.
