@@ -61,12 +61,13 @@ k_gemm_generic(const TA *__restrict__ A, int64_t lda, const TW *__restrict__ W, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 operands on v_mfma_f32_32x32x2_f32. The instruction is an fmaf chain over its two k in ascending order
-// (subnormals included), so with k walked in order every output is the fmaf chain of k_gemm_generic, bit for bit, at
-// twice the vector pipes' rate and without their LDS reads per product. Bound: the fp32 matrix rate (256 flops per
-// clock and CU): a slice of 32 k takes a 64 x 64 wave tile 4096 clocks against 48 KB of loads and LDS reads, so plain
-// double buffering hides everything else. 1018 rows x 3072 / 2048 / 16384 / 2048 columns of the 1B layer:
-// 4.53 ms with fmaf -> see the dispatch below.
+// fp32 operands on the fp32 matrix instructions. Both (32x32x2 and 16x16x4) are fmaf chains over their k in ascending
+// order (subnormals included), so with k walked in order every output is the fmaf chain of k_gemm_generic, bit for bit,
+// at twice the vector pipes' rate and without their LDS reads per product. Bound: the fp32 matrix rate (256 flops per
+// clock and CU) for large products, 125 TFLOP/s reached of 157; the chain over k for small ones: 64 clocks per 2 k in a
+// 32x32 tile, 32 clocks per 4 k in a 16x16 tile.
+// Times with k_gemm_generic -> here: 1018 x 16384 x 2048 2470 -> 549 us, 1018 x 2048 x 8192 1310 -> 326, 512 x 256 x 256
+// 30 -> 4.8, 512 x 256 x 1024 108 -> 12.
 // ------------------------------------------------------------------------------------------------
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
@@ -89,13 +90,17 @@ __device__ __forceinline__ void lds_load16(const float *src, uint32_t lds_addr)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr) : "memory", "m0");
 }
 
-template <int BM, int BN, int WM, int WN>
+// ST stages of 32 k. Two stages (a 128 x 128 tile): two workgroups share a CU and hide each other's barriers and LDS
+// reads, 549 us for the first shape above against 606 with three stages and one workgroup. READ_AHEAD (a lone 64 x 64
+// tile per CU): the fragments of the next four k are read before the current ones are multiplied, 54 against 61 us for
+// 100 x 2048 x 2048 (and 616 against 549 us in the 128 x 128 tile, where the second workgroup does it better).
+template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD>
 __global__ void __launch_bounds__(256, 2)
 k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, float *__restrict__ C, int64_t ldc, int64_t M, int N, int K,
                int tiles_m, int tiles_n)
 {
     static_assert((BM / WM) * (BN / WN) == 4, "four waves");
-    constexpr int NWN = BN / WN, TM = WM / 32, TN = WN / 32, AP = BM / 32, BP = BN / 32, ST = 3;
+    constexpr int NWN = BN / WN, TM = WM / 32, TN = WN / 32, AP = BM / 32, BP = BN / 32;
     constexpr uint32_t SB = (BM + BN) * 128;                 // a stage: rows of 32 floats, 16-byte chunks XOR-swizzled
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -140,29 +145,38 @@ k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, float *__rest
     const bool hi = lane >= 32;                              // lanes 0..31 supply the even k of a pair, 32..63 the odd one
     const int a_frag = (wm * WM + frow) * 128, b_frag = (BM + wn * WN + frow) * 128;
 
-    request(0, 0);
-    request(1, SB);
-    uint32_t cur = 0, fre = 2 * SB;
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s) request(s, s * SB);
+    uint32_t cur = 0, fre = (ST - 1) * SB;
     for (int kt = 0; kt < KT; ++kt) {
-        // slice kt has landed (the youngest slice may be in flight), the stage of slice kt - 1 is read out; for all waves
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(AP + BP) : "memory");
-        request(kt + 2, fre);
+        // slice kt has landed (the ST - 2 younger ones may be in flight), the stage of slice kt - 1 is read out; for all waves
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"((AP + BP) * (ST - 2)) : "memory");
+        request(kt + ST - 1, fre);
         const unsigned char *const st = lds + cur;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {                        // four k
+        f32x4v_t a[2][TM], b[2][TN];                         // fragments of four k
+        auto read = [&](int c, f32x4v_t (&x)[TM], f32x4v_t (&y)[TN]) {
             const int coff = (c ^ fsw) << 4;
-            f32x4v_t a[TM], b[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4v_t *>(st + a_frag + i * 4096 + coff);
+            for (int i = 0; i < TM; ++i) x[i] = *reinterpret_cast<const f32x4v_t *>(st + a_frag + i * 4096 + coff);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const f32x4v_t *>(st + b_frag + j * 4096 + coff);
+            for (int j = 0; j < TN; ++j) y[j] = *reinterpret_cast<const f32x4v_t *>(st + b_frag + j * 4096 + coff);
+        };
+        if (READ_AHEAD) read(0, a[0], b[0]);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int u = READ_AHEAD ? c & 1 : 0;
+            if (!READ_AHEAD) read(c, a[0], b[0]);
+            else if (c < 7) read(c + 1, a[u ^ 1], b[u ^ 1]);
+            if constexpr (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int e = 0; e < 4; e += 2)
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hi ? a[i][e + 1] : a[i][e], hi ? b[j][e + 1] : b[j][e], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hi ? a[u][i][e + 1] : a[u][i][e], hi ? b[u][j][e + 1] : b[u][j][e],
+                                                                         acc[i][j], 0, 0, 0);
+            if constexpr (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
         fre = cur;
         cur = cur + SB == ST * SB ? 0 : cur + SB;
@@ -181,11 +195,85 @@ k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, float *__rest
         }
 }
 
-template <int BM, int BN, int WM, int WN>
+// 32 x 32 tiles of four waves, one 16x16 tile each: a quarter of the tile and of the chain's time per k, for products too
+// small to give every CU a 64 x 64 tile. Pipeline as in k_gemm_tile: four slices of 32 k in flight, the fragments of
+// slice kt + 1 read (4 bytes per lane, conflict-free: 16 rows' chunks fill the 64 banks) while slice kt is multiplied.
+constexpr int F32SMALL_STAGES = 4;
+__global__ void __launch_bounds__(256)
+k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, float *__restrict__ C, int64_t ldc, int64_t M, int N, int K,
+                int tiles_m, int tiles_n)
+{
+    constexpr int ST = F32SMALL_STAGES;
+    constexpr uint32_t SB = 64 * 128;
+    extern __shared__ __align__(16) unsigned char lds[];     // (a static array that only the loads' asm writes would count as unwritten)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) / 8;
+    const int lin = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (lin >= n_tiles) return;
+    const int64_t m0 = (int64_t)(lin % tiles_m) * 32;
+    const int n0 = (lin / tiles_m) * 32;
+    const int chunk = tid & 7, rip = tid >> 3;               // 8 lanes x 16 bytes per row
+    const int sw = (chunk ^ ((rip >> 1) & 7)) * 4;
+    const float *const ap = A + (m0 + rip < M ? m0 + rip : M - 1) * lda + sw;
+    const float *const bp = map.row(n0 + rip < N ? n0 + rip : N - 1) + sw;
+    const int KT = K / 32;
+    auto request = [&](int kt, uint32_t stage) {
+        const int koff = (kt < KT ? kt : KT - 1) * 32;       // past the end: the last slice again, never multiplied
+        lds_load16(ap + koff, stage + (uint32_t)(wave * 1024));
+        lds_load16(bp + koff, stage + (uint32_t)(4096 + wave * 1024));
+    };
+    f32x4v_t acc = {0.f, 0.f, 0.f, 0.f};
+    const int r16 = lane & 15, g = lane >> 4;                // this lane supplies k = 4c + g of row r16 of its wave's tile
+    const int ar = (wave >> 1) * 16 + r16, br = (wave & 1) * 16 + r16;
+    const int a_frag = ar * 128 + g * 4, b_frag = 4096 + br * 128 + g * 4, asw = (ar >> 1) & 7, bsw = (br >> 1) & 7;
+    float a0[8], b0[8], a1[8], b1[8];
+    auto fragments = [&](float (&a)[8], float (&b)[8], uint32_t stage) {
+        const unsigned char *const st = lds + stage;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            a[c] = *reinterpret_cast<const float *>(st + a_frag + ((c ^ asw) << 4));
+            b[c] = *reinterpret_cast<const float *>(st + b_frag + ((c ^ bsw) << 4));
+        }
+    };
+    auto multiply = [&](const float (&a)[8], const float (&b)[8]) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[c], acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int s = 0; s < ST; ++s) request(s, s * SB);
+    uint32_t cur = 0, nxt = SB;                              // the stages of slices kt and kt + 1
+#define SOL_F32_SYNC(N) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(2 * (N)) : "memory")
+    SOL_F32_SYNC(ST - 1);
+    fragments(a0, b0, 0);
+    for (int kt = 0; kt < KT; kt += 2) {
+        SOL_F32_SYNC(ST - 2);                                // slice kt + 1 is there, the stage of slice kt is read out
+        request(kt + ST, cur);
+        fragments(a1, b1, nxt);
+        multiply(a0, b0);
+        cur = nxt; nxt = nxt + SB == ST * SB ? 0 : nxt + SB;
+        if (kt + 1 >= KT) break;
+        SOL_F32_SYNC(ST - 2);
+        request(kt + 1 + ST, cur);
+        fragments(a0, b0, nxt);
+        multiply(a1, b1);
+        cur = nxt; nxt = nxt + SB == ST * SB ? 0 : nxt + SB;
+    }
+#undef SOL_F32_SYNC
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no LDS-direct load outlives its workgroup
+    const int col = n0 + (wave & 1) * 16 + r16;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t row = m0 + (wave >> 1) * 16 + 4 * g + r;
+        if (row < M && col < N) C[row * ldc + col] = acc[r];
+    }
+}
+
+template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD>
 static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st)
 {
-    constexpr size_t lds = 3 * (size_t)(BM + BN) * 128;
-    auto kern = k_gemm_f32mfma<BM, BN, WM, WN>;
+    constexpr size_t lds = (size_t)ST * (BM + BN) * 128;
+    auto kern = k_gemm_f32mfma<BM, BN, WM, WN, ST, READ_AHEAD>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -197,8 +285,8 @@ static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, float *
     return true;
 }
 
-// The matrix rate bounds every tile, so the tile is the one whose rounds over the CUs compute the least: a 64 x 64 tile
-// reads twice the operands per product of a 128 x 128 tile and is charged a tenth more.
+// The tile is the one that ends soonest by what was measured at K = 2048 (us; r rounds of one tile on every CU; the 1B
+// layer's widths, 30 to 1018 rows): 32 x 32: 12 + 10.5 r, 64 x 64: 21 + 36 r, 128 x 128: 15 + 134 r.
 bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w0, int n0, const float *w1, int n1, const float *w2, int n2,
                          int64_t ldw, float *C, int64_t ldc, int64_t M, int K, hipStream_t st)
 {
@@ -210,15 +298,14 @@ bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w0, int n0, c
     if (M <= 0 || N <= 0) return true;
     FMap map{{w0, w1, w2}, {n0, n0 + n1, n0 + n1 + n2}, ldw};
     const int cus = device_cus() > 0 ? device_cus() : 256;
-    auto cost = [&](int bm, int bn, double per) {
-        const int64_t tiles = (M + bm - 1) / bm * ((N + bn - 1) / bn);
-        return (double)((tiles + cus - 1) / cus) * bm * bn * per;
-    };
-    const double c0 = cost(128, 128, 1.0), c1 = cost(64, 128, 1.05), c2 = cost(64, 64, 1.1);
-    if ((M + 63) / 64 * ((N + 63) / 64) > (1ll << 30)) return false;
-    if (c0 <= c1 && c0 <= c2) return launch_f32mfma<128, 128, 64, 64>(A, lda, map, C, ldc, M, (int)N, K, st);
-    if (c1 <= c2) return launch_f32mfma<64, 128, 32, 64>(A, lda, map, C, ldc, M, (int)N, K, st);
-    return launch_f32mfma<64, 64, 32, 32>(A, lda, map, C, ldc, M, (int)N, K, st);
+    auto rounds = [&](int b) { return (double)(((M + b - 1) / b * ((N + b - 1) / b) + cus - 1) / cus); };
+    if ((M + 31) / 32 * ((N + 31) / 32) > (1ll << 30)) return false;
+    const double c32 = 12 + 10.5 * rounds(32), c64 = 21 + 36 * rounds(64), c128 = 15 + 134 * rounds(128);
+    if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, false>(A, lda, map, C, ldc, M, (int)N, K, st);
+    if (c64 <= c32) return launch_f32mfma<64, 64, 32, 32, 3, true>(A, lda, map, C, ldc, M, (int)N, K, st);
+    const int tm = (int)((M + 31) / 32), tn = (int)((N + 31) / 32);
+    hipLaunchKernelGGL(k_gemm_f32small, dim3((tm * tn + 7) / 8 * 8), dim3(256), F32SMALL_STAGES * 64 * 128, st, A, lda, map, C, ldc, M, (int)N, K, tm, tn);
+    return true;
 }
 
 void launch_gemm_generic(const void *A, int a_dtype, int64_t lda, const void *W, int w_dtype, int64_t ldw, float *C,
