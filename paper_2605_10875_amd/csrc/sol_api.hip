@@ -5,7 +5,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <string>
 #include <utility>
 #include <vector>
@@ -34,7 +33,6 @@ struct sol_ctx {
     int device = -1;               // the HIP device the context was created on
     void *static_scratch = nullptr;    // that device's address of `scratch`
     int n_actions = 0;
-    int n_buckets = 1;
     ActionDev *d_table = nullptr;
     float2 *d_rope = nullptr;
     int *d_flags = nullptr;
@@ -143,29 +141,10 @@ extern "C" int sol_create(const sol_model_cfg *cfg, const sol_action_def *table,
     sol_ctx *ctx = new sol_ctx();
     ctx->cfg = *cfg;
     ctx->n_actions = n_actions;
-    // MLP buckets: actions that share (kept channels, effective bit-width) share a bucket
     std::vector<ActionDev> host(n_actions);
-    std::map<std::pair<int64_t, int>, int> bucket_of;
-    const bool q_down = (cfg->quant_sites & SOL_QS_DOWN_IN) != 0;
     for (int a = 0; a < n_actions; ++a) {
         const sol_action_def &d = table[a];
-        uint64_t m = ((uint64_t)d.mlp_keep_num * (uint64_t)cfg->d_ff + d.mlp_keep_den - 1) / d.mlp_keep_den;
-        if (m < 1) m = 1;
-        if (m > (uint64_t)cfg->d_ff) m = (uint64_t)cfg->d_ff;
-        const int b_eff = (!q_down || d.bits >= 16) ? 16 : (int)d.bits;
-        bucket_of.emplace(std::make_pair(-(int64_t)m, -b_eff), 0);   // dense-most bucket first
-    }
-    int nb = 0;
-    for (auto &kv : bucket_of) kv.second = nb++;
-    ctx->n_buckets = nb;
-    for (int a = 0; a < n_actions; ++a) {
-        const sol_action_def &d = table[a];
-        uint64_t m = ((uint64_t)d.mlp_keep_num * (uint64_t)cfg->d_ff + d.mlp_keep_den - 1) / d.mlp_keep_den;
-        if (m < 1) m = 1;
-        if (m > (uint64_t)cfg->d_ff) m = (uint64_t)cfg->d_ff;
-        const int b_eff = (!q_down || d.bits >= 16) ? 16 : (int)d.bits;
-        host[a] = ActionDev{d.keep_num, d.keep_den, d.mlp_keep_num, d.mlp_keep_den, d.bits,
-                            bucket_of[std::make_pair(-(int64_t)m, -b_eff)]};
+        host[a] = ActionDev{d.keep_num, d.keep_den, d.mlp_keep_num, d.mlp_keep_den, d.bits};
     }
     // rotary table: cos/sin(pos * theta^(-2c/dh)), double precision on the host
     const int half = cfg->head_dim / 2;
@@ -276,7 +255,7 @@ struct Carver {
 };
 
 struct LayerWs {
-    RowAct *ra; int32_t *row_bucket, *perm, *bucket_off, *seq_order;
+    RowAct *ra; int32_t *seq_order;
     void *h, *qb, *a, *vt, *kf, *pm;
     float *big32, *o32, *x2, *hn32;
 };
@@ -290,9 +269,6 @@ static void carve_layer(Carver &c, const sol_model_cfg &g, int64_t n_seq, int64_
     if (2 * (int64_t)g.d_ff > wide) wide = 2 * (int64_t)g.d_ff;
     if (g.d_model > wide) wide = g.d_model;
     w.ra = (RowAct *)c.take(sizeof(RowAct) * M);
-    w.row_bucket = (int32_t *)c.take(4 * M);
-    w.perm = (int32_t *)c.take(4 * M);
-    w.bucket_off = (int32_t *)c.take(4 * (MAX_ACTIONS + 1));
     w.seq_order = (int32_t *)c.take(4 * n_seq);
     w.h = c.take(es * M * g.d_model);
     w.qb = c.take(es * M * nq);
@@ -380,9 +356,7 @@ static void prepare_actions(sol_ctx *ctx, const int32_t *ids, int64_t M, LayerWs
 {
     STAGE(ctx, ST_PREPARE, st);
     launch_prepare_rows(ids, ctx->d_table, ctx->n_actions, ctx->cfg.prune_site ? ctx->cfg.d_model : ctx->cfg.d_ff, M,
-                        w.ra, w.row_bucket, ctx->d_flags, st);
-    if (prune_fq_wants_order(ctx->cfg.dtype, ctx->cfg.d_ff))
-        launch_bucket_sort(w.row_bucket, M, ctx->n_buckets, w.perm, w.bucket_off, st);
+                        w.ra, ctx->d_flags, st);
 }
 
 // Few rows (a decode step): the linear layers are bound by reading their weights once and take the skinny GEMM.
@@ -475,10 +449,10 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
         STAGE(ctx, ST_SILU, st);
         launch_silu_mul(w.big32, w.a, dt, M, dff, st, ns_gu);
     }
-    {   // magnitude pruning + quantise (down input), rows visited in bucket order
+    {   // magnitude pruning + quantise (down input)
         STAGE(ctx, ST_PRUNE, st);
         if (g.prune_site == 0 || (qs & SOL_QS_DOWN_IN))      // (pruning elsewhere and no quantiser here: nothing to do)
-            launch_prune_fq(w.a, dt, w.ra, w.perm, qs & SOL_QS_DOWN_IN, M, dff, st, g.prune_site == 0);
+            launch_prune_fq(w.a, dt, w.ra, qs & SOL_QS_DOWN_IN, M, dff, st, g.prune_site == 0);
     }
     bool fused_down = false;
     int ns_down = 1;
@@ -503,7 +477,7 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
     return SOL_OK;
 }
 
-// Launch sequence of one decoder layer (actions already decoded into w.ra / w.perm).
+// Launch sequence of one decoder layer (actions already decoded into w.ra).
 static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_in, void *x_out, const int32_t *pos0,
                       void *kc, void *vc, int n_seq, int T, int L_max, LayerWs &w, hipStream_t st,
                       void *page_meta = nullptr, bool dense_pass = false, const PrefixView *pv = nullptr)
@@ -587,7 +561,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
         else
             launch_rmsnorm_fq(x_in, dt, w.big32, w.x2, lw->w_post_norm, dt, hdst, hdt, w.ra, q_here, M, d, g.rms_eps, st, ns_o);
         if (prune_in) {
-            launch_prune_fq(w.hn32, SOL_F32, w.ra, nullptr, qs & SOL_QS_GATEUP_IN, M, d, st);
+            launch_prune_fq(w.hn32, SOL_F32, w.ra, qs & SOL_QS_GATEUP_IN, M, d, st);
             launch_fq_rows(w.hn32, w.h, dt, w.ra, false, M, d, st);
         }
     }
@@ -820,8 +794,7 @@ extern "C" int sol_kv_refresh(sol_ctx *ctx, const sol_model_weights *mw, const i
     const int64_t M = (int64_t)n_seq * T;
     {
         STAGE(ctx, ST_PREPARE, st);
-        launch_dense_rows(g.prune_site ? g.d_model : g.d_ff, M, lw.ra, lw.row_bucket, st);
-        if (prune_fq_wants_order(g.dtype, g.d_ff)) launch_bucket_sort(lw.row_bucket, M, ctx->n_buckets, lw.perm, lw.bucket_off, st);
+        launch_dense_rows(g.prune_site ? g.d_model : g.d_ff, M, lw.ra, st);
         if (T == 1) launch_seq_order(pos0, n_seq, lw.seq_order, st);
     }
     const void *cur = x_in;
@@ -1022,8 +995,7 @@ static int episode_impl(sol_ctx *ctx, const sol_model_weights *mw, const int32_t
     const int64_t Mp = (int64_t)B * P, M = (int64_t)N * T;
     {   // plans: the prefix runs dense, the suffix under its schedules
         STAGE(ctx, ST_PREPARE, st);
-        launch_dense_rows(g.prune_site ? g.d_model : g.d_ff, Mp, w.pre.ra, w.pre.row_bucket, st);
-        if (prune_fq_wants_order(g.dtype, g.d_ff)) launch_bucket_sort(w.pre.row_bucket, Mp, ctx->n_buckets, w.pre.perm, w.pre.bucket_off, st);
+        launch_dense_rows(g.prune_site ? g.d_model : g.d_ff, Mp, w.pre.ra, st);
         launch_fill_i32(w.pos0, P, N, st);
     }
     prepare_actions(ctx, action_ids, M, w.suf, st);

@@ -9,27 +9,21 @@
 
 namespace sol {
 
-struct ActionDev {  // device copy of one action-table row, with the MLP bucket it belongs to
+struct ActionDev {  // device copy of one action-table row
     uint32_t keep_num, keep_den, mlp_keep_num, mlp_keep_den, bits;
-    int32_t  bucket;
 };
 
 // ---- rows (sol_rows.hip) ---------------------------------------------------------------------
-// Decodes action ids into RowAct (invalid id => dense action + FLAG_BAD_ACTION) and writes each
-// row's MLP bucket. d_ff is the width of the vector the MLP keep fraction applies to (d_ff at the
-// SiLU(gate)*up site, d_model at the MLP-input site).
+// Decodes action ids into RowAct (invalid id => dense action + FLAG_BAD_ACTION). d_ff is the width of the vector the MLP
+// keep fraction applies to (d_ff at the SiLU(gate)*up site, d_model at the MLP-input site).
 void launch_prepare_rows(const int32_t *action_ids, const ActionDev *table, int n_actions, int d_ff,
-                         int64_t M, RowAct *ra, int32_t *row_bucket, int *flags, hipStream_t st);
+                         int64_t M, RowAct *ra, int *flags, hipStream_t st);
 // dst [N][Hkv][L_dst][dh] <- src [N / K][Hkv][P][dh] for positions < P (dh * esize a multiple of 16 bytes).
 void launch_bcast_prefix(const void *src, void *dst, int64_t N, int K, int Hkv, int P, int L_dst, int dh, size_t esize,
                          hipStream_t st);
 void launch_fill_i32(int32_t *p, int v, int64_t n, hipStream_t st);
 // Every row under the dense action (all keys, all `width` channels, no quantiser).
-void launch_dense_rows(int width, int64_t M, RowAct *ra, int32_t *row_bucket, hipStream_t st);
-// Stable counting sort of rows by bucket: perm[slot] = row, bucket_off[b] = first slot of bucket b
-// (n_buckets + 1 entries).
-void launch_bucket_sort(const int32_t *row_bucket, int64_t M, int n_buckets, int32_t *perm,
-                        int32_t *bucket_off, hipStream_t st);
+void launch_dense_rows(int width, int64_t M, RowAct *ra, hipStream_t st);
 // h = FQ(RMSNorm(x [+ add]) * w, bits) ; optionally writes xsum = x + add (fp32).
 // x: [M][d] of x_dtype; add: fp32 [M][d] or NULL; ra NULL or quant disabled => no quantiser.
 // prune: between the norm and the quantiser keep the ra.m largest magnitudes of the row (pruning at the MLP
@@ -48,12 +42,9 @@ void launch_rope_store(const float *qkv32, void *q, void *k_cache, void *v_cache
 // a = silu(g) * u ; gu32 [M][2*dff] (gate cols first) -> a [M][dff]
 void launch_silu_mul(const float *gu32, void *a, int dtype, int64_t M, int dff, hipStream_t st, int nsplit = 1);
 // in place on a [M][dff]: keep the ra.m largest |a| (ties to lower channel), then FQ.
-// Rows are visited in bucket order through perm (NULL = identity).
 // prune = false: no pruning (ra.m then belongs to another site), quantiser only.
-void launch_prune_fq(void *a, int dtype, const RowAct *ra, const int32_t *perm, bool quant, int64_t M, int dff,
+void launch_prune_fq(void *a, int dtype, const RowAct *ra, bool quant, int64_t M, int dff,
                      hipStream_t st, bool prune = true);
-// whether launch_prune_fq uses perm for this type / width (if not, the bucket sort can be skipped)
-bool prune_fq_wants_order(int dtype, int dff);
 // out = x2 + z
 void launch_resid_out(const float *x2, const float *z, void *out, int dtype, int64_t M, int d, hipStream_t st,
                       int nsplit = 1);

@@ -1,4 +1,4 @@
-// Row-wise kernels (one workgroup per token row): action decode + bucketing, RMSNorm with the
+// Row-wise kernels (one workgroup per token row): action decode, RMSNorm with the
 // fake-quantise epilogue, magnitude pruning + quantise, rotary/scatter, residuals, NLL rows and
 // the unit hooks. All HBM-bound; rows are contiguous, so accesses are coalesced.
 #include "sol_internal.h"
@@ -9,27 +9,23 @@ namespace sol {
 // action decode (Method, "Actions and controlled compute": a -> (kappa, rho, q))
 // ------------------------------------------------------------------------------------------------
 __global__ void k_prepare_rows(const int32_t *__restrict__ ids, const ActionDev *__restrict__ table, int n_actions,
-                               int d_ff /* width of the pruned vector */, int64_t M, RowAct *__restrict__ ra, int32_t *__restrict__ row_bucket,
+                               int d_ff /* width of the pruned vector */, int64_t M, RowAct *__restrict__ ra,
                                int *flags)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= M) return;
     const int id = ids[r];
     RowAct a;
-    int bucket = 0;
     if (id < 0 || id >= n_actions) {
         atomicOr(flags, FLAG_BAD_ACTION);
         a.keep_num = 1; a.keep_den = 1; a.m = d_ff; a.bits = 16;
-        bucket = 0;
     } else {
         const ActionDev t = table[id];
         a.keep_num = t.keep_num; a.keep_den = t.keep_den;
         a.m = budget_ceil(t.mlp_keep_num, t.mlp_keep_den, d_ff);
         a.bits = (int)t.bits;
-        bucket = t.bucket;
     }
     ra[r] = a;
-    row_bucket[r] = bucket;
 }
 
 // dst [N][Hkv][L_dst][dh] <- src [N / K][Hkv][P][dh] for positions < P (16-byte pieces): the K schedules of an
@@ -69,93 +65,27 @@ void launch_fill_i32(int32_t *p, int v, int64_t n, hipStream_t st)
 }
 
 // every row under the dense action: keep all keys, all `width` channels, quantiser bypassed
-__global__ void k_dense_rows(int width, int64_t M, RowAct *__restrict__ ra, int32_t *__restrict__ row_bucket)
+__global__ void k_dense_rows(int width, int64_t M, RowAct *__restrict__ ra)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= M) return;
     RowAct a;
     a.keep_num = 1; a.keep_den = 1; a.m = width; a.bits = 16;
     ra[r] = a;
-    row_bucket[r] = 0;
 }
 
-void launch_dense_rows(int width, int64_t M, RowAct *ra, int32_t *row_bucket, hipStream_t st)
+void launch_dense_rows(int width, int64_t M, RowAct *ra, hipStream_t st)
 {
     if (M <= 0) return;
-    hipLaunchKernelGGL(k_dense_rows, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, width, M, ra, row_bucket);
+    hipLaunchKernelGGL(k_dense_rows, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, width, M, ra);
 }
 
 void launch_prepare_rows(const int32_t *action_ids, const ActionDev *table, int n_actions, int d_ff, int64_t M,
-                         RowAct *ra, int32_t *row_bucket, int *flags, hipStream_t st)
+                         RowAct *ra, int *flags, hipStream_t st)
 {
     if (M <= 0) return;
     hipLaunchKernelGGL(k_prepare_rows, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, action_ids, table,
-                       n_actions, d_ff, M, ra, row_bucket, flags);
-}
-
-// ------------------------------------------------------------------------------------------------
-// stable counting sort of rows by MLP bucket (one workgroup; M is at most a few 10^5 rows)
-// ------------------------------------------------------------------------------------------------
-constexpr int SORT_BLOCK = 1024;
-constexpr int SORT_GROUP = 8;
-
-__global__ void __launch_bounds__(SORT_BLOCK)
-k_bucket_sort(const int32_t *__restrict__ row_bucket, int64_t M, int n_buckets, int32_t *__restrict__ perm,
-              int32_t *__restrict__ bucket_off)
-{
-    __shared__ int wtot[SORT_BLOCK / 64];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t seg = (M + SORT_BLOCK - 1) / SORT_BLOCK;
-    const int64_t r0 = (int64_t)tid * seg;
-    const int64_t r1 = (r0 + seg < M) ? r0 + seg : M;
-    int base = 0;
-    for (int g0 = 0; g0 < n_buckets; g0 += SORT_GROUP) {
-        int cnt[SORT_GROUP];
-#pragma unroll
-        for (int b = 0; b < SORT_GROUP; ++b) cnt[b] = 0;
-        for (int64_t r = r0; r < r1; ++r) {
-            const int b = row_bucket[r] - g0;
-#pragma unroll
-            for (int bb = 0; bb < SORT_GROUP; ++bb) cnt[bb] += (b == bb);
-        }
-        int start[SORT_GROUP];
-#pragma unroll
-        for (int b = 0; b < SORT_GROUP; ++b) {
-            int incl = cnt[b];
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += t;
-            }
-            if (lane == 63) wtot[w] = incl;
-            __syncthreads();
-            int woff = 0, total = 0;
-#pragma unroll
-            for (int j = 0; j < SORT_BLOCK / 64; ++j) {
-                const int c = wtot[j];
-                if (j < w) woff += c;
-                total += c;
-            }
-            __syncthreads();
-            start[b] = base + woff + incl - cnt[b];
-            if (tid == 0 && g0 + b < n_buckets) bucket_off[g0 + b] = base;
-            base += total;
-        }
-        for (int64_t r = r0; r < r1; ++r) {
-            const int b = row_bucket[r] - g0;
-#pragma unroll
-            for (int bb = 0; bb < SORT_GROUP; ++bb)
-                if (b == bb) perm[start[bb]++] = (int32_t)r;
-        }
-    }
-    if (tid == 0) bucket_off[n_buckets] = base;
-}
-
-void launch_bucket_sort(const int32_t *row_bucket, int64_t M, int n_buckets, int32_t *perm, int32_t *bucket_off,
-                        hipStream_t st)
-{
-    if (M <= 0) return;
-    hipLaunchKernelGGL(k_bucket_sort, dim3(1), dim3(SORT_BLOCK), 0, st, row_bucket, M, n_buckets, perm, bucket_off);
+                       n_actions, d_ff, M, ra, flags);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -630,7 +560,7 @@ struct MagKeyLds {
 
 template <typename T>
 __global__ void __launch_bounds__(ROW_BLOCK)
-k_prune_fq(T *__restrict__ a, const RowAct *__restrict__ ra, const int32_t *__restrict__ perm, int quant, int prune,
+k_prune_fq(T *__restrict__ a, const RowAct *__restrict__ ra, int quant, int prune,
            int dff)
 {
     extern __shared__ float row[];
@@ -638,11 +568,11 @@ k_prune_fq(T *__restrict__ a, const RowAct *__restrict__ ra, const int32_t *__re
     __shared__ int sh[4];
     __shared__ int wcnt[ROW_BLOCK / 64];
     __shared__ float red[ROW_BLOCK / 64];
-    const int64_t r = perm ? perm[blockIdx.x] : (int64_t)blockIdx.x;
+    const int64_t r = blockIdx.x;
     const RowAct act = ra[r];
     const int bits = quant ? act.bits : 16;
     const int m = prune ? act.m : dff;
-    if (m >= dff && bits >= 16) return;          // dense bucket: the row is already final
+    if (m >= dff && bits >= 16) return;          // dense action: the row is already final
     const int tid = threadIdx.x;
     T *ar = a + r * dff;
     float amax = 0.f;
@@ -700,7 +630,7 @@ typedef short i16x2_r __attribute__((ext_vector_type(2)));
 template <int CHUNKS, int NWV>
 __global__ void __launch_bounds__(64 * NWV)
 __attribute__((amdgpu_waves_per_eu(CHUNKS / NWV <= 16 ? 4 : 2, 8)))
-k_prune_fq_wave(bf16_t *__restrict__ a, const RowAct *__restrict__ ra, const int32_t *__restrict__ perm, int quant,
+k_prune_fq_wave(bf16_t *__restrict__ a, const RowAct *__restrict__ ra, int quant,
                 int prune, int64_t M)
 {
     constexpr int DFF = CHUNKS * 512, CW = CHUNKS / NWV;
@@ -708,13 +638,12 @@ k_prune_fq_wave(bf16_t *__restrict__ a, const RowAct *__restrict__ ra, const int
     __shared__ uint32_t s_x[2][NWV];                         // per-wave partial results, double-buffered
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t slot = blockIdx.x;
-    if (slot >= M) return;
-    const int64_t r = perm ? perm[slot] : slot;
+    const int64_t r = blockIdx.x;
+    if (r >= M) return;
     const RowAct act = ra[r];
     const int bits = __builtin_amdgcn_readfirstlane(quant ? act.bits : 16);
     const int m = __builtin_amdgcn_readfirstlane(prune ? act.m : DFF);
-    if (m >= DFF && bits >= 16) return;                      // dense bucket: the row is already final (whole workgroup)
+    if (m >= DFF && bits >= 16) return;                      // dense action: the row is already final (whole workgroup)
     bf16_t *ar = a + r * DFF + (int64_t)wv * CW * 512;
     u32x4_r d[CW];
 #pragma unroll
@@ -859,24 +788,19 @@ static bool prune_wave_case(int dtype, int dff)
     return c == 2 || c == 4 || c == 8 || c == 16 || c == 22 || c == 28;
 }
 
-// The one-row-per-workgroup kernel wants rows of one action next to each other (workgroups of a CU then
-// run the same number of search steps); the one-row-per-wave kernel has no use for the order.
-bool prune_fq_wants_order(int dtype, int dff) { return !prune_wave_case(dtype, dff); }
-
-void launch_prune_fq(void *a, int dtype, const RowAct *ra, const int32_t *perm, bool quant, int64_t M, int dff,
+void launch_prune_fq(void *a, int dtype, const RowAct *ra, bool quant, int64_t M, int dff,
                      hipStream_t st, bool prune)
 {
     if (M <= 0) return;
     if (prune_wave_case(dtype, dff)) {
-        perm = nullptr;
         const dim3 grid((unsigned)M);
         const bool few = M <= 512 && (dff / 512) % 4 == 0;  // a decode step: four waves per row
 #define SOL_PRUNE_CASE(C)                                                                                       \
     case C:                                                                                                     \
         if (few) hipLaunchKernelGGL((k_prune_fq_wave<C, (C % 4 == 0 ? 4 : 1)>), grid, dim3(C % 4 == 0 ? 256 : 64), 0, st, \
-                                    (bf16_t *)a, ra, perm, quant ? 1 : 0, prune ? 1 : 0, M);                    \
+                                    (bf16_t *)a, ra, quant ? 1 : 0, prune ? 1 : 0, M);                    \
         else hipLaunchKernelGGL((k_prune_fq_wave<C, (C > 16 ? (C % 4 == 0 ? 4 : 2) : 1)>), grid, dim3(64 * (C > 16 ? (C % 4 == 0 ? 4 : 2) : 1)), 0, st, (bf16_t *)a, ra, \
-                                perm, quant ? 1 : 0, prune ? 1 : 0, M);       /* rows of more than 16 chunks: four (two) waves */ \
+                                quant ? 1 : 0, prune ? 1 : 0, M);       /* rows of more than 16 chunks: four (two) waves */ \
         return;
         switch (dff / 512) {
             SOL_PRUNE_CASE(2) SOL_PRUNE_CASE(4) SOL_PRUNE_CASE(8) SOL_PRUNE_CASE(16) SOL_PRUNE_CASE(22)
@@ -887,10 +811,10 @@ void launch_prune_fq(void *a, int dtype, const RowAct *ra, const int32_t *perm, 
     }
     const size_t lds = (size_t)dff * sizeof(float);
     if (dtype == 0)
-        hipLaunchKernelGGL((k_prune_fq<float>), dim3((unsigned)M), dim3(ROW_BLOCK), lds, st, (float *)a, ra, perm,
+        hipLaunchKernelGGL((k_prune_fq<float>), dim3((unsigned)M), dim3(ROW_BLOCK), lds, st, (float *)a, ra,
                            quant ? 1 : 0, prune ? 1 : 0, dff);
     else
-        hipLaunchKernelGGL((k_prune_fq<bf16_t>), dim3((unsigned)M), dim3(ROW_BLOCK), lds, st, (bf16_t *)a, ra, perm,
+        hipLaunchKernelGGL((k_prune_fq<bf16_t>), dim3((unsigned)M), dim3(ROW_BLOCK), lds, st, (bf16_t *)a, ra,
                            quant ? 1 : 0, prune ? 1 : 0, dff);
 }
 
@@ -1220,7 +1144,7 @@ void launch_test_prune_quant(void *a, int dtype, int rows, int n, const int32_t 
     if (rows <= 0 || n <= 0) return;
     RowAct *ra = (RowAct *)scratch;
     hipLaunchKernelGGL(k_fill_rowact, dim3((rows + 255) / 256), dim3(256), 0, st, m, bits, ra, rows);
-    launch_prune_fq(a, dtype, ra, nullptr, true, rows, n, st);
+    launch_prune_fq(a, dtype, ra, true, rows, n, st);
 }
 
 void launch_test_topk(const float *scores, int rows, int n_cols, const int32_t *n_valid, const int32_t *k,
