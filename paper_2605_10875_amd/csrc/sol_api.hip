@@ -258,6 +258,9 @@ struct LayerWs {
     RowAct *ra; int32_t *seq_order;
     void *h, *qb, *a, *vt, *kf, *pm;
     float *big32, *o32, *x2, *hn32;
+    void *dsp = nullptr;                   // scratch of the split decode attention, where the step takes it
+    const float *o_src = nullptr;          // the attention stage's output: o_splits partial sums [M][nq] (o32 and 1 by default)
+    int o_splits = 1;
 };
 
 static void carve_layer(Carver &c, const sol_model_cfg &g, int64_t n_seq, int64_t T, int L_max, LayerWs &w)
@@ -323,16 +326,30 @@ static void carve_stack(Carver &c, const sol_model_cfg &g, int64_t n_seq, int64_
     w.logits = (float *)c.take(head_bytes);
 }
 
+// Scratch bytes of the split decode attention of B sequences, 0 where the step does not take it: shapes and batches
+// outside it, and steps whose scratch would then no longer fit the static array (which therefore serves the same steps as
+// before, with the results of the workspace version).
+static size_t decode_split_bytes(const sol_model_cfg &g, int64_t B, int L_max)
+{
+    if (g.dtype != SOL_BF16 || g.page_size != 1 || g.n_sink || g.n_window || B > (1 << 20)) return 0;
+    const size_t bytes = attn_decode_split_bytes((int)B, L_max, g.n_q_heads, g.n_kv_heads, g.head_dim);
+    if (!bytes) return 0;
+    Carver c(nullptr);
+    StackWs w; carve_stack(c, g, B, 1, false, w);
+    return c.off + bytes + 512 <= SOL_STATIC_SCRATCH_BYTES ? bytes : 0;
+}
+
 extern "C" size_t sol_workspace_bytes(const sol_model_cfg *cfg, int op, int n_seq, int T, int L_max)
 {
-    (void)L_max;
     if (!cfg || n_seq <= 0) return 0;
     Carver c(nullptr);
     if (op == SOL_OP_LAYER_FORWARD) {
         if (T <= 0) return 0;
         LayerWs w; carve_layer(c, *cfg, n_seq, T, L_max, w);
+        if (T == 1) c.take(decode_split_bytes(*cfg, n_seq, L_max));
     } else if (op == SOL_OP_DECODE_STEP) {
         StackWs w; carve_stack(c, *cfg, n_seq, 1, false, w);
+        c.take(decode_split_bytes(*cfg, n_seq, L_max));
     } else if (op == SOL_OP_SCHEDULE_LOGLIK) {
         if (T <= 0) return 0;
         StackWs w; carve_stack(c, *cfg, n_seq, T, true, w);
@@ -400,8 +417,12 @@ static int attn_stage(sol_ctx *ctx, LayerWs &w, const int32_t *pos0, void *kc, v
         if (!tiled && mfma && opt.page > 1 && w.vt && w.pm && T >= 16 && L_max <= 4096 &&
             attn_tile_pages_sel_bytes(M, Hq, L_max, opt.page) <= 4 * (size_t)M * nqkv)   // the masks live in big32
             tiled = launch_attn_tile_pages(w.qb, kc, vc, w.vt, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, opt, st);
-        bool dec = !tiled && fast && T == 1 && pos0 &&
-                   launch_attn_decode(w.qb, kc, vc, w.o32, w.ra, pos0, w.seq_order, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st);
+        w.o_src = w.o32;
+        w.o_splits = 1;
+        bool dec = !tiled && fast && T == 1 && pos0 && w.dsp &&
+                   launch_attn_decode_split(w.qb, kc, vc, w.dsp, w.ra, pos0, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st, &w.o_src, &w.o_splits);
+        dec = dec || (!tiled && fast && T == 1 && pos0 &&
+                   launch_attn_decode(w.qb, kc, vc, w.o32, w.ra, pos0, w.seq_order, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st));
         if (!tiled && !dec && mfma && T == 1 && pos0 && page_meta && opt.page > 1) {
             // page rule with caller-kept metadata: the new key joins its page, then bounds come from the metadata
             dec = launch_page_meta_update(kc, pos0, page_meta, n_seq, L_max, Hkv, dh, opt.page, st) &&
@@ -527,7 +548,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     if (int rc = attn_stage(ctx, w, pos0, kc, vc, n_seq, T, L_max, st, page_meta, dense_pass, pv)) return rc;
     {   // quantise (o-proj input)
         STAGE(ctx, ST_QUANT_O, st);
-        launch_fq_rows(w.o32, w.qb, dt, w.ra, qs & SOL_QS_O_IN, M, nq, st);
+        launch_fq_rows(w.o_src, w.qb, dt, w.ra, qs & SOL_QS_O_IN, M, nq, st, w.o_splits);
     }
     bool fused_o = false;
     int ns_o = 1;
@@ -579,6 +600,16 @@ static int check_layer_weights(sol_ctx *ctx, const sol_layer_weights *w)
     return SOL_OK;
 }
 
+// The split decode attention's scratch behind the other pieces; a workspace without room for it (sized for a shorter cache)
+// leaves the step to the one-workgroup-per-item kernel.
+static void take_decode_split(Carver &c, const sol_model_cfg &g, int B, int L_max, size_t ws_bytes, LayerWs &w)
+{
+    const size_t bytes = decode_split_bytes(g, B, L_max);
+    if (!bytes) return;
+    void *p = c.take(bytes);
+    if (c.off + 256 <= ws_bytes) w.dsp = p;
+}
+
 extern "C" int sol_layer_forward(sol_ctx *ctx, const sol_layer_weights *w, const void *x_in, void *x_out,
                                  const int32_t *action_ids, const int32_t *pos0, void *k_cache, void *v_cache,
                                  int n_seq, int T, int L_max, void *workspace, size_t ws_bytes, void *stream)
@@ -591,12 +622,13 @@ extern "C" int sol_layer_forward(sol_ctx *ctx, const sol_layer_weights *w, const
     if (x_in == x_out) return fail(ctx, SOL_ERR_INVALID_ARG, "x_in and x_out must not alias");
     if (L_max > ctx->cfg.max_positions) return fail(ctx, SOL_ERR_INVALID_ARG, "L_max exceeds cfg.max_positions");
     if (T > L_max) return fail(ctx, SOL_ERR_CACHE_OVERFLOW, "T tokens cannot fit a cache of L_max positions");
-    const size_t need = sol_workspace_bytes(&ctx->cfg, SOL_OP_LAYER_FORWARD, n_seq, T, L_max);
-    if (!workspace || ws_bytes < need)
-        return fail(ctx, SOL_ERR_WORKSPACE, "workspace too small: need " + std::to_string(need) + " bytes");
-    hipStream_t st = (hipStream_t)stream;
     Carver c(workspace);
     LayerWs lw; carve_layer(c, ctx->cfg, n_seq, T, L_max, lw);
+    if (!workspace || ws_bytes < c.off + 256)
+        return fail(ctx, SOL_ERR_WORKSPACE, "workspace too small: need " +
+                    std::to_string(sol_workspace_bytes(&ctx->cfg, SOL_OP_LAYER_FORWARD, n_seq, T, L_max)) + " bytes");
+    hipStream_t st = (hipStream_t)stream;
+    if (T == 1 && pos0) take_decode_split(c, ctx->cfg, n_seq, L_max, ws_bytes, lw);
     prepare_actions(ctx, action_ids, (int64_t)n_seq * T, lw, st);
     if (T == 1 && pos0) launch_seq_order(pos0, n_seq, lw.seq_order, st);
     return layer_impl(ctx, w, x_in, x_out, pos0, k_cache, v_cache, n_seq, T, L_max, lw, st);
@@ -668,12 +700,13 @@ static int decode_step_impl(sol_ctx *ctx, const sol_model_weights *mw, const int
     if (B < 0 || L_max <= 0) return fail(ctx, SOL_ERR_INVALID_ARG, "negative size");
     if (L_max > g.max_positions) return fail(ctx, SOL_ERR_INVALID_ARG, "L_max exceeds cfg.max_positions");
     if (B == 0) return SOL_OK;
-    const size_t need = sol_workspace_bytes(&g, SOL_OP_DECODE_STEP, B, 1, L_max);
-    if (!workspace || ws_bytes < need)
-        return fail(ctx, SOL_ERR_WORKSPACE, "workspace too small: need " + std::to_string(need) + " bytes");
-    hipStream_t st = (hipStream_t)stream;
     Carver c(workspace);
     StackWs w; carve_stack(c, g, B, 1, false, w);
+    if (!workspace || ws_bytes < c.off + 256)
+        return fail(ctx, SOL_ERR_WORKSPACE, "workspace too small: need " +
+                    std::to_string(sol_workspace_bytes(&g, SOL_OP_DECODE_STEP, B, 1, L_max)) + " bytes");
+    hipStream_t st = (hipStream_t)stream;
+    take_decode_split(c, g, B, L_max, ws_bytes, w.layer);
     prepare_actions(ctx, action_ids, B, w.layer, st);
     launch_seq_order(cache_len, B, w.layer.seq_order, st);
     const void *cur = x_in;
@@ -1079,7 +1112,10 @@ extern "C" int sol_test_attention_stage(sol_ctx *ctx, const void *q, const int32
     if (T == 1 && pos0) launch_seq_order(pos0, n_seq, lw.seq_order, st);
     lw.qb = const_cast<void *>(q);             // the stage only reads the queries
     lw.o32 = o_out;
+    if (T == 1 && pos0) take_decode_split(c, ctx->cfg, n_seq, L_max, ws_bytes, lw);
     if (int rc = attn_stage(ctx, lw, pos0, k_cache, v_cache, n_seq, T, L_max, st, nullptr, false, nullptr)) return rc;
+    if (lw.o_src != o_out)                                     // partial sums of a split decode attention
+        launch_fq_rows(lw.o_src, o_out, SOL_F32, nullptr, false, (int64_t)n_seq * T, ctx->cfg.n_q_heads * ctx->cfg.head_dim, st, lw.o_splits);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, SOL_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return SOL_OK;

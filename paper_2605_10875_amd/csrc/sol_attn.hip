@@ -1168,16 +1168,70 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
 //   3. softmax numerators back to LDS, 4. V rows gathered where any head kept the key.
 // =================================================================================================
 constexpr int DEC_WAVES = 16, DEC_BLOCK = DEC_WAVES * 64, DEC_HPB = 4, DEC_GW = DEC_WAVES / DEC_HPB;
-// The last phases of the decode kernels: sc holds the softmax numerators of the HPB heads ([HPB][lpad], 0 for
-// dropped keys), s_den the per-wave partial denominators ([head][DEC_GW]); o_row receives HPB * DH outputs.
-//   4. o = sum_j p_j v_j, reading only V rows kept by at least one head; 5. reduction over lanes and waves.
-template <int DH>
-__device__ __forceinline__ void decode_pv_tail(float *sc, int lpad, int n, const bf16_t *__restrict__ vbase,
-                                               const float *s_den, float *__restrict__ o_row)
+// The halving steps lane ^ O, lane ^ 2 O, .. lane ^ 32, with every index a constant (as one loop over an array they end in
+// compare / select chains of thousands of instructions wherever the loop is unrolled too late).
+template <int N> struct DecVals { float v[N]; };
+template <int O, int N>
+__device__ __forceinline__ auto dec_halve(const DecVals<N> &a, int lane, int &fbase)
 {
-    constexpr int VEC = 8, LPK = DH / VEC, KPI = DEC_BLOCK / LPK;
+    DecVals<N / 2> r;
+    const bool up = (lane & O) != 0;
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        const float keep = up ? a.v[i + N / 2] : a.v[i], send = up ? a.v[i] : a.v[i + N / 2];
+        r.v[i] = keep + __shfl_xor(send, O, 64);
+    }
+    fbase += up ? N / 2 : 0;
+    if constexpr (O < 32) return dec_halve<2 * O>(r, lane, fbase);
+    else return r;
+}
+
+// Sums acc (head x 8 channels of this lane's key slot) over the key slots of the workgroup's NW waves through sc, whose
+// readers must be done with it only at the barrier inside; o_row receives HPB * DH sums over den(head).
+template <int DH, int NW, class Den>
+__device__ __forceinline__ void decode_pv_reduce(const float (&acc)[DEC_HPB][8], float *sc, Den den, float *__restrict__ o_row)
+{
+    constexpr int VEC = 8, LPK = DH / VEC;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Reduce over the key slots of a wave (lanes with equal cs) by halving butterflies: at each step a lane
+    // keeps one half of its values and hands the other half to its partner, so the 4 * VEC values per lane
+    // end as 4 * VEC * LPK / 64 fully reduced ones; then across waves in fixed order.
+    DecVals<DEC_HPB * VEC> flat;
+#pragma unroll
+    for (int i = 0; i < DEC_HPB * VEC; ++i) flat.v[i] = acc[i / VEC][i % VEC];
+    int fbase = 0;                                             // first flattened (head, element) index this lane keeps
+    const auto kept = dec_halve<LPK>(flat, lane, fbase);
+    const float *accf = kept.v;
+    constexpr int NKEEP = DEC_HPB * VEC * LPK / 64;            // 4 (head_dim 64) or 8 (head_dim 128)
+    __syncthreads();                                           // all reads of the numerators are done
+    float *ored = sc;                                          // [NW][HPB][DH]
+    {
+        const int hh = fbase / VEC, e0 = fbase - hh * VEC;     // NKEEP values of one head, elements e0..e0+NKEEP-1
+        float *dst = ored + ((size_t)w * DEC_HPB + hh) * DH + (lane & (LPK - 1)) * VEC + e0;
+#pragma unroll
+        for (int i = 0; i < NKEEP; i += 4)
+            *reinterpret_cast<f32x4_a *>(dst + i) = f32x4_a{accf[i], accf[i + 1], accf[i + 2], accf[i + 3]};
+    }
+    __syncthreads();
+    for (int idx = tid; idx < DEC_HPB * DH; idx += NW * 64) {
+        const int hh = idx / DH;
+        float t = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) t += ored[(size_t)ww * DEC_HPB * DH + idx];
+        o_row[idx] = t / den(hh);
+    }
+}
+
+// The last phases of the decode kernels: sc holds the softmax numerators of the HPB heads ([HPB][lpad], 0 for
+// dropped keys), den(head) the denominators (called after a barrier); o_row receives HPB * DH outputs. NW waves.
+//   4. o = sum_j p_j v_j, reading only V rows kept by at least one head; 5. reduction over lanes and waves.
+template <int DH, int NW, class Den>
+__device__ __forceinline__ void decode_pv_tail(float *sc, int lpad, int n, const bf16_t *__restrict__ vbase,
+                                               Den den, float *__restrict__ o_row)
+{
+    constexpr int VEC = 8, LPK = DH / VEC, KPI = NW * 64 / LPK;
+    const int tid = threadIdx.x;
     // ---- 4. o = sum p_j v_j over rows any head kept ---------------------------------------------------
     const int ks = tid / LPK, cs = tid - ks * LPK;
     float acc[DEC_HPB][VEC];
@@ -1217,48 +1271,7 @@ __device__ __forceinline__ void decode_pv_tail(float *sc, int lpad, int n, const
             }
         }
     }
-    // Reduce over the key slots of a wave (lanes with equal cs) by halving butterflies: at each step a lane
-    // keeps one half of its values and hands the other half to its partner, so the 4 * VEC values per lane
-    // end as 4 * VEC * LPK / 64 fully reduced ones; then across waves in fixed order.
-    float *accf = &acc[0][0];
-    int fbase = 0;                                             // first flattened (head, element) index this lane keeps
-    {
-        int nv = DEC_HPB * VEC;
-#pragma unroll
-        for (int o = LPK; o < 64; o <<= 1) {
-            nv >>= 1;
-            const bool up = (lane & o) != 0;
-#pragma unroll
-            for (int i = 0; i < DEC_HPB * VEC / 2; ++i) {
-                if (i < nv) {
-                    const float keep = up ? accf[i + nv] : accf[i];
-                    const float send = up ? accf[i] : accf[i + nv];
-                    accf[i] = keep + __shfl_xor(send, o, 64);
-                }
-            }
-            fbase += up ? nv : 0;
-        }
-    }
-    constexpr int NKEEP = DEC_HPB * VEC * LPK / 64;            // 4 (head_dim 64) or 8 (head_dim 128)
-    __syncthreads();                                           // all reads of the numerators are done
-    float *ored = sc;                                          // [DEC_WAVES][HPB][DH]
-    {
-        const int hh = fbase / VEC, e0 = fbase - hh * VEC;     // NKEEP values of one head, elements e0..e0+NKEEP-1
-        float *dst = ored + ((size_t)w * DEC_HPB + hh) * DH + (lane & (LPK - 1)) * VEC + e0;
-#pragma unroll
-        for (int i = 0; i < NKEEP; i += 4)
-            *reinterpret_cast<f32x4_a *>(dst + i) = f32x4_a{accf[i], accf[i + 1], accf[i + 2], accf[i + 3]};
-    }
-    __syncthreads();
-    for (int idx = tid; idx < DEC_HPB * DH; idx += DEC_BLOCK) {
-        const int hh = idx / DH;
-        float t = 0.f, dsum = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < DEC_WAVES; ++ww) t += ored[(size_t)ww * DEC_HPB * DH + idx];
-#pragma unroll
-        for (int i = 0; i < DEC_GW; ++i) dsum += s_den[hh * DEC_GW + i];
-        o_row[idx] = t / dsum;
-    }
+    decode_pv_reduce<DH, NW>(acc, sc, den, o_row);
 }
 
 template <int DH, int SLOTS>
@@ -1483,7 +1496,12 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
     if (lane == 0) s_den[w] = den;
     __syncthreads();
 
-    decode_pv_tail<DH>(sc, LPAD, n, vbase, s_den, o32 + (int64_t)s * (Hq * DH) + (int64_t)h0 * DH);
+    decode_pv_tail<DH, DEC_WAVES>(sc, LPAD, n, vbase, [&](int hh) {
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < DEC_GW; ++i) d += s_den[hh * DEC_GW + i];
+        return d;
+    }, o32 + (int64_t)s * (Hq * DH) + (int64_t)h0 * DH);
 }
 
 template <int DH, int SLOTS>
@@ -1502,6 +1520,308 @@ static bool launch_attn_decode_t(const void *q, const void *kc, const void *vc, 
     }
     hipLaunchKernelGGL(kern, dim3(Hkv, B), dim3(DEC_BLOCK), lds, st, (const bf16_t *)q, (const bf16_t *)kc,
                        (const bf16_t *)vc, o32, ra, cache_len, seq_order, L_max, Hq, Hkv, 1.0f / sqrtf((float)DH), flags);
+    return true;
+}
+
+// =================================================================================================
+// The same attention for few sequences: with B * Hkv items for 256 CUs the one-workgroup-per-item kernel leaves most of
+// the chip idle and takes an item's whole latency (39 us at 4096 keys for any B up to 32). Here an item's keys are
+// spread over workgroups, in three launches (4.1 + 4.4 + 5.7 us there) with the scores between them in global memory (16
+// bytes per key and KV head against the key's 128 or 256 bytes of K; they stay in the caches):
+//   k_dec_scores  : scores of DSP_KEYS keys for the 4 heads of a KV group (the MFMA sequence of k_attn_decode)
+//   k_dec_select  : per head, 16 waves: the exact threshold of the budget, the last kept tie, the maximum and denominator
+//   k_dec_values  : softmax numerators of a range of keys and their sum over the V rows -> partial outputs, which the row
+//                   quantiser folds in split order
+// Bound: launch latencies for one or two sequences, HBM (V rows of dropped keys included) above.
+// =================================================================================================
+constexpr int DSP_KEYS = 256;                                // keys of a k_dec_scores workgroup: four tiles of 16 per wave
+struct __align__(16) DecSel { uint32_t thr; float mx, den; int jstar; };
+
+template <int DH>
+__global__ void __launch_bounds__(256)
+k_dec_scores(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, float *__restrict__ scores,
+             const int32_t *__restrict__ cache_len, int L_max, int Hq, int Hkv, int lpad, float scale, int *flags)
+{
+    constexpr int KK = DH / 32, U = DSP_KEYS / 64;           // key tiles of a wave, all in flight
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int kvh = blockIdx.y, s = blockIdx.z, h0 = kvh * DEC_HPB;
+    const int p0 = __builtin_amdgcn_readfirstlane(cache_len[s]);
+    if (p0 < 0 || p0 + 1 > L_max) {
+        if (threadIdx.x == 0) atomicOr(flags, FLAG_CACHE_OVERFLOW);
+        return;
+    }
+    const int n = p0 + 1, kt0 = (int)blockIdx.x * (DSP_KEYS / 16) + w * U;
+    if (kt0 * 16 >= n) return;
+    const bf16_t *kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
+    bf16x8_a qf[KK], kf[U][KK];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        int key = (kt0 + u) * 16 + l16;
+        if (key >= n) key = n - 1;
+        const bf16_t *kp = kbase + (int64_t)key * DH + lg * 8;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) kf[u][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(kp + kk * 32));
+    }
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+        u32x4_a v = {0u, 0u, 0u, 0u};
+        if (l16 < DEC_HPB)
+            v = *reinterpret_cast<const u32x4_a *>(q + (int64_t)s * (Hq * DH) + (int64_t)(h0 + l16) * DH + kk * 32 + lg * 8);
+        qf[kk] = __builtin_bit_cast(bf16x8_a, v);
+    }
+    float *row = scores + ((int64_t)s * Hq + h0 + l16) * lpad;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        floatx4_a acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[u][kk], qf[kk], acc, 0, 0, 0);
+        const int j = (kt0 + u) * 16 + lg * 4;               // entries from n on are never read (lpad is a multiple of 64)
+        if (l16 < DEC_HPB && j < n)
+            *reinterpret_cast<f32x4_a *>(row + j) = f32x4_a{acc[0] * scale, acc[1] * scale, acc[2] * scale, acc[3] * scale};
+    }
+}
+
+constexpr int DSEL_WAVES = 16;                               // of one head: a round of the search counts SLOTS columns per lane
+template <int SLOTS>
+__global__ void __launch_bounds__(DSEL_WAVES * 64)
+k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const RowAct *__restrict__ ra,
+             const int32_t *__restrict__ cache_len, int L_max, int Hq, int lpad)
+{
+    constexpr int SLICE = SLOTS * 64, NJ = SLOTS / 4;
+    __shared__ int s_cnt[2][DSEL_WAVES], s_gt[DSEL_WAVES], s_tie[DSEL_WAVES], s_last;
+    __shared__ uint32_t s_min[DSEL_WAVES], s_max[DSEL_WAVES];
+    __shared__ float s_den[DSEL_WAVES];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int head = blockIdx.x, s = blockIdx.y;
+    const int p0 = __builtin_amdgcn_readfirstlane(cache_len[s]);
+    if (p0 < 0 || p0 + 1 > L_max) return;
+    const int n = p0 + 1, base = w * SLICE;
+    int n_loc = n - base;
+    n_loc = n_loc < 0 ? 0 : (n_loc > SLICE ? SLICE : n_loc); // columns held by this wave
+    const float *row = scores + ((int64_t)s * Hq + head) * lpad + base;
+    uint32_t key[SLOTS];
+    uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int c = 256 * j + 4 * lane;
+        f32x4_a v = {0.f, 0.f, 0.f, 0.f};
+        if (c < n_loc) v = *reinterpret_cast<const f32x4_a *>(row + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool valid = c + e < n_loc;
+            const uint32_t kv = valid ? score_key(v[e]) : 0u;
+            key[4 * j + e] = kv;
+            kmax = kv > kmax ? kv : kmax;
+            kmin = (valid && kv < kmin) ? kv : kmin;
+        }
+    }
+    kmax = wave_max_u32(kmax);
+    kmin = wave_min_u32(kmin);
+    if (lane == 0) { s_max[w] = kmax; s_min[w] = kmin; }
+    __syncthreads();
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < DSEL_WAVES; ++i) {
+        lo = s_min[i] < lo ? s_min[i] : lo;
+        hi = s_max[i] > hi ? s_max[i] : hi;
+    }
+    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+    const float mx = score_unkey(hi);                        // the head's best score, always kept
+    const RowAct act = ra[s];
+    const int b = __builtin_amdgcn_readfirstlane(budget_ceil(act.keep_num, act.keep_den, n));
+    // the search of k_attn_decode: count(key >= lo) >= b, count(key >= hi + 1) < b; every wave runs the same steps
+    uint32_t thr = 1u;                                       // budget keeps all: every valid key passes
+    bool done = b >= n, exact = true;
+    float flo = score_unkey(lo), fhi = score_unkey(hi), glo = (float)(n - b) + 0.5f, ghi = 0.5f - (float)b;
+    int side = 0;
+    for (int it = 0; it < 48 && !done; ++it) {
+        if (lo >= hi) { thr = lo; exact = false; break; }
+        const float fp = __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
+        uint32_t mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fp));
+        if (it >= 12 || !(mid > lo && mid <= hi)) mid = lo + ((hi - lo + 1u) >> 1);
+        const int c = wave_count_ge<SLOTS>(key, n_loc, mid);
+        if (lane == 0) s_cnt[it & 1][w] = c;
+        __syncthreads();
+        int cnt = 0;
+#pragma unroll
+        for (int i = 0; i < DSEL_WAVES; ++i) cnt += s_cnt[it & 1][i];
+        cnt = __builtin_amdgcn_readfirstlane(cnt);
+        const float g = (float)(cnt - b) + 0.5f;
+        if (cnt == b) { thr = mid; done = true; }
+        else if (cnt > b) {
+            lo = mid; flo = score_unkey(mid); glo = g;
+            if (side > 0) ghi *= 0.5f;
+            side = 1;
+        } else {
+            hi = mid - 1u; fhi = score_unkey(hi); ghi = g;
+            if (side < 0) glo *= 0.5f;
+            side = -1;
+        }
+    }
+    // ties at the threshold go to the lower columns: the last one kept
+    int jstar = 0x7FFFFFFF;
+    if (b < n && !exact) {                                   // the same for all waves
+        int gt = 0, eq = 0;
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i) {
+            gt += __popcll(__ballot(key[i] > thr));
+            eq += __popcll(__ballot(key[i] == thr));
+        }
+        if (lane == 0) { s_gt[w] = gt; s_tie[w] = eq; }
+        if (threadIdx.x == 0) s_last = 0x7FFFFFFF;
+        __syncthreads();
+        int quota = b;
+#pragma unroll
+        for (int i = 0; i < DSEL_WAVES; ++i) quota -= s_gt[i];
+        for (int i = 0; i < w; ++i) quota -= s_tie[i];       // ties left for this wave's columns
+        quota = __builtin_amdgcn_readfirstlane(quota);
+        if (quota >= 1 && quota <= eq) {                     // exactly one wave holds the quota-th tie
+            int taken = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                int below = 0, here = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned long long bal = __ballot(key[4 * j + e] == thr);
+                    below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, below));
+                    here += __popcll(bal);
+                }
+                int rank = taken + below;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (key[4 * j + e] == thr && rank++ == quota - 1) s_last = base + 256 * j + 4 * lane + e;
+                taken += here;
+            }
+        }
+        __syncthreads();
+        jstar = s_last;
+    }
+    float den = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int c = 256 * j + 4 * lane + e;
+            const uint32_t kv = key[4 * j + e];
+            if (c < n_loc && (kv > thr || (kv == thr && base + c <= jstar))) den += __expf(score_unkey(kv) - mx);
+        }
+    den = wave_sum_dpp(den);
+    if (lane == 0) s_den[w] = den;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < DSEL_WAVES; ++i) d += s_den[i];
+        sel[(int64_t)s * Hq + head] = DecSel{thr, mx, d, jstar};
+    }
+}
+
+// grid (ranges of 256 keys, Hkv, B): a range's V rows are all requested (kept or not) together with its scores, so that a
+// workgroup waits for memory once; part [ranges][B][Hq * DH]. 8 threads per channel of the head: 4 rows of 8 channels per
+// thread. The code is kept short on purpose: a launch this short is bound by latencies, instruction fetches among them
+// (6 us for one sequence of the 1B shape at 4096 keys).
+template <int DH>
+__global__ void __launch_bounds__(8 * DH)
+k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, const bf16_t *__restrict__ vc,
+             float *__restrict__ part, const int32_t *__restrict__ cache_len, int L_max, int Hq, int Hkv, int lpad)
+{
+    constexpr int NT = 8 * DH, LPK = DH / 8, KPI = NT / LPK, NV = DSP_KEYS / KPI, HPT = DEC_HPB * DSP_KEYS / NT;
+    static_assert(NV == 4 && KPI == 64, "");
+    __shared__ __align__(16) float sc[NT / 64 * DEC_HPB * DH > DEC_HPB * DSP_KEYS ? NT / 64 * DEC_HPB * DH : DEC_HPB * DSP_KEYS];
+    const int tid = threadIdx.x, kvh = blockIdx.y, s = blockIdx.z, h0 = kvh * DEC_HPB;
+    const int p0 = __builtin_amdgcn_readfirstlane(cache_len[s]);
+    if (p0 < 0 || p0 + 1 > L_max) return;
+    const int k0 = (int)blockIdx.x * DSP_KEYS;
+    int n = p0 + 1 - k0;
+    n = n < 0 ? 0 : (n > DSP_KEYS ? DSP_KEYS : n);
+    const DecSel *sr = sel + (int64_t)s * Hq + h0;
+    const bf16_t *vbase = vc + (((int64_t)s * Hkv + kvh) * (int64_t)L_max + k0) * DH;
+    const int ks = tid / LPK, cs = tid - ks * LPK, key = tid & (DSP_KEYS - 1), hb = tid / DSP_KEYS * HPT;
+    u32x4_a vv[NV];
+    float v4[HPT];
+#pragma unroll
+    for (int hh = 0; hh < HPT; ++hh) v4[hh] = key < n ? scores[((int64_t)s * Hq + h0 + hb + hh) * lpad + k0 + key] : 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const int j = ks + u * KPI;
+        vv[u] = u32x4_a{0u, 0u, 0u, 0u};
+        if (j < n) vv[u] = *reinterpret_cast<const u32x4_a *>(vbase + (int64_t)j * DH + cs * 8);
+    }
+#pragma unroll
+    for (int hh = 0; hh < HPT; ++hh) {
+        const DecSel d = sr[hb + hh];
+        const uint32_t kv = score_key(v4[hh]);
+        const bool kept = key < n && (kv > d.thr || (kv == d.thr && k0 + key <= d.jstar));
+        sc[(hb + hh) * DSP_KEYS + key] = kept ? __expf(v4[hh] - d.mx) : 0.f;
+    }
+    __syncthreads();
+    float acc[DEC_HPB][8];
+#pragma unroll
+    for (int hh = 0; hh < DEC_HPB; ++hh)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[hh][e] = 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        float p[DEC_HPB];
+        bool any = false;
+#pragma unroll
+        for (int hh = 0; hh < DEC_HPB; ++hh) { p[hh] = sc[hh * DSP_KEYS + ks + u * KPI]; any |= p[hh] != 0.f; }
+#pragma unroll
+        for (int wi = 0; wi < 4; ++wi) {
+            const uint32_t v = any ? vv[u][wi] : 0u;         // a row that no head kept may hold anything
+            const float a = __uint_as_float(v << 16), b = __uint_as_float(v & 0xFFFF0000u);
+#pragma unroll
+            for (int hh = 0; hh < DEC_HPB; ++hh) {
+                acc[hh][2 * wi] = fmaf(p[hh], a, acc[hh][2 * wi]);
+                acc[hh][2 * wi + 1] = fmaf(p[hh], b, acc[hh][2 * wi + 1]);
+            }
+        }
+    }
+    decode_pv_reduce<DH, NT / 64>(acc, sc, [&](int hh) { return sr[hh].den; }, part + (((int64_t)blockIdx.x * gridDim.z + s) * Hq + h0) * DH);
+}
+
+// Scratch of the split path for B sequences: scores, selection rows and partial outputs. 0: the shape, or B, is not its.
+// It pays while few items leave most CUs of the one-workgroup-per-item kernel idle and their rows are long enough for that
+// kernel's latency to show; measured per layer of a graph-replayed step (us, one workgroup per item -> split; caches of
+// 3/4 L .. L keys): 1B shape, B = 1: L 1000 91 -> 93, 2000 101 -> 96, 4096 127 -> 99, 8192 155 -> 105; B = 8: 2000 108 ->
+// 105, 8192 159 -> 131; B = 12: 2000 109 -> 114, 4096 134 -> 126; B = 16: 4096 136 -> 135, 8192 166 -> 170; 8B shape,
+// L = 8192: B = 1 238 -> 161, B = 8 263 -> 212, B = 12 266 -> 252. Hence the line below.
+static int dsp_lpad(int L_max) { return (L_max + DSP_KEYS - 1) / DSP_KEYS * DSP_KEYS; }
+size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh)
+{
+    if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || L_max > 9216 || L_max < 1) return 0;
+    const int64_t items = (int64_t)B * Hkv;
+    if (items > 96 || L_max < 1536 || L_max < 42 * items) return 0;
+    return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)(dsp_lpad(L_max) / DSP_KEYS) * dh * 4);
+}
+
+// B sequences as launch_attn_decode, in three launches; writes nsplit partial outputs [nsplit][B][Hq * dh] at *part.
+bool launch_attn_decode_split(const void *q, const void *k_cache, const void *v_cache, void *ws, const RowAct *ra,
+                              const int32_t *cache_len, int B, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st,
+                              const float **part_out, int *nsplit_out)
+{
+    if (!cache_len || !attn_decode_split_bytes(B, L_max, Hq, Hkv, dh)) return false;
+    const int lpad = dsp_lpad(L_max);
+    float *scores = (float *)ws;
+    DecSel *sel = (DecSel *)(scores + (size_t)B * Hq * lpad);
+    float *part = (float *)(sel + (size_t)B * Hq);
+    const int ranges = lpad / DSP_KEYS;
+    const float scale = 1.0f / sqrtf((float)dh);
+    const dim3 g1(lpad / DSP_KEYS, Hkv, B), g2(Hq, B);
+    if (dh == 64) hipLaunchKernelGGL(k_dec_scores<64>, g1, dim3(256), 0, st, (const bf16_t *)q, (const bf16_t *)k_cache, scores, cache_len, L_max, Hq, Hkv, lpad, scale, flags);
+    else hipLaunchKernelGGL(k_dec_scores<128>, g1, dim3(256), 0, st, (const bf16_t *)q, (const bf16_t *)k_cache, scores, cache_len, L_max, Hq, Hkv, lpad, scale, flags);
+#define SOL_DEC_SEL(SL) hipLaunchKernelGGL(k_dec_select<SL>, g2, dim3(DSEL_WAVES * 64), 0, st, scores, sel, ra, cache_len, L_max, Hq, lpad)
+    if (L_max <= 4096) SOL_DEC_SEL(4);
+    else if (L_max <= 8192) SOL_DEC_SEL(8);
+    else SOL_DEC_SEL(12);
+#undef SOL_DEC_SEL
+    if (dh == 64) hipLaunchKernelGGL(k_dec_values<64>, g1, dim3(512), 0, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad);
+    else hipLaunchKernelGGL(k_dec_values<128>, g1, dim3(1024), 0, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad);
+    *part_out = part;
+    *nsplit_out = ranges;
     return true;
 }
 
@@ -1976,7 +2296,12 @@ k_attn_decode_paged(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc,
         if (lane == 0) s_den[w] = den;
         __syncthreads();
     }
-    decode_pv_tail<DH>(sc, lpad, n, vbase, s_den, o32 + (int64_t)s * (Hq * DH) + (int64_t)h0 * DH);
+    decode_pv_tail<DH, DEC_WAVES>(sc, lpad, n, vbase, [&](int hh) {
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < DEC_GW; ++i) d += s_den[hh * DEC_GW + i];
+        return d;
+    }, o32 + (int64_t)s * (Hq * DH) + (int64_t)h0 * DH);
 }
 
 template <int DH, int SLOTS>

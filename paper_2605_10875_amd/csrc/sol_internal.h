@@ -32,9 +32,9 @@ void launch_dense_rows(int width, int64_t M, RowAct *ra, hipStream_t st);
 bool launch_rmsnorm_fq(const void *x, int x_dtype, const float *add, float *xsum, const void *w, int w_dtype,
                        void *h, int h_dtype, const RowAct *ra, bool quant, int64_t M, int d, float eps,
                        hipStream_t st, int nsplit = 1, bool prune = false);
-// out = FQ(in, bits) row-wise; in fp32 [M][n] -> out dtype.
+// out = FQ(in, bits) row-wise; in fp32 [nsplit][M][n] (partial sums, folded in split order) -> out dtype.
 void launch_fq_rows(const float *in, void *out, int out_dtype, const RowAct *ra, bool quant, int64_t M, int n,
-                    hipStream_t st);
+                    hipStream_t st, int nsplit = 1);
 // rotary + scatter: qkv32 [M][(Hq+2Hkv)*dh] -> q [M][Hq*dh], K/V caches at position pos0[s]+i.
 void launch_rope_store(const float *qkv32, void *q, void *k_cache, void *v_cache, int dtype, const float2 *rope,
                        const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int *flags,
@@ -137,6 +137,12 @@ void launch_seq_order(const int32_t *cache_len, int B, int32_t *order, hipStream
 bool launch_attn_decode(const void *q, const void *k_cache, const void *v_cache, float *o32, const RowAct *ra,
                         const int32_t *cache_len, const int32_t *seq_order, int B, int L_max, int Hq, int Hkv, int dh,
                         int *flags, hipStream_t st);
+// The same for few sequences, an item's keys spread over workgroups: scratch bytes (0: not covered, or too many sequences)
+// and the launches; the outputs are *nsplit partial ones, [nsplit][B][Hq * dh] at *part, to be summed in split order.
+size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh);
+bool launch_attn_decode_split(const void *q, const void *k_cache, const void *v_cache, void *ws, const RowAct *ra,
+                              const int32_t *cache_len, int B, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st,
+                              const float **part, int *nsplit);
 // Page metadata of a bf16 K cache for the page rule (page size S >= 2): meta [n_seq][Hkv][ceil(L_max/S)][2*dh],
 // per page the channel-wise [maximum | minimum] of its keys. build: from keys [0, len[s]); update: the key at
 // pos[s] joins its page. head_dim 64 / 128.
