@@ -256,7 +256,7 @@ struct Carver {
 
 struct LayerWs {
     RowAct *ra; int32_t *seq_order;
-    void *h, *qb, *a, *vt, *kf, *pm;
+    void *h, *qb, *a, *kf, *pm;
     float *big32, *o32, *x2, *hn32;
     void *dsp = nullptr;                   // scratch of the split decode attention, where the step takes it
     const float *o_src = nullptr;          // the attention stage's output: o_splits partial sums [M][nq] (o32 and 1 by default)
@@ -287,11 +287,9 @@ static void carve_layer(Carver &c, const sol_model_cfg &g, int64_t n_seq, int64_
     w.o32 = (float *)c.take(4 * M * nq);
     w.x2 = (float *)c.take(4 * M * g.d_model);
     w.hn32 = (float *)c.take(g.prune_site == 1 ? 4 * M * g.d_model : 0);   // fp32 post-norm row, pruned at the MLP input
-    // transposed V copy for the tiled attention kernel (batched bf16 pass only)
     const bool tiled = g.dtype == SOL_BF16 && T >= 16 && L_max <= 4096;
-    w.vt = c.take(tiled ? es * n_seq * g.n_kv_heads * g.head_dim * (size_t)attn_tile_lpadv(L_max) : 0);
-    // K in MFMA operand order for the threshold kernel
-    w.kf = c.take(tiled ? es * n_seq * g.n_kv_heads * g.head_dim * (size_t)attn_tile_lpadv(L_max) : 0);
+    // K in MFMA operand order for the threshold kernel (batched bf16 pass only)
+    w.kf = c.take(tiled ? es * n_seq * g.n_kv_heads * g.head_dim * (size_t)attn_tile_lpad(L_max) : 0);
     // per-key page extremes for the tiled kernels under the page rule
     w.pm = c.take(tiled && g.page_size > 1 ? attn_tile_pages_meta_bytes(n_seq, g.n_kv_heads, L_max, g.head_dim) : 0);
 }
@@ -384,7 +382,7 @@ static bool use_skinny(const sol_model_cfg &g, int64_t M)
 
 // Attention stage of the layer: causal scores over cache positions [0, pos], the budgeted selection of the token's
 // action, softmax over the kept keys, times V. Reads w.qb and the caches, writes w.o32 (fp32, before the quantiser of
-// the output projection's input); w.vt / w.pm / w.big32 are scratch.
+// the output projection's input); w.kf / w.pm / w.big32 are scratch.
 static int attn_stage(sol_ctx *ctx, LayerWs &w, const int32_t *pos0, void *kc, void *vc, int n_seq, int T, int L_max,
                       hipStream_t st, void *page_meta, bool dense_pass, const PrefixView *pv)
 {
@@ -400,23 +398,23 @@ static int attn_stage(sol_ctx *ctx, LayerWs &w, const int32_t *pos0, void *kc, v
         if (!dense_pass) { opt.page = g.page_size; opt.n_sink = g.n_sink; opt.n_window = g.n_window; }   // dense rows keep every key under any rule
         const bool fast = mfma && opt.plain();       // the tiled and decode kernels know the plain top-k rule only
         if (pv) {   // sequences on shared prefix caches: the tiled kernels with two-segment addressing, or nothing
-            bool ok = mfma && w.vt;
+            bool ok = mfma && w.kf;
             if (ok && opt.plain())
-                ok = launch_attn_tile_prefix(w.qb, kc, vc, w.vt, w.big32, w.o32, w.ra, pos0, n_seq, T, Hq, Hkv, dh, *pv, st);
+                ok = launch_attn_tile_prefix(w.qb, kc, vc, w.big32, w.o32, w.ra, pos0, n_seq, T, Hq, Hkv, dh, *pv, st);
             else if (ok)   // page rule (the masks live in big32)
                 ok = opt.page > 1 && w.pm && attn_tile_pages_sel_bytes(M, Hq, pv->P + T, opt.page) <= 4 * (size_t)M * nqkv &&
-                     launch_attn_tile_pages_prefix(w.qb, kc, vc, w.vt, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, Hq, Hkv,
+                     launch_attn_tile_pages_prefix(w.qb, kc, vc, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, Hq, Hkv,
                                                    dh, opt, *pv, st);
             if (!ok) return fail(ctx, SOL_ERR_UNSUPPORTED, "shared-prefix attention: shape outside the tiled kernels");
         }
         bool tiled = pv != nullptr;
-        tiled = tiled || (dense_pass && mfma && w.vt && T >= 16 && L_max <= 4096 &&
-                          launch_attn_tile_dense(w.qb, kc, vc, w.vt, w.o32, pos0, n_seq, T, L_max, Hq, Hkv, dh, st));
-        tiled = tiled || (fast && w.vt && w.kf && T >= 16 && L_max <= 4096 &&
-                          launch_attn_tile(w.qb, kc, vc, w.vt, w.kf, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, st));
-        if (!tiled && mfma && opt.page > 1 && w.vt && w.pm && T >= 16 && L_max <= 4096 &&
+        tiled = tiled || (dense_pass && mfma && w.kf && T >= 16 && L_max <= 4096 &&
+                          launch_attn_tile_dense(w.qb, kc, vc, w.o32, pos0, n_seq, T, L_max, Hq, Hkv, dh, st));
+        tiled = tiled || (fast && w.kf && T >= 16 && L_max <= 4096 &&
+                          launch_attn_tile(w.qb, kc, vc, w.kf, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, st));
+        if (!tiled && mfma && opt.page > 1 && w.pm && T >= 16 && L_max <= 4096 &&
             attn_tile_pages_sel_bytes(M, Hq, L_max, opt.page) <= 4 * (size_t)M * nqkv)   // the masks live in big32
-            tiled = launch_attn_tile_pages(w.qb, kc, vc, w.vt, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, opt, st);
+            tiled = launch_attn_tile_pages(w.qb, kc, vc, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, opt, st);
         w.o_src = w.o32;
         w.o_splits = 1;
         bool dec = !tiled && fast && T == 1 && pos0 && w.dsp &&
@@ -973,7 +971,7 @@ static void carve_episode(Carver &c, const sol_model_cfg &g, int64_t B, int64_t 
         pv.k = (const bf16_t *)t.pkc; pv.P = (int)P; pv.K = (int)K; pv.crows = (int)T;
         const int64_t M = B * K * T;
         const int nqkv = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim;
-        twoseg = t.suf.vt && t.pre.vt &&
+        twoseg = t.suf.kf && t.pre.kf &&
                  (plain ? attn_tile_prefix_ok(t.st.kc, (int)(B * K), (int)T, g.n_q_heads, g.n_kv_heads, g.head_dim, pv)
                         : t.suf.pm && t.pre.pm &&
                           attn_tile_pages_prefix_ok((int)(B * K), (int)T, g.n_q_heads, g.n_kv_heads, g.head_dim, g.page_size, pv) &&
@@ -1042,10 +1040,10 @@ static int episode_impl(sol_ctx *ctx, const sol_model_weights *mw, const int32_t
         // layer l of the prefix (dense, once per input) fills the prefix cache; every schedule starts from a copy
         if (int rc = layer_impl(ctx, &mw->layers[l], pcur, pnxt, nullptr, w.pkc, w.pvc, B, P, P, w.pre, st, nullptr, true)) return rc;
         std::swap(pcur, pnxt);
-        if (w.twoseg) {   // the schedules read the prefix K (and the transposed V the prefix pass left in its workspace) in place
+        if (w.twoseg) {   // the schedules read the prefix K and V in place
             PrefixView pv;
-            pv.k = (const bf16_t *)w.pkc; pv.vt = (const bf16_t *)w.pre.vt;
-            pv.P = P; pv.K = K; pv.lpadv = attn_tile_lpadv(P); pv.crows = T;
+            pv.k = (const bf16_t *)w.pkc; pv.v = (const bf16_t *)w.pvc;
+            pv.P = P; pv.K = K; pv.crows = T;
             if (g.page_size <= 1 && P + T > 1024 && w.pre.kf && launch_attn_frag_k(w.pkc, w.pre.kf, nullptr, B, P, P, g.n_kv_heads, g.head_dim, st))
                 pv.kf = (const bf16_t *)w.pre.kf;     // long rows: the threshold kernel reads the prefix keys in operand order
             if (g.page_size > 1) {   // page rule: the prefix keys' metadata rows, once per input (the dense prefix pass has no use for them)

@@ -922,6 +922,24 @@ template <int DH> __device__ __forceinline__ int pv_swz_k(int row)
     if constexpr (DH == 64) return ((row >> 1) & 1) | (((row >> 3) & 3) << 1);   // rows {0-3, 8-11, 16-19, 24-27} (+4)
     else return (row & 3) | (((row >> 3) & 3) << 2);
 }
+// The transposing read takes, per group of 16 lanes, 4 keys (lanes 4 j .. 4 j + 3: key j) x 16 channels (4 per lane) and
+// hands lane i the 4 keys of channel i. The 64 lanes of a read touch 32 bytes each of 16 rows: the 32-byte windows of a row
+// are XOR-ed with row bits so that 8 of these rows fill the 64 banks (rows 4 apart, the second read, swizzle alike).
+template <int DH> __device__ __forceinline__ int pv_swz_v(int row)
+{
+    return DH == 64 ? (row & 2) | ((row >> 1) & 4) : ((row & 3) << 1) | (row & 8);
+}
+typedef short s16x4_a __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_a lds_s16x4;
+// keys key0 .. key0 + 7 (key0: this lane group's, a multiple of 8) of channel 16 * dt + l16
+template <int DH> __device__ __forceinline__ bf16x8_a pv_read_v(const unsigned char *vb, int key0, int dt, int l16)
+{
+    const int row = key0 + (l16 >> 2);
+    const unsigned char *p = vb + row * (DH * 2) + (((dt * 2) ^ pv_swz_v<DH>(row)) << 4) + (l16 & 3) * 8;
+    const s16x4_a a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+    const s16x4_a b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * DH * 2));
+    return __builtin_bit_cast(bf16x8_a, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 // softmax numerators of one 32-key sub-chunk for one query tile, as the A operand (hi and lo bf16
 // halves) of the P V product. st[kt][r] is the score of key  kbase + 8*lg + 4*kt + r.
@@ -953,8 +971,11 @@ __device__ __forceinline__ void pv_probs(const floatx4_a (&st)[2], float scale, 
     plo = __builtin_bit_cast(bf16x8_a, lo);
 }
 
-// PRE: as in k_attn_select; vt then is the transposed copy of the own cache ([n_seq][Hkv][DH][lpadv], positions
-// pv.P..) and pv.vt that of the prefix cache ([inputs][Hkv][DH][pv.lpadv]); 64-key chunks never straddle pv.P.
+// V chunks are staged as they lie in the cache, rows of DH channels, and read with the transposing LDS load into the B
+// operand of P V (8 consecutive keys of a channel per lane); a transposed copy in memory was a pass over the whole V cache
+// per layer (85 of 396 us for a refresh of 64 x 4096 keys).
+// PRE: as in k_attn_select; kc and vc then hold the sequence's own positions, from pv.P on, pv.k and pv.v the prefix;
+// 64-key chunks never straddle pv.P.
 // NQT: query tiles of 16 rows per workgroup (2; 1 for passes of at most 16 rows per sequence).
 // Occupancy floors (4+ heads per group): four waves per SIMD at head size 64 (128 registers; the 18 values that do not
 // fit are spilled outside the chunk loop), two at head size 128 (256 registers, no spills). Left alone the compiler takes
@@ -962,16 +983,16 @@ __device__ __forceinline__ void pv_probs(const floatx4_a (&st)[2], float scale, 
 // overlap with: 2.90 -> 1.81 ms per launch at the 8B shape with 4096-token sequences.
 template <int DH, int G, bool PRE, int NQT>
 __global__ void __launch_bounds__(G * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 && G >= 4 ? 4 : (DH == 128 && G >= 4 ? 2 : 1), 8)))
-k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vt,
+k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc,
           const SelRow *__restrict__ sel, float *__restrict__ o32, const int32_t *__restrict__ pos0, int Tn, int L_max, int Hq,
-          int Hkv, int lpadv, float scale, PrefixView pv)
+          int Hkv, float scale, PrefixView pv)
 {
     constexpr int NT = G * 64, KK = DH / 32, DT = DH / 16, KC = 64, QT = 16 * NQT;
     constexpr int KP = DH / 8;                              // 16-byte pieces per K row
-    constexpr int K_PIECES = KC * KP / NT, V_PIECES = DH * (KC / 8) / NT;
+    constexpr int PIECES = KC * KP / NT;                     // of K and of V, per thread and chunk
     constexpr int K_BYTES = KC * DH * 2, STAGE = 2 * K_BYTES;
-    static_assert(KC * KP % NT == 0 && DH * (KC / 8) % NT == 0, "chunk / thread mismatch");
-    extern __shared__ __align__(16) unsigned char pvl[];   // 2 stages of { K chunk, V^T chunk }
+    static_assert(KC * KP % NT == 0, "chunk / thread mismatch");
+    extern __shared__ __align__(16) unsigned char pvl[];   // 2 stages of { K chunk, V chunk }
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1004,13 +1025,13 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
     const int n_max = p0 + q0 + rows;                      // keys seen by the block's last live row
     const int n_chunks = (n_max + KC - 1) / KC;
     const bf16_t *kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
-    const bf16_t *vbase = vt + ((int64_t)s * Hkv + kvh) * (int64_t)DH * lpadv;
+    const bf16_t *vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
     const bf16_t *kpre = nullptr, *vpre = nullptr;
     if constexpr (PRE) {                                    // own segment addressed by absolute key: bases minus P keys
         kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)pv.crows * DH - (int64_t)pv.P * DH;
-        vbase = vbase - pv.P;
+        vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)pv.crows * DH - (int64_t)pv.P * DH;
         kpre = pv.k + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)pv.P * DH;
-        vpre = pv.vt + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)DH * pv.lpadv;
+        vpre = pv.v + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)pv.P * DH;
     }
 
     // per-lane query state: lane l16 of every lane group owns query q0 + 16*qt + l16
@@ -1042,34 +1063,27 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
         for (int dt = 0; dt < DT; ++dt) oacc[qt][dt] = floatx4_a{0.f, 0.f, 0.f, 0.f};
 
     // staging: global -> registers -> LDS, one chunk ahead
-    u32x4_a kreg0[K_PIECES], vreg0[V_PIECES];
+    u32x4_a kreg0[PIECES], vreg0[PIECES];
 #define SOL_PV_GLOAD(KR, VR, CH_)                                                                                  \
     {                                                                                                      \
         const int key0_ = (CH_) * KC;                                                                      \
         const bool pre_ = PRE && key0_ < pv.P;              /* chunk-uniform: P is a multiple of the chunk */ \
         const bf16_t *kb_ = pre_ ? kpre : kbase, *vb_ = pre_ ? vpre : vbase;                               \
-        const int64_t vs_ = pre_ ? pv.lpadv : lpadv;                                                       \
-        _Pragma("unroll") for (int i = 0; i < K_PIECES; ++i) {                                             \
+        _Pragma("unroll") for (int i = 0; i < PIECES; ++i) {                                             \
             const int pc = i * NT + tid, row = pc / KP, piece = pc - row * KP;                             \
             int key = key0_ + row;                                                                         \
             if (key >= n_max) key = n_max - 1;              /* never used unmasked: beyond every row */     \
             KR[i] = *reinterpret_cast<const u32x4_a *>(kb_ + (int64_t)key * DH + piece * 8);               \
-        }                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < V_PIECES; ++i) {                                             \
-            const int pc = i * NT + tid, d = pc >> 3, piece = pc & 7;                                      \
-            VR[i] = *reinterpret_cast<const u32x4_a *>(vb_ + (int64_t)d * vs_ + key0_ + piece * 8);        \
+            VR[i] = *reinterpret_cast<const u32x4_a *>(vb_ + (int64_t)key * DH + piece * 8);               \
         }                                                                                                  \
     }
 #define SOL_PV_LSTORE(KR, VR, STG_)                                                                                \
     {                                                                                                      \
         unsigned char *kb_ = pvl + (STG_) * STAGE, *vb_ = kb_ + K_BYTES;                                   \
-        _Pragma("unroll") for (int i = 0; i < K_PIECES; ++i) {                                             \
+        _Pragma("unroll") for (int i = 0; i < PIECES; ++i) {                                             \
             const int pc = i * NT + tid, row = pc / KP, piece = pc - row * KP;                             \
             *reinterpret_cast<u32x4_a *>(kb_ + row * (DH * 2) + ((piece ^ pv_swz_k<DH>(row)) << 4)) = KR[i]; \
-        }                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < V_PIECES; ++i) {                                             \
-            const int pc = i * NT + tid, d = pc >> 3, piece = pc & 7;                                      \
-            *reinterpret_cast<u32x4_a *>(vb_ + d * (KC * 2) + ((piece ^ ((d >> 1) & 7)) << 4)) = VR[i];    \
+            *reinterpret_cast<u32x4_a *>(vb_ + row * (DH * 2) + ((piece ^ pv_swz_v<DH>(row)) << 4)) = VR[i]; \
         }                                                                                                  \
     }
 
@@ -1119,9 +1133,7 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const int d = dt * 16 + l16;
-                    const bf16x8_a vf = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(
-                        vb + d * (KC * 2) + (((cc * 4 + lg) ^ ((d >> 1) & 7)) << 4)));
+                    const bf16x8_a vf = pv_read_v<DH>(vb, cc * 32 + 8 * lg, dt, l16);
 #pragma unroll
                     for (int qt = 0; qt < NQT; ++qt) {
                         oacc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo[qt], vf, oacc[qt][dt], 0, 0, 0);
@@ -2353,44 +2365,6 @@ bool launch_attn_decode_paged(const void *q, const void *k_cache, const void *v_
     return false;
 }
 
-// V cache [s][kvh][key][dh] -> vt [s][kvh][dh][lpadv] for keys < pos0[s] + Tn, zero beyond (lpadv a multiple of 64).
-// 16 bytes per lane on both sides of memory: 8 channels of a key in, 8 keys of a channel out; the tile's LDS rows are
-// DH + 2 elements apart (an odd number of words), which puts the 8 keys a lane gathers for its output, and the lanes
-// of a wave, on different banks.
-template <int DH>
-__global__ void __launch_bounds__(256)
-k_transpose_v(const bf16_t *__restrict__ vc, bf16_t *__restrict__ vt, const int32_t *__restrict__ pos0, int Tn, int L_max,
-              int Hkv, int lpadv)
-{
-    constexpr int KP = DH / 8;                               // 16-byte pieces per key
-    __shared__ __align__(4) bf16_t tile[64][DH + 2];
-    const int kb = blockIdx.x * 64, kvh = blockIdx.y, s = blockIdx.z;
-    const int p0 = pos0 ? pos0[s] : 0;
-    int len = p0 + Tn;
-    if (p0 < 0 || len > L_max) len = 0;
-    const bf16_t *src = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
-    bf16_t *dst = vt + ((int64_t)s * Hkv + kvh) * (int64_t)DH * lpadv;
-    for (int idx = threadIdx.x; idx < 64 * KP; idx += 256) {
-        const int k = idx / KP, p = idx - k * KP;
-        u32x4_a v = {0u, 0u, 0u, 0u};
-        if (kb + k < len) v = *reinterpret_cast<const u32x4_a *>(src + (int64_t)(kb + k) * DH + p * 8);
-        uint32_t *row = reinterpret_cast<uint32_t *>(&tile[k][p * 8]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) row[e] = v[e];
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < DH * 8; idx += 256) {
-        const int d = idx >> 3, kp = idx & 7;                // channel d, keys kb + 8 * kp .. + 7
-        if (kb + kp * 8 < lpadv) {
-            u32x4_a o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                o[e] = (uint32_t)tile[kp * 8 + 2 * e][d] | ((uint32_t)tile[kp * 8 + 2 * e + 1][d] << 16);
-            *reinterpret_cast<u32x4_a *>(dst + (int64_t)d * lpadv + kb + kp * 8) = o;
-        }
-    }
-}
-
 // K cache [s][kvh][key][dh] -> kfr [s][kvh][tile of 16 keys][dh / 32][64 lanes][8]: lane (l16, lg) of piece kk holds
 // channels 32*kk + 8*lg .. + 7 of key 16*tile + l16, the A operand of mfma_f32_16x16x32_bf16 for that tile; keys from
 // pos0[s] + Tn on are zero. attn_lpad64(L_max) keys per (s, kvh).
@@ -2445,8 +2419,8 @@ static bool launch_attn_select_t(const void *q, const void *kc, SelRow *sel, con
 }
 
 template <int DH, int G, bool PRE = false>
-static bool launch_attn_pv_t(const void *q, const void *kc, const void *vt, const SelRow *sel, float *o32,
-                             const int32_t *pos0, int n_seq, int Tn, int L_max, int Hq, int Hkv, int lpadv, hipStream_t st,
+static bool launch_attn_pv_t(const void *q, const void *kc, const void *vc, const SelRow *sel, float *o32,
+                             const int32_t *pos0, int n_seq, int Tn, int L_max, int Hq, int Hkv, hipStream_t st,
                              PrefixView pv = PrefixView())
 {
     const size_t lds = 4 * (size_t)64 * DH * 2;
@@ -2461,11 +2435,11 @@ static bool launch_attn_pv_t(const void *q, const void *kc, const void *vt, cons
     }
     if (Tn <= 16)                                            // one tile of 16 query rows per workgroup
         hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 1>), dim3(1, Hkv, n_seq), dim3(G * 64), lds, st, (const bf16_t *)q,
-                           (const bf16_t *)kc, (const bf16_t *)vt, sel, o32, pos0, Tn, L_max, Hq, Hkv, lpadv,
+                           (const bf16_t *)kc, (const bf16_t *)vc, sel, o32, pos0, Tn, L_max, Hq, Hkv,
                            1.0f / sqrtf((float)DH), pv);
     else
         hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 2>), dim3(((Tn + 31) / 32 + 1) / 2, Hkv, n_seq), dim3(G * 64), lds, st,
-                           (const bf16_t *)q, (const bf16_t *)kc, (const bf16_t *)vt, sel, o32, pos0, Tn, L_max, Hq, Hkv, lpadv,
+                           (const bf16_t *)q, (const bf16_t *)kc, (const bf16_t *)vc, sel, o32, pos0, Tn, L_max, Hq, Hkv,
                            1.0f / sqrtf((float)DH), pv);
     return true;
 }
@@ -2672,15 +2646,15 @@ template <int DH, int G, int W, bool PRE, int NQT>
 // configuration; head size 128 with 4+ heads per group: 2 waves per SIMD, 256 registers instead of 410, 4.51 -> 2.44 ms
 // at the 8B shape with 4096-token sequences)
 __global__ void __launch_bounds__(G * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? (NQT == 1 ? 4 : 3) : (G >= 4 ? 2 : 1), 8)))
-k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vt,
+k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc,
                 const unsigned long long *__restrict__ selp, float *__restrict__ o32, const int32_t *__restrict__ pos0, int Tn,
-                int L_max, int Hq, int Hkv, int lpadv, float scale, int log2S, int n_sink, int n_window, PrefixView pv)
+                int L_max, int Hq, int Hkv, float scale, int log2S, int n_sink, int n_window, PrefixView pv)
 {
     constexpr int NT = G * 64, KK = DH / 32, DT = DH / 16, KC = 64, QT = 16 * NQT;
     constexpr int KP = DH / 8;
-    constexpr int K_PIECES = KC * KP / NT, V_PIECES = DH * (KC / 8) / NT;
+    constexpr int PIECES = KC * KP / NT;                     // of K and of V, per thread and chunk
     constexpr int K_BYTES = KC * DH * 2, STAGE = 2 * K_BYTES;
-    static_assert(KC * KP % NT == 0 && DH * (KC / 8) % NT == 0, "chunk / thread mismatch");
+    static_assert(KC * KP % NT == 0, "chunk / thread mismatch");
     extern __shared__ __align__(16) unsigned char pvl[];
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
@@ -2697,13 +2671,13 @@ k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, con
     const int n_max = p0 + q0 + rows;
     const int n_chunks = (n_max + KC - 1) / KC;
     const bf16_t *kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
-    const bf16_t *vbase = vt + ((int64_t)s * Hkv + kvh) * (int64_t)DH * lpadv;
+    const bf16_t *vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
     const bf16_t *kpre = nullptr, *vpre = nullptr;
     if constexpr (PRE) {                                    // own segment addressed by absolute key: bases minus P keys
         kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)pv.crows * DH - (int64_t)pv.P * DH;
-        vbase = vbase - pv.P;
+        vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)pv.crows * DH - (int64_t)pv.P * DH;
         kpre = pv.k + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)pv.P * DH;
-        vpre = pv.vt + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)DH * pv.lpadv;
+        vpre = pv.v + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)pv.P * DH;
     }
     const float sl2 = scale * 1.44269504088896341f;          // scores in the log2 domain
 
@@ -2737,34 +2711,27 @@ k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, con
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) oacc[qt][dt] = floatx4_a{0.f, 0.f, 0.f, 0.f};
 
-    u32x4_a kreg0[K_PIECES], vreg0[V_PIECES];
+    u32x4_a kreg0[PIECES], vreg0[PIECES];
 #define SOL_PV_GLOAD(KR, VR, CH_)                                                                                  \
     {                                                                                                      \
         const int key0_ = (CH_) * KC;                                                                      \
         const bool pre_ = PRE && key0_ < pv.P;              /* chunk-uniform: P is a multiple of the chunk */ \
         const bf16_t *kb_ = pre_ ? kpre : kbase, *vb_ = pre_ ? vpre : vbase;                               \
-        const int64_t vs_ = pre_ ? pv.lpadv : lpadv;                                                       \
-        _Pragma("unroll") for (int i = 0; i < K_PIECES; ++i) {                                             \
+        _Pragma("unroll") for (int i = 0; i < PIECES; ++i) {                                             \
             const int pc = i * NT + tid, row = pc / KP, piece = pc - row * KP;                             \
             int key = key0_ + row;                                                                         \
             if (key >= n_max) key = n_max - 1;                                                             \
             KR[i] = *reinterpret_cast<const u32x4_a *>(kb_ + (int64_t)key * DH + piece * 8);               \
-        }                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < V_PIECES; ++i) {                                             \
-            const int pc = i * NT + tid, d = pc >> 3, piece = pc & 7;                                      \
-            VR[i] = *reinterpret_cast<const u32x4_a *>(vb_ + (int64_t)d * vs_ + key0_ + piece * 8);        \
+            VR[i] = *reinterpret_cast<const u32x4_a *>(vb_ + (int64_t)key * DH + piece * 8);               \
         }                                                                                                  \
     }
 #define SOL_PV_LSTORE(KR, VR, STG_)                                                                                \
     {                                                                                                      \
         unsigned char *kb_ = pvl + (STG_) * STAGE, *vb_ = kb_ + K_BYTES;                                   \
-        _Pragma("unroll") for (int i = 0; i < K_PIECES; ++i) {                                             \
+        _Pragma("unroll") for (int i = 0; i < PIECES; ++i) {                                             \
             const int pc = i * NT + tid, row = pc / KP, piece = pc - row * KP;                             \
             *reinterpret_cast<u32x4_a *>(kb_ + row * (DH * 2) + ((piece ^ pv_swz_k<DH>(row)) << 4)) = KR[i]; \
-        }                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < V_PIECES; ++i) {                                             \
-            const int pc = i * NT + tid, d = pc >> 3, piece = pc & 7;                                      \
-            *reinterpret_cast<u32x4_a *>(vb_ + d * (KC * 2) + ((piece ^ ((d >> 1) & 7)) << 4)) = VR[i];    \
+            *reinterpret_cast<u32x4_a *>(vb_ + row * (DH * 2) + ((piece ^ pv_swz_v<DH>(row)) << 4)) = VR[i]; \
         }                                                                                                  \
     }
     SOL_PV_GLOAD(kreg0, vreg0, 0);
@@ -2867,9 +2834,7 @@ k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, con
                 }
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
-                    const int d = dt * 16 + l16;
-                    const bf16x8_a vf = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(
-                        vb + d * (KC * 2) + (((cc * 4 + lg) ^ ((d >> 1) & 7)) << 4)));
+                    const bf16x8_a vf = pv_read_v<DH>(vb, cc * 32 + 8 * lg, dt, l16);
 #pragma unroll
                     for (int qt = 0; qt < NQT; ++qt) {
                         oacc[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo[qt], vf, oacc[qt][dt], 0, 0, 0);
@@ -2902,7 +2867,7 @@ k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, con
     }   // pass
 }
 
-int attn_tile_lpadv(int L_max) { return attn_lpad64(L_max); }
+int attn_tile_lpad(int L_max) { return attn_lpad64(L_max); }
 size_t attn_tile_sel_bytes(int64_t rows, int Hq) { return (size_t)rows * Hq * sizeof(SelRow); }
 
 bool launch_attn_frag_k(const void *k_cache, void *kfr, const int32_t *pos0, int n_seq, int T, int L_max, int Hkv, int dh,
@@ -2918,7 +2883,7 @@ bool launch_attn_frag_k(const void *k_cache, void *kfr, const int32_t *pos0, int
     return true;
 }
 
-bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, void *vt, void *kfr, void *sel_ws, float *o32,
+bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, void *kfr, void *sel_ws, float *o32,
                       const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh,
                       hipStream_t st)
 {
@@ -2926,15 +2891,7 @@ bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, v
     const int G = Hkv > 0 ? Hq / Hkv : 0;
     if ((dh != 64 && dh != 128) || L_max > 4096 || T < 16 || G * Hkv != Hq || (G != 1 && G != 2 && G != 4 && G != 8))
         return false;
-    const int lpadv = attn_tile_lpadv(L_max);
     SelRow *sel = (SelRow *)sel_ws;
-    const dim3 tg((lpadv + 63) / 64, Hkv, n_seq);
-    if (dh == 64)
-        hipLaunchKernelGGL((k_transpose_v<64>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
-    else
-        hipLaunchKernelGGL((k_transpose_v<128>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
     // K in MFMA operand order for the threshold kernel, which reads all causal keys once per block of 8 or 16 query rows
     // (up to 256 keys the copy does not pay)
     const bool frag = L_max > 256;
@@ -2961,8 +2918,8 @@ bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, v
 #undef SOL_SEL
     if (!ok) return false;
 #define SOL_PV(G_)                                                                                                   \
-    return dh == 64 ? launch_attn_pv_t<64, G_>(q, k_cache, vt, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, st)  \
-                    : launch_attn_pv_t<128, G_>(q, k_cache, vt, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, st)
+    return dh == 64 ? launch_attn_pv_t<64, G_>(q, k_cache, v_cache, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, st)  \
+                    : launch_attn_pv_t<128, G_>(q, k_cache, v_cache, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, st)
     if (G == 1) { SOL_PV(1); }
     if (G == 2) { SOL_PV(2); }
     if (G == 4) { SOL_PV(4); }
@@ -2971,7 +2928,7 @@ bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, v
 }
 
 // launch_attn_tile for sequences that share prefix caches (PrefixView): k_cache / v_cache hold positions pv.P.. only
-// ([n_seq][Hkv][pv.crows][dh]), vt is scratch for their transposed copy ([n_seq][Hkv][dh][attn_tile_lpadv(pv.crows)]);
+// ([n_seq][Hkv][pv.crows][dh]);
 // every sequence's T rows sit at positions pv.P .. pv.P + T - 1. Returns false (nothing launched) outside the shapes
 // of launch_attn_tile, if pv.P is not a multiple of 64 or the caches lie 2^31 elements or more apart.
 // shape and address limits of launch_attn_tile_prefix (only differences of the pointers are looked at)
@@ -2998,23 +2955,15 @@ bool attn_tile_prefix_ok(const void *k_cache, int n_seq, int T, int Hq, int Hkv,
     return true;
 }
 
-bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_cache, void *vt, void *sel_ws, float *o32,
+bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_cache, void *sel_ws, float *o32,
                              const RowAct *ra, const int32_t *pos0, int n_seq, int T, int Hq, int Hkv, int dh, PrefixView pv,
                              hipStream_t st)
 {
     if ((int64_t)n_seq * T <= 0) return true;
     if (pv.kf && !attn_tile_prefix_ok(k_cache, n_seq, T, Hq, Hkv, dh, pv)) pv.kf = nullptr;   // copy out of reach: do without
-    if (!pv.k || !pv.vt || !attn_tile_prefix_ok(k_cache, n_seq, T, Hq, Hkv, dh, pv)) return false;
+    if (!pv.k || !pv.v || !attn_tile_prefix_ok(k_cache, n_seq, T, Hq, Hkv, dh, pv)) return false;
     const int G = Hq / Hkv, L_max = pv.P + T;
-    const int lpadv = attn_tile_lpadv(pv.crows);
     SelRow *sel = (SelRow *)sel_ws;
-    const dim3 tg((lpadv + 63) / 64, Hkv, n_seq);
-    if (dh == 64)
-        hipLaunchKernelGGL((k_transpose_v<64>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt,
-                           (const int32_t *)nullptr, T, pv.crows, Hkv, lpadv);
-    else
-        hipLaunchKernelGGL((k_transpose_v<128>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt,
-                           (const int32_t *)nullptr, T, pv.crows, Hkv, lpadv);
     bool ok;
     // rows longer than 1024 keys read the prefix keys from their copy in operand order, if the view has one
 #define SOL_SEL(BQ, SL, KF)                                                                                          \
@@ -3033,8 +2982,8 @@ bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_c
 #undef SOL_SEL
     if (!ok) return false;
 #define SOL_PV(G_)                                                                                                   \
-    return dh == 64 ? launch_attn_pv_t<64, G_, true>(q, k_cache, vt, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, st, pv)  \
-                    : launch_attn_pv_t<128, G_, true>(q, k_cache, vt, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, st, pv)
+    return dh == 64 ? launch_attn_pv_t<64, G_, true>(q, k_cache, v_cache, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, st, pv)  \
+                    : launch_attn_pv_t<128, G_, true>(q, k_cache, v_cache, sel, o32, pos0, n_seq, T, L_max, Hq, Hkv, st, pv)
     if (G == 1) { SOL_PV(1); }
     if (G == 2) { SOL_PV(2); }
     if (G == 4) { SOL_PV(4); }
@@ -3042,11 +2991,11 @@ bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_c
 #undef SOL_PV
 }
 
-// PRE: kc / vt / pm belong to the sequences' own keys (pv.crows rows each, positions pv.P..), L_max = pv.P + T.
+// PRE: kc / vc / pm belong to the sequences' own keys (pv.crows rows each, positions pv.P..), L_max = pv.P + T.
 template <int DH, int W, bool PRE = false>
-static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *vt, void *pm, void *selp, float *o32,
+static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *vc, void *pm, void *selp, float *o32,
                                      const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv,
-                                     int lpadv, int log2S, AttnOpts opt, hipStream_t st, PrefixView pv = PrefixView())
+                                     int log2S, AttnOpts opt, hipStream_t st, PrefixView pv = PrefixView())
 {
     const int S = 1 << log2S, G = Hq / Hkv;
     constexpr int ppb = 256 / (DH / 8);
@@ -3071,8 +3020,8 @@ static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *
             attr_done = true;                                                                                        \
         }                                                                                                            \
         hipLaunchKernelGGL(kern, dim3(((T + 16 * NQT_ - 1) / (16 * NQT_) + 1) / 2, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
-                           (const bf16_t *)kc, (const bf16_t *)vt, (const unsigned long long *)selp, o32, pos0, T, L_max, Hq, \
-                           Hkv, lpadv, scale, log2S, opt.n_sink, opt.n_window, pv);                                  \
+                           (const bf16_t *)kc, (const bf16_t *)vc, (const unsigned long long *)selp, o32, pos0, T, L_max, Hq, \
+                           Hkv, scale, log2S, opt.n_sink, opt.n_window, pv);                                  \
         return true;                                                                                                 \
     }
     if (T <= 16) {                                           // one tile of 16 query rows per workgroup
@@ -3090,21 +3039,13 @@ static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *
 
 // Dense causal attention for rows that keep every key (prefill, cache refresh): the flash-style kernel alone, with
 // its running maximum, no threshold pass. Shapes of launch_attn_tile.
-bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_cache, void *vt, float *o32,
+bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_cache, float *o32,
                             const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, hipStream_t st)
 {
     if ((int64_t)n_seq * T <= 0) return true;
     const int G = Hkv > 0 ? Hq / Hkv : 0;
-    if ((dh != 64 && dh != 128) || L_max > 4096 || T < 16 || G * Hkv != Hq || (G != 1 && G != 2 && G != 4 && G != 8) || !vt)
+    if ((dh != 64 && dh != 128) || L_max > 4096 || T < 16 || G * Hkv != Hq || (G != 1 && G != 2 && G != 4 && G != 8))
         return false;
-    const int lpadv = attn_tile_lpadv(L_max);
-    const dim3 tg((lpadv + 63) / 64, Hkv, n_seq);
-    if (dh == 64)
-        hipLaunchKernelGGL((k_transpose_v<64>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
-    else
-        hipLaunchKernelGGL((k_transpose_v<128>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
     const size_t lds = 4 * (size_t)64 * dh * 2;
     const float scale = 1.0f / sqrtf((float)dh);
 #define SOL_PVD2(DH_, G_, NQT_)                                                                                      \
@@ -3114,8 +3055,8 @@ bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_ca
                                 (int)lds) != hipSuccess)                                                             \
             return false;                                                                                            \
         hipLaunchKernelGGL(kern, dim3(((T + 16 * NQT_ - 1) / (16 * NQT_) + 1) / 2, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
-                           (const bf16_t *)k_cache, (const bf16_t *)vt, (const unsigned long long *)nullptr, o32, pos0, T, \
-                           L_max, Hq, Hkv, lpadv, scale, 6, 0, 0, PrefixView());                                     \
+                           (const bf16_t *)k_cache, (const bf16_t *)v_cache, (const unsigned long long *)nullptr, o32, pos0, T, \
+                           L_max, Hq, Hkv, scale, 6, 0, 0, PrefixView());                                     \
         return true;                                                                                                 \
     }
 #define SOL_PVD(DH_, G_) { if (T <= 16) SOL_PVD2(DH_, G_, 1) SOL_PVD2(DH_, G_, 2) }
@@ -3138,7 +3079,7 @@ size_t attn_tile_pages_sel_bytes(int64_t rows, int Hq, int L_max, int S) { retur
 
 // Batched bf16 attention under the page rule: page size a power of two in [4, 64], at most 256 pages, the limits of
 // launch_attn_tile otherwise. pm: attn_tile_pages_meta_bytes of scratch, selp: attn_tile_pages_sel_bytes.
-bool launch_attn_tile_pages(const void *q, const void *k_cache, const void *v_cache, void *vt, void *pm, void *selp,
+bool launch_attn_tile_pages(const void *q, const void *k_cache, const void *v_cache, void *pm, void *selp,
                             float *o32, const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv,
                             int dh, AttnOpts opt, hipStream_t st)
 {
@@ -3146,22 +3087,14 @@ bool launch_attn_tile_pages(const void *q, const void *k_cache, const void *v_ca
     const int G = Hkv > 0 ? Hq / Hkv : 0, S = opt.page;
     if ((dh != 64 && dh != 128) || L_max > 4096 || T < 16 || G * Hkv != Hq || (G != 1 && G != 2 && G != 4 && G != 8))
         return false;
-    if (S < 4 || S > 64 || (S & (S - 1)) || !pm || !vt) return false;
+    if (S < 4 || S > 64 || (S & (S - 1)) || !pm) return false;
     int log2S = 0;
     while ((1 << log2S) < S) ++log2S;
     const int n_words = ((L_max + S - 1) / S + 63) / 64;
     if (n_words > 4) return false;
-    const int lpadv = attn_tile_lpadv(L_max);
-    const dim3 tg((lpadv + 63) / 64, Hkv, n_seq);
-    if (dh == 64)
-        hipLaunchKernelGGL((k_transpose_v<64>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
-    else
-        hipLaunchKernelGGL((k_transpose_v<128>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt, pos0, T,
-                           L_max, Hkv, lpadv);
 #define SOL_TP(W_)                                                                                                   \
-    return dh == 64 ? launch_attn_tile_pages_t<64, W_>(q, k_cache, vt, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, log2S, opt, st) \
-                    : launch_attn_tile_pages_t<128, W_>(q, k_cache, vt, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, log2S, opt, st)
+    return dh == 64 ? launch_attn_tile_pages_t<64, W_>(q, k_cache, v_cache, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, log2S, opt, st) \
+                    : launch_attn_tile_pages_t<128, W_>(q, k_cache, v_cache, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, log2S, opt, st)
     if (n_words == 1) { SOL_TP(1); }
     if (n_words == 2) { SOL_TP(2); }
     SOL_TP(4);
@@ -3195,31 +3128,23 @@ bool attn_tile_pages_prefix_ok(int n_seq, int T, int Hq, int Hkv, int dh, int S,
     return pv.P > 0 && pv.P % 64 == 0 && pv.P % (16 * S) == 0 && pv.K >= 1 && n_seq % pv.K == 0 && T <= pv.crows;
 }
 
-// launch_attn_tile_pages for sequences that share prefix caches (PrefixView: pv.k, pv.vt and pv.pm of the input's
-// prefix, written by the prefix pass and launch_page_prefix_meta); k_cache / v_cache / vt / pm hold the sequences'
+// launch_attn_tile_pages for sequences that share prefix caches (PrefixView: pv.k, pv.v and pv.pm of the input's
+// prefix, written by the prefix pass and launch_page_prefix_meta); k_cache / v_cache / pm hold the sequences'
 // own pv.crows positions from pv.P on.
-bool launch_attn_tile_pages_prefix(const void *q, const void *k_cache, const void *v_cache, void *vt, void *pm, void *selp,
+bool launch_attn_tile_pages_prefix(const void *q, const void *k_cache, const void *v_cache, void *pm, void *selp,
                                    float *o32, const RowAct *ra, const int32_t *pos0, int n_seq, int T, int Hq, int Hkv,
                                    int dh, AttnOpts opt, PrefixView pv, hipStream_t st)
 {
     if ((int64_t)n_seq * T <= 0) return true;
     const int S = opt.page;
-    if (!pv.k || !pv.vt || !pv.pm || !pm || !vt || !attn_tile_pages_prefix_ok(n_seq, T, Hq, Hkv, dh, S, pv)) return false;
+    if (!pv.k || !pv.v || !pv.pm || !pm || !attn_tile_pages_prefix_ok(n_seq, T, Hq, Hkv, dh, S, pv)) return false;
     const int L_max = pv.P + T;
     int log2S = 0;
     while ((1 << log2S) < S) ++log2S;
     const int n_words = ((L_max + S - 1) / S + 63) / 64;
-    const int lpadv = attn_tile_lpadv(pv.crows);
-    const dim3 tg((lpadv + 63) / 64, Hkv, n_seq);
-    if (dh == 64)
-        hipLaunchKernelGGL((k_transpose_v<64>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt,
-                           (const int32_t *)nullptr, T, pv.crows, Hkv, lpadv);
-    else
-        hipLaunchKernelGGL((k_transpose_v<128>), tg, dim3(256), 0, st, (const bf16_t *)v_cache, (bf16_t *)vt,
-                           (const int32_t *)nullptr, T, pv.crows, Hkv, lpadv);
 #define SOL_TPP(W_)                                                                                                  \
-    return dh == 64 ? launch_attn_tile_pages_t<64, W_, true>(q, k_cache, vt, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, log2S, opt, st, pv) \
-                    : launch_attn_tile_pages_t<128, W_, true>(q, k_cache, vt, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, lpadv, log2S, opt, st, pv)
+    return dh == 64 ? launch_attn_tile_pages_t<64, W_, true>(q, k_cache, v_cache, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, log2S, opt, st, pv) \
+                    : launch_attn_tile_pages_t<128, W_, true>(q, k_cache, v_cache, pm, selp, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, log2S, opt, st, pv)
     if (n_words == 1) { SOL_TPP(1); }
     if (n_words == 2) { SOL_TPP(2); }
     SOL_TPP(4);

@@ -156,50 +156,49 @@ bool launch_attn_decode_paged(const void *q, const void *k_cache, const void *v_
                               const RowAct *ra, const int32_t *cache_len, const int32_t *seq_order, int B, int L_max, int Hq,
                               int Hkv, int dh, AttnOpts opt, int *flags, hipStream_t st);
 // A prefix cache shared by groups of K consecutive sequences (the schedules of one input): keys [0, P) of sequence s
-// come from k / vt of input s / K ([inputs][Hkv][P][dh], transposed copy [inputs][Hkv][dh][lpadv]); the sequence's own
+// come from k / v of input s / K ([inputs][Hkv][P][dh]); the sequence's own
 // cache then holds positions P.. only, crows rows per (sequence, KV head). P a multiple of 64.
 struct PrefixView {
-    const bf16_t *k = nullptr, *vt = nullptr;
+    const bf16_t *k = nullptr, *v = nullptr;
     const bf16_t *kf = nullptr;           // optional: the prefix K caches in MFMA operand order (launch_attn_frag_k)
-    int P = 0, K = 1, lpadv = 0, crows = 0;
+    int P = 0, K = 1, crows = 0;
     const bf16_t *pm = nullptr;           // page rule: metadata rows of the prefix keys ([inputs][Hkv][P][2 * dh])
 };
 bool launch_page_prefix_meta(const void *k_cache, void *pm, int n_seq, int P, int Hkv, int dh, int S, hipStream_t st);
 bool attn_tile_pages_prefix_ok(int n_seq, int T, int Hq, int Hkv, int dh, int S, const PrefixView &pv);
-bool launch_attn_tile_pages_prefix(const void *q, const void *k_cache, const void *v_cache, void *vt, void *pm, void *selp,
+bool launch_attn_tile_pages_prefix(const void *q, const void *k_cache, const void *v_cache, void *pm, void *selp,
                                    float *o32, const RowAct *ra, const int32_t *pos0, int n_seq, int T, int Hq, int Hkv,
                                    int dh, AttnOpts opt, PrefixView pv, hipStream_t st);
 // Batched bf16 attention (L_max <= 4096, head_dim 64 or 128, 1/2/4/8 query heads per KV head): a threshold
-// kernel followed by a flash-style masked softmax * V kernel. vt is workspace for the transposed V copy
-// (n_seq * Hkv * dh * attn_tile_lpadv(L_max) elements), kfr for the copy of K in MFMA operand order (as many),
+// kernel followed by a flash-style masked softmax * V kernel. kfr is workspace for the copy of K in MFMA operand order
+// (n_seq * Hkv * dh * attn_tile_lpad(L_max) elements),
 // sel_ws for the per-(row, head) thresholds (attn_tile_sel_bytes(rows, Hq) bytes).
-bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, void *vt, void *kfr, void *sel_ws, float *o32,
+bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, void *kfr, void *sel_ws, float *o32,
                       const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh,
                       hipStream_t st);
 size_t attn_tile_sel_bytes(int64_t rows, int Hq);
-// K cache [n_seq][Hkv][L_max][dh] -> kfr [n_seq][Hkv][attn_tile_lpadv(L_max) / 16][dh / 32][64][8], the order in which
+// K cache [n_seq][Hkv][L_max][dh] -> kfr [n_seq][Hkv][attn_tile_lpad(L_max) / 16][dh / 32][64][8], the order in which
 // the threshold kernel's MFMAs take it (keys from pos0[s] + T on are zero; pos0 == nullptr: 0). False: head size.
 bool launch_attn_frag_k(const void *k_cache, void *kfr, const int32_t *pos0, int n_seq, int T, int L_max, int Hkv, int dh,
                         hipStream_t st);
-// The same for sequences that share prefix caches: k_cache / v_cache hold positions pv.P.. only, vt is scratch for
-// their transposed copy (n_seq * Hkv * dh * attn_tile_lpadv(pv.crows) elements); the T rows of every sequence sit at
+// The same for sequences that share prefix caches: k_cache / v_cache hold positions pv.P.. only; the T rows of every sequence sit at
 // positions pv.P.. (pos0 must say so). False if a shape or address limit is not met (nothing launched).
 bool attn_tile_prefix_ok(const void *k_cache, int n_seq, int T, int Hq, int Hkv, int dh, const PrefixView &pv);
-bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_cache, void *vt, void *sel_ws, float *o32,
+bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_cache, void *sel_ws, float *o32,
                              const RowAct *ra, const int32_t *pos0, int n_seq, int T, int Hq, int Hkv, int dh, PrefixView pv,
                              hipStream_t st);
 // The same under the page rule (page size a power of two in [4, 64], at most 256 pages) with sink / window keys:
 // per-key prefix extremes of the pages (pm scratch), a bit mask of kept pages per (row, head) (selp scratch), then
 // the flash-style kernel with a running maximum.
-bool launch_attn_tile_pages(const void *q, const void *k_cache, const void *v_cache, void *vt, void *pm, void *selp,
+bool launch_attn_tile_pages(const void *q, const void *k_cache, const void *v_cache, void *pm, void *selp,
                             float *o32, const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv,
                             int dh, AttnOpts opt, hipStream_t st);
 size_t attn_tile_pages_meta_bytes(int64_t n_seq, int Hkv, int L_max, int dh);
 // Dense causal attention (every row keeps every key): the flash-style kernel alone. Shapes of launch_attn_tile.
-bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_cache, void *vt, float *o32,
+bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_cache, float *o32,
                             const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, hipStream_t st);
 size_t attn_tile_pages_sel_bytes(int64_t rows, int Hq, int L_max, int S);
-int attn_tile_lpadv(int L_max);
+int attn_tile_lpad(int L_max);
 
 // ---- reward reduction (sol_reward.hip) ----------------------------------------------------------
 struct RewardCfg { float alpha_kappa, alpha_rho, alpha_eta, tau, gamma, eps; };
