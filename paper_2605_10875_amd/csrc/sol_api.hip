@@ -450,7 +450,9 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
     int ns_gu = 1;
     {   // gate / up (+ SiLU(gate)*up when fused)
         STAGE(ctx, ST_GATEUP, st);
-        if (skinny) {
+        if (skinny && gemv_rows_ok(M)) fused_gu = launch_gemv_gateup_silu(w.h, lw->w_gate, lw->w_up, w.a, M, dff, d, st);
+        if (fused_gu) {
+        } else if (skinny) {
             ns_gu = skinny_splits((int)M, 2 * dff, d);
             if (!launch_gemm_skinny(w.h, d, lw->w_gate, dff, lw->w_up, dff, nullptr, 0, (int)M, d, w.big32, ns_gu, st))
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM (gate / up): unsupported shape");
@@ -478,7 +480,13 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
     const bool q_out = (qs & SOL_QS_MLP_OUT) != 0;   // the MLP output is quantised as a whole row before the residual add
     {   // down projection (+ residual when fused)
         STAGE(ctx, ST_DOWN, st);
-        if (skinny) {
+        bool done = false;
+        if (skinny && gemv_rows_ok(M)) {
+            if (q_out) done = launch_gemv_f32(w.a, lw->w_down, w.big32, M, d, dff, st);
+            else done = fused_down = launch_gemv_resid_out(w.a, lw->w_down, w.x2, x_out, M, d, dff, st);
+        }
+        if (done) {
+        } else if (skinny) {
             ns_down = skinny_splits((int)M, d, dff);
             if (!launch_gemm_skinny(w.a, dff, lw->w_down, d, nullptr, 0, nullptr, 0, (int)M, dff, w.big32, ns_down, st))
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM (down): unsupported shape");
@@ -522,7 +530,11 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     int ns_qkv = 1;
     {   // q/k/v projections (+ rotary and cache write when fused)
         STAGE(ctx, ST_QKV, st);
-        if (skinny) {
+        if (skinny && gemv_rows_ok(M))
+            fused_qkv = launch_gemv_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, n_seq, T, L_max, Hq, Hkv,
+                                             dh, d, ctx->d_flags, st, crows);
+        if (fused_qkv) {
+        } else if (skinny) {
             ns_qkv = skinny_splits((int)M, nqkv, d);
             if (!launch_gemm_skinny(w.h, d, lw->wq, nq, lw->wk, nkv, lw->wv, nkv, (int)M, d, w.big32, ns_qkv, st))
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM: unsupported shape");
@@ -552,7 +564,9 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     int ns_o = 1;
     {   // output projection (+ residual when fused: x2 = x + attn)
         STAGE(ctx, ST_OPROJ, st);
-        if (skinny) {
+        if (skinny && gemv_rows_ok(M)) fused_o = launch_gemv_resid_f32(w.qb, lw->wo, x_in, w.x2, M, d, nq, st);
+        if (fused_o) {
+        } else if (skinny) {
             ns_o = skinny_splits((int)M, d, nq);
             if (!launch_gemm_skinny(w.qb, nq, lw->wo, d, nullptr, 0, nullptr, 0, (int)M, nq, w.big32, ns_o, st))
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM (output projection): unsupported shape");

@@ -120,6 +120,19 @@ bool launch_gemm_skinny(const void *x, int64_t ldx, const void *w0, int n0, cons
                         int n2, int M, int K, float *partial, int nsplit, hipStream_t st);
 int skinny_splits(int M, int Nv, int K);
 
+// ---- linear maps of very few rows with what follows them (sol_gemv.hip) --------------------------
+// Up to GEMV_MAX_ROWS bf16 rows, K a multiple of 512; otherwise false (nothing launched). Arguments as the MFMA launchers
+// of the same names; no scratch. launch_gemv_f32: C [M][N].
+constexpr int GEMV_MAX_ROWS = 4;
+bool gemv_rows_ok(int64_t M);
+bool launch_gemv_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
+                          const float2 *rope, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int d,
+                          int *flags, hipStream_t st, int cache_rows = 0);
+bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, float *out, int64_t M, int N, int K, hipStream_t st);
+bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int64_t M, int dff, int d, hipStream_t st);
+bool launch_gemv_resid_out(const void *a, const void *w, const float *x2, void *out, int64_t M, int N, int K, hipStream_t st);
+bool launch_gemv_f32(const void *a, const void *w, float *C, int64_t M, int N, int K, hipStream_t st);
+
 // ---- attention (sol_attn.hip) ----------------------------------------------------------------
 // One query row per workgroup group: scores over cache positions [0, pos], budgeted top-k,
 // softmax over kept keys, times V. o32: fp32 [M][Hq*dh]. Returns false if the shape is unsupported.

@@ -1,0 +1,51 @@
+"""Layers of one to four rows (the linear maps whose waves finish their sums) and of five (the K-split kernel), against the
+oracle under non-quantising actions: sequences and tokens per sequence, widths of one and of several chunks of K with a
+short last one, the page preset's MLP path (pruning at the MLP input, quantiser on the output off), both head sizes."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import check_rows, dev, dev_weights, host
+import oracle
+from paper_2605_10875_amd import sol, synth
+
+pytestmark = pytest.mark.gpu
+
+TABLE = synth.action_table((0.25, 0.5, 1.0), (0.0, 0.5), (16,))
+
+
+@pytest.mark.parametrize("opts", [{}, dict(prune_site=1, quant_sites=sol.QS_MLP_OUT)], ids=["default", "mlp_in"])
+@pytest.mark.parametrize("shape", [synth.ModelShape(512, 8, 2, 64, 2560), synth.ModelShape(2560, 4, 1, 128, 1024)],
+                         ids=["head64", "head128"])
+@pytest.mark.parametrize("n_seq,T", [(1, 1), (2, 1), (1, 3), (4, 1), (2, 2), (5, 1)])
+def test_layer_of_few_rows(n_seq, T, shape, opts):
+    L = 40
+    w = synth.layer_weights(shape, 11, bf16=True)
+    x = synth.hidden_states(n_seq, T, shape.d_model, 12, bf16=True)
+    ids = synth.iid_actions(len(TABLE), (n_seq, T), 13)
+    pos0 = (7 * np.arange(n_seq) % (L - T)).astype(np.int32)
+    kc, vc = synth.kv_cache(n_seq, shape.n_kv_heads, L, shape.head_dim, 14, bf16=True)
+    ko, vo = kc.copy(), vc.copy()
+    ref, _ = oracle.layer_forward(oracle.make_cfg(shape, act_bf16=True, **opts), oracle.make_table(TABLE), w, x, ids, ko, vo, pos0=pos0)
+    ctx = sol.Sol(shape, TABLE, max_positions=L, **opts)
+    kd, vd = dev(kc, sol.BF16), dev(vc, sol.BF16)
+    out = ctx.layer_forward(dev_weights(w, sol.BF16), dev(x, sol.BF16), dev(ids), kd, vd, pos0=dev(pos0))
+    assert ctx.device_status() == sol.OK
+    # the contract for rows of non-quantising actions
+    check_rows(host(out), ref, 2e-2, 2e-2, 0.0, "layer output", median=1e-2)
+    check_rows(host(kd), ko, 2e-2, 2e-2, 0.0, "K cache")
+    check_rows(host(vd), vo, 2e-2, 2e-2, 0.0, "V cache")
+
+
+def test_a_row_that_does_not_fit_is_skipped_and_flagged():
+    shape, L = synth.ModelShape(512, 8, 2, 64, 1024), 16
+    w = dev_weights(synth.layer_weights(shape, 1, bf16=True), sol.BF16)
+    x = dev(synth.hidden_states(2, 1, 512, 2, bf16=True), sol.BF16)
+    ids = torch.zeros((2, 1), dtype=torch.int32, device="cuda")
+    kc, vc = (dev(t, sol.BF16) for t in synth.kv_cache(2, 2, L, 64, 3, bf16=True))
+    before = kc.clone()
+    ctx = sol.Sol(shape, TABLE, max_positions=L)
+    ctx.layer_forward(w, x, ids, kc, vc, pos0=torch.tensor([3, L], dtype=torch.int32, device="cuda"))
+    assert ctx.device_status() == sol.ERR_CACHE_OVERFLOW
+    assert torch.equal(kc[1], before[1]) and not torch.equal(kc[0, :, 3], before[0, :, 3])
+    assert torch.equal(kc[0, :, :3], before[0, :, :3]) and torch.equal(kc[0, :, 4:], before[0, :, 4:])
