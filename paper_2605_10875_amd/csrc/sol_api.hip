@@ -260,6 +260,7 @@ struct LayerWs {
     float *big32, *o32, *x2, *hn32;
     void *dsp = nullptr;                   // scratch of the split decode attention, where the step takes it
     const float *o_src = nullptr;          // the attention stage's output: o_splits partial sums [M][nq] (o32 and 1 by default)
+    const DecSel *o_sel = nullptr;         // with several partial sums: their denominators
     int o_splits = 1;
 };
 
@@ -416,9 +417,10 @@ static int attn_stage(sol_ctx *ctx, LayerWs &w, const int32_t *pos0, void *kc, v
             attn_tile_pages_sel_bytes(M, Hq, L_max, opt.page) <= 4 * (size_t)M * nqkv)   // the masks live in big32
             tiled = launch_attn_tile_pages(w.qb, kc, vc, w.pm, w.big32, w.o32, w.ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, opt, st);
         w.o_src = w.o32;
+        w.o_sel = nullptr;
         w.o_splits = 1;
         bool dec = !tiled && fast && T == 1 && pos0 && w.dsp &&
-                   launch_attn_decode_split(w.qb, kc, vc, w.dsp, w.ra, pos0, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st, &w.o_src, &w.o_splits);
+                   launch_attn_decode_split(w.qb, kc, vc, w.dsp, w.ra, pos0, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st, &w.o_src, &w.o_sel, &w.o_splits);
         dec = dec || (!tiled && fast && T == 1 && pos0 &&
                    launch_attn_decode(w.qb, kc, vc, w.o32, w.ra, pos0, w.seq_order, n_seq, L_max, Hq, Hkv, dh, ctx->d_flags, st));
         if (!tiled && !dec && mfma && T == 1 && pos0 && page_meta && opt.page > 1) {
@@ -450,7 +452,7 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
     int ns_gu = 1;
     {   // gate / up (+ SiLU(gate)*up when fused)
         STAGE(ctx, ST_GATEUP, st);
-        if (skinny && gemv_rows_ok(M)) fused_gu = launch_gemv_gateup_silu(w.h, lw->w_gate, lw->w_up, w.a, M, dff, d, st);
+        if (skinny && M == 1) fused_gu = launch_gemv_gateup_silu(w.h, lw->w_gate, lw->w_up, w.a, dff, d, st);
         if (fused_gu) {
         } else if (skinny) {
             ns_gu = skinny_splits((int)M, 2 * dff, d);
@@ -481,9 +483,9 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
     {   // down projection (+ residual when fused)
         STAGE(ctx, ST_DOWN, st);
         bool done = false;
-        if (skinny && gemv_rows_ok(M)) {
-            if (q_out) done = launch_gemv_f32(w.a, lw->w_down, w.big32, M, d, dff, st);
-            else done = fused_down = launch_gemv_resid_out(w.a, lw->w_down, w.x2, x_out, M, d, dff, st);
+        if (skinny && M == 1) {
+            if (q_out) done = launch_gemv_f32(w.a, lw->w_down, w.big32, d, dff, st);
+            else done = fused_down = launch_gemv_resid_out(w.a, lw->w_down, w.x2, x_out, d, dff, st);
         }
         if (done) {
         } else if (skinny) {
@@ -530,8 +532,8 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     int ns_qkv = 1;
     {   // q/k/v projections (+ rotary and cache write when fused)
         STAGE(ctx, ST_QKV, st);
-        if (skinny && gemv_rows_ok(M))
-            fused_qkv = launch_gemv_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, n_seq, T, L_max, Hq, Hkv,
+        if (skinny && M == 1)
+            fused_qkv = launch_gemv_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, L_max, Hq, Hkv,
                                              dh, d, ctx->d_flags, st, crows);
         if (fused_qkv) {
         } else if (skinny) {
@@ -558,13 +560,13 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     if (int rc = attn_stage(ctx, w, pos0, kc, vc, n_seq, T, L_max, st, page_meta, dense_pass, pv)) return rc;
     {   // quantise (o-proj input)
         STAGE(ctx, ST_QUANT_O, st);
-        launch_fq_rows(w.o_src, w.qb, dt, w.ra, qs & SOL_QS_O_IN, M, nq, st, w.o_splits);
+        launch_fq_rows(w.o_src, w.qb, dt, w.ra, qs & SOL_QS_O_IN, M, nq, st, w.o_splits, w.o_sel, dh);
     }
     bool fused_o = false;
     int ns_o = 1;
     {   // output projection (+ residual when fused: x2 = x + attn)
         STAGE(ctx, ST_OPROJ, st);
-        if (skinny && gemv_rows_ok(M)) fused_o = launch_gemv_resid_f32(w.qb, lw->wo, x_in, w.x2, M, d, nq, st);
+        if (skinny && M == 1) fused_o = launch_gemv_resid_f32(w.qb, lw->wo, x_in, w.x2, d, nq, st);
         if (fused_o) {
         } else if (skinny) {
             ns_o = skinny_splits((int)M, d, nq);
@@ -1127,7 +1129,8 @@ extern "C" int sol_test_attention_stage(sol_ctx *ctx, const void *q, const int32
     if (T == 1 && pos0) take_decode_split(c, ctx->cfg, n_seq, L_max, ws_bytes, lw);
     if (int rc = attn_stage(ctx, lw, pos0, k_cache, v_cache, n_seq, T, L_max, st, nullptr, false, nullptr)) return rc;
     if (lw.o_src != o_out)                                     // partial sums of a split decode attention
-        launch_fq_rows(lw.o_src, o_out, SOL_F32, nullptr, false, (int64_t)n_seq * T, ctx->cfg.n_q_heads * ctx->cfg.head_dim, st, lw.o_splits);
+        launch_fq_rows(lw.o_src, o_out, SOL_F32, nullptr, false, (int64_t)n_seq * T, ctx->cfg.n_q_heads * ctx->cfg.head_dim, st, lw.o_splits,
+                       lw.o_sel, ctx->cfg.head_dim);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, SOL_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return SOL_OK;

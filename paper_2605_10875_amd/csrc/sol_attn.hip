@@ -1198,43 +1198,6 @@ __device__ __forceinline__ auto dec_halve(const DecVals<N> &a, int lane, int &fb
     else return r;
 }
 
-// Sums acc (head x 8 channels of this lane's key slot) over the key slots of the workgroup's NW waves through sc, whose
-// readers must be done with it only at the barrier inside; o_row receives HPB * DH sums over den(head).
-template <int DH, int NW, class Den>
-__device__ __forceinline__ void decode_pv_reduce(const float (&acc)[DEC_HPB][8], float *sc, Den den, float *__restrict__ o_row)
-{
-    constexpr int VEC = 8, LPK = DH / VEC;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Reduce over the key slots of a wave (lanes with equal cs) by halving butterflies: at each step a lane
-    // keeps one half of its values and hands the other half to its partner, so the 4 * VEC values per lane
-    // end as 4 * VEC * LPK / 64 fully reduced ones; then across waves in fixed order.
-    DecVals<DEC_HPB * VEC> flat;
-#pragma unroll
-    for (int i = 0; i < DEC_HPB * VEC; ++i) flat.v[i] = acc[i / VEC][i % VEC];
-    int fbase = 0;                                             // first flattened (head, element) index this lane keeps
-    const auto kept = dec_halve<LPK>(flat, lane, fbase);
-    const float *accf = kept.v;
-    constexpr int NKEEP = DEC_HPB * VEC * LPK / 64;            // 4 (head_dim 64) or 8 (head_dim 128)
-    __syncthreads();                                           // all reads of the numerators are done
-    float *ored = sc;                                          // [NW][HPB][DH]
-    {
-        const int hh = fbase / VEC, e0 = fbase - hh * VEC;     // NKEEP values of one head, elements e0..e0+NKEEP-1
-        float *dst = ored + ((size_t)w * DEC_HPB + hh) * DH + (lane & (LPK - 1)) * VEC + e0;
-#pragma unroll
-        for (int i = 0; i < NKEEP; i += 4)
-            *reinterpret_cast<f32x4_a *>(dst + i) = f32x4_a{accf[i], accf[i + 1], accf[i + 2], accf[i + 3]};
-    }
-    __syncthreads();
-    for (int idx = tid; idx < DEC_HPB * DH; idx += NW * 64) {
-        const int hh = idx / DH;
-        float t = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < NW; ++ww) t += ored[(size_t)ww * DEC_HPB * DH + idx];
-        o_row[idx] = t / den(hh);
-    }
-}
-
 // The last phases of the decode kernels: sc holds the softmax numerators of the HPB heads ([HPB][lpad], 0 for
 // dropped keys), den(head) the denominators (called after a barrier); o_row receives HPB * DH outputs. NW waves.
 //   4. o = sum_j p_j v_j, reading only V rows kept by at least one head; 5. reduction over lanes and waves.
@@ -1283,7 +1246,35 @@ __device__ __forceinline__ void decode_pv_tail(float *sc, int lpad, int n, const
             }
         }
     }
-    decode_pv_reduce<DH, NW>(acc, sc, den, o_row);
+    // ---- 5. reduction --------------------------------------------------------------------------------
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Reduce over the key slots of a wave (lanes with equal cs) by halving butterflies: at each step a lane
+    // keeps one half of its values and hands the other half to its partner, so the 4 * VEC values per lane
+    // end as 4 * VEC * LPK / 64 fully reduced ones; then across waves in fixed order.
+    DecVals<DEC_HPB * VEC> flat;
+#pragma unroll
+    for (int i = 0; i < DEC_HPB * VEC; ++i) flat.v[i] = acc[i / VEC][i % VEC];
+    int fbase = 0;                                             // first flattened (head, element) index this lane keeps
+    const auto kept = dec_halve<LPK>(flat, lane, fbase);
+    const float *accf = kept.v;
+    constexpr int NKEEP = DEC_HPB * VEC * LPK / 64;            // 4 (head_dim 64) or 8 (head_dim 128)
+    __syncthreads();                                           // all reads of the numerators are done
+    float *ored = sc;                                          // [NW][HPB][DH]
+    {
+        const int hh = fbase / VEC, e0 = fbase - hh * VEC;     // NKEEP values of one head, elements e0..e0+NKEEP-1
+        float *dst = ored + ((size_t)w * DEC_HPB + hh) * DH + (lane & (LPK - 1)) * VEC + e0;
+#pragma unroll
+        for (int i = 0; i < NKEEP; i += 4)
+            *reinterpret_cast<f32x4_a *>(dst + i) = f32x4_a{accf[i], accf[i + 1], accf[i + 2], accf[i + 3]};
+    }
+    __syncthreads();
+    for (int idx = tid; idx < DEC_HPB * DH; idx += NW * 64) {
+        const int hh = idx / DH;
+        float t = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) t += ored[(size_t)ww * DEC_HPB * DH + idx];
+        o_row[idx] = t / den(hh);
+    }
 }
 
 template <int DH, int SLOTS>
@@ -1538,16 +1529,17 @@ static bool launch_attn_decode_t(const void *q, const void *kc, const void *vc, 
 // =================================================================================================
 // The same attention for few sequences: with B * Hkv items for 256 CUs the one-workgroup-per-item kernel leaves most of
 // the chip idle and takes an item's whole latency (39 us at 4096 keys for any B up to 32). Here an item's keys are
-// spread over workgroups, in three launches (4.1 + 4.4 + 5.7 us there) with the scores between them in global memory (16
-// bytes per key and KV head against the key's 128 or 256 bytes of K; they stay in the caches):
+// spread over workgroups, in three launches (4.0 + 4.7 + 6.9 us there) with the scores between them in global memory (16
+// bytes per key and KV head against the key's 128 or 256 bytes of K; they stay in the caches). Every sum is made in the
+// order of that kernel, so that a sequence's result does not depend on how many others there are:
 //   k_dec_scores  : scores of DSP_KEYS keys for the 4 heads of a KV group (the MFMA sequence of k_attn_decode)
 //   k_dec_select  : per head, 16 waves: the exact threshold of the budget, the last kept tie, the maximum and denominator
-//   k_dec_values  : softmax numerators of a range of keys and their sum over the V rows -> partial outputs, which the row
-//                   quantiser folds in split order
+//   k_dec_values  : softmax numerators of a sixteenth of the keys and their sum over the V rows -> partial outputs, which
+//                   the row quantiser sums in order and divides
 // Bound: launch latencies for one or two sequences, HBM (V rows of dropped keys included) above.
 // =================================================================================================
 constexpr int DSP_KEYS = 256;                                // keys of a k_dec_scores workgroup: four tiles of 16 per wave
-struct __align__(16) DecSel { uint32_t thr; float mx, den; int jstar; };
+constexpr int DSP_MAX_L = 9216;
 
 template <int DH>
 __global__ void __launch_bounds__(256)
@@ -1595,7 +1587,8 @@ k_dec_scores(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, float 
 }
 
 constexpr int DSEL_WAVES = 16;                               // of one head: a round of the search counts SLOTS columns per lane
-template <int SLOTS>
+// NJU: SLOTS / 4 of k_attn_decode for the same L_max, which says how its denominator is summed
+template <int SLOTS, int NJU>
 __global__ void __launch_bounds__(DSEL_WAVES * 64)
 k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const RowAct *__restrict__ ra,
              const int32_t *__restrict__ cache_len, int L_max, int Hq, int lpad)
@@ -1603,7 +1596,9 @@ k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const R
     constexpr int SLICE = SLOTS * 64, NJ = SLOTS / 4;
     __shared__ int s_cnt[2][DSEL_WAVES], s_gt[DSEL_WAVES], s_tie[DSEL_WAVES], s_last;
     __shared__ uint32_t s_min[DSEL_WAVES], s_max[DSEL_WAVES];
-    __shared__ float s_den[DSEL_WAVES];
+    __shared__ float s_den[DEC_GW];
+    __shared__ __align__(16) float s_p[DSEL_WAVES * SLICE];
+    static_assert(DEC_GW * NJU * 256 <= DSEL_WAVES * SLICE, "");
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int head = blockIdx.x, s = blockIdx.y;
@@ -1711,129 +1706,151 @@ k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const R
         __syncthreads();
         jstar = s_last;
     }
-    float den = 0.f;
+    // the denominator, in the order of k_attn_decode: DEC_GW waves with NJU blocks of 256 columns each
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NJ; ++j) {
+        const int c = 256 * j + 4 * lane;
+        f32x4_a p;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int c = 256 * j + 4 * lane + e;
             const uint32_t kv = key[4 * j + e];
-            if (c < n_loc && (kv > thr || (kv == thr && base + c <= jstar))) den += __expf(score_unkey(kv) - mx);
+            const bool kept = c + e < n_loc && (kv > thr || (kv == thr && base + c + e <= jstar));
+            p[e] = kept ? __expf(score_unkey(kv) - mx) : 0.f;
         }
-    den = wave_sum_dpp(den);
-    if (lane == 0) s_den[w] = den;
+        *reinterpret_cast<f32x4_a *>(s_p + base + c) = p;
+    }
+    __syncthreads();
+    if (w < DEC_GW) {
+        float den = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJU; ++j) {
+            const f32x4_a p = *reinterpret_cast<const f32x4_a *>(s_p + (w * NJU + j) * 256 + 4 * lane);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) den += p[e];
+        }
+        den = wave_sum_dpp(den);
+        if (lane == 0) s_den[w] = den;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         float d = 0.f;
 #pragma unroll
-        for (int i = 0; i < DSEL_WAVES; ++i) d += s_den[i];
+        for (int i = 0; i < DEC_GW; ++i) d += s_den[i];
         sel[(int64_t)s * Hq + head] = DecSel{thr, mx, d, jstar};
     }
 }
 
-// grid (ranges of 256 keys, Hkv, B): a range's V rows are all requested (kept or not) together with its scores, so that a
-// workgroup waits for memory once; part [ranges][B][Hq * DH]. 8 threads per channel of the head: 4 rows of 8 channels per
-// thread. The code is kept short on purpose: a launch this short is bound by latencies, instruction fetches among them
-// (6 us for one sequence of the 1B shape at 4096 keys).
+// grid (16, Hkv, B): workgroup ww does what wave ww of k_attn_decode does, its key slots and its order of sums, and wave h
+// one of the KV head's four query heads: part [16][B][Hq * DH], which the row quantiser sums and divides as that kernel
+// does. All V rows of the slots (kept or not) go straight to LDS, up to DSV_STEPS steps at once, so that a workgroup waits
+// for memory once and the four waves read each row from there. The loops stay rolled on purpose: a launch this short is
+// bound by latencies, instruction fetches among them (unrolled, with V in registers: 11.3 us at one sequence of the 1B
+// shape and 4096 keys).
+constexpr int DSV_STEPS = 48;                                // 1 KB of V each
 template <int DH>
-__global__ void __launch_bounds__(8 * DH)
+__global__ void __launch_bounds__(256)
 k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, const bf16_t *__restrict__ vc,
-             float *__restrict__ part, const int32_t *__restrict__ cache_len, int L_max, int Hq, int Hkv, int lpad)
+             float *__restrict__ part, const int32_t *__restrict__ cache_len, int L_max, int Hq, int Hkv, int lpad, int cap)
 {
-    constexpr int NT = 8 * DH, LPK = DH / 8, KPI = NT / LPK, NV = DSP_KEYS / KPI, HPT = DEC_HPB * DSP_KEYS / NT;
-    static_assert(NV == 4 && KPI == 64, "");
-    __shared__ __align__(16) float sc[NT / 64 * DEC_HPB * DH > DEC_HPB * DSP_KEYS ? NT / 64 * DEC_HPB * DH : DEC_HPB * DSP_KEYS];
-    const int tid = threadIdx.x, kvh = blockIdx.y, s = blockIdx.z, h0 = kvh * DEC_HPB;
+    constexpr int LPK = DH / 8, SPW = 64 / LPK, KPI = DEC_WAVES * SPW;
+    extern __shared__ __align__(16) unsigned char dvl[];     // [cap][64 lanes][8] bf16, then numerators [4][steps * SPW]
+    const int lane = threadIdx.x & 63, slot = lane / LPK, cs = lane - slot * LPK;
+    const int h = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int kvh = blockIdx.y, s = blockIdx.z, head = kvh * DEC_HPB + h, first = (int)blockIdx.x * SPW;
     const int p0 = __builtin_amdgcn_readfirstlane(cache_len[s]);
     if (p0 < 0 || p0 + 1 > L_max) return;
-    const int k0 = (int)blockIdx.x * DSP_KEYS;
-    int n = p0 + 1 - k0;
-    n = n < 0 ? 0 : (n > DSP_KEYS ? DSP_KEYS : n);
-    const DecSel *sr = sel + (int64_t)s * Hq + h0;
-    const bf16_t *vbase = vc + (((int64_t)s * Hkv + kvh) * (int64_t)L_max + k0) * DH;
-    const int ks = tid / LPK, cs = tid - ks * LPK, key = tid & (DSP_KEYS - 1), hb = tid / DSP_KEYS * HPT;
-    u32x4_a vv[NV];
-    float v4[HPT];
+    const int n = p0 + 1, nit = (n + KPI - 1) / KPI;
+    const bf16_t *vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH + cs * 8;
+    const DecSel d = sel[(int64_t)s * Hq + head];
+    const float *srow = scores + ((int64_t)s * Hq + head) * lpad;
+    float *my = reinterpret_cast<float *>(dvl + (size_t)cap * 1024) + h * ((L_max + KPI - 1) / KPI) * SPW;
+    DecVals<8> acc;
 #pragma unroll
-    for (int hh = 0; hh < HPT; ++hh) v4[hh] = key < n ? scores[((int64_t)s * Hq + h0 + hb + hh) * lpad + k0 + key] : 0.f;
+    for (int e = 0; e < 8; ++e) acc.v[e] = 0.f;
+    for (int c0 = 0; c0 < nit; c0 += cap) {
+        const int c1 = c0 + cap < nit ? c0 + cap : nit;
+        if (c0) __syncthreads();                             // the previous steps' rows have been read
+        for (int i = c0 + h; i < c1; i += DEC_HPB) {
+            int j = i * KPI + first + slot;
+            if (j >= n) j = n - 1;                           // weight 0
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                         ::"v"(vbase + (int64_t)j * DH), "s"((i - c0) * 1024) : "memory", "m0");
+        }
+        if (c0 == 0) {
+#pragma unroll 4
+            for (int i = lane; i < nit * SPW; i += 64) {     // this wave's numerators, the slots of a step together
+                const int j = i / SPW * KPI + first + i % SPW;
+                const float v = srow[j < n ? j : n - 1];
+                const uint32_t kv = score_key(v);
+                const bool kept = j < n && (kv > d.thr || (kv == d.thr && j <= d.jstar));
+                my[i] = kept ? __expf(v - d.mx) : 0.f;
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+#pragma unroll 4
+        for (int i = c0; i < c1; ++i) {
+            const u32x4_a v = *reinterpret_cast<const u32x4_a *>(dvl + (i - c0) * 1024 + lane * 16);
+            const float p = my[i * SPW + slot];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        const int j = ks + u * KPI;
-        vv[u] = u32x4_a{0u, 0u, 0u, 0u};
-        if (j < n) vv[u] = *reinterpret_cast<const u32x4_a *>(vbase + (int64_t)j * DH + cs * 8);
-    }
-#pragma unroll
-    for (int hh = 0; hh < HPT; ++hh) {
-        const DecSel d = sr[hb + hh];
-        const uint32_t kv = score_key(v4[hh]);
-        const bool kept = key < n && (kv > d.thr || (kv == d.thr && k0 + key <= d.jstar));
-        sc[(hb + hh) * DSP_KEYS + key] = kept ? __expf(v4[hh] - d.mx) : 0.f;
-    }
-    __syncthreads();
-    float acc[DEC_HPB][8];
-#pragma unroll
-    for (int hh = 0; hh < DEC_HPB; ++hh)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[hh][e] = 0.f;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        float p[DEC_HPB];
-        bool any = false;
-#pragma unroll
-        for (int hh = 0; hh < DEC_HPB; ++hh) { p[hh] = sc[hh * DSP_KEYS + ks + u * KPI]; any |= p[hh] != 0.f; }
-#pragma unroll
-        for (int wi = 0; wi < 4; ++wi) {
-            const uint32_t v = any ? vv[u][wi] : 0u;         // a row that no head kept may hold anything
-            const float a = __uint_as_float(v << 16), b = __uint_as_float(v & 0xFFFF0000u);
-#pragma unroll
-            for (int hh = 0; hh < DEC_HPB; ++hh) {
-                acc[hh][2 * wi] = fmaf(p[hh], a, acc[hh][2 * wi]);
-                acc[hh][2 * wi + 1] = fmaf(p[hh], b, acc[hh][2 * wi + 1]);
+            for (int wi = 0; wi < 4; ++wi) {
+                const uint32_t x = p != 0.f ? v[wi] : 0u;    // a row that the head dropped may hold anything
+                acc.v[2 * wi] = fmaf(p, __uint_as_float(x << 16), acc.v[2 * wi]);
+                acc.v[2 * wi + 1] = fmaf(p, __uint_as_float(x & 0xFFFF0000u), acc.v[2 * wi + 1]);
             }
         }
     }
-    decode_pv_reduce<DH, NT / 64>(acc, sc, [&](int hh) { return sr[hh].den; }, part + (((int64_t)blockIdx.x * gridDim.z + s) * Hq + h0) * DH);
+    int fbase = 0;
+    const auto kept = dec_halve<LPK>(acc, lane, fbase);
+    float *dst = part + (((int64_t)blockIdx.x * gridDim.z + s) * Hq + head) * DH + cs * 8 + fbase;
+#pragma unroll
+    for (int i = 0; i < LPK / 8; ++i) dst[i] = kept.v[i];
 }
 
 // Scratch of the split path for B sequences: scores, selection rows and partial outputs. 0: the shape, or B, is not its.
 // It pays while few items leave most CUs of the one-workgroup-per-item kernel idle and their rows are long enough for that
 // kernel's latency to show; measured per layer of a graph-replayed step (us, one workgroup per item -> split; caches of
-// 3/4 L .. L keys): 1B shape, B = 1: L 1000 91 -> 93, 2000 101 -> 96, 4096 127 -> 99, 8192 155 -> 105; B = 8: 2000 108 ->
-// 105, 8192 159 -> 131; B = 12: 2000 109 -> 114, 4096 134 -> 126; B = 16: 4096 136 -> 135, 8192 166 -> 170; 8B shape,
-// L = 8192: B = 1 238 -> 161, B = 8 263 -> 212, B = 12 266 -> 252. Hence the line below.
+// 3/4 L .. L keys): 1B shape, B = 1: L 1600 77 -> 73, 4096 103 -> 79, 8192 132 -> 86; B = 4: 2000 105 -> 100, 8192 155 ->
+// 121; B = 8: 4096 132 -> 119; B = 12: 2000 (not split) 108, 4096 133 -> 131, 8192 161 -> 159; 8B shape, L = 8192: B = 1
+// 219 -> 142, B = 8 268 -> 223, B = 12 273 -> 257. Hence the line below. (A split by ranges of 256 keys, its partial
+// outputs divided by the denominator, took 2 to 9 us less per layer, but then a step's rounding changed with B.)
 static int dsp_lpad(int L_max) { return (L_max + DSP_KEYS - 1) / DSP_KEYS * DSP_KEYS; }
 size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh)
 {
-    if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || L_max > 9216 || L_max < 1) return 0;
+    if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || L_max > DSP_MAX_L || L_max < 1) return 0;
     const int64_t items = (int64_t)B * Hkv;
     if (items > 96 || L_max < 1536 || L_max < 42 * items) return 0;
-    return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)(dsp_lpad(L_max) / DSP_KEYS) * dh * 4);
+    return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)DEC_WAVES * dh * 4);
 }
 
-// B sequences as launch_attn_decode, in three launches; writes nsplit partial outputs [nsplit][B][Hq * dh] at *part.
+// B sequences as launch_attn_decode, in three launches; writes nsplit partial outputs [nsplit][B][Hq * dh] at *part,
+// to be summed in that order and divided by (*sel)[B][Hq].den: then the bits are launch_attn_decode's.
 bool launch_attn_decode_split(const void *q, const void *k_cache, const void *v_cache, void *ws, const RowAct *ra,
                               const int32_t *cache_len, int B, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st,
-                              const float **part_out, int *nsplit_out)
+                              const float **part_out, const DecSel **sel_out, int *nsplit_out)
 {
     if (!cache_len || !attn_decode_split_bytes(B, L_max, Hq, Hkv, dh)) return false;
     const int lpad = dsp_lpad(L_max);
     float *scores = (float *)ws;
     DecSel *sel = (DecSel *)(scores + (size_t)B * Hq * lpad);
     float *part = (float *)(sel + (size_t)B * Hq);
-    const int ranges = lpad / DSP_KEYS;
     const float scale = 1.0f / sqrtf((float)dh);
-    const dim3 g1(lpad / DSP_KEYS, Hkv, B), g2(Hq, B);
+    const dim3 g1(lpad / DSP_KEYS, Hkv, B), g2(Hq, B), g3(DEC_WAVES, Hkv, B);
     if (dh == 64) hipLaunchKernelGGL(k_dec_scores<64>, g1, dim3(256), 0, st, (const bf16_t *)q, (const bf16_t *)k_cache, scores, cache_len, L_max, Hq, Hkv, lpad, scale, flags);
     else hipLaunchKernelGGL(k_dec_scores<128>, g1, dim3(256), 0, st, (const bf16_t *)q, (const bf16_t *)k_cache, scores, cache_len, L_max, Hq, Hkv, lpad, scale, flags);
-#define SOL_DEC_SEL(SL) hipLaunchKernelGGL(k_dec_select<SL>, g2, dim3(DSEL_WAVES * 64), 0, st, scores, sel, ra, cache_len, L_max, Hq, lpad)
-    if (L_max <= 4096) SOL_DEC_SEL(4);
-    else if (L_max <= 8192) SOL_DEC_SEL(8);
-    else SOL_DEC_SEL(12);
+#define SOL_DEC_SEL(SL, NJU) hipLaunchKernelGGL((k_dec_select<SL, NJU>), g2, dim3(DSEL_WAVES * 64), 0, st, scores, sel, ra, cache_len, L_max, Hq, lpad)
+    if (L_max <= 2048) SOL_DEC_SEL(4, 2);
+    else if (L_max <= 4096) SOL_DEC_SEL(4, 4);
+    else if (L_max <= 8192) SOL_DEC_SEL(8, 8);
+    else SOL_DEC_SEL(12, 9);
 #undef SOL_DEC_SEL
-    if (dh == 64) hipLaunchKernelGGL(k_dec_values<64>, g1, dim3(512), 0, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad);
-    else hipLaunchKernelGGL(k_dec_values<128>, g1, dim3(1024), 0, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad);
+    const int steps = (L_max + 8192 / dh - 1) / (8192 / dh), rounds = (steps + DSV_STEPS - 1) / DSV_STEPS, cap = (steps + rounds - 1) / rounds;
+    const size_t lds = (size_t)cap * 1024 + (size_t)DEC_HPB * steps * (512 / dh) * 4;   // at most 57 KB
+    if (dh == 64) hipLaunchKernelGGL(k_dec_values<64>, g3, dim3(256), lds, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad, cap);
+    else hipLaunchKernelGGL(k_dec_values<128>, g3, dim3(256), lds, st, scores, sel, (const bf16_t *)v_cache, part, cache_len, L_max, Hq, Hkv, lpad, cap);
     *part_out = part;
-    *nsplit_out = ranges;
+    *sel_out = sel;
+    *nsplit_out = DEC_WAVES;
     return true;
 }
 

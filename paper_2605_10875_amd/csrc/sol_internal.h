@@ -32,9 +32,12 @@ void launch_dense_rows(int width, int64_t M, RowAct *ra, hipStream_t st);
 bool launch_rmsnorm_fq(const void *x, int x_dtype, const float *add, float *xsum, const void *w, int w_dtype,
                        void *h, int h_dtype, const RowAct *ra, bool quant, int64_t M, int d, float eps,
                        hipStream_t st, int nsplit = 1, bool prune = false);
+// One head's key selection in a split decode attention: the threshold, the last tie kept, the best score, the denominator.
+struct __align__(16) DecSel { uint32_t thr; float mx, den; int jstar; };
 // out = FQ(in, bits) row-wise; in fp32 [nsplit][M][n] (partial sums, folded in split order) -> out dtype.
+// sel [M][n / dh] (with nsplit > 1): the sums of each dh columns are divided by its den first.
 void launch_fq_rows(const float *in, void *out, int out_dtype, const RowAct *ra, bool quant, int64_t M, int n,
-                    hipStream_t st, int nsplit = 1);
+                    hipStream_t st, int nsplit = 1, const DecSel *sel = nullptr, int dh = 1);
 // rotary + scatter: qkv32 [M][(Hq+2Hkv)*dh] -> q [M][Hq*dh], K/V caches at position pos0[s]+i.
 void launch_rope_store(const float *qkv32, void *q, void *k_cache, void *v_cache, int dtype, const float2 *rope,
                        const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int *flags,
@@ -120,18 +123,16 @@ bool launch_gemm_skinny(const void *x, int64_t ldx, const void *w0, int n0, cons
                         int n2, int M, int K, float *partial, int nsplit, hipStream_t st);
 int skinny_splits(int M, int Nv, int K);
 
-// ---- linear maps of very few rows with what follows them (sol_gemv.hip) --------------------------
-// Up to GEMV_MAX_ROWS bf16 rows, K a multiple of 512; otherwise false (nothing launched). Arguments as the MFMA launchers
-// of the same names; no scratch. launch_gemv_f32: C [M][N].
-constexpr int GEMV_MAX_ROWS = 4;
-bool gemv_rows_ok(int64_t M);
+// ---- linear maps of one row with what follows them (sol_gemv.hip) --------------------------
+// One bf16 row, K a multiple of 512; otherwise false (nothing launched). Arguments as the MFMA launchers of the same names;
+// no scratch. launch_gemv_f32: C [N].
 bool launch_gemv_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
-                          const float2 *rope, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int d,
+                          const float2 *rope, const int32_t *pos0, int L_max, int Hq, int Hkv, int dh, int d,
                           int *flags, hipStream_t st, int cache_rows = 0);
-bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, float *out, int64_t M, int N, int K, hipStream_t st);
-bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int64_t M, int dff, int d, hipStream_t st);
-bool launch_gemv_resid_out(const void *a, const void *w, const float *x2, void *out, int64_t M, int N, int K, hipStream_t st);
-bool launch_gemv_f32(const void *a, const void *w, float *C, int64_t M, int N, int K, hipStream_t st);
+bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, float *out, int N, int K, hipStream_t st);
+bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int dff, int d, hipStream_t st);
+bool launch_gemv_resid_out(const void *a, const void *w, const float *x2, void *out, int N, int K, hipStream_t st);
+bool launch_gemv_f32(const void *a, const void *w, float *C, int N, int K, hipStream_t st);
 
 // ---- attention (sol_attn.hip) ----------------------------------------------------------------
 // One query row per workgroup group: scores over cache positions [0, pos], budgeted top-k,
@@ -151,11 +152,11 @@ bool launch_attn_decode(const void *q, const void *k_cache, const void *v_cache,
                         const int32_t *cache_len, const int32_t *seq_order, int B, int L_max, int Hq, int Hkv, int dh,
                         int *flags, hipStream_t st);
 // The same for few sequences, an item's keys spread over workgroups: scratch bytes (0: not covered, or too many sequences)
-// and the launches; the outputs are *nsplit partial ones, [nsplit][B][Hq * dh] at *part, to be summed in split order.
+// and the launches; the outputs are *nsplit partial ones, [nsplit][B][Hq * dh] at *part, for launch_fq_rows with *sel.
 size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh);
 bool launch_attn_decode_split(const void *q, const void *k_cache, const void *v_cache, void *ws, const RowAct *ra,
                               const int32_t *cache_len, int B, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st,
-                              const float **part, int *nsplit);
+                              const float **part, const DecSel **sel, int *nsplit);
 // Page metadata of a bf16 K cache for the page rule (page size S >= 2): meta [n_seq][Hkv][ceil(L_max/S)][2*dh],
 // per page the channel-wise [maximum | minimum] of its keys. build: from keys [0, len[s]); update: the key at
 // pos[s] joins its page. head_dim 64 / 128.

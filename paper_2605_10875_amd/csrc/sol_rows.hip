@@ -423,15 +423,17 @@ bool launch_rmsnorm_fq(const void *x, int x_dtype, const float *add, float *xsum
 // partial sums of a thread in flight together (one row of 136 KB: 2.7 us; with one wave per row 9.8 us for 64 KB)
 __global__ void __launch_bounds__(1024)
 k_fold_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, bf16_t *__restrict__ out,
-               const RowAct *__restrict__ ra, int quant, int n)
+               const RowAct *__restrict__ ra, int quant, int n, const DecSel *__restrict__ sel, int dsh)
 {
     __shared__ uint32_t red[16];
     const int64_t r = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
     const float *ip = in + r * n + 4 * tid;
+    const float den = sel ? sel[r * (n >> dsh) + (4 * tid >> dsh)].den : 1.f;
     f32x4_w v = *reinterpret_cast<const f32x4_w *>(ip);
 #pragma unroll 8
     for (int sp = 1; sp < nsplit; ++sp) v += *reinterpret_cast<const f32x4_w *>(ip + sp * split_stride);
+    if (sel) v /= den;
     const int bits = (quant && ra) ? ra[r].bits : 16;
     if (bits < 16) {
         const float a = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
@@ -454,7 +456,8 @@ k_fold_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, b
 
 template <typename TO>
 __global__ void __launch_bounds__(ROW_BLOCK)
-k_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, TO *__restrict__ out, const RowAct *__restrict__ ra, int quant, int n)
+k_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, TO *__restrict__ out, const RowAct *__restrict__ ra, int quant, int n,
+          const DecSel *__restrict__ sel, int dsh)
 {
     __shared__ float red[ROW_BLOCK / 64];
     const int64_t r = blockIdx.x;
@@ -462,7 +465,7 @@ k_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, TO *__
     auto value = [&](int j) {
         float v = in[r * n + j];
         for (int sp = 1; sp < nsplit; ++sp) v += in[sp * split_stride + r * n + j];
-        return v;
+        return sel ? v / sel[r * (n >> dsh) + (j >> dsh)].den : v;
     };
     TO *orow = out + r * n;
     const int bits = (quant && ra) ? ra[r].bits : 16;
@@ -481,12 +484,13 @@ k_fq_rows(const float *__restrict__ in, int nsplit, int64_t split_stride, TO *__
 }
 
 void launch_fq_rows(const float *in, void *out, int out_dtype, const RowAct *ra, bool quant, int64_t M, int n,
-                    hipStream_t st, int nsplit)
+                    hipStream_t st, int nsplit, const DecSel *sel, int dh)
 {
     if (M <= 0) return;
     const int64_t ss = M * (int64_t)n;
+    const int dsh = __builtin_ctz((unsigned)dh);             // with sel: 64 or 128
     if (out_dtype == 1 && nsplit > 1 && n % 256 == 0 && n <= 4096) {
-        hipLaunchKernelGGL(k_fold_fq_rows, dim3((unsigned)M), dim3(n / 4), 0, st, in, nsplit, ss, (bf16_t *)out, ra, quant ? 1 : 0, n);
+        hipLaunchKernelGGL(k_fold_fq_rows, dim3((unsigned)M), dim3(n / 4), 0, st, in, nsplit, ss, (bf16_t *)out, ra, quant ? 1 : 0, n, sel, dsh);
         return;
     }
     if (out_dtype == 1 && nsplit == 1 && (n == 2048 || n == 4096)) {
@@ -497,10 +501,10 @@ void launch_fq_rows(const float *in, void *out, int out_dtype, const RowAct *ra,
     }
     if (out_dtype == 0)
         hipLaunchKernelGGL((k_fq_rows<float>), dim3((unsigned)M), dim3(ROW_BLOCK), 0, st, in, nsplit, ss, (float *)out, ra,
-                           quant ? 1 : 0, n);
+                           quant ? 1 : 0, n, sel, dsh);
     else
         hipLaunchKernelGGL((k_fq_rows<bf16_t>), dim3((unsigned)M), dim3(ROW_BLOCK), 0, st, in, nsplit, ss, (bf16_t *)out, ra,
-                           quant ? 1 : 0, n);
+                           quant ? 1 : 0, n, sel, dsh);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1,6 +1,6 @@
 """Decode attention of few sequences (an item's keys spread over workgroups) against the oracle's attention: cache lengths
-around the edges of its ranges and of the dispatch line (1536 positions), tied scores whose quota ends inside a wave's
-columns, a skipped sequence, both head sizes."""
+around the edges of its blocks and of the dispatch line (1536 positions), tied scores whose quota ends inside a wave's
+columns, a skipped sequence, both head sizes; and against the kernel of many sequences, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -32,9 +32,13 @@ def test_attention_of_few_sequences(dh, L, lens, dup):
     q = synth.round_to_bf16(rng.standard_normal((B, 4 * hkv * dh)).astype(np.float32))
     ids = np.arange(B, dtype=np.int32) % len(TABLE)
     ctx = sol.Sol(shape, TABLE, max_positions=L)
-    o = host(ctx.test_attention_stage(dev(q, sol.BF16).view(B, 1, -1), dev(ids).view(B, 1), dev(k, sol.BF16), dev(v, sol.BF16),
-                                      pos0=dev(np.array(lens, np.int32)))).reshape(B, 4 * hkv, dh)
+    args = [dev(q, sol.BF16).view(B, 1, -1), dev(ids).view(B, 1), dev(k, sol.BF16), dev(v, sol.BF16), dev(np.array(lens, np.int32))]
+    out = ctx.test_attention_stage(*args[:4], pos0=args[4])
+    # the same sequences among enough others for the one-workgroup-per-item kernel: the same sums in the same order
+    many = [t.repeat((50 // B,) + (1,) * (t.dim() - 1)) for t in args]
+    assert torch.equal(ctx.test_attention_stage(*many[:4], pos0=many[4])[:B], out)
     assert ctx.device_status() == sol.OK
+    o = host(out).reshape(B, 4 * hkv, dh)
     for s, p in enumerate(lens):
         n, a = p + 1, TABLE[ids[s]]
         for h in range(4 * hkv):
