@@ -4,8 +4,8 @@
 // (k_gemm_skinny, sol_gemm_mfma.hip), whose epilogues are kernels of their own.
 // Bound: HBM (weights once) for the wide maps, launch and load latency for the narrow ones. A layer of a graph-replayed
 // decode step with a cache of 300 keys (us, K-split MFMA kernel -> here): 1B shape 87.9 -> 66.7, 8B shape 144.5 -> 119.7;
-// gate / up of the 1B shape: 12.6 us, 5.3 TB/s. For more rows the K-split kernel stays: the same layout took 1 + rows
-// vector instructions per weight, less time than that kernel up to four rows (4 rows, 1B: 90.8 -> 81.9; 5: 92.1 -> 96.9).
+// gate / up of the 1B shape: 12.6 us, 5.3 TB/s. More rows stay with the K-split kernel: with a template over rows this one
+// was faster up to four (4 rows, 1B: 90.8 -> 81.9; 5: 92.1 -> 96.9), but batches of two to four then rounded unlike larger ones.
 #include "sol_internal.h"
 
 namespace sol {
