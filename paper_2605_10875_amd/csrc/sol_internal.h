@@ -124,8 +124,8 @@ bool launch_gemm_skinny(const void *x, int64_t ldx, const void *w0, int n0, cons
 int skinny_splits(int M, int Nv, int K);
 
 // ---- linear maps of one row with what follows them (sol_gemv.hip) --------------------------
-// One bf16 row, K a multiple of 512; otherwise false (nothing launched). Arguments as the MFMA launchers of the same names;
-// no scratch. launch_gemv_f32: C [N].
+// One bf16 row, with the sums of launch_gemm_skinny and skinny_splits(1, ..); false (nothing launched) beyond 32 splits or 62 KB
+// of activations. Arguments as the MFMA launchers of the same names; no scratch. launch_gemv_f32: C [N].
 bool launch_gemv_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
                           const float2 *rope, const int32_t *pos0, int L_max, int Hq, int Hkv, int dh, int d,
                           int *flags, hipStream_t st, int cache_rows = 0);

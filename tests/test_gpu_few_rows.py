@@ -1,6 +1,7 @@
 """Layers of one row (the linear maps whose waves finish their sums) and of a few more (the K-split kernel), against the
 oracle under non-quantising actions: sequences and tokens per sequence, widths of one and of several chunks of K with a
-short last one, the page preset's MLP path (pruning at the MLP input, quantiser on the output off), both head sizes."""
+short last one, the page preset's MLP path (pruning at the MLP input, quantiser on the output off), both head sizes; and a
+row alone against the same row among others, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -53,3 +54,35 @@ def test_a_row_that_does_not_fit_is_skipped_and_flagged():
     for t, b in ((kc, before[0]), (vc, before[1])):
         assert not torch.equal(t[0, :, 3], b[0, :, 3])
         assert torch.equal(t[0, :, :3], b[0, :, :3]) and torch.equal(t[0, :, 4:], b[0, :, 4:])
+
+
+# widths whose maps split K in 4, 16 and 32; in 10 and 20 (no powers of two); in 2 and in more than a wave takes (K-split kernel)
+@pytest.mark.parametrize("opts", [{}, dict(prune_site=1, quant_sites=sol.QS_MLP_OUT)], ids=["default", "mlp_in"])
+@pytest.mark.parametrize("shape", [synth.LLAMA_1B, synth.ModelShape(2560, 20, 4, 128, 1280), synth.ModelShape(1024, 4, 1, 64, 14336)],
+                         ids=["1b", "odd_splits", "wide"])
+def test_a_row_alone_has_the_bits_it_has_among_others(shape, opts):
+    L, n = 40, 5
+    g = torch.Generator(device="cuda").manual_seed(shape.d_ff)
+
+    def rnd(*size, scale=1.0):
+        return torch.randn(size, generator=g, device="cuda").mul_(scale).to(torch.bfloat16)
+
+    d, nq, nkv, ff = shape.d_model, shape.n_q_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim, shape.d_ff
+    w = {k: rnd(*size, scale=0.02) for k, size in dict(wq=(nq, d), wk=(nkv, d), wv=(nkv, d), wo=(d, nq), w_gate=(ff, d),
+                                                       w_up=(ff, d), w_down=(d, ff)).items()}
+    w["w_in_norm"], w["w_post_norm"] = rnd(d), rnd(d)
+    x, kc, vc = rnd(n, 1, d), rnd(n, shape.n_kv_heads, L, shape.head_dim), rnd(n, shape.n_kv_heads, L, shape.head_dim)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda").view(n, 1) % len(TABLE)
+    pos0 = 7 * torch.arange(n, dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, TABLE, max_positions=L, **opts)
+
+    def layer(rows):
+        k, v = kc[rows].clone(), vc[rows].clone()
+        return ctx.layer_forward(w, x[rows].clone(), ids[rows].clone(), k, v, pos0=pos0[rows].clone()), k, v
+
+    among = {m: layer(slice(0, m)) for m in (2, n)}
+    for i in range(n):
+        for alone, m in ((layer(slice(i, i + 1)), m) for m in among if i < m):
+            for a, b in zip(alone, among[m]):
+                assert torch.equal(a[0], b[i]), (i, m)
+    assert ctx.device_status() == sol.OK
