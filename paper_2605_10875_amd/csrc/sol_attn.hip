@@ -1812,12 +1812,14 @@ k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, c
 // kernel's latency to show; measured per layer of a graph-replayed step (us, one workgroup per item -> split; caches of
 // 3/4 L .. L keys): 1B shape, B = 1: L 1600 77 -> 73, 4096 103 -> 79, 8192 132 -> 86; B = 4: 2000 105 -> 100, 8192 155 ->
 // 121; B = 8: 4096 132 -> 119; B = 12: 2000 (not split) 108, 4096 133 -> 131, 8192 161 -> 159; 8B shape, L = 8192: B = 1
-// 219 -> 142, B = 8 268 -> 223, B = 12 273 -> 257. Hence the line below. (A split by ranges of 256 keys, its partial
+// 219 -> 142, B = 8 268 -> 223, B = 12 273 -> 257. Hence the line below. Rows of more than 4096 outputs are outside
+// k_fold_fq_rows, and the general quantiser reads the sixteen parts with one workgroup: 64 query heads of 128, 2000 keys, 251 ->
+// 332. (A split by ranges of 256 keys, its partial
 // outputs divided by the denominator, took 2 to 9 us less per layer, but then a step's rounding changed with B.)
 static int dsp_lpad(int L_max) { return (L_max + DSP_KEYS - 1) / DSP_KEYS * DSP_KEYS; }
 size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh)
 {
-    if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || L_max > DSP_MAX_L || L_max < 1) return 0;
+    if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || Hq * dh > 4096 || L_max > DSP_MAX_L || L_max < 1) return 0;
     const int64_t items = (int64_t)B * Hkv;
     if (items > 96 || L_max < 1536 || L_max < 42 * items) return 0;
     return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)DEC_WAVES * dh * 4);

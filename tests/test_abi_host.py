@@ -106,3 +106,14 @@ def test_page_meta_bytes_is_host_arithmetic():
     plain = sol.make_cfg(synth.LLAMA_1B, sol.BF16, 8200)
     assert sol.lib().sol_page_meta_bytes(C.byref(plain), 64, 8200) == 0          # page size 1 has no metadata
     assert sol.lib().sol_page_meta_bytes(C.byref(cfg), 0, 8200) == 0
+
+
+def test_split_decode_attention_is_for_rows_that_its_fold_covers():
+    # the split form's scratch shows in the workspace: asked for at 4096 outputs per row, not at 8192, where one
+    # workgroup would read sixteen partial rows
+    def extra(heads):
+        cfg = sol.make_cfg(synth.ModelShape(1024, heads, heads // 4, 128, 1024), sol.BF16, 8192)
+        return sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, 1, 1, 8192) - sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, 1, 1, 1024)
+
+    assert extra(32) > 0
+    assert extra(64) == 0
