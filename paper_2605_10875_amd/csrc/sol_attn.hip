@@ -1809,19 +1809,22 @@ k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, c
 
 // Scratch of the split path for B sequences: scores, selection rows and partial outputs. 0: the shape, or B, is not its.
 // It pays while few items leave most CUs of the one-workgroup-per-item kernel idle and their rows are long enough for that
-// kernel's latency to show; measured per layer of a graph-replayed step (us, one workgroup per item -> split; caches of
-// 3/4 L .. L keys): 1B shape, B = 1: L 1600 77 -> 73, 4096 103 -> 79, 8192 132 -> 86; B = 4: 2000 105 -> 100, 8192 155 ->
-// 121; B = 8: 4096 132 -> 119; B = 12: 2000 (not split) 108, 4096 133 -> 131, 8192 161 -> 159; 8B shape, L = 8192: B = 1
-// 219 -> 142, B = 8 268 -> 223, B = 12 273 -> 257. Hence the line below. Rows of more than 4096 outputs are outside
-// k_fold_fq_rows, and the general quantiser reads the sixteen parts with one workgroup: 64 query heads of 128, 2000 keys, 251 ->
-// 332. (A split by ranges of 256 keys, its partial
-// outputs divided by the denominator, took 2 to 9 us less per layer, but then a step's rounding changed with B.)
+// kernel's latency to show. What a row holds is not known here, only what its cache can hold: rows of few keys pay for the two
+// launches more and the wider fold. Per layer of a graph-replayed step, caches of 8192 positions (us, one workgroup per item ->
+// split, at 300 / 1000 / 2000 / 8000 keys): 1B shape, B = 1: 73 -> 75, 80 -> 76, 92 -> 77, 131 -> 87; B = 4: 95 -> 100,
+// 102 -> 102, 116 -> 106, 154 -> 119; 8B shape, B = 1: 126 -> 129, 136 -> 131, 152 -> 132, 227 -> 144; B = 4: 153 -> 163,
+// 166 -> 167, 184 -> 170, 259 -> 190. Not taken: 1B, B = 8: 97 -> 108, 105 -> 110, 117 -> 114, 157 -> 133; B = 12: 100 -> 118,
+// 107 -> 120, 120 -> 127, 159 -> 156; 8B, B = 8: 156 -> 174, 168 -> 179, 190 -> 188, 263 -> 226. So the line is drawn at 32
+// items, and at twice the keys at which both take the same time (500, 700 and 900 keys at 8, 16 and 32 items). Rows of more
+// than 4096 outputs are outside k_fold_fq_rows, and the general quantiser reads the sixteen parts with one workgroup: 64 query
+// heads of 128, 2000 keys, 251 -> 332. (A split by ranges of 256 keys, its partial outputs divided by the denominator, took 2 to
+// 9 us less per layer, but then a step's rounding changed with B.)
 static int dsp_lpad(int L_max) { return (L_max + DSP_KEYS - 1) / DSP_KEYS * DSP_KEYS; }
 size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh)
 {
     if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || Hq * dh > 4096 || L_max > DSP_MAX_L || L_max < 1) return 0;
     const int64_t items = (int64_t)B * Hkv;
-    if (items > 96 || L_max < 1536 || L_max < 42 * items) return 0;
+    if (items > 32 || L_max < 1536 || L_max < 64 * items) return 0;
     return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)DEC_WAVES * dh * 4);
 }
 

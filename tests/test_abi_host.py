@@ -108,12 +108,14 @@ def test_page_meta_bytes_is_host_arithmetic():
     assert sol.lib().sol_page_meta_bytes(C.byref(cfg), 0, 8200) == 0
 
 
-def test_split_decode_attention_is_for_rows_that_its_fold_covers():
-    # the split form's scratch shows in the workspace: asked for at 4096 outputs per row, not at 8192, where one
-    # workgroup would read sixteen partial rows
-    def extra(heads):
-        cfg = sol.make_cfg(synth.ModelShape(1024, heads, heads // 4, 128, 1024), sol.BF16, 8192)
-        return sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, 1, 1, 8192) - sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, 1, 1, 1024)
+def test_split_decode_attention_where_it_pays():
+    # the split form's scratch shows in the workspace
+    def split(heads, B, L):
+        cfg = sol.make_cfg(synth.ModelShape(1024, heads, heads // 4, 128, 1024), sol.BF16, 9216)
+        return sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, B, 1, L) > sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, B, 1, 1024)
 
-    assert extra(32) > 0
-    assert extra(64) == 0
+    assert split(32, 1, 8192)
+    assert not split(64, 1, 8192)                  # 8192 outputs per row: outside the kernel that folds the parts
+    assert split(32, 4, 8192) and not split(32, 5, 8192)      # 32 items; rows of few keys would lose more than they gain
+    assert split(32, 1, 1536) and not split(32, 1, 1535)
+    assert split(32, 4, 2048) and not split(32, 4, 2047)
