@@ -493,10 +493,20 @@ k_target_logit(const bf16_t *__restrict__ hf, const bf16_t *__restrict__ lm_head
 // nll = max + log(sum_t s_t * exp(m_t - max)) - target logit over part [n_wt][Mp]. A workgroup takes 32 rows; half wave q
 // of its 32 takes the tiles t = q, q + 32, ... of these rows (it reads 32 consecutive entries of a tile), keeps the first
 // 32 of them in registers (all of them up to 1024 tiles; the others are read twice), and adds them up under the row's
-// maximum; the 32 sums of a row are added in order: the same sequence of operations for every row, whatever the batch.
+// maximum; the 32 sums of a row are added by one thread: the same sequence of operations for every row, whatever the batch.
+// All sums are trees: 4e-8 (rms, of the sum) from 64 bits at 1002 tiles, where a running maximum and sum is 7e-8 off and a
+// chain of 32 and 32 additions 9e-8.
 // Bound: latency for few rows (one load and one exchange each for maximum and sum; a running maximum was a chain of a load
-// and two exponentials per tile: 28 us for 64 rows of 1002 tiles, now 6.8), HBM for many (4.8 TB/s at 32768).
+// and two exponentials per tile: 28 us for 64 rows of 1002 tiles, now 8.5), HBM for many (4.3 TB/s at 32768).
 constexpr int NLL_FIN_TILES = 32;                              // per half wave in registers
+template <int N> __device__ __forceinline__ float tree_sum(float (&v)[N])
+{
+#pragma unroll
+    for (int w = N / 2; w >= 1; w >>= 1)
+#pragma unroll
+        for (int u = 0; u < w; ++u) v[u] += v[u + w];
+    return v[0];
+}
 __global__ void __launch_bounds__(1024)
 k_nll_finish_cols(const float2 *__restrict__ part, const float *__restrict__ tgt_logit, int n_wt, int64_t M, int64_t Mp,
                   float *__restrict__ nll)
@@ -504,6 +514,7 @@ k_nll_finish_cols(const float2 *__restrict__ part, const float *__restrict__ tgt
     __shared__ float fold[32][33];
     const int rl = threadIdx.x & 31, q = threadIdx.x >> 5;
     const int64_t r = (int64_t)blockIdx.x * 32 + rl;           // r < Mp: the grid covers ceil(M / 32) * 32 <= Mp rows
+    const int t_more = 32 * NLL_FIN_TILES;                     // tiles from here on are read twice, 8 per step and half wave
     float2 v[NLL_FIN_TILES];
 #pragma unroll
     for (int u = 0; u < NLL_FIN_TILES; ++u) {
@@ -514,26 +525,32 @@ k_nll_finish_cols(const float2 *__restrict__ part, const float *__restrict__ tgt
     float mx = v[0].x;
 #pragma unroll
     for (int u = 1; u < NLL_FIN_TILES; ++u) mx = fmaxf(mx, v[u].x);
-    for (int t = q + 32 * NLL_FIN_TILES; t < n_wt; t += 32) mx = fmaxf(mx, part[(int64_t)t * Mp + r].x);
+    for (int t = q + t_more; t < n_wt; t += 32) mx = fmaxf(mx, part[(int64_t)t * Mp + r].x);
     fold[q][rl] = mx;
     __syncthreads();
 #pragma unroll 8
     for (int i = 0; i < 32; ++i) mx = fmaxf(mx, fold[i][rl]);
     __syncthreads();
-    float se = 0.f;
+    float s[NLL_FIN_TILES];
 #pragma unroll
-    for (int u = 0; u < NLL_FIN_TILES; ++u) se += v[u].y * __expf(v[u].x - mx);
-    for (int t = q + 32 * NLL_FIN_TILES; t < n_wt; t += 32) {
-        const float2 w = part[(int64_t)t * Mp + r];
-        se += w.y * __expf(w.x - mx);
+    for (int u = 0; u < NLL_FIN_TILES; ++u) s[u] = v[u].y * expf(v[u].x - mx);
+    float se = tree_sum(s);
+    for (int t0 = q + t_more; t0 < n_wt; t0 += 8 * 32) {
+        float m[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int t = t0 + 32 * u;
+            const float2 w = t < n_wt ? part[(int64_t)t * Mp + r] : make_float2(-INFINITY, 0.f);
+            m[u] = w.y * expf(w.x - mx);
+        }
+        se += tree_sum(m);
     }
     fold[q][rl] = se;
     __syncthreads();
     if (q != 0 || r >= M) return;
-    se = 0.f;
-#pragma unroll 8
-    for (int i = 0; i < 32; ++i) se += fold[i][rl];
-    nll[r] = (mx + logf(se)) - tgt_logit[r];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) s[i] = fold[i][rl];
+    nll[r] = (mx + logf(tree_sum(s))) - tgt_logit[r];
 }
 
 // Register r of accumulator tile (i, j) is row 32*i + 8*(r/4) + 4*(lane/32) + r%4, column 32*j + lane%32
@@ -1222,7 +1239,7 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
                        broadcast_g ? 1 : 0, V, row_tgt, flags);
     if (Mp > M) launch_fill_i32((int32_t *)((bf16_t *)hf + M * K), 0, (Mp - M) * K / 2, st);   // K is even
     const BMap bt = plain_map(hf, (int)Mp, K);
-        EpiNllCols epc{part, Mp};
+    const EpiNllCols epc{part, Mp};
     if (!launch_mfma<SOL_TILE>((const bf16_t *)lm_head, K, bt, V, (int)Mp, K, epc, st)) return false;
     hipLaunchKernelGGL(k_target_logit, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const bf16_t *)hf,
                        (const bf16_t *)lm_head, row_tgt, M, K, tgt_logit);
