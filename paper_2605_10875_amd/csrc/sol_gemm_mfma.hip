@@ -190,19 +190,16 @@ struct EpiSiluMul {
 // rotary embedding on q and k heads (pairs (c, c + dh/2)), q -> [M][nq], k/v -> caches.
 // row_sp[row] = (sequence, absolute position) of the row, position -1 if its sequence does not fit the
 // cache (written by k_row_positions before the GEMM).
-// own * cos -+ partner * sin (lower / upper half of the head). Which of the two products is rounded before the sum is spelled
-// out, so that it does not depend on the tile: the sine's, and in the upper half of calls that are not made of whole tiles
-// (WHOLE, see launch_gemm_qkv_rope) the cosine's. Both are one rounding short of exact; left to the compiler, the last bit of a
-// row's q and K would change with the tiles that its call is dealt to.
-template <bool WHOLE>
+// own * cos -+ partner * sin (lower / upper half of the head). Which of the two products is rounded before the sum (the sine's in
+// the lower half, the cosine's in the upper) is spelled out: left to the compiler, it differed between the epilogues, and the last
+// bit of a row's q and K with the tiles that its call was dealt to.
 __device__ __forceinline__ float rotated(float own, float partner, float2 cs, bool lo)
 {
-    if (lo) return __builtin_fmaf(own, cs.x, -(partner * cs.y));
-    return WHOLE ? __builtin_fmaf(own, cs.x, partner * cs.y) : __builtin_fmaf(partner, cs.y, own * cs.x);
+    return lo ? __builtin_fmaf(own, cs.x, -(partner * cs.y)) : __builtin_fmaf(partner, cs.y, own * cs.x);
 }
 template <int TN> struct AuxRope { float2 t0[TN], t1[TN]; int2 sp0, sp1; };
 
-template <int DHT, bool WHOLE>                          // head size: 64 or 128; rotated()
+template <int DHT>                                      // head size: 64 or 128
 struct EpiQkvRope {
     static constexpr bool persistent_walk = true;
     bf16_t *q, *kc, *vc;
@@ -258,8 +255,8 @@ struct EpiQkvRope {
                 const bool lo = ((32 * j) & (dh - 1)) < half;                 // the same for every c < 32
                 const int jp = lo ? j + half / 32 : j - half / 32;            // tile of the partner column
                 const float y0 = v0[jp], y1 = v1[jp];
-                o0 = rotated<WHOLE>(o0, y0, x.t0[j], lo);
-                o1 = rotated<WHOLE>(o1, y1, x.t1[j], lo);
+                o0 = rotated(o0, y0, x.t0[j], lo);
+                o1 = rotated(o1, y1, x.t1[j], lo);
             }
             const int hj = (32 * j) / dh;                // head inside the tile of column 32*j + c
             const int64_t off = (seg == 0) ? 32 * j : (int64_t)hj * hstep + 32 * j;
@@ -274,7 +271,7 @@ struct EpiQkvRope {
 // traffic, as long as the MFMA part of a K = 2048 tile. Here the positions come from arithmetic on the tile's first
 // row (two scalar loads of pos0 per tile), so every table load can be issued at once, and they run two groups of four
 // rows ahead of the rotation and the stores. Values and destinations are those of EpiQkvRope.
-template <int DHT, bool WHOLE>
+template <int DHT>
 struct EpiQkvRopeTile {
     static constexpr bool persistent_walk = false;       // inside the persistent walk, next to the held fragments, it spills
     static constexpr bool whole_tile = true;
@@ -371,8 +368,8 @@ struct EpiQkvRopeTile {
                         const int dd = (cj0 & (half - 1)) / 32;
                         const float y0 = acc[i][jp][r], y1 = acc[i][jp][r + 1];
                         const float2 a0 = cs[n % 3][e][dd], a1 = cs[n % 3][e + 1][dd];
-                        o0 = rotated<WHOLE>(o0, y0, a0, lo);
-                        o1 = rotated<WHOLE>(o1, y1, a1, lo);
+                        o0 = rotated(o0, y0, a0, lo);
+                        o1 = rotated(o1, y1, a1, lo);
                     }
                     // the neighbour's values of both rows (lanes c ^ 1); even columns store (own, neighbour's) of the
                     // first row, odd columns (neighbour's, own) of the second
@@ -1110,7 +1107,7 @@ static bool rope_tile_ok(int T, int L_max, int crows, int Hkv, int dh)
 {
     return T >= 128 && (int64_t)(Hkv + 1) * crows * dh * 2 < (1ll << 31) && (int64_t)L_max * dh * 4 < (1ll << 31);
 }
-template <int DHT, bool WHOLE>
+template <int DHT>
 static bool launch_qkv_rope(const bf16_t *h, const BMap &bm, bf16_t *q, bf16_t *kc, bf16_t *vc, const float2 *rope,
                             const int32_t *pos0, int n_seq, int T, int L_max, int crows, int Hq, int Hkv, int d, int *flags,
                             int2 *row_sp, hipStream_t st)
@@ -1127,15 +1124,15 @@ static bool launch_qkv_rope(const bf16_t *h, const BMap &bm, bf16_t *q, bf16_t *
     if (!(tiles && sure && plan.big == M))                    // the rows' (sequence, position) table, and the flags
         hipLaunchKernelGGL(k_row_positions, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, pos0, M, T, L_max, row_sp, flags);
     if (tiles) {
-        EpiQkvRopeTile<DHT, WHOLE> te{q, kc, vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
+        EpiQkvRopeTile<DHT> te{q, kc, vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
         if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, te, st)) return false;
     }
     if (plan.big > 0 && !(tiles && sure)) {
-        EpiQkvRope<DHT, false> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
+        EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
         if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, epi, st)) return false;
     }
     if (plan.big == M) return true;
-    EpiQkvRope<DHT, WHOLE> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, nullptr};
+    EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, nullptr};
     return launch_small<DHT>(plan.small, h, d, bm, plan.big, M, N, d, epi, st);
 }
 
@@ -1152,9 +1149,7 @@ bool launch_gemm_qkv_rope(const void *h, const void *wq, const void *wk, const v
     bm.base[0] = (const bf16_t *)wq; bm.base[1] = (const bf16_t *)wk; bm.base[2] = (const bf16_t *)wv;
     bm.seg_end[0] = nq; bm.seg_end[1] = nq + nkv; bm.seg_end[2] = nq + 2 * nkv;
     bm.mode = 0; bm.half = 0; bm.ld = d;
-    const bool whole = (int64_t)n_seq * T % 256 == 0 && rope_tile_ok(T, L_max, crows, Hkv, dh);
-    auto *const go = dh == 64 ? (whole ? launch_qkv_rope<64, true> : launch_qkv_rope<64, false>)
-                              : (whole ? launch_qkv_rope<128, true> : launch_qkv_rope<128, false>);
+    auto *const go = dh == 64 ? launch_qkv_rope<64> : launch_qkv_rope<128>;
     return go((const bf16_t *)h, bm, (bf16_t *)q, (bf16_t *)kc, (bf16_t *)vc, rope, pos0, n_seq, T, L_max, crows, Hq, Hkv, d,
               flags, (int2 *)row_sp_ws, st);
 }

@@ -1,6 +1,6 @@
 """The bf16 GEMM's smaller tiles: every tile the row rule can take, at the edges of its range, against the fp64 product;
-and the same rows in products of other heights, which take other tiles: equal bit for bit (a sequence's results do not
-depend on what else the call holds)."""
+and the same rows in products of other heights, which take other tiles, the same sequences in layer calls of other sizes, of whole
+tiles and not, and beside a sequence that does not fit: equal bit for bit."""
 import pytest
 import torch
 
@@ -35,7 +35,7 @@ def test_the_tile_does_not_show(M):
 @pytest.mark.parametrize("shape", [synth.LLAMA_1B, synth.LLAMA_8B], ids=["head64", "head128"])
 @pytest.mark.parametrize("rule", [{}, sol.PAPER_PRESET], ids=["topk", "pages"])
 def test_a_layer_row_does_not_depend_on_the_batch(shape, rule):
-    """One sequence of 160 tokens alone, with 2, 6, 12 and 29 others: small tiles, mixtures and whole rounds of large ones
+    """One sequence of 160 tokens alone, with 2, 6, 7, 12, 15 and 29 others: small tiles, mixtures and whole rounds of large ones
     in all four fused epilogues, with the sequences at different cache positions."""
     T, n = 160, 30
     g = torch.Generator(device="cuda").manual_seed(3)
@@ -54,10 +54,42 @@ def test_a_layer_row_does_not_depend_on_the_batch(shape, rule):
     kc, vc = (rnd(n, shape.n_kv_heads, L, shape.head_dim).to(torch.bfloat16) for _ in range(2))
     ctx = sol.Sol(shape, synth.TABLE_C2, max_positions=L, **rule)
     outs = []
-    for m in (1, 3, 7, 13, n):
+    for m in (1, 3, 7, 8, 13, 16, n):
         k, v = kc[:m].clone(), vc[:m].clone()
         y = ctx.layer_forward(w, x[:m].contiguous(), ids[:m].contiguous(), k, v, pos0=pos0[:m].contiguous())
         outs.append((y[0], k[0], v[0]))
     assert ctx.device_status() == sol.OK
     for o in outs[1:]:
         assert all(torch.equal(p, q) for p, q in zip(o, outs[0]))
+
+
+def test_rotated_rows_do_not_depend_on_the_rows_in_the_call():
+    """32 sequences of 136 tokens in one call (17 whole tiles of 256 rows), each alone (one ragged tile), and among one that
+    does not fit its cache, also in the next call before the status is read. 4.5 million keys in each half of the heads: a
+    last bit of the fp32 rotation that differs changes some sixty of their bf16 values."""
+    shape, T, n = synth.ModelShape(512, 32, 32, 64, 256), 136, 32
+    g = torch.Generator(device="cuda").manual_seed(4)
+
+    def rnd(*sz):
+        return torch.randn(sz, generator=g, device="cuda").to(torch.bfloat16)
+
+    w = dict(wq=rnd(2048, 512), wk=rnd(2048, 512), wv=rnd(2048, 512), wo=rnd(512, 2048), w_gate=rnd(256, 512), w_up=rnd(256, 512),
+             w_down=rnd(512, 256), w_in_norm=rnd(512), w_post_norm=rnd(512))
+    x, ids = rnd(n, T, 512), torch.zeros((n, T), dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, [synth.DENSE_ACTION], max_positions=T)
+
+    def layer(rows, pos0=None):
+        k, v = (torch.zeros((x[rows].shape[0], 32, T, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        return ctx.layer_forward(w, x[rows].contiguous(), ids[rows].contiguous(), k, v, pos0=pos0), k, v
+
+    whole = layer(slice(0, n))
+    assert ctx.device_status() == sol.OK
+    for i in range(n):
+        assert all(torch.equal(a[0], b[i]) for a, b in zip(layer(slice(i, i + 1)), whole)), i
+    pos0 = torch.zeros(n, dtype=torch.int32, device="cuda")
+    pos0[5] = 1
+    rest = [i for i in range(n) if i != 5]
+    flagged, after = layer(slice(0, n), pos0), layer(slice(0, n), torch.zeros_like(pos0))
+    assert ctx.device_status() == sol.ERR_CACHE_OVERFLOW
+    for a, b, c in zip(flagged, after, whole):
+        assert torch.equal(a[rest], c[rest]) and torch.equal(b, c)
