@@ -44,7 +44,7 @@ typedef enum {
     SOL_OK = 0,
     SOL_ERR_INVALID_ARG = -1,   /* null pointer, non-positive size, inconsistent shape          */
     SOL_ERR_UNSUPPORTED = -2,   /* valid request this build has no kernel for                    */
-    SOL_ERR_WORKSPACE = -3,     /* workspace pointer null / smaller than sol_workspace_bytes     */
+    SOL_ERR_WORKSPACE = -3,     /* workspace pointer null / too small (see sol_workspace_bytes)  */
     SOL_ERR_ACTION = -4,        /* action table entry or action id out of range                  */
     SOL_ERR_CACHE_OVERFLOW = -5,/* tokens would be written past L_max                            */
     SOL_ERR_HIP = -6            /* a HIP runtime call failed (text in sol_last_error)            */
@@ -128,7 +128,10 @@ const char *sol_last_error(const sol_ctx *ctx);
 
 /* Bytes of device workspace the operation needs for these sizes (host-only arithmetic).
  * LAYER_FORWARD: (n_seq, T, L_max). DECODE_STEP: (B, ignored, L_max).
- * SCHEDULE_LOGLIK: (B*G, T, ignored). Returns 0 for an invalid request. */
+ * SCHEDULE_LOGLIK: (B*G, T, ignored). Returns 0 for an invalid request. A smaller workspace is refused
+ * with SOL_ERR_WORKSPACE, with one exception: DECODE_STEP, and LAYER_FORWARD with T = 1, include scratch
+ * for a faster attention kernel of few sequences in long caches; a workspace that lacks no more than
+ * that (one sized for a smaller L_max) is accepted, and the call gives the same results without it. */
 size_t sol_workspace_bytes(const sol_model_cfg *cfg, int op, int n_seq, int T, int L_max);
 
 /* One decoder layer over T tokens per sequence, each under its own action:

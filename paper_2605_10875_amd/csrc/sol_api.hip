@@ -338,17 +338,33 @@ static size_t decode_split_bytes(const sol_model_cfg &g, int64_t B, int L_max)
     return c.off + bytes + 512 <= SOL_STATIC_SCRATCH_BYTES ? bytes : 0;
 }
 
+// Bytes of a decode step's pieces for n sequences, the split attention's scratch among them for every batch up to n that takes
+// it: few sequences need more than a few more of them, and a workspace sized for a program's largest batch serves the smaller ones.
+template <class Base>
+static size_t decode_bytes(const sol_model_cfg &g, int64_t n, int L_max, const Base &base)
+{
+    size_t need = base(n);
+    for (int64_t b = 1; b <= n && b <= DECODE_SPLIT_MAX_B; ++b)
+        if (const size_t split = decode_split_bytes(g, b, L_max)) {
+            Carver c(nullptr);
+            c.take(base(b));
+            c.take(split);
+            if (c.off > need) need = c.off;
+        }
+    return need;
+}
+
 extern "C" size_t sol_workspace_bytes(const sol_model_cfg *cfg, int op, int n_seq, int T, int L_max)
 {
     if (!cfg || n_seq <= 0) return 0;
     Carver c(nullptr);
     if (op == SOL_OP_LAYER_FORWARD) {
         if (T <= 0) return 0;
+        if (T == 1)
+            return decode_bytes(*cfg, n_seq, L_max, [&](int64_t n) { Carver p(nullptr); LayerWs w; carve_layer(p, *cfg, n, 1, L_max, w); return p.off; }) + 256;
         LayerWs w; carve_layer(c, *cfg, n_seq, T, L_max, w);
-        if (T == 1) c.take(decode_split_bytes(*cfg, n_seq, L_max));
     } else if (op == SOL_OP_DECODE_STEP) {
-        StackWs w; carve_stack(c, *cfg, n_seq, 1, false, w);
-        c.take(decode_split_bytes(*cfg, n_seq, L_max));
+        return decode_bytes(*cfg, n_seq, L_max, [&](int64_t n) { Carver p(nullptr); StackWs w; carve_stack(p, *cfg, n, 1, false, w); return p.off; }) + 256;
     } else if (op == SOL_OP_SCHEDULE_LOGLIK) {
         if (T <= 0) return 0;
         StackWs w; carve_stack(c, *cfg, n_seq, T, true, w);

@@ -1824,6 +1824,7 @@ size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh)
 {
     if (B <= 0 || Hq != DEC_HPB * Hkv || (dh != 64 && dh != 128) || Hq * dh > 4096 || L_max > DSP_MAX_L || L_max < 1) return 0;
     const int64_t items = (int64_t)B * Hkv;
+    static_assert(DECODE_SPLIT_MAX_B >= 32, "");
     if (items > 32 || L_max < 1536 || L_max < 64 * items) return 0;
     return (size_t)B * Hq * ((size_t)dsp_lpad(L_max) * 4 + sizeof(DecSel) + (size_t)DEC_WAVES * dh * 4);
 }

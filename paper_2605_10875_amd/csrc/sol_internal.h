@@ -153,6 +153,7 @@ bool launch_attn_decode(const void *q, const void *k_cache, const void *v_cache,
                         int *flags, hipStream_t st);
 // The same for few sequences, an item's keys spread over workgroups: scratch bytes (0: not covered, or too many sequences)
 // and the launches; the outputs are *nsplit partial ones, [nsplit][B][Hq * dh] at *part, for launch_fq_rows with *sel.
+constexpr int DECODE_SPLIT_MAX_B = 32;            // sequences at most (of one KV head)
 size_t attn_decode_split_bytes(int B, int L_max, int Hq, int Hkv, int dh);
 bool launch_attn_decode_split(const void *q, const void *k_cache, const void *v_cache, void *ws, const RowAct *ra,
                               const int32_t *cache_len, int B, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st,

@@ -108,14 +108,25 @@ def test_page_meta_bytes_is_host_arithmetic():
     assert sol.lib().sol_page_meta_bytes(C.byref(cfg), 0, 8200) == 0
 
 
+def _decode_bytes(heads, B, L):
+    return sol.workspace_bytes(sol.make_cfg(synth.ModelShape(1024, heads, heads // 4, 128, 1024), sol.BF16, 9216), sol.OP_DECODE_STEP, B, 1, L)
+
+
 def test_split_decode_attention_where_it_pays():
-    # the split form's scratch shows in the workspace
+    # the split form's scratch shows in the workspace: more than at 1024 positions, where no batch takes it, and more than the
+    # next smaller batch needs
     def split(heads, B, L):
-        cfg = sol.make_cfg(synth.ModelShape(1024, heads, heads // 4, 128, 1024), sol.BF16, 9216)
-        return sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, B, 1, L) > sol.workspace_bytes(cfg, sol.OP_DECODE_STEP, B, 1, 1024)
+        return _decode_bytes(heads, B, L) > max(_decode_bytes(heads, B, 1024), _decode_bytes(heads, B - 1, L))
 
     assert split(32, 1, 8192)
     assert not split(64, 1, 8192)                  # 8192 outputs per row: outside the kernel that folds the parts
     assert split(32, 4, 8192) and not split(32, 5, 8192)      # 32 items; rows of few keys would lose more than they gain
     assert split(32, 1, 1536) and not split(32, 1, 1535)
     assert split(32, 4, 2048) and not split(32, 4, 2047)
+
+
+@pytest.mark.parametrize("shape", [synth.LLAMA_1B, synth.LLAMA_8B], ids=["1b", "8b"])
+def test_a_decode_workspace_serves_smaller_batches(shape):
+    for L in (1024, 1536, 8192):
+        need = [sol.workspace_bytes(sol.make_cfg(shape, sol.BF16, 9216), sol.OP_DECODE_STEP, B, 1, L) for B in range(1, 65)]
+        assert need == sorted(need)
