@@ -998,25 +998,30 @@ static bool launch_mfma(const bf16_t *A, int64_t lda, const BMap &bmap, int64_t 
     if (Nv % BN || K % (2 * BK) || K < 2 * BK) return false;
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
     constexpr size_t lds = 2 * (size_t)(BM + BN) * 128;
-    auto kern = k_gemm_mfma<BM, BN, WM, WN, Epi, false>;
-    auto kern_p = k_gemm_mfma<BM, BN, WM, WN, Epi, true>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern_p), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return false;
-        attr_done = true;
-    }
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = Nv / BN;
     const int n_tiles = tiles_m * tiles_n;
     const int per_xcd = (n_tiles + 7) / 8;
-    // several tiles per CU and no ragged tile: the persistent walk, one workgroup per CU (CUs / 8 per XCD)
-    const int wg_xcd = device_cus() / 8;
-    if (SOL_GEMM_PERSIST && Epi::persistent_walk && wg_xcd > 0 && per_xcd > wg_xcd && M % BM == 0) {
-        hipLaunchKernelGGL(kern_p, dim3(wg_xcd * 8), dim3(NT), lds, st, A, lda, bmap, M, Nv, K, tiles_m, tiles_n, epi);
-        return true;
+    if constexpr (SOL_GEMM_PERSIST && Epi::persistent_walk) {
+        // several tiles per CU and no ragged tile: the persistent walk, one workgroup per CU (CUs / 8 per XCD)
+        const int wg_xcd = device_cus() / 8;
+        if (wg_xcd > 0 && per_xcd > wg_xcd && M % BM == 0) {
+            auto kern = k_gemm_mfma<BM, BN, WM, WN, Epi, true>;
+            static bool attr_done = false;
+            if (!attr_done) {
+                if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds) != hipSuccess) return false;
+                attr_done = true;
+            }
+            hipLaunchKernelGGL(kern, dim3(wg_xcd * 8), dim3(NT), lds, st, A, lda, bmap, M, Nv, K, tiles_m, tiles_n, epi);
+            return true;
+        }
+    }
+    auto kern = k_gemm_mfma<BM, BN, WM, WN, Epi, false>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess) return false;
+        attr_done = true;
     }
     hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(NT), lds, st, A, lda, bmap, M, Nv, K, tiles_m, tiles_n, epi);
     return true;
