@@ -1,6 +1,7 @@
 """Decode attention of few sequences (an item's keys spread over workgroups) against the oracle's attention: cache lengths
 around the edges of its blocks and of the dispatch line (1536 positions), tied scores whose quota ends inside a wave's
-columns, a skipped sequence, both head sizes; and against the kernel of many sequences, bit for bit."""
+columns, a skipped sequence, both head sizes; against the kernel of many sequences, bit for bit, in every class of cache
+lengths; and a step with its scratch, without it and in the static scratch."""
 import numpy as np
 import pytest
 import torch
@@ -17,8 +18,12 @@ TABLE = synth.action_table((0.0625, 0.25, 1.0), (0.0,), (16,))
 @pytest.mark.parametrize("dh,L,lens,dup", [
     (64, 1535, (0, 700, 1534), 0),             # the one-workgroup-per-item kernel, for comparison
     (64, 1536, (0, 255, 256, 257, 1535), 0),
-    (64, 4097, (1023, 1024, 4096), 5),         # five distinct keys: every budget ends inside a tie
+    (64, 4096, (2048, 4095), 0),
+    (64, 4096, (2047, 3000, 4095), 3),         # three distinct keys: every budget ends inside a tie
+    (64, 4097, (1023, 1024, 4096), 5),
+    (64, 8192, (4100, 8191), 0),
     (128, 2048, (63, 64, 1999, 2047), 0),
+    (128, 8192, (4096, 8191), 6),
     (128, 9216, (8191, 9215), 7),
 ])
 def test_attention_of_few_sequences(dh, L, lens, dup):
@@ -35,7 +40,9 @@ def test_attention_of_few_sequences(dh, L, lens, dup):
     args = [dev(q, sol.BF16).view(B, 1, -1), dev(ids).view(B, 1), dev(k, sol.BF16), dev(v, sol.BF16), dev(np.array(lens, np.int32))]
     out = ctx.test_attention_stage(*args[:4], pos0=args[4])
     # the same sequences among enough others for the one-workgroup-per-item kernel: the same sums in the same order
-    many = [t.repeat((50 // B,) + (1,) * (t.dim() - 1)) for t in args]
+    reps = -(-100 // (B * hkv))
+    assert B * hkv <= 32 < reps * B * hkv
+    many = [t.repeat((reps,) + (1,) * (t.dim() - 1)) for t in args]
     assert torch.equal(ctx.test_attention_stage(*many[:4], pos0=many[4])[:B], out)
     assert ctx.device_status() == sol.OK
     o = host(out).reshape(B, 4 * hkv, dh)
@@ -60,3 +67,36 @@ def test_a_sequence_that_does_not_fit_is_skipped_and_flagged():
     bad = ctx.test_attention_stage(q, ids, k, v, pos0=torch.tensor([900, L], dtype=torch.int32, device="cuda"))
     assert ctx.device_status() == sol.ERR_CACHE_OVERFLOW
     assert torch.equal(ok[0], bad[0])
+
+
+@pytest.mark.parametrize("dh,L", [(64, 1536), (128, 4200)])
+def test_a_step_does_not_depend_on_where_its_scratch_is(dh, L):
+    """With the split attention's scratch, in a workspace that lacks it (one workgroup per item) and in the static scratch."""
+    shape, B = synth.ModelShape(256, 8, 2, dh, 256, 2), 3
+    g = torch.Generator(device="cuda").manual_seed(dh)
+
+    def rnd(*size, scale=1.0):
+        return torch.randn(size, generator=g, device="cuda").mul_(scale).to(torch.bfloat16)
+
+    nq, nkv = 8 * dh, 2 * dh
+    layers = [dict(wq=rnd(nq, 256, scale=0.1), wk=rnd(nkv, 256, scale=0.1), wv=rnd(nkv, 256, scale=0.1), wo=rnd(256, nq, scale=0.1),
+                   w_gate=rnd(256, 256, scale=0.1), w_up=rnd(256, 256, scale=0.1), w_down=rnd(256, 256, scale=0.1),
+                   w_in_norm=rnd(256), w_post_norm=rnd(256)) for _ in range(2)]
+    kc, vc = ([rnd(B, 2, L, dh) for _ in range(2)] for _ in range(2))
+    x, ids = rnd(B, 256), torch.arange(B, dtype=torch.int32, device="cuda")
+    lens = torch.tensor([L - 1, L // 2, 700], dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, TABLE, max_positions=L)
+    full, short = (sol.workspace_bytes(ctx.cfg, sol.OP_DECODE_STEP, B, 1, n) for n in (L, 1024))
+    assert full > short
+
+    def step(call, **kw):
+        k, v = [t.clone() for t in kc], [t.clone() for t in vc]
+        out, _ = call(layers, None, ids, lens, k, v, x_in=x, **kw)
+        return [out] + k + v
+
+    ref = step(ctx.decode_step, workspace=torch.empty(full, dtype=torch.uint8, device="cuda"))
+    for other in (step(ctx.decode_step, workspace=torch.empty(short, dtype=torch.uint8, device="cuda")), step(ctx.decode_step_static)):
+        assert all(torch.equal(a, b) for a, b in zip(ref, other))
+    assert ctx.device_status() == sol.OK
+    with pytest.raises(sol.SolError):
+        ctx.decode_step(layers, None, ids, lens, kc, vc, x_in=x, workspace=torch.empty(short - 256, dtype=torch.uint8, device="cuda"))
