@@ -2664,11 +2664,13 @@ __device__ __forceinline__ float max_over_lane_groups(float v)
 // PRE: two-segment addressing as in k_attn_pv. NQT: query tiles of 16 rows per workgroup (2; 1 for passes of at most
 // 16 rows per sequence, where a second tile would be all dead rows).
 template <int DH, int G, int W, bool PRE, int NQT>
-// (head size 64: a floor of 3 / 4 waves per SIMD caps the registers at 168 / 128; left alone the compiler takes 218 and
-// 138 and the exp / pack chains of the softmax have nothing to overlap with: 0.94 -> 0.74 ms at C2 under the paper's
-// configuration; head size 128 with 4+ heads per group: 2 waves per SIMD, 256 registers instead of 410, 4.51 -> 2.44 ms
-// at the 8B shape with 4096-token sequences)
-__global__ void __launch_bounds__(G * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? (NQT == 1 ? 4 : 3) : (G >= 4 ? 2 : 1), 8)))
+// (4+ heads per group. Head size 64: a floor of 3 / 4 waves per SIMD caps the registers at 168 / 128; left alone the compiler
+// takes 218 and 138 and the exp / pack chains of the softmax have nothing to overlap with: 0.94 -> 0.74 ms at C2 under the paper's
+// configuration; head size 128: 2 waves per SIMD, 256 registers instead of 410, 4.51 -> 2.44 ms at the 8B shape with 4096-token
+// sequences. 1 or 2 heads per group: a wave holds 4 or 2 times as much of a staged chunk, five workgroups of 1 or 2 waves fill the
+// LDS anyway, and the floor's cap only spilled: head size 64, 32 heads, 2 x 2048 tokens, 1 per group 623 -> 194 us (498 with the
+// transposed copy of V), 2 per group 138 -> 110)
+__global__ void __launch_bounds__(G * 64) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 : (G == 2 ? (DH == 64 ? 2 : 1) : (DH == 64 ? (NQT == 1 ? 4 : 3) : 2)), 8)))
 k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf16_t *__restrict__ vc,
                 const unsigned long long *__restrict__ selp, float *__restrict__ o32, const int32_t *__restrict__ pos0, int Tn,
                 int L_max, int Hq, int Hkv, float scale, int log2S, int n_sink, int n_window, PrefixView pv)
