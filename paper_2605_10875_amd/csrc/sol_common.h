@@ -34,6 +34,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// rotation of a pair (x0, x1) by (cos, sin) in a decode step; which product is rounded before the sum is spelled out, so that a
+// row does not depend on the kernel that its step takes
+__device__ __forceinline__ float2 rotate_pair(float x0, float x1, float2 cs)
+{
+    return make_float2(__builtin_fmaf(x0, cs.x, -(x1 * cs.y)), __builtin_fmaf(x1, cs.x, x0 * cs.y));
+}
+
 __device__ __forceinline__ float ld(const float *p) { return *p; }
 __device__ __forceinline__ float ld(const bf16_t *p) { return bf16_to_f32(*p); }
 __device__ __forceinline__ void st(float *p, float v) { *p = v; }

@@ -856,12 +856,12 @@ k_gemm_mfma(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t M, int
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same product with smaller tiles, for row counts whose 256 x 256 tiles would leave CUs idle. ST LDS stages filled
-// by LDS-direct loads. AHEAD (one workgroup per CU): the fragments of slice kt + 1 are read while slice kt is multiplied
-// and ST slices are in flight, so a step is bound by the CU's load path (about 85 GB/s whatever the tile: 0.19 us per
-// slice of a 64 x 64 tile, 0.39 us of 128 x 128). Without AHEAD two workgroups share a CU (two stages of a 128 x 128
-// tile each) and hide each other's barriers and LDS reads. Every output is the chain of 32x32x16 MFMAs over k that
-// k_gemm_mfma runs, so the tile does not show in the results (bit for bit).
+// The same product with smaller tiles, for row counts whose 256 x 256 tiles would leave CUs idle; plan_gemm gives a CU at
+// most one workgroup. ST LDS stages filled by LDS-direct loads, so that ST slices are in flight. A step reads the fragments
+// of slice kt + 1 and multiplies slice kt; their order is the compiler's, which keeps only part of the next slice's fragments
+// in registers (61 to 91 for the 32 x 32 and 32 x 64 wave tiles). Bound: a step's time goes with its bytes, 0.19 us per slice
+// of a 64 x 64 tile (16 KB) and 0.39 us of 128 x 128 (32 KB), about 85 GB/s for one CU alone. Every output is the chain of
+// 32x32x16 MFMAs over k that k_gemm_mfma runs, so the tile does not show in the results (bit for bit).
 // ------------------------------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, int ST, class Epi>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
@@ -1039,6 +1039,8 @@ constexpr int SOL_WN = 128;
 // projections of the 1B and 8B shapes; what a round takes hardly depends on how many CUs it fills):
 //   64 x 64: 0.23   128 x 64: 0.36   128 x 128: 0.5   128 x 256: 0.75
 // (down projection of the 1B shape, 256 x 256 -> rule: 333 rows 122 -> 28 us, 1024 rows 123 -> 43, 2048 rows 125 -> 69.)
+// The q/k/v map with heads of 128 has 64 x 128 tiles in place of both 64-column ones, and goes by the same costs: 8B shape, 80
+// rows 80 -> 36 us, 333 rows 86 -> 44, 512 rows 77 -> 45, 1024 rows 82 -> 65, from 1500 rows on 256 x 256 tiles.
 // So a call takes the smallest tile of which every CU gets at most one; with more rows than that, whole rounds of
 // 256 x 256 tiles first and the smaller tile for the rest where that ends sooner than a last round that is nearly
 // empty. The tile does not show in the results.

@@ -173,8 +173,8 @@ k_gemv(GemvArgs a)
     if (MODE == GV_QKV) {
         bf16_t *dst = seg == 0 ? (bf16_t *)a.out + head * a.dh : (seg == 1 ? a.kc : a.vc) + ((int64_t)head * a.crows + pos) * a.dh;
         if (seg < 2) {
-            const float y0 = __builtin_fmaf(y[0], cs.x, -(y[1] * cs.y)), y1 = __builtin_fmaf(y[1], cs.x, y[0] * cs.y);
-            y[0] = y0; y[1] = y1;
+            const float2 z = rotate_pair(y[0], y[1], cs);
+            y[0] = z.x; y[1] = z.y;
         }
         st(dst + c, y[0]);
         st(dst + c + half, y[1]);

@@ -538,11 +538,11 @@ k_rope_store(const float *__restrict__ qkv, int nsplit, int64_t split_stride, T 
     const int c = threadIdx.x;                             // < half
     if (slot < Hq + Hkv) {                                 // q or k head: rotate the pair (c, c + half)
         const float x0 = val(in + c), x1 = val(in + c + half);
-        const float2 t = rope[(int64_t)pos * half + c];
+        const float2 y = rotate_pair(x0, x1, rope[(int64_t)pos * half + c]);
         T *dst = slot < Hq ? q + r * (int64_t)(Hq * dh) + slot * dh
                            : kc + (((int64_t)s * Hkv + (slot - Hq)) * crows + pos) * dh;
-        st(dst + c, x0 * t.x - x1 * t.y);
-        st(dst + c + half, x1 * t.x + x0 * t.y);
+        st(dst + c, y.x);
+        st(dst + c + half, y.y);
     } else {
         T *dst = vc + (((int64_t)s * Hkv + (slot - Hq - Hkv)) * crows + pos) * dh;
         st(dst + c, val(in + c));
