@@ -23,7 +23,11 @@
  *     [n_seq][T][d_model]. KV caches are [n_seq][n_kv_heads][L_max][head_dim] with keys stored
  *     after the rotary embedding. Element type of weights, activations and caches is cfg.dtype.
  *   - Determinism: a sequence's outputs do not depend on what else is in the batch, nor on its
- *     slot; no floating-point atomics, no data-dependent reduction order.
+ *     slot; no floating-point atomics, no data-dependent reduction order. The number of rows in a
+ *     bf16 call (n_seq * T) matters in one way: up to 64 rows, the linear maps add partial sums over
+ *     K whose number falls as the rows grow (Llama-3.2-1B: the same for 1..16, 17..32 and 33..64
+ *     rows; Llama-3.1-8B: for 1..64), and from 65 rows on they run one chain, so that the last bits
+ *     of a row may differ between these classes.
  *
  * Numerics with dtype = SOL_BF16: contractions run on bf16 inputs with fp32 accumulation; the
  * tensors handed between operators (normed+quantised linear inputs, q, k, v, attention output,
