@@ -310,7 +310,7 @@ typedef float f32x4_a __attribute__((ext_vector_type(4)));
 //
 //   k_attn_select   per (sequence, query head, BQ query rows): all causal scores of the rows by MFMA into
 //                   LDS as fp32, then per row the row maximum and -- when the budget is below the row
-//                   length -- the exact threshold of the b largest scores (wave bisection on ballots).
+//                   length -- the exact threshold of the b largest scores (two or four rows per wave).
 //                   Output per (row, head): { thr, max, jstar }: a key is kept iff
 //                   s > thr  or  (s == thr and key index <= jstar).
 //   k_attn_pv       per (sequence, KV head, 32 query rows), one wave per query head of the group: streams
@@ -363,351 +363,256 @@ __device__ __forceinline__ int wave_tie_last(const float (&key)[SLOTS], int n, f
     return result;
 }
 
-// number of scores >= pivot, the pivot in a vector register (the same value in every lane). NG > 0: the first NG groups of
-// 256 columns; NG == 0: every group that starts below n. The row is held as the scores themselves (-inf past its end)
-// and compared as floats: that counts what comparing order-preserving keys counts (-0 and +0 are one value either way,
-// subnormals are not flushed, there are no NaNs), and the row needs no conversion when it is loaded.
-template <int SLOTS, int NG>
-__device__ __forceinline__ int wave_count_ge_v(const float (&key)[SLOTS], int n, float pivot)
+// ---- R rows of one wave searched together ----------------------------------------------------------------------------
+// The row a lane group (64 / R lanes) keeps the search state of: lanes [r * 64 / R, (r + 1) * 64 / R) hold row r's, so the
+// interpolation and the bracket updates, ~35 vector instructions per step, are done once for all R rows; only the counts
+// (two vector instructions per 64 scores) are per row. A pivot goes to its row's compares through a scalar register
+// (readlane); the lanes' counts of all rows are summed by one exchange that leaves each row's in its group.
+template <class T> __device__ __forceinline__ void swap_lanes32(T &a, T &b)     // upper half of a <-> lower half of b
 {
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < (NG ? NG : SLOTS / 4); ++j)
-        if (NG || 256 * j < n) {
-            unsigned long long m[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) asm("v_cmp_ge_f32_e64 %0, %1, %2" : "=s"(m[e]) : "v"(key[4 * j + e]), "v"(pivot));
-            cnt += (__popcll(m[0]) + __popcll(m[1])) + (__popcll(m[2]) + __popcll(m[3]));
-        }
-    return cnt;
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]), b = __builtin_bit_cast(T, (uint32_t)r[1]);
+}
+template <class T> __device__ __forceinline__ void swap_lanes16(T &a, T &b)     // odd rows of 16 lanes of a <-> even rows of b
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]), b = __builtin_bit_cast(T, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void set_lane(int &v, int x, int lane_imm)   // v of lane lane_imm (a constant) = x (uniform)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(lane_imm));
+}
+struct OpMaxF { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fmaxf(a, b); } };
+struct OpMinF { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fminf(a, b); } };
+struct OpAddI { __device__ __forceinline__ int operator()(int a, int b) const { return a + b; } };
+// every lane of a row of 16 has a source under these controls: bound_ctrl lets the compiler fold the move into the operation
+template <int CTRL, class T> __device__ __forceinline__ T dpp_of(T v)
+{
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+// x[r]: the lanes' parts of row r; result: in the lanes of group r the whole of row r
+template <int R, class T, class Op> __device__ __forceinline__ T group_reduce(const T (&x)[R], Op op)
+{
+    static_assert(R == 2 || R == 4, "two or four rows per wave");
+    T v, a = x[0], b = x[R / 2];
+    swap_lanes32(a, b);
+    v = op(a, b);
+    if constexpr (R == 4) {
+        T c = x[1], d = x[3];
+        swap_lanes32(c, d);
+        T e = op(c, d);
+        swap_lanes16(v, e);
+        v = op(v, e);
+    }
+    v = op(v, dpp_of<0xB1>(v));                          // quad_perm [1,0,3,2]
+    v = op(v, dpp_of<0x4E>(v));                          // quad_perm [2,3,0,1]
+    v = op(v, dpp_of<0x141>(v));                         // row_half_mirror
+    v = op(v, dpp_of<0x140>(v));                         // row_mirror
+    if constexpr (R == 2) {
+        T w = v;
+        swap_lanes16(v, w);
+        v = op(v, w);
+    }
+    return v;
 }
 
-// the same count with one dispatch per call on the row's number of 256-column groups ng = ceil(n / 256), for a search
-// loop that exists once (the variant with a side job): long rows only
-template <int SLOTS>
-__device__ __forceinline__ int wave_count_ge_sw(const float (&key)[SLOTS], int n, int ng, float pivot)
+// What a wave gathers from its rows' scores while they come in: extremes over all of them, sum and sum of squares over
+// the first two of every four columns (they only place the first pivot)
+template <int R> struct RowStats {
+    float mx[R], mn[R], s1[R], s2[R];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) mx[r] = -__builtin_inff(), mn[r] = __builtin_inff(), s1[r] = 0.f, s2[r] = 0.f;
+    }
+};
+// columns col0 + 4 * lane + e (e < 4) of row r (n valid columns) into four registers; -inf past the row's end
+template <int R>
+__device__ __forceinline__ void row_take4(RowStats<R> &st, int r, f32x4_a v, int col0, int n, int lane, float &k0, float &k1,
+                                          float &k2, float &k3)
 {
-    static_assert(SLOTS == 20 || SLOTS == 32 || SLOTS == 64, "long-row variants");
-    if constexpr (SLOTS == 20) {
-        return ng == 5 ? wave_count_ge_v<SLOTS, 5>(key, n, pivot) : wave_count_ge_v<SLOTS, 0>(key, n, pivot);
-    } else if constexpr (SLOTS == 32) {
-        switch (ng) {
-        case 8: return wave_count_ge_v<SLOTS, 8>(key, n, pivot);
-        case 7: return wave_count_ge_v<SLOTS, 7>(key, n, pivot);
-        case 6: return wave_count_ge_v<SLOTS, 6>(key, n, pivot);
-        case 5: return wave_count_ge_v<SLOTS, 5>(key, n, pivot);
-        default: return wave_count_ge_v<SLOTS, 0>(key, n, pivot);
-        }
+    if (col0 + 256 <= n) {
+        k0 = v[0], k1 = v[1], k2 = v[2], k3 = v[3];
+        st.mx[r] = __builtin_fmaxf(__builtin_fmaxf(st.mx[r], v[0]), v[1]);
+        st.mx[r] = __builtin_fmaxf(__builtin_fmaxf(st.mx[r], v[2]), v[3]);
+        st.mn[r] = __builtin_fminf(__builtin_fminf(st.mn[r], v[0]), v[1]);
+        st.mn[r] = __builtin_fminf(__builtin_fminf(st.mn[r], v[2]), v[3]);
+        st.s1[r] += v[0];
+        st.s1[r] += v[1];
+        st.s2[r] = __builtin_fmaf(v[0], v[0], st.s2[r]);
+        st.s2[r] = __builtin_fmaf(v[1], v[1], st.s2[r]);
     } else {
-        switch (ng) {
-        case 16: return wave_count_ge_v<SLOTS, 16>(key, n, pivot);
-        case 15: return wave_count_ge_v<SLOTS, 15>(key, n, pivot);
-        case 14: return wave_count_ge_v<SLOTS, 14>(key, n, pivot);
-        case 13: return wave_count_ge_v<SLOTS, 13>(key, n, pivot);
-        case 12: return wave_count_ge_v<SLOTS, 12>(key, n, pivot);
-        case 11: return wave_count_ge_v<SLOTS, 11>(key, n, pivot);
-        case 10: return wave_count_ge_v<SLOTS, 10>(key, n, pivot);
-        case 9: return wave_count_ge_v<SLOTS, 9>(key, n, pivot);
-        default: return wave_count_ge_v<SLOTS, 0>(key, n, pivot);
+        float k[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool valid = col0 + 4 * lane + e < n;
+            k[e] = valid ? v[e] : -__builtin_inff();
+            st.mx[r] = __builtin_fmaxf(st.mx[r], k[e]);
+            st.mn[r] = valid ? __builtin_fminf(st.mn[r], v[e]) : st.mn[r];
+            if (e < 2) {
+                const float x = valid ? v[e] : 0.f;
+                st.s1[r] += x;
+                st.s2[r] = __builtin_fmaf(x, x, st.s2[r]);
+            }
         }
+        k0 = k[0], k1 = k[1], k2 = k[2], k3 = k[3];
     }
 }
 
-// One row's search from the bracket [lo, hi] (count(key >= lo) >= b, count(key >= hi + 1) < b): returns the bracket
-// closed on the threshold key (lo == hi), or exact = true and a pivot with exactly b keys at or above it.
-// With g(x) = #(key >= x) - b + 1/2, g(lo) > 0 > g(hi + 1). The pivot is the zero of the straight line through the
-// two ends in the score domain (regula falsi with the Illinois correction: an end that stays put twice in a row has
-// its weight halved), clamped into (lo, hi] so that every step shrinks the bracket; on smooth score distributions
-// this lands between the b-th and (b+1)-th largest score in about 6 steps where bisection of the key needs about
-// 14. From the 13th step on the pivot is the midpoint of the key range, which bounds the worst case.
-// The bracket and the line live in vector registers and are updated by selects although every lane holds the same
-// values: the loop is bound by the scalar unit, which already counts the compare masks, and a CU has four vector
-// pipes to its one scalar pipe.
-// side: called once per step, after the count: work of the caller's that does not depend on the search and that the
-// steps' vector and scalar instructions can hide (k_attn_select: the score tiles of the workgroup's next block)
-struct NoSide { __device__ __forceinline__ void operator()() const {} };
-template <int SLOTS, int NG, class Side>
-__device__ __forceinline__ uint32_t wave_search_thr(const float (&key)[SLOTS], int n, int b, uint32_t lo_s, uint32_t hi_s,
-                                                    bool &exact, Side &side)
+// number of this lane's scores >= pivot (uniform) in the first ng groups of 256 columns: a compare and an add with carry
+// per 64 scores. One dispatch, then straight-line code. Rows shorter than the variant's class (the first rows of a wave at
+// the class's edge) count every group of the class.
+template <int SLOTS, int NG> __device__ __forceinline__ int wave_count_ge_n(const float (&key)[SLOTS], float pivot)
 {
-    uint32_t lo = lo_s, hi = hi_s;
-    asm volatile("" : "+v"(lo), "+v"(hi));               // from here on the compiler treats the bracket as per-lane data
-    // counts enter the line as log-odds, t(c) = log2((c + 1/2) / (n - c + 1/2)) - t(b - 1/2): for bell-shaped score
-    // distributions t is close to linear in the score where the count itself is S-shaped
-    // uniform and fixed over the loop: kept in scalar registers (the vector registers are what limits the kernel's occupancy)
-    const float nh = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)n + 0.5f)));
-    const float t_b = __int_as_float(__builtin_amdgcn_readfirstlane(
-        __float_as_int(__builtin_amdgcn_logf((float)b * __builtin_amdgcn_rcpf((float)(n - b) + 1.0f)))));
-    float flo = score_unkey(lo), fhi = score_unkey(hi);
-    float glo = __builtin_amdgcn_logf(nh * 2.0f) - t_b, ghi = -__builtin_amdgcn_logf(nh * 2.0f) - t_b;
-    float w_up = 1.0f, w_dn = 1.0f;                      // what the end that stays put is scaled by if the step goes up / down
-    exact = false;
-    for (int it = 0; __ballot(lo < hi) != 0ull; ++it) {
-        const float fp = __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
-        const uint32_t ufp = __float_as_uint(fp);         // as score_key; which of the two zeros' keys a pivot takes is immaterial
-        uint32_t mid = ufp ^ ((uint32_t)((int32_t)ufp >> 31) | 0x80000000u);
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < 4 * NG; ++j) cnt += key[j] >= pivot ? 1 : 0;
+    return cnt;
+}
+template <int SLOTS>
+__device__ __forceinline__ int wave_count_ge_s(const float (&key)[SLOTS], int ng, float pivot)
+{
+    if constexpr (SLOTS == 4) {
+        return wave_count_ge_n<SLOTS, 1>(key, pivot);
+    } else if constexpr (SLOTS == 16) {
+        if (ng <= 2) return ng == 1 ? wave_count_ge_n<SLOTS, 1>(key, pivot) : wave_count_ge_n<SLOTS, 2>(key, pivot);
+        return ng == 3 ? wave_count_ge_n<SLOTS, 3>(key, pivot) : wave_count_ge_n<SLOTS, 4>(key, pivot);
+    } else if constexpr (SLOTS == 20) {
+        return wave_count_ge_n<SLOTS, 5>(key, pivot);
+    } else if constexpr (SLOTS == 32) {
+        if (ng <= 6) return ng <= 5 ? wave_count_ge_n<SLOTS, 5>(key, pivot) : wave_count_ge_n<SLOTS, 6>(key, pivot);
+        return ng == 7 ? wave_count_ge_n<SLOTS, 7>(key, pivot) : wave_count_ge_n<SLOTS, 8>(key, pivot);
+    } else {
+        static_assert(SLOTS == 64, "variants of the threshold kernel");
+        if (ng <= 12) {
+            if (ng <= 10) return ng <= 9 ? wave_count_ge_n<SLOTS, 9>(key, pivot) : wave_count_ge_n<SLOTS, 10>(key, pivot);
+            return ng == 11 ? wave_count_ge_n<SLOTS, 11>(key, pivot) : wave_count_ge_n<SLOTS, 12>(key, pivot);
+        }
+        if (ng <= 14) return ng == 13 ? wave_count_ge_n<SLOTS, 13>(key, pivot) : wave_count_ge_n<SLOTS, 14>(key, pivot);
+        return ng == 15 ? wave_count_ge_n<SLOTS, 15>(key, pivot) : wave_count_ge_n<SLOTS, 16>(key, pivot);
+    }
+}
+
+// The search itself. In lane group r: n and b of row r (open: b < n, the row is there), fmx / fmn its extremes, s1 / s2 the
+// sums of RowStats. Returns row r's threshold in its group's first lane (-inf where not open) and the index of the last kept key
+// among those equal to it (INT_MAX when all of them are kept).
+// The threshold is a pivot with exactly b scores at or above it, or the b-th largest score itself where ties leave no such
+// pivot. The first pivot is the quantile of a normal distribution with the row's mean and variance (Abramowitz & Stegun
+// 26.2.23), the second a Newton step with that distribution's density; then regula falsi between the ends of the bracket,
+// whose weights are the counts' log-odds, log2((c + 1/2) / (n - c + 1/2)) (close to linear in the score for bell-shaped
+// rows), with the Illinois correction (an end that stays put is scaled by a half), and from the 13th step on the middle
+// of the bracket in key space, which bounds the worst case. Every pivot is clamped into the open bracket, so every step
+// shrinks it. In a simulation 4.5 steps on normal rows of 512 .. 3072 scores, 6 on heavy-tailed ones, where regula falsi
+// from the row's extremes takes 6.4 and 7.5.
+template <int R, int SLOTS>
+__device__ __forceinline__ float wave_search_rows(const float (&key)[R][SLOTS], int ng, int n, int b, bool open, float fmx,
+                                                  float fmn, float s1, float s2, int lane, int &jstar)
+{
+    constexpr int W = 64 / R;
+    ng = __builtin_amdgcn_readfirstlane(ng);
+    unsigned long long first = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) first |= 1ull << (r * W);
+    auto to_key = [](float v) {
+        const uint32_t u = __float_as_uint(v);
+        return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+    };
+    uint32_t lo = to_key(fmn + 0.0f), hi = to_key(fmx + 0.0f);       // -0 + 0 = +0
+    hi = open ? hi : lo;
+    const float nf = (float)n, bf = (float)b, nh = nf + 0.5f;
+    const float t_b = __builtin_amdgcn_logf(bf * __builtin_amdgcn_rcpf((nf - bf) + 1.0f));
+    float flo = fmn, fhi = fmx;
+    const float t_n = __builtin_amdgcn_logf(nh * 2.0f);
+    float glo = t_n - t_b, ghi = -t_n - t_b;
+    float w_up = 1.0f, w_dn = 1.0f;
+    float fp, slope;
+    {
+        const float inv = __builtin_amdgcn_rcpf((float)((n >> 2) * 2 + ((n & 3) < 2 ? (n & 3) : 2)));
+        const float mean = s1 * inv;
+        const float sd = __builtin_amdgcn_sqrtf(__builtin_fmaxf(__builtin_fmaf(s2, inv, -mean * mean), 0.f));
+        const float p = (bf - 0.5f) * __builtin_amdgcn_rcpf(nf);     // upper tail at the threshold
+        const float t = __builtin_amdgcn_sqrtf(-1.3862943611f * __builtin_amdgcn_logf(__builtin_fminf(p, 1.0f - p)));
+        const float num = __builtin_fmaf(__builtin_fmaf(0.010328f, t, 0.802853f), t, 2.515517f);
+        const float den = __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(0.001308f, t, 0.189269f), t, 1.432788f), t, 1.0f);
+        const float z = t - num * __builtin_amdgcn_rcpf(den);
+        fp = __builtin_fmaf(sd, p < 0.5f ? z : -z, mean);
+        // one count more or less moves the pivot by sd / (n * density)
+        slope = sd * 2.5066283f * __builtin_amdgcn_exp2f(0.72134752f * z * z) * __builtin_amdgcn_rcpf(nf);
+    }
+    unsigned long long exact = 0;
+    for (int it = 0;; ++it) {
+        asm volatile("" : "+s"(it));                     // no peeled copies of the loop: the counts are most of the code
+        const bool act = lo < hi;
+        const unsigned long long todo = __ballot(act) & first;
+        if (todo == 0) break;
+        uint32_t mid = to_key(fp);
         mid = __builtin_elementwise_max(mid, lo + 1u);
         mid = __builtin_elementwise_min(mid, hi);
-        if (__builtin_amdgcn_readfirstlane(it) >= 12) {   // a branch that is hardly ever taken, not five instructions per step
-            mid = lo + ((hi - lo + 1u) >> 1);
-            asm volatile("" : "+v"(mid));
-        }
-        // score_unkey as a shift and one three-input bit operation (the sign mask passes through an empty asm, or the
-        // compiler turns it back into a compare and a select)
+        if (it >= 12) mid = lo + ((hi - lo + 1u) >> 1);
         int32_t sgn = (int32_t)mid >> 31;
-        asm("" : "+v"(sgn));
+        asm("" : "+v"(sgn));                             // or the compiler makes a compare and a select of it
         const float fmid = __uint_as_float(mid ^ (~(uint32_t)sgn | 0x80000000u));
-        int cnt;
-        if constexpr (NG < 0) cnt = wave_count_ge_sw<SLOTS>(key, n, (n + 255) >> 8, fmid);
-        else cnt = wave_count_ge_v<SLOTS, NG>(key, n, fmid);
-        side();
-        if (cnt == b) { exact = true; lo = mid; break; }
+        int part[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            part[r] = 0;
+            if (todo & (1ull << (r * W)))
+                part[r] = wave_count_ge_s<SLOTS>(key[r], ng, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fmid), r * W)));
+        }
+        const int cnt = group_reduce<R>(part, OpAddI());
         const float cf = (float)cnt;
         const float g = __builtin_amdgcn_logf((cf + 0.5f) * __builtin_amdgcn_rcpf(nh - cf)) - t_b;
-        const bool up = cnt > b;                          // the pivot becomes the lower end, else pivot - 1 the upper
-        const float glo_w = glo * w_dn, ghi_w = ghi * w_up;
-        lo = up ? mid : lo;
-        hi = up ? hi : mid - 1u;
+        const bool eq = act && cnt == b, up = act && cnt > b, dn = act && cnt < b;
+        exact |= __ballot(eq);
+        lo = eq || up ? mid : lo;
+        hi = eq ? mid : (dn ? mid - 1u : hi);
         flo = up ? fmid : flo;
         fhi = up ? fhi : fmid;
+        const float glo_w = glo * w_dn, ghi_w = ghi * w_up;
         glo = up ? g : glo_w;
         ghi = up ? ghi_w : g;
         w_up = up ? 0.5f : 1.0f;
         w_dn = up ? 1.0f : 0.5f;
+        if (it == 0) fp = __builtin_fmaf(cf - bf, slope, fmid);
+        else fp = __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
     }
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
-}
-
-// finishes one row's search from the bracket [lo, hi] (see wave_select_topk): returns the threshold key
-// and the index of the last kept key among those equal to it (INT_MAX when all of them are kept)
-template <int SLOTS, class Side>
-__device__ __forceinline__ uint32_t wave_select_thr(const float (&key)[SLOTS], int n_in, int b_in, uint32_t lo_in,
-                                                    uint32_t hi_in, int lane, int &jstar, Side &side)
-{
-    const int n = __builtin_amdgcn_readfirstlane(n_in), b = __builtin_amdgcn_readfirstlane(b_in);
-    const uint32_t lo0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo_in);
-    const uint32_t hi0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi_in);
     jstar = 0x7FFFFFFF;
-    bool exact;
-    uint32_t lo;
-    if constexpr (!std::is_same<Side, NoSide>::value && SLOTS > 16) {
-        lo = wave_search_thr<SLOTS, -1, Side>(key, n, b, lo0, hi0, exact, side);   // the side job's code exists once
-    } else if constexpr (SLOTS <= 16) {                  // one copy of the loop per row length in groups: no per-step dispatch
-        const int ng = (n + 255) >> 8;
-        if (ng <= 1) lo = wave_search_thr<SLOTS, 1, Side>(key, n, b, lo0, hi0, exact, side);
-        else if (SLOTS >= 8 && ng == 2) lo = wave_search_thr<SLOTS, (SLOTS >= 8 ? 2 : 1), Side>(key, n, b, lo0, hi0, exact, side);
-        else if (SLOTS >= 12 && ng == 3) lo = wave_search_thr<SLOTS, (SLOTS >= 12 ? 3 : 1), Side>(key, n, b, lo0, hi0, exact, side);
-        else lo = wave_search_thr<SLOTS, SLOTS / 4, Side>(key, n, b, lo0, hi0, exact, side);
-    } else if constexpr (SLOTS == 20) {                  // rows of 1025..1280 keys (a 1024-token prefix plus a short episode)
-        if (((n + 255) >> 8) == 5) lo = wave_search_thr<SLOTS, 5, Side>(key, n, b, lo0, hi0, exact, side);
-        else lo = wave_search_thr<SLOTS, 0, Side>(key, n, b, lo0, hi0, exact, side);
-    } else if constexpr (SLOTS == 32) {                  // rows of 1025..2048 keys: 5..8 groups (shorter ones take the general loop)
-        const int ng = (n + 255) >> 8;
-        if (ng == 8) lo = wave_search_thr<SLOTS, 8, Side>(key, n, b, lo0, hi0, exact, side);
-        else if (ng == 7) lo = wave_search_thr<SLOTS, 7, Side>(key, n, b, lo0, hi0, exact, side);
-        else if (ng == 6) lo = wave_search_thr<SLOTS, 6, Side>(key, n, b, lo0, hi0, exact, side);
-        else if (ng == 5) lo = wave_search_thr<SLOTS, 5, Side>(key, n, b, lo0, hi0, exact, side);
-        else lo = wave_search_thr<SLOTS, 0, Side>(key, n, b, lo0, hi0, exact, side);
-    } else if constexpr (SLOTS == 64) {                  // rows of 2049..4096 keys: 9..16 groups
-        const int ng = (n + 255) >> 8;
-        switch (ng) {
-        case 16: lo = wave_search_thr<SLOTS, 16, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 15: lo = wave_search_thr<SLOTS, 15, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 14: lo = wave_search_thr<SLOTS, 14, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 13: lo = wave_search_thr<SLOTS, 13, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 12: lo = wave_search_thr<SLOTS, 12, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 11: lo = wave_search_thr<SLOTS, 11, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 10: lo = wave_search_thr<SLOTS, 10, Side>(key, n, b, lo0, hi0, exact, side); break;
-        case 9: lo = wave_search_thr<SLOTS, 9, Side>(key, n, b, lo0, hi0, exact, side); break;
-        default: lo = wave_search_thr<SLOTS, 0, Side>(key, n, b, lo0, hi0, exact, side); break;
-        }
-    } else {
-        lo = wave_search_thr<SLOTS, 0, Side>(key, n, b, lo0, hi0, exact, side);
-    }
-    if (exact) return lo;
-    float flo = score_unkey(lo), fnext = score_unkey(lo + 1u);
-    asm volatile("" : "+v"(flo), "+v"(fnext));           // vector registers, as the counting compare takes them
-    const int n_ge = wave_count_ge_v<SLOTS, 0>(key, n, flo);
-    if (n_ge > b) {                                      // more keys equal to the threshold than the budget has room for
-        const int n_gt = (lo == 0xFFFFFFFFu) ? 0 : wave_count_ge_v<SLOTS, 0>(key, n, fnext);
-        jstar = wave_tie_last<SLOTS>(key, n, flo, b - n_gt, lane);
-    }
-    return lo;
-}
-
-template <int SLOTS>
-__device__ __forceinline__ uint32_t wave_select_thr(const float (&key)[SLOTS], int n_in, int b_in, uint32_t lo_in,
-                                                    uint32_t hi_in, int lane, int &jstar)
-{
-    NoSide none;
-    return wave_select_thr<SLOTS, NoSide>(key, n_in, b_in, lo_in, hi_in, lane, jstar, none);
-}
-
-// loads a score row from LDS as it is (-inf for columns >= n: below every pivot of the search); the row's maximum and
-// minimum come back as order-preserving keys (-0.0 counts as +0.0), the bracket the search starts from
-template <int SLOTS>
-__device__ __forceinline__ void sel_row_load(const float *row, int n, int lane, float (&key)[SLOTS], uint32_t &kmax_out,
-                                             uint32_t &kmin_out)
-{
-    // score_key as shift / or / xor; the extremes are taken on the floats (three-input max and min), which order like the keys
-    auto to_key = [](float v) {
-        const uint32_t u = __float_as_uint(v + 0.0f);      // -0 + 0 = +0
-        return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-    };
-    float fmax = -__builtin_inff(), fmin = __builtin_inff();
+    const float thr = score_unkey(lo);
+    const unsigned long long closed = __ballot(open) & first & ~exact;      // the bracket closed on a score
+    if (closed) {
+        const float next = score_unkey(lo + 1u);
 #pragma unroll
-    for (int j = 0; j < SLOTS / 4; ++j) {
-        if (256 * (j + 1) <= n) {                          // every column of the group is a key of the row
-            const f32x4_a v = *reinterpret_cast<const f32x4_a *>(row + 256 * j + 4 * lane);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = v[e];
-            fmax = __builtin_fmaxf(__builtin_fmaxf(fmax, v[0]), v[1]);
-            fmax = __builtin_fmaxf(__builtin_fmaxf(fmax, v[2]), v[3]);
-            fmin = __builtin_fminf(__builtin_fminf(fmin, v[0]), v[1]);
-            fmin = __builtin_fminf(__builtin_fminf(fmin, v[2]), v[3]);
-        } else if (256 * j < n) {
-            const f32x4_a v = *reinterpret_cast<const f32x4_a *>(row + 256 * j + 4 * lane);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool valid = 256 * j + 4 * lane + e < n;
-                key[4 * j + e] = valid ? v[e] : -__builtin_inff();
-                fmax = valid ? __builtin_fmaxf(fmax, v[e]) : fmax;
-                fmin = valid ? __builtin_fminf(fmin, v[e]) : fmin;
+        for (int r = 0; r < R; ++r)
+            if (closed & (1ull << (r * W))) {
+                const float ft = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(thr), r * W));
+                const float fn = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(next), r * W));
+                const int nr = __builtin_amdgcn_readlane(n, r * W), br = __builtin_amdgcn_readlane(b, r * W);
+                const float n_ge = wave_sum_dpp((float)wave_count_ge_s<SLOTS>(key[r], ng, ft));
+                if (n_ge > (float)br) {                  // more scores equal to the threshold than the budget takes
+                    const int n_gt = (int)wave_sum_dpp((float)wave_count_ge_s<SLOTS>(key[r], ng, fn));
+                    const int js = wave_tie_last<SLOTS>(key[r], nr, ft, br - n_gt, lane);
+                    set_lane(jstar, js, r * W);
+                }
             }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[4 * j + e] = -__builtin_inff();
-        }
     }
-    kmax_out = wave_max_u32(to_key(fmax));                 // a lane without a valid column holds -inf / +inf: below / above every score
-    kmin_out = wave_min_u32(to_key(fmin));
+    return open ? thr : -__builtin_inff();
 }
 
-// ---- pieces of k_attn_select's score phase; they expand where qf, kbase, kdelta, pv, sc, scale, lane, l16, lg, w and
-// n_kt (key tiles of the block) are in scope: the kernel itself and SelSide below ----
-    // K tile KT_ (clamped to the last tile / key of the block) into SET_[U_]: lane (l16, lg) gets 8 channels at 8*lg of
-    // key 16*tile + l16 for every 32-channel piece
-#define SOL_SEL_LOADK(SET_, U_, KT_, KEY0_, NKEYS_)                                                        \
-    {   /* addresses as a uniform base plus a 32-bit byte offset per lane: one address register per load, no 64-bit sums */ \
-        const char *kb_ = reinterpret_cast<const char *>(kbase);                                           \
-        if constexpr (KF && PRE) {      /* prefix tiles from the operand-order copy, own tiles from the own cache */ \
-            int kt_ = (KT_);                                                                               \
-            if (kt_ * 16 >= (NKEYS_)) kt_ = ((NKEYS_) - 1) >> 4;                                           \
-            const bool in_pre = kt_ * 16 < pv.P;            /* wave-uniform; pv.P is a multiple of 64 */   \
-            int key = kt_ * 16 + l16;                                                                      \
-            if (key >= (NKEYS_)) key = (NKEYS_) - 1;                                                       \
-            const uint32_t off = in_pre ? (uint32_t)kt_ * (uint32_t)(KK * 512) + (uint32_t)(lane * 8)      \
-                                        : kdelta + (uint32_t)key * (uint32_t)DH + (uint32_t)(lg * 8);      \
-            const uint32_t step = in_pre ? 1024u : 64u;                                                    \
-            _Pragma("unroll") for (int kk = 0; kk < KK; ++kk)                                              \
-                SET_[U_][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(kb_ + (off * 2u + kk * step))); \
-        } else if constexpr (KF) {                                                                         \
-            int kt_ = (KT_);                                                                               \
-            if (kt_ * 16 >= (NKEYS_)) kt_ = ((NKEYS_) - 1) >> 4;                                           \
-            const uint32_t fo = ((uint32_t)kt_ * (uint32_t)(KK * 512) + (uint32_t)((KEY0_) * 8)) * 2u;     \
-            _Pragma("unroll") for (int kk = 0; kk < KK; ++kk)                                              \
-                SET_[U_][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(kb_ + fo + kk * 1024)); \
-        } else {                                                                                           \
-            int key = (KEY0_) + (U_) * NW * 16;                                                            \
-            if (key >= (NKEYS_)) key = (NKEYS_) - 1;                                                       \
-            uint32_t ko = (uint32_t)key * (uint32_t)DH + (uint32_t)(lg * 8);                               \
-            if constexpr (PRE) ko += key >= pv.P ? kdelta : 0u;                                            \
-            ko *= 2u;                                                                                      \
-            _Pragma("unroll") for (int kk = 0; kk < KK; ++kk)                                              \
-                SET_[U_][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(kb_ + ko + kk * 64)); \
-        }                                                                                                  \
-    }
-    // group of UH tiles from this wave's tile T0_ on (stride NW), if the group has a tile below the block's last key.
-    // EACH_: tiles past the last key are not loaded (the prefetch of the next block, issued before a long search);
-    // otherwise they re-read the last tile, which keeps the loads of a group free of branches.
-#define SOL_SEL_LOADG(SET_, T0_, NKEYS_, EACH_)                                                            \
-    if ((T0_) * 16 < (NKEYS_)) {                                                                           \
-        int key0_ = KF ? lane : (T0_) * 16 + l16;                                                          \
-        asm volatile("" : "+v"(key0_));   /* recomputed per group: hoisted copies of all the indices spill */ \
-        _Pragma("unroll") for (int u = 0; u < UH; ++u) {                                                   \
-            if (!(EACH_) || ((T0_) + u * NW) * 16 < (NKEYS_)) SOL_SEL_LOADK(SET_, u, (T0_) + u * NW, key0_, NKEYS_) \
-        }                                                                                                  \
-    }
-    // q fragments and the first two groups of K tiles of query block QB_
-#define SOL_SEL_LOAD(QB_)                                                                                  \
-    {                                                                                                      \
-        const int q0_ = q_lo + (QB_) * BQ;                                                                 \
-        const int nmax_ = p0 + (q_hi < q0_ + BQ ? q_hi : q0_ + BQ);                                        \
-        _Pragma("unroll") for (int rt = 0; rt < RT; ++rt) {                                                \
-            int qr = q0_ + rt * 16 + l16;                                                                  \
-            if (qr >= Tn) qr = Tn - 1;                                                                     \
-            const uint32_t qo = ((uint32_t)qr * (uint32_t)(Hq * DH) + (uint32_t)(lg * 8)) * 2u;            \
-            _Pragma("unroll") for (int kk = 0; kk < KK; ++kk)                                              \
-                qf[rt][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(              \
-                                                    reinterpret_cast<const char *>(qbase) + qo + kk * 64)); \
-        }                                                                                                  \
-        SOL_SEL_LOADG(ka, w, nmax_, true)                                                                  \
-        if constexpr (DB) SOL_SEL_LOADG(kb, w + UH * NW, nmax_, true)                                      \
-    }
-    // S^T tile = K tile (rows) x Q^T (columns): lane (l16, lg) gets keys 4*lg..4*lg+3 of query l16
-#define SOL_SEL_MFMA(SET_, U_, KT_)                                                                        \
-    _Pragma("unroll") for (int rt = 0; rt < RT; ++rt) {                                                    \
-        floatx4_a acc = {0.f, 0.f, 0.f, 0.f};                                                              \
-        _Pragma("unroll") for (int kk = 0; kk < KK; ++kk)                                                  \
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(SET_[U_][kk], qf[rt][kk], acc, 0, 0, 0);         \
-        const int row = rt * 16 + l16;                                                                     \
-        if (row < BQ)                                                                                      \
-            *reinterpret_cast<f32x4_a *>(sc + row * LS + (KT_) * 16 + 4 * lg) =                            \
-                f32x4_a{acc[0] * scale, acc[1] * scale, acc[2] * scale, acc[3] * scale};                   \
-    }
-#define SOL_SEL_MFMAG(SET_, T0_)                                                                           \
-    _Pragma("unroll") for (int u = 0; u < UH; ++u) {                                                       \
-        const int kt = (T0_) + u * NW;                                                                     \
-        if (kt < n_kt) { SOL_SEL_MFMA(SET_, u, kt); }                                                      \
-    }
-
-
-// The score phase of k_attn_select as a side job of the threshold search (long rows): the fragments in registers and
-// what the macros above refer to, under the same names. One call multiplies the next two groups of key tiles of the
-// block [n_max keys, n_kt tiles] (one per register set) into the LDS rows sc and requests the two groups after them;
-// nothing once the block's tiles are through (tcur >= n_kt).
-template <int BQ, int SLOTS, int DH, int NW, bool PRE, bool KF> struct SelSide {
-    static constexpr int LPAD = SLOTS * 64, LS = LPAD + 4; // row stride = 4 mod 64 floats: the 16 query rows of a
-                                                           // 128-bit store hit 16 different bank groups
-    static constexpr int RT = (BQ + 15) / 16, KK = DH / 32;
-    // key tiles held per wave. Head size 128, rows up to 2048 keys: 2, with which the kernel fits 128 registers and a
-    // second workgroup fits the CU (4 tiles: 168 registers, one workgroup; 1.28 -> 0.83 ms for the 1025..2048-key rows
-    // of 4096-token sequences at the 8B shape). The 20-slot variant at head size 64 likewise: 80 registers and 41 KB
-    // of LDS, so three workgroups share a CU (episode pass, 16 rows per sequence on a 1024-token prefix: 272 -> 199 us
-    // per launch; on long walks, rows of 1025..1280 keys at C3, it gains nothing over the 32-slot variant)
-    static constexpr int UA = (SLOTS <= 16 && DH <= 64) ? 8 : ((SLOTS <= 32 && DH > 64) || SLOTS == 20) ? 2 : 4;
-    // Rows longer than what the waves hold at once (SLOTS > 16): two register sets of UH key tiles each, one in flight
-    // while the other is multiplied. Shorter rows: one set, all of it loaded while the block before is searched.
-    static constexpr bool DB = SLOTS > 16;
-    static constexpr int UH = DB ? UA / 2 : UA;
-    static constexpr int GS = UH * NW;                     // tiles per group over the workgroup
-    bf16x8_a qf[RT][KK], ka[UH][KK], kb[DB ? UH : 1][KK];
-    const bf16_t *kbase;
-    uint32_t kdelta;
-    PrefixView pv;
-    float *sc;
-    float scale;
-    int lane, l16, lg, w;
-    int n_max, n_kt, tcur;
-    __device__ __forceinline__ void operator()()
-    {
-        if (tcur < n_kt) {
-            SOL_SEL_MFMAG(ka, tcur)
-            SOL_SEL_LOADG(ka, tcur + 2 * GS, n_max, false)
-            if (tcur + GS < n_kt) {
-                SOL_SEL_MFMAG(kb, tcur + GS)
-                SOL_SEL_LOADG(kb, tcur + 3 * GS, n_max, false)
-            }
-            tcur += 2 * GS;
-        }
-    }
-};
-
-// A workgroup walks several blocks of BQ query rows of one (sequence, head): while the waves search the
-// thresholds of one block, the q and K fragments of the next are already on their way into registers,
-// so the global-load latency of the score phase is hidden. Blocks are dealt to the nb workgroups of a
-// (sequence, head) in zigzag order (k-th visit: block nb*k + bi for even k, nb*k + nb-1-bi for odd k),
-// which gives every workgroup the same number of causal keys.
+// Thresholds: one workgroup of 8 waves takes blocks of 8 * R query rows of one (sequence, head). The scores of a block are
+// made in parts of SC keys: the waves stream the part's key tiles (two register sets in flight where they fit) and multiply
+// them into the LDS, and after a barrier every wave takes its R rows' piece of the part into registers, so that the LDS
+// holds a part of a row instead of the whole and does not bound the rows per block. When the last part is in, a wave
+// searches its R rows together (wave_search_rows) and goes straight on to the first part of the next block, whose first
+// tiles were requested ahead of the search: waves whose search is short stream keys while the others still search.
+// Blocks of 16 rows fill the 16 query columns of the MFMA, and all causal K passes through the CU's L1 once per block: with
+// whole rows in the LDS only 8 rows of 4096 keys fit, half the columns were multiplied for nothing and the K stream was twice
+// as long. Two rows per wave share the search's bookkeeping (see wave_search_rows). Measured per launch, before and after:
+// rows of 2049 .. 4096 keys at head size 128 (8 x 4096 tokens) 3.88 -> 2.24 ms, of 1025 .. 2048 keys 0.75 -> 0.51 ms there
+// and 1.19 -> 0.79 ms at head size 64 (16 x 2048 tokens), up to 1024 keys 0.51 -> 0.38 ms.
+// Bound (2049 .. 4096 keys, of 2.24 ms, by builds with pieces taken out): K stream 0.75 (at the 57 bytes per clock that an L2
+// feeds a CU), products and LDS writes 0.3, taking the rows out of the LDS 0.45, search 0.75; a second buffer, so that half
+// of the waves do their scores while the others take rows or search, was slower (2.43: smaller parts, more barriers), and so
+// were parts of 256 keys behind a barrier each (2.49).
 // PRE: keys [0, pv.P) of sequence s are read from the prefix cache of input s / pv.K (shared by the pv.K schedules
 // of that input), keys from pv.P on from the sequence's own cache kc, which holds positions pv.P.. only
 // ([n_seq][Hkv][crows][DH]); pv.P is a multiple of 64 and the two caches lie less than 2^31 elements apart.
@@ -715,22 +620,29 @@ template <int BQ, int SLOTS, int DH, int NW, bool PRE, bool KF> struct SelSide {
 // in which the 16 bytes a lane feeds to one MFMA are contiguous over the lanes: a fragment load reads 1 KB in a row
 // (8 full cache lines) where the same load from the cache itself picks 64-byte pieces out of 16 rows. The values in
 // the registers are the same either way. With PRE the sequence's own keys (positions pv.P..) still come from its cache.
-template <int BQ, int SLOTS, int DH, int NW, bool PRE, bool KF>
-__global__ void __launch_bounds__(NW * 64)
-__attribute__((amdgpu_waves_per_eu(SLOTS == 20 && DH <= 64 ? 6 : SLOTS <= 32 ? 4 : 2, SLOTS <= 16 ? 4 : 8)))
+// Blocks are dealt to the nb workgroups of a (sequence, head) in zigzag order (k-th visit: block nb*k + bi for even k,
+// nb*k + nb-1-bi for odd k), which gives every workgroup the same number of causal keys.
+template <int SLOTS, int DH, int R, int U, int NS, int SC> struct SelShape {
+    static constexpr int NW = 8, BQ = NW * R, RT = (BQ + 15) / 16, KK = DH / 32, PARTS = (SLOTS * 64 + SC - 1) / SC;
+    static constexpr int GT = NW * U;                      // key tiles of a group: U per wave
+    static constexpr int LS = SC + 4;                      // row stride = 4 mod 64 floats: the 16 query rows of a 128-bit
+                                                           // store hit 16 different bank groups
+    static constexpr int LDS = BQ * LS * 4;
+    static_assert(SC % 256 == 0 && SC % (GT * NS * 16) == 0 && BQ % 16 == 0, "parts of whole 256-column groups and whole rounds of the register sets");
+};
+template <int SLOTS, int DH, int R, int U, int NS, int SC, bool PRE, bool KF>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SLOTS <= 32 ? 4 : 2, 8)))
 k_attn_select(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, SelRow *__restrict__ sel,
-              const RowAct *__restrict__ ra, const int32_t *__restrict__ pos0, int Tn, int L_max, int Hq, int Hkv,
-              float scale, int nb, PrefixView pv, int n_lo, int n_hi)
+                   const RowAct *__restrict__ ra, const int32_t *__restrict__ pos0, int Tn, int L_max, int Hq, int Hkv,
+                   float scale, int nb, PrefixView pv, int n_lo, int n_hi)
 {
-    using Frags = SelSide<BQ, SLOTS, DH, NW, PRE, KF>;
-    constexpr int LS = Frags::LS, RT = Frags::RT, KK = Frags::KK, UH = Frags::UH, GS = Frags::GS;
-    constexpr bool DB = Frags::DB;
+    using Sh = SelShape<SLOTS, DH, R, U, NS, SC>;
+    constexpr int NW = Sh::NW, BQ = Sh::BQ, RT = Sh::RT, KK = Sh::KK, GT = Sh::GT, LS = Sh::LS, W = 64 / R;
     extern __shared__ __align__(16) float sc[];            // [BQ][LS]
-    __shared__ int next_row;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int bi = blockIdx.x, h = blockIdx.y, s = blockIdx.z;
+    const int bi = blockIdx.x, h = blockIdx.y, s = blockIdx.z, kvh = h / (Hq / Hkv);
     const int p0 = pos0 ? pos0[s] : 0;
     if (p0 < 0 || p0 + Tn > L_max) return;                 // flagged by the projection kernel; sequence skipped
     // this launch takes the rows whose key count n = p0 + row + 1 lies in (n_lo, n_hi]: rows [q_lo, q_hi) of the sequence
@@ -739,160 +651,202 @@ k_attn_select(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, SelRo
     const int q_hi = n_hi - p0 < 0 ? 0 : (n_hi - p0 > Tn ? Tn : n_hi - p0);
     if (q_hi <= q_lo) return;                              // whole workgroup, before any barrier
     const int n_qb = (q_hi - q_lo + BQ - 1) / BQ;
-    const int kvh = h / (Hq / Hkv);
     // wave-uniform bases + 32-bit per-lane offsets: one address register per load instead of two
     const bf16_t *kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)(KF ? attn_lpad64(L_max) : L_max) * DH;
-    uint32_t kdelta = 0u;                                   // PRE: offset of the own cache (minus P rows) from the prefix cache
+    uint32_t kdelta = 0u;                                  // PRE: offset of the own cache (minus P rows) from the prefix cache
     if constexpr (PRE) {
         const bf16_t *own = kc + ((int64_t)s * Hkv + kvh) * (int64_t)pv.crows * DH - (int64_t)pv.P * DH;
         kbase = (KF ? pv.kf : pv.k) + ((int64_t)(s / pv.K) * Hkv + kvh) * (int64_t)pv.P * DH;
         kdelta = (uint32_t)__builtin_amdgcn_readfirstlane((int)(own - kbase));
     }
-    const bf16_t *qbase = q + (int64_t)s * Tn * (int64_t)(Hq * DH) + (int64_t)h * DH;
+    const char *const kb = reinterpret_cast<const char *>(kbase);
+    const char *const qb0 = reinterpret_cast<const char *>(q + (int64_t)s * Tn * (int64_t)(Hq * DH) + (int64_t)h * DH);
     const int l16 = lane & 15, lg = lane >> 4;
 
-    Frags fr;                                              // the fragments, and the score phase as the search's side job
-    auto &qf = fr.qf;
-    auto &ka = fr.ka;
-    auto &kb = fr.kb;
-    fr.kbase = kbase, fr.kdelta = kdelta, fr.pv = pv, fr.sc = sc, fr.scale = scale;
-    fr.lane = lane, fr.l16 = l16, fr.lg = lg, fr.w = w;
-    fr.n_max = 0, fr.n_kt = 0, fr.tcur = 0;
+    // q fragments ahead of the search too, where the registers leave room
+    constexpr bool Q_AHEAD = SLOTS > 32 || R * SLOTS + (RT + NS * U) * KK * 4 <= 88;
+    // of the next block's first group, the tiles that are requested ahead of the search (the others behind it)
+    constexpr int U_AHEAD = (NS == 1 && SLOTS <= 32 && R * SLOTS + U * KK * 4 > 88) ? U / 2 : U;
+    bf16x8_a qf[RT][KK], kf[NS][U][KK];                    // group g's key tiles in set g % NS
+
+    auto load_q = [&](int q0) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            int qr = q0 + rt * 16 + l16;
+            if (qr >= Tn) qr = Tn - 1;
+            const uint32_t qo = ((uint32_t)qr * (uint32_t)(Hq * DH) + (uint32_t)(lg * 8)) * 2u;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) qf[rt][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(qb0 + qo + kk * 64));
+        }
+    };
+    // this wave's key tiles t0 + w, t0 + NW + w, .. into a set (none from the block's n_keys-th key on): lane (l16, lg) gets
+    // 8 channels at 8 * lg of key 16 * tile + l16 for every 32-channel piece
+    auto load_k = [&](bf16x8_a (&set)[U][KK], int t0, int n_keys, int u0, int u1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kt = t0 + u * NW + w;
+            if (u < u0 || u >= u1 || kt * 16 >= n_keys) continue;
+            const char *base;                              // uniform: the lanes' own part is one 32-bit offset
+            uint32_t off;
+            int step;
+            if constexpr (KF) {
+                base = kb + (uint32_t)kt * (uint32_t)(KK * 1024), off = (uint32_t)lane * 16u, step = 1024;
+            }
+            if (!KF || (PRE && kt * 16 >= pv.P)) {         // from the cache itself (with KF: the sequence's own keys)
+                int key_i = kt * 16 + l16;
+                if (key_i >= n_keys) key_i = n_keys - 1;
+                base = kb + ((PRE && kt * 16 >= pv.P) ? (uint64_t)kdelta * 2u : 0u);
+                off = ((uint32_t)key_i * (uint32_t)DH + (uint32_t)(lg * 8)) * 2u, step = 64;
+            }
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) set[u][kk] = __builtin_bit_cast(bf16x8_a, *reinterpret_cast<const u32x4_a *>(base + off + kk * step));
+        }
+    };
+
+    // S^T tile = K tile (rows) x Q^T (columns): lane (l16, lg) gets keys 4 * lg .. 4 * lg + 3 of query l16. The group's
+    // tiles t0 + w .. of a block of n_kt tiles into the LDS; t_part: the part's first tile
+    auto score_group = [&](const bf16x8_a (&set)[U][KK], int t0, int t_part, int n_kt) {
+        float *const dst = sc + l16 * LS + (t0 - t_part + w) * 16 + 4 * lg;
+        floatx4_a acc[U][RT];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    acc[u][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set[u][kk], qf[rt][kk], kk ? acc[u][rt] : floatx4_a{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)                // a tile past the last one: the set's old values, in columns that nobody reads
+                *reinterpret_cast<f32x4_a *>(dst + rt * 16 * LS + u * NW * 16) =
+                    f32x4_a{acc[u][rt][0] * scale, acc[u][rt][1] * scale, acc[u][rt][2] * scale, acc[u][rt][3] * scale};
+    };
+
     int visit = 0, qb = bi;
     if (qb >= n_qb) return;
-    SOL_SEL_LOAD(qb);
-    if constexpr (DB) {
-        // Long rows, one row per wave. The score phase is bound by what the CU's L1 delivers and the search by the
-        // vector and scalar pipes, so a wave does both at once: while it searches its row of block k (in registers; the
-        // LDS rows are free once every wave has taken its own) each step of the search also multiplies one group of key
-        // tiles of block k + 1 into LDS and requests the group after the next. What the search leaves over is done behind
-        // it. The barriers wait for LDS only (s_waitcnt lgkmcnt): global loads and the result's store stay in flight.
-        static_assert(BQ == NW, "one row per wave");
+#pragma unroll
+    for (int i = 0; i < NS; ++i)                           // a set may be multiplied before it was ever loaded (see score_group)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kf[i][u][kk] = __builtin_bit_cast(bf16x8_a, u32x4_a{0u, 0u, 0u, 0u});
+    {
+        const int q0 = q_lo + qb * BQ, n_max = p0 + (q_hi < q0 + BQ ? q_hi : q0 + BQ);
+        if (Q_AHEAD) load_q(q0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) load_k(kf[i], i * GT, n_max, 0, U_AHEAD);
+    }
+    // the barriers wait for LDS only: global loads and the result's store stay in flight
 #define SOL_SEL_BARRIER asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
-        {                                                   // scores of the workgroup's first block
-            const int q0 = q_lo + qb * BQ;
-            const int rows = (q_hi - q0 < BQ) ? (q_hi - q0) : BQ;
-            const int n_max = p0 + q0 + rows;
-            const int n_kt = (n_max + 15) >> 4;
-            for (int t0 = w;; t0 += 2 * GS) {
-                SOL_SEL_MFMAG(ka, t0)
-                SOL_SEL_LOADG(ka, t0 + 2 * GS, n_max, false)
-                if (t0 + GS >= n_kt) break;
-                SOL_SEL_MFMAG(kb, t0 + GS)
-                SOL_SEL_LOADG(kb, t0 + 3 * GS, n_max, false)
-                if (t0 + 2 * GS >= n_kt) break;
-            }
-        }
-        while (true) {
-            const int q0 = q_lo + qb * BQ;
-            const int rows = (q_hi - q0 < BQ) ? (q_hi - q0) : BQ;
-            ++visit;
-            const int qb_next = nb * visit + ((visit & 1) ? nb - 1 - bi : bi);
-            const bool more = qb_next < n_qb;
-            const bool have = w < rows;                     // this wave's row of the block
-            const int n = p0 + q0 + w + 1;
-            RowAct act = RowAct();
-            if (have) act = ra[(int64_t)s * Tn + q0 + w];
-            fr.n_max = 0, fr.n_kt = 0;                      // the next block's
-            if (more) {
-                SOL_SEL_LOAD(qb_next);
-                const int q0n = q_lo + qb_next * BQ;
-                fr.n_max = p0 + (q_hi < q0n + BQ ? q_hi : q0n + BQ);
-                fr.n_kt = (fr.n_max + 15) >> 4;
-            }
-            SOL_SEL_BARRIER;                                // the block's scores are complete
-            float key[SLOTS];
-            uint32_t kmax = 0u, kmin = 0u;
-            if (have) sel_row_load<SLOTS>(sc + w * LS, n, lane, key, kmax, kmin);
-            SOL_SEL_BARRIER;                                // every row is in registers: LDS may be overwritten
-            fr.tcur = w;
-            if (have) {
-                const int b = budget_ceil(act.keep_num, act.keep_den, n);
-                uint32_t thr = 0u;                          // key 0: below every score, everything kept
-                int js = 0x7FFFFFFF;
-                if (b < n) thr = wave_select_thr<SLOTS>(key, n, b, kmin, kmax, lane, js, fr);
-                if (lane == 0)
-                    sel[((int64_t)s * Tn + q0 + w) * Hq + h] =
-                        SelRow{thr ? score_unkey(thr) : -__builtin_inff(), score_unkey(kmax), js, 0};
-            }
-            if (!more) break;
-            while (fr.tcur < fr.n_kt) fr();
-            qb = qb_next;
-        }
-#undef SOL_SEL_BARRIER
-    } else {
     while (true) {
         const int q0 = q_lo + qb * BQ;
         const int rows = (q_hi - q0 < BQ) ? (q_hi - q0) : BQ;
-        const int n_max = p0 + q0 + rows;
-        const int n_kt = (n_max + 15) >> 4;
-        // ---- scores of this block into LDS: the loads of a group of tiles go out while the group before it is multiplied ----
-        SOL_SEL_MFMAG(ka, w)
-        for (int t0 = w + GS; t0 < n_kt; t0 += GS) {
-            SOL_SEL_LOADG(ka, t0, n_max, false)
-            SOL_SEL_MFMAG(ka, t0)
+        const int n_max = p0 + q0 + rows, n_kt = (n_max + 15) >> 4;
+        const int n_first = p0 + q0 + w * R + 1;           // keys of the wave's first row
+        if (!Q_AHEAD) load_q(q0);
+        if (U_AHEAD < U) load_k(kf[0], 0, n_max, U_AHEAD, U);
+        float key[R][SLOTS];
+        RowStats<R> st;
+        st.clear();
+        // rows' actions: lane group r takes row r's
+        const int my_row = w * R + lane / W;
+        RowAct act = RowAct();
+        if (my_row < rows) act = ra[(int64_t)s * Tn + q0 + my_row];
+        const int n = p0 + q0 + my_row + 1;
+        const int b = my_row < rows ? budget_ceil(act.keep_num, act.keep_den, n) : n;
+#pragma unroll
+        for (int part = 0; part < Sh::PARTS; ++part) {
+            constexpr int PT = SC / 16;                    // tiles of a part
+            if (part * SC < n_max) {
+                const int t_end = n_kt < (part + 1) * PT ? n_kt : (part + 1) * PT;
+                for (int t0 = part * PT; t0 < t_end; t0 += NS * GT) {
+#pragma unroll
+                    for (int i = 0; i < NS; ++i)
+                        if (t0 + i * GT < t_end) {
+                            score_group(kf[i], t0 + i * GT, part * PT, n_kt);
+                            if (t0 + (i + NS) * GT < n_kt) load_k(kf[i], t0 + (i + NS) * GT, n_max, 0, U);
+                        }
+                }
+                SOL_SEL_BARRIER;                           // the part is complete
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int g = 0; g < SC / 256; ++g) {
+                        const int j = part * (SC / 256) + g;
+                        if (4 * j >= SLOTS) continue;
+                        if (256 * j < n_max)
+                            row_take4<R>(st, r, *reinterpret_cast<const f32x4_a *>(sc + (w * R + r) * LS + 256 * g + 4 * lane), 256 * j,
+                                         n_first + r, lane, key[r][4 * j], key[r][4 * j + 1], key[r][4 * j + 2], key[r][4 * j + 3]);
+                        else key[r][4 * j] = key[r][4 * j + 1] = key[r][4 * j + 2] = key[r][4 * j + 3] = -__builtin_inff();
+                    }
+                SOL_SEL_BARRIER;                           // every wave has its rows' pieces: the next part may be written
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = part * (SC / 64); j < (part + 1) * (SC / 64) && j < SLOTS; ++j) key[r][j] = -__builtin_inff();
+            }
         }
-        if (tid == 0) next_row = NW;
-        __syncthreads();
-        // ---- next block's fragments on their way while this block's rows are searched ----
         ++visit;
         const int qb_next = nb * visit + ((visit & 1) ? nb - 1 - bi : bi);
         const bool more = qb_next < n_qb;
-        if (more) SOL_SEL_LOAD(qb_next);
-        // ---- per row: maximum, and the threshold when the budget is below the row length ----
-        // the first NW rows go one to each wave, the others to whichever wave is free first
-        for (int r = w; r < rows;) {
-            const int n = p0 + q0 + r + 1;
-            const RowAct act = ra[(int64_t)s * Tn + q0 + r];
-            const int b = budget_ceil(act.keep_num, act.keep_den, n);
-            float key[SLOTS];
-            uint32_t kmax, kmin;
-            sel_row_load<SLOTS>(sc + r * LS, n, lane, key, kmax, kmin);
-            uint32_t thr = 0u;                             // key 0: below every score, everything kept
-            int js = 0x7FFFFFFF;
-            if (b < n) thr = wave_select_thr<SLOTS>(key, n, b, kmin, kmax, lane, js);
-            int r_next = 0;
-            if (lane == 0) {
-                sel[((int64_t)s * Tn + q0 + r) * Hq + h] =
-                    SelRow{thr ? score_unkey(thr) : -__builtin_inff(), score_unkey(kmax), js, 0};
-                r_next = atomicAdd(&next_row, 1);
-            }
-            r = __builtin_amdgcn_readfirstlane(r_next);
+        if (more) {
+            const int q0n = q_lo + qb_next * BQ;
+            if (Q_AHEAD) load_q(q0n);
+#pragma unroll
+            for (int i = 0; i < NS; ++i) load_k(kf[i], i * GT, p0 + (q_hi < q0n + BQ ? q_hi : q0n + BQ), 0, U_AHEAD);
         }
+        const float fmx = group_reduce<R>(st.mx, OpMaxF()), fmn = group_reduce<R>(st.mn, OpMinF());
+        const float s1 = group_reduce<R>(st.s1, OpAddF()), s2 = group_reduce<R>(st.s2, OpAddF());
+        int js;
+        const float thr = wave_search_rows<R, SLOTS>(key, (n_first + R - 1 + 255) >> 8, n, b, b < n, fmx, fmn, s1, s2, lane, js);
+        if (lane % W == 0 && my_row < rows) sel[((int64_t)s * Tn + q0 + my_row) * Hq + h] = SelRow{thr, fmx + 0.0f, js, 0};
         if (!more) break;
-        __syncthreads();                                   // every row is in registers or done: LDS may be overwritten
         qb = qb_next;
     }
-    }
-#undef SOL_SEL_LOADK
-#undef SOL_SEL_LOADG
-#undef SOL_SEL_LOAD
-#undef SOL_SEL_MFMA
-#undef SOL_SEL_MFMAG
+#undef SOL_SEL_BARRIER
 }
 
-// Unit hook: the row stage of k_attn_select (keys from an fp32 score row in LDS, threshold search, tie index) on caller
-// rows, one wave per row; keep[r][j] = 1 for the kept columns, by the same rule k_attn_pv applies to {thr, jstar}.
-template <int SLOTS>
-__global__ void __launch_bounds__(64) k_test_select_rows(const float *__restrict__ scores, int n_cols, const int32_t *__restrict__ n_valid,
-                                                         const int32_t *__restrict__ kk, uint8_t *__restrict__ keep)
+// Unit hook: the row stage of k_attn_select (scores of R rows into registers, threshold search, tie index) on caller
+// rows, R per wave; keep[r][j] = 1 for the kept columns, by the same rule k_attn_pv applies to {thr, jstar}.
+template <int SLOTS, int R>
+__global__ void __launch_bounds__(64) k_test_select_rows(const float *__restrict__ scores, int rows, int n_cols,
+                                                         const int32_t *__restrict__ n_valid, const int32_t *__restrict__ kk,
+                                                         uint8_t *__restrict__ keep)
 {
-    extern __shared__ __align__(16) float sc[];              // [SLOTS * 64]
-    const int lane = threadIdx.x, r = blockIdx.x;
-    const float *row = scores + (int64_t)r * n_cols;
-    const int n = n_valid[r], b = kk[r];
-    for (int j = lane; j < SLOTS * 64; j += 64) sc[j] = j < n ? row[j] : 0.f;
-    __syncthreads();
-    float key[SLOTS];
-    uint32_t kmax, kmin;
-    sel_row_load<SLOTS>(sc, n, lane, key, kmax, kmin);
-    uint32_t thr = 0u;
-    int js = 0x7FFFFFFF;
-    if (b < n) thr = wave_select_thr<SLOTS>(key, n, b, kmin, kmax, lane, js);
-    const float fthr = thr ? score_unkey(thr) : -__builtin_inff();
-    for (int j = lane; j < n_cols; j += 64) {
-        const float sv = j < n ? sc[j] : 0.f;
-        keep[(int64_t)r * n_cols + j] = (j < n && (sv > fthr || (sv == fthr && j <= js))) ? 1 : 0;
+    extern __shared__ __align__(16) float sc[];              // [R][SLOTS * 64]
+    constexpr int W = 64 / R, LP = SLOTS * 64;
+    const int lane = threadIdx.x, r0 = blockIdx.x * R;
+    float key[R][SLOTS];
+    RowStats<R> st;
+    st.clear();
+    int n_top = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool there = r0 + r < rows;
+        const int n = there ? n_valid[r0 + r] : 1;
+        n_top = n > n_top ? n : n_top;
+        for (int j = lane; j < LP; j += 64) sc[r * LP + j] = (there && j < n) ? scores[(int64_t)(r0 + r) * n_cols + j] : 0.f;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SLOTS / 4; ++j)
+            row_take4<R>(st, r, *reinterpret_cast<const f32x4_a *>(sc + r * LP + 256 * j + 4 * lane), 256 * j, n, lane,
+                         key[r][4 * j], key[r][4 * j + 1], key[r][4 * j + 2], key[r][4 * j + 3]);
+    }
+    const float fmx = group_reduce<R>(st.mx, OpMaxF()), fmn = group_reduce<R>(st.mn, OpMinF());
+    const float s1 = group_reduce<R>(st.s1, OpAddF()), s2 = group_reduce<R>(st.s2, OpAddF());
+    const int mine = r0 + lane / W;
+    const int n = mine < rows ? n_valid[mine] : 1, b = mine < rows ? kk[mine] : 1;
+    int js;
+    const float thr = wave_search_rows<R, SLOTS>(key, (n_top + 255) >> 8, n, b, b < n, fmx, fmn, s1, s2, lane, js);
+    for (int r = 0; r < R && r0 + r < rows; ++r) {
+        const float fthr = __shfl(thr, r * W, 64);
+        const int jr = __shfl(js, r * W, 64), nr = n_valid[r0 + r];
+        for (int j = lane; j < n_cols; j += 64) {
+            const float sv = j < nr ? sc[r * LP + j] : 0.f;
+            keep[(int64_t)(r0 + r) * n_cols + j] = (j < nr && (sv > fthr || (sv == fthr && j <= jr))) ? 1 : 0;
+        }
     }
 }
 
@@ -900,14 +854,14 @@ bool launch_test_attn_threshold(const float *scores, int rows, int n_cols, const
                                 uint8_t *keep_out, hipStream_t st)
 {
     if (n_cols > 4096) return false;
-#define SOL_TSEL(SL)                                                                                                 \
-    hipLaunchKernelGGL((k_test_select_rows<SL>), dim3(rows), dim3(64), (size_t)(SL) * 64 * 4, st, scores, n_cols, n_valid, k, \
-                       keep_out)
-    if (n_cols <= 256) SOL_TSEL(4);                          // the variants of launch_attn_tile
-    else if (n_cols <= 1024) SOL_TSEL(16);
-    else if (n_cols <= 1280) SOL_TSEL(20);
-    else if (n_cols <= 2048) SOL_TSEL(32);
-    else SOL_TSEL(64);
+#define SOL_TSEL(SL, R_)                                                                                             \
+    hipLaunchKernelGGL((k_test_select_rows<SL, R_>), dim3((rows + R_ - 1) / R_), dim3(64), (size_t)(R_) * (SL) * 64 * 4, st, \
+                       scores, rows, n_cols, n_valid, k, keep_out)
+    if (n_cols <= 256) SOL_TSEL(4, 4);                       // the variants of launch_attn_tile
+    else if (n_cols <= 1024) SOL_TSEL(16, 4);
+    else if (n_cols <= 1280) SOL_TSEL(20, 2);
+    else if (n_cols <= 2048) SOL_TSEL(32, 2);
+    else SOL_TSEL(64, 2);
 #undef SOL_TSEL
     return true;
 }
@@ -2414,17 +2368,17 @@ k_frag_k(const bf16_t *__restrict__ kc, bf16_t *__restrict__ kfr, const int32_t 
 }
 
 // rows whose key count lies in (n_lo, n_hi] (all rows by default); SLOTS * 64 >= min(n_hi, L_max) is the caller's business
-template <int BQ, int SLOTS, int DH, int NW, bool PRE = false, bool KF = false>
+template <int SLOTS, int DH, int R, int U, int NS, int SC, bool PRE, bool KF>
 static bool launch_attn_select_t(const void *q, const void *kc, SelRow *sel, const RowAct *ra, const int32_t *pos0,
                                  int n_seq, int Tn, int L_max, int Hq, int Hkv, hipStream_t st, PrefixView pv = PrefixView(),
                                  int n_lo = 0, int n_hi = 1 << 30)
 {
-    auto kern = k_attn_select<BQ, SLOTS, DH, NW, PRE, KF>;
-    const size_t lds = (size_t)BQ * (SLOTS * 64 + 4) * 4;
+    using Sh = SelShape<SLOTS, DH, R, U, NS, SC>;
+    constexpr int BQ = Sh::BQ;
+    auto kern = k_attn_select<SLOTS, DH, R, U, NS, SC, PRE, KF>;
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS) != hipSuccess)
             return false;
         attr_done = true;
     }
@@ -2436,7 +2390,7 @@ static bool launch_attn_select_t(const void *q, const void *kc, SelRow *sel, con
     int nb = (int)((4096 + (int64_t)Hq * n_seq - 1) / ((int64_t)Hq * n_seq));
     if (nb > n_qb) nb = n_qb;
     if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(kern, dim3(nb, Hq, n_seq), dim3(NW * 64), lds, st, (const bf16_t *)q, (const bf16_t *)kc, sel, ra,
+    hipLaunchKernelGGL(kern, dim3(nb, Hq, n_seq), dim3(512), Sh::LDS, st, (const bf16_t *)q, (const bf16_t *)kc, sel, ra,
                        pos0, Tn, L_max, Hq, Hkv, 1.0f / sqrtf((float)DH), nb, pv, n_lo, n_hi);
     return true;
 }
@@ -2925,21 +2879,21 @@ bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, v
     // class of row lengths: the rows of a long sequence that see at most 1024 (2048) keys go to the variant for that
     // length, with its larger blocks and higher occupancy, not to the one the sequence's last row needs.
     bool ok;
-#define SOL_SEL(BQ, SL, KF, LO, HI)                                                                                  \
-    ok = dh == 64 ? launch_attn_select_t<BQ, SL, 64, 8, false, KF>(q, KF ? kfr : k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, PrefixView(), LO, HI)  \
-                  : launch_attn_select_t<BQ, SL, 128, 8, false, KF>(q, KF ? kfr : k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, PrefixView(), LO, HI)
+#define SOL_SEL2(SL, DH_, R, U, NS, SC, KF, LO, HI)                                                                  \
+    launch_attn_select_t<SL, DH_, R, U, NS, SC, false, KF>(q, KF ? kfr : k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, PrefixView(), LO, HI)
+#define SOL_SEL(SL, R64, U64, NS64, SC64, R128, U128, NS128, SC128, KF, LO, HI)                                      \
+    ok = dh == 64 ? SOL_SEL2(SL, 64, R64, U64, NS64, SC64, KF, LO, HI) : SOL_SEL2(SL, 128, R128, U128, NS128, SC128, KF, LO, HI)
+    // Rows per wave, key tiles and register sets in flight, keys per part. Four rows per wave where they fit 128 registers (up to
+    // 1024 keys at head size 64: 0.38 against 0.49 ms with two); parts so that two workgroups share a CU's LDS; in the longest
+    // class the registers hold one workgroup per CU, so a part takes most of the LDS.
     constexpr int ALL = 1 << 30;
-    if (L_max <= 256) { SOL_SEL(32, 4, false, 0, ALL); }
-    else if (L_max <= 1024) { SOL_SEL(16, 16, true, 0, ALL); }
+    if (L_max <= 256) { SOL_SEL(4, 4, 2, 1, 256, 4, 2, 1, 256, false, 0, ALL); }
     else {
-        SOL_SEL(16, 16, true, 0, 1024);
-        if (ok && L_max <= 1280) { SOL_SEL(8, 20, true, 1024, ALL); }       // a 1024-token prefix plus a short episode
-        else if (ok && L_max <= 2048) { SOL_SEL(8, 32, true, 1024, ALL); }
-        else if (ok) {
-            SOL_SEL(8, 32, true, 1024, 2048);
-            if (ok) { SOL_SEL(8, 64, true, 2048, ALL); }
-        }
+        SOL_SEL(16, 4, 2, 1, 512, 2, 2, 1, 1024, true, 0, 1024);
+        if (ok && L_max > 1024) { SOL_SEL(32, 2, 2, 1, 1024, 2, 2, 1, 1024, true, 1024, 2048); }
+        if (ok && L_max > 2048) { SOL_SEL(64, 2, 4, 1, 2048, 2, 4, 1, 2048, true, 2048, ALL); }
     }
+#undef SOL_SEL2
 #undef SOL_SEL
     if (!ok) return false;
 #define SOL_PV(G_)                                                                                                   \
@@ -2991,19 +2945,18 @@ bool launch_attn_tile_prefix(const void *q, const void *k_cache, const void *v_c
     SelRow *sel = (SelRow *)sel_ws;
     bool ok;
     // rows longer than 1024 keys read the prefix keys from their copy in operand order, if the view has one
-#define SOL_SEL(BQ, SL, KF)                                                                                          \
-    ok = dh == 64 ? launch_attn_select_t<BQ, SL, 64, 8, true, KF>(q, k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, pv) \
-                  : launch_attn_select_t<BQ, SL, 128, 8, true, KF>(q, k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, pv)
-    if (L_max <= 256) { SOL_SEL(32, 4, false); }
-    else if (L_max <= 1024) { SOL_SEL(16, 16, false); }
-    else if (!pv.kf) {
-        if (L_max <= 1280) { SOL_SEL(8, 20, false); }
-        else if (L_max <= 2048) { SOL_SEL(8, 32, false); }
-        else { SOL_SEL(8, 64, false); }
+#define SOL_SEL2(SL, DH_, U, NS, SC, KF) launch_attn_select_t<SL, DH_, 2, U, NS, SC, true, KF>(q, k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, pv)
+#define SOL_SEL(SL, U64, NS64, U128, NS128, SC, KF) ok = dh == 64 ? SOL_SEL2(SL, 64, U64, NS64, SC, KF) : SOL_SEL2(SL, 128, U128, NS128, SC, KF)
+    if (L_max <= 256) { SOL_SEL(4, 2, 1, 2, 1, 256, false); }
+    else if (L_max <= 1024) { SOL_SEL(16, 2, 1, 2, 1, 1024, false); }
+    else if (L_max <= 1280) {
+        if (pv.kf) { SOL_SEL(20, 2, 1, 2, 1, 768, true); } else { SOL_SEL(20, 2, 1, 2, 1, 768, false); }
+    } else if (L_max <= 2048) {
+        if (pv.kf) { SOL_SEL(32, 2, 1, 2, 1, 1024, true); } else { SOL_SEL(32, 2, 1, 2, 1, 1024, false); }
+    } else {
+        if (pv.kf) { SOL_SEL(64, 4, 2, 2, 2, 2048, true); } else { SOL_SEL(64, 4, 2, 2, 2, 2048, false); }
     }
-    else if (L_max <= 1280) { SOL_SEL(8, 20, true); }
-    else if (L_max <= 2048) { SOL_SEL(8, 32, true); }
-    else { SOL_SEL(8, 64, true); }
+#undef SOL_SEL2
 #undef SOL_SEL
     if (!ok) return false;
 #define SOL_PV(G_)                                                                                                   \
