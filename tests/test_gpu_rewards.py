@@ -46,6 +46,12 @@ def test_reward_advantages(B, G, T, with_eff, gamma):
     assert np.abs(host(out["adv"]) - ref["adv"]).max() < 1e-4
 
 
+@pytest.mark.parametrize("B,G,T,with_eff,gamma", [(2, 4, 2047, True, 0.99), (2, 4, 2049, True, 0.99), (1, 3, 4500, False, 1023 / 1024), (1, 2, 513, False, 1.0)])
+def test_reward_advantages_across_waves_and_tiles(B, G, T, with_eff, gamma):
+    """the return-to-go is scanned over 8 steps per thread, 512 per wave and tiles of 2048 (gamma of the longest: exact in 32 bits)"""
+    test_reward_advantages(B, G, T, with_eff, gamma)
+
+
 def test_reward_flags_an_action_outside_the_table_and_rejects_bad_settings():
     nll, ids, targets, _ = _case(1, 2, 5, 7100, False)
     ids[0, 1, 3] = len(TABLE)
