@@ -930,7 +930,7 @@ __device__ __forceinline__ void pv_probs(const floatx4_a (&st)[2], float scale, 
 // per layer (85 of 396 us for a refresh of 64 x 4096 keys).
 // PRE: as in k_attn_select; kc and vc then hold the sequence's own positions, from pv.P on, pv.k and pv.v the prefix;
 // 64-key chunks never straddle pv.P.
-// NQT: query tiles of 16 rows per workgroup (2; 1 for passes of at most 16 rows per sequence).
+// NQT: query tiles of 16 rows per workgroup and block (see pv_split).
 // Occupancy floors (4+ heads per group): four waves per SIMD at head size 64 (128 registers; the 18 values that do not
 // fit are spilled outside the chunk loop), two at head size 128 (256 registers, no spills). Left alone the compiler takes
 // 186 and 328 registers, and with one wave per SIMD the softmax's exp / pack chains and the MFMAs have nothing to
@@ -970,10 +970,12 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
     // A workgroup takes query blocks n_qb - 1 - x and x: every workgroup streams the same number of causal keys.
     // With one block per workgroup the lifetimes differ by a factor of up to n_qb, and slots freed by the short
     // workgroups of a launch were seen to stay empty until the long ones around them had ended.
+    // A grid of one workgroup per block: no partners (few blocks: every CU gets one at most, see pv_split).
     const int n_qb = (Tn + QT - 1) / QT;
+    const bool alone = (int)gridDim.x >= n_qb;
     for (int pass = 0; pass < 2; ++pass) {
     const int qb = pass == 0 ? n_qb - 1 - bx : bx;
-    if (pass == 1 && qb >= n_qb - 1 - bx) break;            // the middle block of an odd count is its own partner
+    if (pass == 1 && (alone || qb >= n_qb - 1 - bx)) break; // the middle block of an odd count is its own partner
     const int q0 = qb * QT;
     const int rows = (Tn - q0 < QT) ? (Tn - q0) : QT;
     const int n_max = p0 + q0 + rows;                      // keys seen by the block's last live row
@@ -2395,6 +2397,24 @@ static bool launch_attn_select_t(const void *q, const void *kc, SelRow *sel, con
     return true;
 }
 
+// How the softmax V kernels deal a sequence's query rows to workgroups: tiles of 16 rows per workgroup and block, workgroups
+// per (sequence, KV head). Two tiles per block share the K and V reads from LDS, and a workgroup takes a late and an early block
+// so that all of them last equally long: the better one as soon as such workgroups fill the chip (one round of `slots`). With
+// fewer, blocks of one tile, and as long as these do not fill the chip either, one block per workgroup. 1B shape, us, pairs
+// of two tiles / pairs of one / one: 333 rows 21 / 12 / 10; 2 x 700 rows 32 / 24 / 22; 3 x 1000 rows 54 / 44 / 43; 8 x 250 rows
+// 20 / 14 / 16; page rule, 14 x 437 rows 63 / 53 / 55; 16 x 2048 rows 560 / 640 / 660; refresh of 8 x 64 rows 129 / 83 / 47; 8B
+// shape: 333 rows 21 / 17 / 14, page rule, 3 x 1777 rows 260 / 283 / 307.
+struct PvSplit { int tiles, grid; };
+static PvSplit pv_split(int T, int64_t groups, int dh, int G)
+{
+    if (T <= 16) return PvSplit{1, 1};
+    const int cus = device_cus() > 0 ? device_cus() : 256;
+    const int64_t slots = (int64_t)cus * (dh == 64 ? 4 : 2) / (G == 8 ? 2 : 1);      // resident workgroups (registers, LDS)
+    const int pairs = ((T + 31) / 32 + 1) / 2, blocks = (T + 15) / 16;
+    if (pairs * groups >= slots) return PvSplit{2, pairs};
+    return PvSplit{1, blocks * groups < slots ? blocks : (blocks + 1) / 2};
+}
+
 template <int DH, int G, bool PRE = false>
 static bool launch_attn_pv_t(const void *q, const void *kc, const void *vc, const SelRow *sel, float *o32,
                              const int32_t *pos0, int n_seq, int Tn, int L_max, int Hq, int Hkv, hipStream_t st,
@@ -2410,12 +2430,13 @@ static bool launch_attn_pv_t(const void *q, const void *kc, const void *vc, cons
             return false;
         attr_done = true;
     }
-    if (Tn <= 16)                                            // one tile of 16 query rows per workgroup
-        hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 1>), dim3(1, Hkv, n_seq), dim3(G * 64), lds, st, (const bf16_t *)q,
+    const PvSplit sp = pv_split(Tn, (int64_t)n_seq * Hkv, DH, G);
+    if (sp.tiles == 1)                                       // one tile of 16 query rows per workgroup
+        hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 1>), dim3(sp.grid, Hkv, n_seq), dim3(G * 64), lds, st, (const bf16_t *)q,
                            (const bf16_t *)kc, (const bf16_t *)vc, sel, o32, pos0, Tn, L_max, Hq, Hkv,
                            1.0f / sqrtf((float)DH), pv);
     else
-        hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 2>), dim3(((Tn + 31) / 32 + 1) / 2, Hkv, n_seq), dim3(G * 64), lds, st,
+        hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 2>), dim3(sp.grid, Hkv, n_seq), dim3(G * 64), lds, st,
                            (const bf16_t *)q, (const bf16_t *)kc, (const bf16_t *)vc, sel, o32, pos0, Tn, L_max, Hq, Hkv,
                            1.0f / sqrtf((float)DH), pv);
     return true;
@@ -2615,8 +2636,7 @@ __device__ __forceinline__ float max_over_lane_groups(float v)
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// PRE: two-segment addressing as in k_attn_pv. NQT: query tiles of 16 rows per workgroup (2; 1 for passes of at most
-// 16 rows per sequence, where a second tile would be all dead rows).
+// PRE: two-segment addressing as in k_attn_pv. NQT: query tiles of 16 rows per workgroup and block (see pv_split).
 template <int DH, int G, int W, bool PRE, int NQT>
 // (4+ heads per group. Head size 64: a floor of 3 / 4 waves per SIMD caps the registers at 168 / 128; left alone the compiler
 // takes 218 and 138 and the exp / pack chains of the softmax have nothing to overlap with: 0.94 -> 0.74 ms at C2 under the paper's
@@ -2642,9 +2662,10 @@ k_attn_pv_pages(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, con
     const int p0 = pos0 ? pos0[s] : 0;
     if (p0 < 0 || p0 + Tn > L_max) return;
     const int n_qb = (Tn + QT - 1) / QT;
+    const bool alone = (int)gridDim.x >= n_qb;
     for (int pass = 0; pass < 2; ++pass) {                  // query blocks n_qb - 1 - x and x, as in k_attn_pv
     const int qb = pass == 0 ? n_qb - 1 - (int)blockIdx.x : (int)blockIdx.x;
-    if (pass == 1 && qb >= n_qb - 1 - (int)blockIdx.x) break;
+    if (pass == 1 && (alone || qb >= n_qb - 1 - (int)blockIdx.x)) break;
     const int q0 = qb * QT;
     const int rows = (Tn - q0 < QT) ? (Tn - q0) : QT;
     const int n_max = p0 + q0 + rows;
@@ -2997,12 +3018,13 @@ static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *
                 return false;                                                                                        \
             attr_done = true;                                                                                        \
         }                                                                                                            \
-        hipLaunchKernelGGL(kern, dim3(((T + 16 * NQT_ - 1) / (16 * NQT_) + 1) / 2, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
+        hipLaunchKernelGGL(kern, dim3(sp.grid, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
                            (const bf16_t *)kc, (const bf16_t *)vc, (const unsigned long long *)selp, o32, pos0, T, L_max, Hq, \
                            Hkv, scale, log2S, opt.n_sink, opt.n_window, pv);                                  \
         return true;                                                                                                 \
     }
-    if (T <= 16) {                                           // one tile of 16 query rows per workgroup
+    const PvSplit sp = pv_split(T, (int64_t)n_seq * Hkv, DH, G);
+    if (sp.tiles == 1) {                                     // one tile of 16 query rows per workgroup
         if (G == 1) SOL_PVP(1, 1)
         if (G == 2) SOL_PVP(2, 1)
         if (G == 4) SOL_PVP(4, 1)
@@ -3032,12 +3054,13 @@ bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_ca
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,    \
                                 (int)lds) != hipSuccess)                                                             \
             return false;                                                                                            \
-        hipLaunchKernelGGL(kern, dim3(((T + 16 * NQT_ - 1) / (16 * NQT_) + 1) / 2, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
+        hipLaunchKernelGGL(kern, dim3(sp.grid, Hkv, n_seq), dim3(G_ * 64), lds, st, (const bf16_t *)q, \
                            (const bf16_t *)k_cache, (const bf16_t *)v_cache, (const unsigned long long *)nullptr, o32, pos0, T, \
                            L_max, Hq, Hkv, scale, 6, 0, 0, PrefixView());                                     \
         return true;                                                                                                 \
     }
-#define SOL_PVD(DH_, G_) { if (T <= 16) SOL_PVD2(DH_, G_, 1) SOL_PVD2(DH_, G_, 2) }
+    const PvSplit sp = pv_split(T, (int64_t)n_seq * Hkv, dh, G);
+#define SOL_PVD(DH_, G_) { if (sp.tiles == 1) SOL_PVD2(DH_, G_, 1) SOL_PVD2(DH_, G_, 2) }
     if (dh == 64) {
         if (G == 1) SOL_PVD(64, 1)
         if (G == 2) SOL_PVD(64, 2)

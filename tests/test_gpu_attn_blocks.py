@@ -47,3 +47,23 @@ def test_attention_at_the_edges_of_blocks_and_parts(dh, Hq, Hkv, T, last):
     err = torch.cat(err)
     print(f"row error median {err.median():.1e} max {err.max():.1e}, over 1e-3: {(err > 1e-3).double().mean():.4f}")
     assert err.median() < 1e-4 and (err > 1e-3).double().mean() <= 0.01 and err.max() < 1 / 15
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("rule", [{}, sol.PAPER_PRESET], ids=["topk", "pages"])
+def test_a_sequence_has_the_bits_it_has_among_others(dh, rule):
+    """1, 25 and 300 sequences of 200 rows: one block of 16 rows per workgroup, pairs of them, pairs of blocks of 32 rows"""
+    g = torch.Generator(device="cuda").manual_seed(dh)
+    T, Hq, Hkv = 200, 16, 4
+    shape = synth.ModelShape(d_model=256, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=256, n_layers=1, vocab=100)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()  # noqa: E731
+    q, kc, vc = rnd(1, T, Hq * dh), rnd(1, Hkv, T, dh), rnd(1, Hkv, T, dh)
+    ids = torch.randint(0, len(TABLE), (1, T), generator=g, device="cuda", dtype=torch.int32)
+    ctx = sol.Sol(shape, TABLE, dtype=sol.BF16, max_positions=T, **rule)
+    want = ctx.test_attention_stage(q, ids, kc, vc)
+    for n in (25, 300):
+        many = lambda t: t.expand(n, *t.shape[1:]).contiguous()  # noqa: E731
+        got = ctx.test_attention_stage(many(q), many(ids), many(kc), many(vc))
+        assert torch.equal(got, many(want)), n
+    assert ctx.device_status() == sol.OK
+    ctx.close()
