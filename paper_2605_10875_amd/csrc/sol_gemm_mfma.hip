@@ -1099,12 +1099,14 @@ static bool launch_small(int cfg, const bf16_t *A, int64_t lda, const BMap &bmap
 {
     if (Nv % 256 || K % (2 * BK) || K < 2 * BK) return false;
     if constexpr (WN == 128) {                               // a head of 128 in one wave tile: no 64-column tiles
-        if (cfg <= 1) return launch_tile<64, 128, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        if (cfg <= 1) return launch_tile<64, 128, 32, 128, 6>(A, lda, bmap, m_first, M, Nv, K, epi, st);
         if (cfg == 2) return launch_tile<128, 128, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
         return launch_tile<128, 256, 32, 128, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
     } else {
+        // slices in flight: at 24 KB each the 64 x 128 and 128 x 64 tiles gain from six (down projection of the 8B shape, 333 rows:
+        // three 94 us, six 85; 1B shape, 1024 rows: 52.5, 49.5); 64 x 64 with eight and 128 x 128 with five measure as here
         if (cfg == 0) return launch_tile<64, 64, 32, WN, 4>(A, lda, bmap, m_first, M, Nv, K, epi, st);
-        if (cfg == 1) return launch_tile<128, 64, 32, WN, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
+        if (cfg == 1) return launch_tile<128, 64, 32, WN, 6>(A, lda, bmap, m_first, M, Nv, K, epi, st);
         if (cfg == 2) return launch_tile<128, 128, 32, 64, 4>(A, lda, bmap, m_first, M, Nv, K, epi, st);
         return launch_tile<128, 256, 64, 64, 3>(A, lda, bmap, m_first, M, Nv, K, epi, st);
     }
