@@ -144,6 +144,27 @@ def test_prune_quant_kernel_bit_exact(n, dtype, rows):
         assert np.array_equal(out[r], want), (r, m[r], bits[r], np.flatnonzero(out[r] != want)[:8])
 
 
+@pytest.mark.parametrize("n,rows", [(1024, 24), (2048, 600), (8192, 24), (8192, 600), (11264, 600), (14336, 24)])
+def test_prune_search_at_extreme_ranks_and_rows(n, rows):
+    """the search for the m-th magnitude where its first pivots are far off: ranks 1, 2, n - 2 and n - 1, rows of many
+    binades, of one value, of two values, half zeros, one element 2^60 times the others (no quantiser: the kept values)"""
+    from paper_2605_10875_amd import synth
+    rng = np.random.default_rng(n + rows)
+    a = rng.standard_normal((rows, n)).astype(np.float32)
+    a[1::7] *= np.exp(rng.uniform(-60, 60, a[1::7].shape)).astype(np.float32)
+    a[2::7] = 1.25
+    a[3::7] = np.where(a[3::7] > 0, 3.0, -1e-30)
+    a[4::7, ::2] = 0.0
+    a[5::7, n // 3] = 2.0 ** 60
+    a[6::7] *= 1e-38                                                # subnormals among them
+    a = synth.round_to_bf16(a)
+    m = np.array([(1, 2, n - 1, n - 2, n // 2, n // 16, 7)[(r // 7) % 7] for r in range(rows)], np.int32)
+    out = host(sol.prune_quant(dev(a).to(torch.bfloat16), dev(m), dev(np.full(rows, 16, np.int32))))
+    for r in range(rows):
+        want = a[r] * oracle.topm_mask(a[r], int(m[r]))
+        assert np.array_equal(out[r], want), (r, m[r], np.flatnonzero(out[r] != want)[:8])
+
+
 def test_quant_codes_worked_examples():
     with open(os.path.join(GOLDEN, "fake_quant_worked.txt")) as f:
         for line in f:
