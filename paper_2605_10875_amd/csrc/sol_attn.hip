@@ -263,12 +263,18 @@ static bool launch_attn_rows_t(const void *q, const void *kc, const void *vc, fl
     return true;
 }
 
+static bool launch_attn_f32(const float *q, const float *kc, const float *vc, float *o32, const RowAct *ra, const int32_t *pos0,
+                            int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st);
+
 bool launch_attn_rows(const void *q, const void *k_cache, const void *v_cache, int dtype, float *o32,
                       const RowAct *ra, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh,
                       int *flags, hipStream_t st, AttnOpts opt)
 {
     if ((int64_t)n_seq * T <= 0) return true;
     if (opt.page < 1 || opt.n_sink < 0 || opt.n_window < 0) return false;
+    if (dtype == 0 && opt.page == 1 && opt.n_sink == 0 && opt.n_window == 0 &&
+        launch_attn_f32((const float *)q, (const float *)k_cache, (const float *)v_cache, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, flags, st))
+        return true;
     const int vec = dtype == 0 ? 4 : 8;
     if (dh % vec) return false;
     const int lpk = dh / vec;
@@ -863,6 +869,248 @@ bool launch_test_attn_threshold(const float *scores, int rows, int n_cols, const
     else if (n_cols <= 2048) SOL_TSEL(32, 2);
     else SOL_TSEL(64, 2);
 #undef SOL_TSEL
+    return true;
+}
+
+// ---- fp32 attention of batched passes, plain top-k rule --------------------------------------------------------------
+// One workgroup of four waves per (sequence, head, 16 query rows), rows of at most 1024 keys: scores by the fp32 matrix
+// instruction into the LDS, four rows per wave searched as in k_attn_select, numerators back into the LDS, P V by the fp32
+// matrix instruction. Every sum is made in the order of k_attn_rows with 256 threads, so that the results are its bits (a score
+// that rounds otherwise swaps kept keys here and there):
+//   - a score: groups of four channels, each one instruction from zero (k adds in order, as a chain of fma), then the tree
+//     over the groups c, c ^ DH/8, .., c ^ 1 that its lanes' exchanges make. A lane loads 16 bytes, a group's four channels;
+//     lane group lg wants channel lg of every group: a 4 x 4 transposition of registers and lane groups (transpose4).
+//   - the denominator: chains over columns 256 apart, then lanes 32, 16, 8, 4, 2, 1 apart, then groups of 64 in order.
+//   - an output: a chain over the keys KPI apart for every slot (key mod KPI), so that the k of an instruction is four
+//     consecutive keys of a slot; slots of a wave as a tree, waves in order.
+// A NaN or an infinity in a V row that a query does not keep would reach it through a product with 0: results that are not
+// finite are made again over the kept keys alone.
+// Bound: vector instructions (search, exponentials, the trees) and latency. k_attn_rows, a workgroup per row with a radix
+// select in the LDS, took 250 us for 2 x 509 rows of 32 heads of 64, this 98; 19.0 us for 4 x 128 rows of 4 heads, this 16.5.
+__device__ __forceinline__ void transpose4(f32x4_a &v)        // [element][lane group] -> [lane group][element]
+{
+    float a = v[0], b = v[1], c = v[2], d = v[3];
+    swap_lanes32(a, c);
+    swap_lanes32(b, d);
+    swap_lanes16(a, b);
+    swap_lanes16(c, d);
+    v = f32x4_a{a, b, c, d};
+}
+template <int DH>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
+k_attn_f32(const float *__restrict__ q, const float *__restrict__ kc, const float *__restrict__ vc, float *__restrict__ o32,
+           const RowAct *__restrict__ ra, const int32_t *__restrict__ pos0, int Tn, int L_max, int Hq, int Hkv, float scale,
+           int LS, int *flags)
+{
+    constexpr int NW = 4, R = 4, SLOTS = 16, W = 16, NI = DH / 16, NC = DH / 64;
+    constexpr int KPI = 1024 / DH, SPW = KPI / NW;         // key slots, and slots of a wave
+    extern __shared__ __align__(16) float sc[];            // [16][LS] scores, then numerators; [NW][16][DH] the waves' outputs
+    __shared__ float s_inv[16];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = blockIdx.y, s = blockIdx.z, kvh = h / (Hq / Hkv), q0 = blockIdx.x * 16;
+    const int p0 = pos0 ? pos0[s] : 0;
+    if (p0 < 0 || p0 + Tn > L_max) {                       // the sequence does not fit its cache: skipped
+        if (tid == 0) atomicOr(flags, FLAG_CACHE_OVERFLOW);
+        return;
+    }
+    const int rows = Tn - q0 < 16 ? Tn - q0 : 16;
+    const int n_max = p0 + q0 + rows, n_kt = (n_max + 15) >> 4;
+    const float *const kb = kc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
+    const float *const vb = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
+    const int64_t row0 = (int64_t)s * Tn + q0;
+
+    // ---- scores: the waves take key tiles of 16 in turn -------------------------------------------
+    f32x4_a qf[NI], kf[2][NI];                             // channels 16 i + 4 lg .. + 3; transposed: channel lg of groups 4 i .. 4 i + 3
+    {
+        const int qr = l16 < rows ? l16 : rows - 1;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            qf[i] = *reinterpret_cast<const f32x4_a *>(q + (row0 + qr) * (int64_t)(Hq * DH) + (int64_t)h * DH + 16 * i + 4 * lg);
+            transpose4(qf[i]);
+        }
+    }
+    auto load_k = [&](int kt, f32x4_a (&k)[NI]) {
+        int key = kt * 16 + l16;
+        key = key < n_max ? key : n_max - 1;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) k[i] = *reinterpret_cast<const f32x4_a *>(kb + (int64_t)key * DH + 16 * i + 4 * lg);
+    };
+    auto score = [&](int kt, f32x4_a (&k)[NI]) {           // lane (l16, lg): keys 4 lg .. 4 lg + 3 of query l16
+#pragma unroll
+        for (int i = 0; i < NI; ++i) transpose4(k[i]);
+        const floatx4_a zero = {0.f, 0.f, 0.f, 0.f};
+        floatx4_a t[2 * NI];
+#pragma unroll
+        for (int c = 0; c < 2 * NI; ++c) {                 // groups c and c + DH / 8
+            const int d = c + 2 * NI;
+            t[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c / 4][c % 4], qf[c / 4][c % 4], zero, 0, 0, 0) +
+                   __builtin_amdgcn_mfma_f32_16x16x4f32(k[d / 4][d % 4], qf[d / 4][d % 4], zero, 0, 0, 0);
+        }
+#pragma unroll
+        for (int o = NI; o > 0; o >>= 1)
+#pragma unroll
+            for (int c = 0; c < o; ++c) t[c] = t[c] + t[c + o];
+        *reinterpret_cast<f32x4_a *>(sc + l16 * LS + kt * 16 + 4 * lg) =
+            f32x4_a{t[0][0] * scale, t[0][1] * scale, t[0][2] * scale, t[0][3] * scale};
+    };
+    if (w < n_kt) load_k(w, kf[0]);
+    for (int kt = w; kt < n_kt; kt += 2 * NW) {
+        if (kt + NW < n_kt) load_k(kt + NW, kf[1]);
+        score(kt, kf[0]);
+        if (kt + 2 * NW < n_kt) load_k(kt + 2 * NW, kf[0]);
+        if (kt + NW < n_kt) score(kt + NW, kf[1]);
+    }
+    const int my_row = w * R + lane / W;                   // lane group r: row w * R + r
+    RowAct act = RowAct();
+    if (my_row < rows) act = ra[row0 + my_row];
+    const int n = p0 + q0 + my_row + 1;
+    const int b = my_row < rows ? budget_ceil(act.keep_num, act.keep_den, n) : n;
+    __syncthreads();
+
+    // ---- thresholds, numerators -----------------------------------------------------------------
+    {
+        const int n_first = p0 + q0 + w * R + 1;
+        float key[R][SLOTS];
+        RowStats<R> st;
+        st.clear();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < SLOTS / 4; ++j) {
+                if (256 * j < n_max)                       // LS covers whole groups of 256 columns
+                    row_take4<R>(st, r, *reinterpret_cast<const f32x4_a *>(sc + (w * R + r) * LS + 256 * j + 4 * lane), 256 * j, n_first + r,
+                                 lane, key[r][4 * j], key[r][4 * j + 1], key[r][4 * j + 2], key[r][4 * j + 3]);
+                else key[r][4 * j] = key[r][4 * j + 1] = key[r][4 * j + 2] = key[r][4 * j + 3] = -__builtin_inff();
+            }
+        const float fmx = group_reduce<R>(st.mx, OpMaxF()), fmn = group_reduce<R>(st.mn, OpMinF());
+        const float s1 = group_reduce<R>(st.s1, OpAddF()), s2 = group_reduce<R>(st.s2, OpAddF());
+        int js;
+        const float thr = wave_search_rows<R, SLOTS>(key, (n_first + R - 1 + 255) >> 8, n, b, b < n, fmx, fmn, s1, s2, lane, js);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float rt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(thr), r * W));
+            const float rm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fmx), r * W));
+            const int rj = __builtin_amdgcn_readlane(js, r * W);
+            f32x4_a den = {0.f, 0.f, 0.f, 0.f};            // of columns 4 * lane + e, 256 + 4 * lane + e, ..
+#pragma unroll
+            for (int j = 0; j < SLOTS / 4; ++j)
+                if (256 * j < n_max) {
+                    f32x4_a pr;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float sv = key[r][4 * j + e];  // dropped: below the threshold, or a tie that loses (a NaN is kept)
+                        const bool drop = sv < rt || (sv == rt && 256 * j + 4 * lane + e > rj);
+                        pr[e] = drop ? 0.f : expf(sv - rm);
+                        den[e] += pr[e];
+                    }
+                    *reinterpret_cast<f32x4_a *>(sc + (w * R + r) * LS + 256 * j + 4 * lane) = pr;
+                }
+            // columns 32, 16, 8, 4 apart: lanes 8, 4, 2, 1 apart in a row of 16 (rotations: what they meet has that period)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                den[e] += dpp_of<0x128>(den[e]);           // row_ror:8
+                den[e] += dpp_of<0x124>(den[e]);           // row_ror:4
+                den[e] += dpp_of<0x122>(den[e]);           // row_ror:2
+                den[e] += dpp_of<0x121>(den[e]);           // row_ror:1
+            }
+            const float d64 = (den[0] + den[2]) + (den[1] + den[3]);
+            float d = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d64), 16 * i));
+            if (lane == 0) s_inv[w * R + r] = 1.0f / d;
+        }
+    }
+    __syncthreads();
+
+    // ---- P V: slots SPW * w .. of KPI, four keys of a slot per instruction -----------------------------
+    constexpr int KCH = 4 * KPI;
+    floatx4_a acc[SPW][NC][4];                             // [slot][64 channels][channel 4 l16 + e]
+#pragma unroll
+    for (int a = 0; a < SPW; ++a)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[a][c][e] = floatx4_a{0.f, 0.f, 0.f, 0.f};
+    f32x4_a vf[2][SPW][NC];
+    auto load_v = [&](int k0, f32x4_a (&v)[SPW][NC]) {
+#pragma unroll
+        for (int a = 0; a < SPW; ++a) {
+            int k = k0 + KPI * lg + SPW * w + a;
+            k = k < n_max ? k : n_max - 1;                 // its numerators are 0
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[a][c] = *reinterpret_cast<const f32x4_a *>(vb + (int64_t)k * DH + 64 * c + 4 * l16);
+        }
+    };
+    auto product = [&](int k0, const f32x4_a (&v)[SPW][NC]) {
+        const float *const pr = sc + l16 * LS + k0 + KPI * lg + SPW * w;
+        float pa[SPW];
+#pragma unroll
+        for (int a = 0; a < SPW; ++a) pa[a] = pr[a];
+#pragma unroll
+        for (int a = 0; a < SPW; ++a)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[a][c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[a], v[a][c][e], acc[a][c][e], 0, 0, 0);
+    };
+    load_v(0, vf[0]);
+    for (int k0 = 0; k0 < n_max; k0 += 2 * KCH) {
+        if (k0 + KCH < n_max) load_v(k0 + KCH, vf[1]);
+        product(k0, vf[0]);
+        if (k0 + 2 * KCH < n_max) load_v(k0 + 2 * KCH, vf[0]);
+        if (k0 + KCH < n_max) product(k0 + KCH, vf[1]);
+    }
+    // lane (l16, lg) register r is query 4 lg + r, channels 64 c + 4 l16 + e; the waves' parts meet in the LDS
+    float *const red = sc + 16 * LS;                       // [NW][16][DH]
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            f32x4_a t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                t[e] = acc[0][c][e][r] + acc[1][c][e][r];
+                if constexpr (SPW == 4) t[e] += acc[2][c][e][r] + acc[3][c][e][r];
+            }
+            *reinterpret_cast<f32x4_a *>(red + (w * 16 + 4 * lg + r) * DH + 64 * c + 4 * l16) = t;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int el = (i * 256 + tid) * 4, r = el / DH, ch = el - r * DH;
+        if (r >= rows) continue;
+        f32x4_a y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int a = 0; a < NW; ++a) y += *reinterpret_cast<const f32x4_a *>(red + a * 16 * DH + el);
+        y *= s_inv[r];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (!(__builtin_fabsf(y[e]) < __builtin_inff())) {
+                float z = 0.f;
+                for (int j = 0; j < p0 + q0 + r + 1; ++j) {
+                    const float pj = sc[r * LS + j];
+                    if (pj != 0.f) z = __builtin_fmaf(pj, vb[(int64_t)j * DH + ch + e], z);
+                }
+                y[e] = z * s_inv[r];
+            }
+        *reinterpret_cast<f32x4_a *>(o32 + (row0 + r) * (int64_t)(Hq * DH) + (int64_t)h * DH + ch) = y;
+    }
+}
+
+// Passes of 16 rows per sequence or more on caches of at most 1024 positions: fewer rows leave most of a block's 16 columns
+// empty, longer rows do not fit the search's registers; both stay with k_attn_rows.
+static bool launch_attn_f32(const float *q, const float *kc, const float *vc, float *o32, const RowAct *ra, const int32_t *pos0,
+                            int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st)
+{
+    if ((dh != 64 && dh != 128) || T < 16 || L_max > 1024 || Hkv <= 0 || Hq % Hkv || Hq > 65535 || n_seq > 65535) return false;
+    const int LS = (L_max + 255) / 256 * 256 + 4;          // row stride = 4 mod 64 floats
+    const size_t lds = ((size_t)16 * LS + 4 * 16 * dh) * 4;
+    auto kern = dh == 64 ? k_attn_f32<64> : k_attn_f32<128>;
+    if (lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024) != hipSuccess)
+        return false;
+    hipLaunchKernelGGL(kern, dim3((T + 15) / 16, Hq, n_seq), dim3(256), lds, st, q, kc, vc, o32, ra, pos0, T, L_max, Hq, Hkv,
+                       1.0f / sqrtf((float)dh), LS, flags);
     return true;
 }
 

@@ -67,3 +67,54 @@ def test_a_sequence_has_the_bits_it_has_among_others(dh, rule):
         assert torch.equal(got, many(want)), n
     assert ctx.device_status() == sol.OK
     ctx.close()
+
+
+def _attend64(q, k, v, pos, budget):
+    """q [T][dh] at positions pos, k and v [L][dh]: softmax over the `budget` largest causal scores, in 64 bits"""
+    x = q.double() @ k.double().t().contiguous() / q.shape[-1] ** 0.5
+    x = x.masked_fill(torch.arange(k.shape[0], device="cuda")[None] > pos[:, None], -torch.inf)
+    kth = x.sort(-1, descending=True).values.gather(1, (budget - 1)[:, None])
+    return torch.softmax(x.masked_fill(x < kth, -torch.inf), -1) @ v.double()
+
+
+@pytest.mark.parametrize("last", [16, 17, 31, 64, 255, 256, 257, 509, 513, 1000, 1023, 1024])
+@pytest.mark.parametrize("dh,Hq,Hkv,T", [(64, 4, 2, 16), (128, 4, 4, 33)])
+def test_fp32_attention_of_blocks_of_rows(dh, Hq, Hkv, T, last):
+    """fp32 q, K, V: scores in four chains of dh / 4 products, outputs in chains of n / 16, trees above: 2^-24 times a few,
+    times the score's size in the exponent (up to about 16): under 1e-5 of a row's largest value; a swapped near-tie
+    (2^-21 of the scores' scale apart) moves a row by a kept key's weight: at most 1 % of rows."""
+    T = min(T, last)
+    g = torch.Generator(device="cuda").manual_seed(last * 3 + dh)
+    shape = synth.ModelShape(d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=256, n_layers=1, vocab=100)
+    ends = (last, max(T, last - 9))
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    q, kc, vc = rnd(2, T, Hq * dh), rnd(2, Hkv, last, dh), rnd(2, Hkv, last, dh)
+    ids = torch.randint(0, len(TABLE), (2, T), generator=g, device="cuda", dtype=torch.int32)
+    pos0 = torch.tensor([e - T for e in ends], dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, TABLE, dtype=sol.F32, max_positions=last)
+    o = ctx.test_attention_stage(q, ids, kc, vc, pos0=pos0)
+    keep = torch.tensor([[a[0], a[1]] for a in TABLE], device="cuda")[ids.long()]
+    err = []
+    for s in range(2):
+        pos = int(pos0[s]) + torch.arange(T, device="cuda")
+        budget = torch.minimum(-(-keep[s, :, 0] * (pos + 1) // keep[s, :, 1]), pos + 1)
+        for h in range(Hq):
+            c = slice(h * dh, (h + 1) * dh)
+            want = _attend64(q[s, :, c], kc[s, h // (Hq // Hkv)], vc[s, h // (Hq // Hkv)], pos, budget)
+            err.append((o[s, :, c].double() - want).abs().amax(1) / want.abs().amax(1))
+    err = torch.cat(err)
+    assert (err > 1e-5).double().mean() <= 0.01 and err.median() < 2e-6, (err.max(), err.median())
+    # the kernel that takes a workgroup per row (caches of more than 1024 positions) makes every sum in the same order
+    pad = lambda t: torch.cat([t, t.new_zeros((2, Hkv, 1100 - last, dh))], 2).contiguous()  # noqa: E731
+    wide = sol.Sol(shape, TABLE, dtype=sol.F32, max_positions=1100)
+    assert torch.equal(o, wide.test_attention_stage(q, ids, pad(kc), pad(vc), pos0=pos0))
+    wide.close()
+    # what a row does not see does not reach it: the V row of the last position, under the causal mask of all rows but the last
+    vc[0, :, -1] = torch.inf
+    clean = vc.clone()
+    clean[0, :, -1] = 0.0
+    a, b = (ctx.test_attention_stage(q, ids, kc, t, pos0=pos0) for t in (vc, clean))
+    assert torch.isfinite(a[0, :-1]).all() and (a[0, :-1] - b[0, :-1]).abs().max() < 1e-5 * b.abs().max()
+    assert torch.equal(a[1], b[1])
+    assert ctx.device_status() == sol.OK
+    ctx.close()
