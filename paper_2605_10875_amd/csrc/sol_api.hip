@@ -476,9 +476,9 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM (gate / up): unsupported shape");
         } else {
             fused_gu = mfma && launch_gemm_gateup_silu(w.h, lw->w_gate, lw->w_up, w.a, M, dff, d, st);
-            if (!fused_gu && !(dt == SOL_F32 && launch_gemm_f32rows((const float *)w.h, d, (const float *)lw->w_gate, dff,
-                                                                    (const float *)lw->w_up, dff, nullptr, 0, d, w.big32,
-                                                                    2 * (int64_t)dff, M, d, st))) {
+            if (dt == SOL_F32)
+                fused_gu = launch_gemm_f32_silu((const float *)w.h, (const float *)lw->w_gate, (const float *)lw->w_up, (float *)w.a, M, dff, d, st);
+            if (!fused_gu) {
                 launch_gemm_generic(w.h, dt, d, lw->w_gate, dt, d, w.big32, 2 * (int64_t)dff, M, dff, d, st);
                 launch_gemm_generic(w.h, dt, d, lw->w_up, dt, d, w.big32 + dff, 2 * (int64_t)dff, M, dff, d, st);
             }
@@ -509,7 +509,9 @@ static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void
             if (!launch_gemm_skinny(w.a, dff, lw->w_down, d, nullptr, 0, nullptr, 0, (int)M, dff, w.big32, ns_down, st))
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM (down): unsupported shape");
         } else {
-            fused_down = mfma && !q_out && launch_gemm_resid_out(w.a, lw->w_down, w.x2, x_out, M, d, dff, st);
+            if (!q_out)
+                fused_down = mfma ? launch_gemm_resid_out(w.a, lw->w_down, w.x2, x_out, M, d, dff, st)
+                                  : launch_gemm_f32_resid((const float *)w.a, (const float *)lw->w_down, w.x2, (float *)x_out, M, d, dff, st);
             if (!fused_down && !(mfma && launch_gemm_f32(w.a, lw->w_down, w.big32, d, M, d, dff, st)))
                 launch_gemm_generic(w.a, dt, dff, lw->w_down, dt, dff, w.big32, d, M, d, dff, st);
         }
@@ -559,9 +561,11 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
         } else {
             fused_qkv = mfma && launch_gemm_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, n_seq,
                                                      T, L_max, Hq, Hkv, dh, d, ctx->d_flags, w.big32, st, crows);
-            if (!fused_qkv && !(dt == SOL_F32 && launch_gemm_f32rows((const float *)w.h, d, (const float *)lw->wq, nq,
-                                                                     (const float *)lw->wk, nkv, (const float *)lw->wv, nkv, d,
-                                                                     w.big32, nqkv, M, d, st))) {
+            if (dt == SOL_F32)
+                fused_qkv = launch_gemm_f32_qkv((const float *)w.h, (const float *)lw->wq, (const float *)lw->wk, (const float *)lw->wv,
+                                                (float *)w.qb, (float *)kcw, (float *)vcw, ctx->d_rope, pos0, n_seq, T, L_max, Hq, Hkv,
+                                                dh, d, ctx->d_flags, st, crows);
+            if (!fused_qkv) {
                 launch_gemm_generic(w.h, dt, d, lw->wq, dt, d, w.big32, nqkv, M, nq, d, st);
                 launch_gemm_generic(w.h, dt, d, lw->wk, dt, d, w.big32 + nq, nqkv, M, nkv, d, st);
                 launch_gemm_generic(w.h, dt, d, lw->wv, dt, d, w.big32 + nq + nkv, nqkv, M, nkv, d, st);

@@ -41,6 +41,9 @@ __device__ __forceinline__ float2 rotate_pair(float x0, float x1, float2 cs)
     return make_float2(__builtin_fmaf(x0, cs.x, -(x1 * cs.y)), __builtin_fmaf(x1, cs.x, x0 * cs.y));
 }
 
+// SwiGLU: g * sigmoid(g) * u
+__device__ __forceinline__ float silu_mul(float g, float u) { return (g / (1.0f + expf(-g))) * u; }
+
 __device__ __forceinline__ float ld(const float *p) { return *p; }
 __device__ __forceinline__ float ld(const bf16_t *p) { return bf16_to_f32(*p); }
 __device__ __forceinline__ void st(float *p, float v) { *p = v; }

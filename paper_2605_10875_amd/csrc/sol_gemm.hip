@@ -1,5 +1,5 @@
 // GEMMs  C[M][N] = A[M][K] * W[N][K]^T  (both operands K-contiguous).
-//   launch_gemm_f32rows : fp32 operands on the fp32 matrix instructions, up to three stacked weight matrices.
+//   launch_gemm_f32*    : fp32 operands on the fp32 matrix instructions, also with what follows the product in a layer.
 //   launch_gemm_generic : any shape / dtype, fp32 FMA on LDS tiles, fp32 output: what the MFMA kernels do not cover.
 #include "sol_internal.h"
 
@@ -72,17 +72,113 @@ k_gemm_generic(const TA *__restrict__ A, int64_t lda, const TW *__restrict__ W, 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 
-struct FMap {                        // output column -> weight row of up to three stacked matrices [n][ldw]
+enum { FMAP_STACKED, FMAP_PAIRS, FMAP_ROPE };
+struct FMap {                        // output column -> weight row of up to three matrices [n][ldw]
     const float *base[3];
     int end[3];
     int64_t ldw;
+    int mode, dh;                    // stacked; pairs: column 2 c of base[0]'s row c, 2 c + 1 of base[1]'s; rope: stacked heads of dh
+                                     // rows, columns 2 c and 2 c + 1 of a head its rows c and c + dh / 2
     __device__ __forceinline__ const float *row(int v) const
     {
-        if (v < end[0]) return base[0] + (int64_t)v * ldw;
-        if (v < end[1]) return base[1] + (int64_t)(v - end[0]) * ldw;
-        return base[2] + (int64_t)(v - end[1]) * ldw;
+        if (mode == FMAP_PAIRS) return base[v & 1] + (int64_t)(v >> 1) * ldw;
+        const int seg = v < end[0] ? 0 : (v < end[1] ? 1 : 2);
+        v -= seg == 0 ? 0 : end[seg - 1];
+        if (mode == FMAP_ROPE) {
+            const int head = v / dh, i = v - head * dh;
+            v = head * dh + (i & 1) * (dh >> 1) + (i >> 1);
+        }
+        return base[seg] + (int64_t)v * ldw;
     }
 };
+
+// What becomes of a product. A lane of the accumulators holds one column of several rows; column(v) is what it needs to know
+// of it, early(row, ..) reads what it needs of memory (ahead of the K loop where a tile is small), put(row, .., x, y) gets the
+// product x and, if `pairs`, the neighbouring column's y (lane ^ 1: the columns 2 c and 2 c + 1 that FMAP_PAIRS and FMAP_ROPE
+// put side by side). The values are those of the separate kernels (k_silu_mul, k_rope_store, k_resid_out), whose passes over
+// the product these save. Measured: a one-layer model's call over 4 x 128 tokens, 95.0 -> 88.5 us (a launch of about 4 us each);
+// a 1B layer over 2 x 509 tokens, 1311 -> 1303 us (the three kernels took 45 us; their work now ends the product's tiles, and
+// the gate / up weights arrive from two matrices). (0 + x: their sum over one split.)
+struct F32Store {
+    static constexpr bool pairs = false;
+    float *C; int64_t ldc;
+    struct Col { float *p; };
+    __device__ __forceinline__ Col column(int v) const { return Col{C + v}; }
+    struct Early {};
+    __device__ __forceinline__ Early early(int64_t, const Col &) const { return Early(); }
+    __device__ __forceinline__ void put(int64_t row, const Col &c, const Early &, float x, float) const { c.p[row * ldc] = x; }
+};
+struct F32Resid {                    // out = x2 + product
+    static constexpr bool pairs = false;
+    const float *x2; float *out; int64_t ldc;
+    struct Col { int v; };
+    __device__ __forceinline__ Col column(int v) const { return Col{v}; }
+    struct Early { float x2; };
+    __device__ __forceinline__ Early early(int64_t row, const Col &c) const { return Early{x2[row * ldc + c.v]}; }
+    __device__ __forceinline__ void put(int64_t row, const Col &c, const Early &e, float x, float) const
+    {
+        out[row * ldc + c.v] = e.x2 + (0.f + x);
+    }
+};
+struct F32Silu {                     // a = silu(gate) * up; FMAP_PAIRS of gate and up
+    static constexpr bool pairs = true;
+    float *a; int64_t ldc;
+    struct Col { int v; };
+    __device__ __forceinline__ Col column(int v) const { return Col{v}; }
+    struct Early {};
+    __device__ __forceinline__ Early early(int64_t, const Col &) const { return Early(); }
+    __device__ __forceinline__ void put(int64_t row, const Col &c, const Early &, float x, float y) const
+    {
+        if ((c.v & 1) == 0) a[row * ldc + (c.v >> 1)] = silu_mul(0.f + x, 0.f + y);
+    }
+};
+struct F32Qkv {                      // rotary on q and k heads, q -> [M][nq], K / V -> caches; FMAP_ROPE of q, k and v
+    static constexpr bool pairs = true;
+    float *q, *kc, *vc;
+    const float2 *rope; const int32_t *pos0;
+    int Tn, L_max, crows, Hq, Hkv, dh;
+    int *flags;
+    struct Col { int slot, c; bool odd, first; };
+    __device__ __forceinline__ Col column(int v) const
+    {
+        const int slot = v / dh, i = v - slot * dh;
+        return Col{slot, i >> 1, (i & 1) != 0, v == 0};
+    }
+    struct Early { uint32_t s; int pos; float2 cs; };        // sequence; position, -1 where the sequence does not fit its cache
+    __device__ __forceinline__ Early early(int64_t row, const Col &c) const
+    {
+        const uint32_t r = (uint32_t)row, s = r / (uint32_t)Tn;
+        const int p0 = pos0 ? pos0[s] : 0;
+        Early e{s, p0 < 0 || p0 + Tn > L_max ? -1 : p0 + (int)(r - s * (uint32_t)Tn), {1.f, 0.f}};
+        if (e.pos >= 0 && c.slot < Hq + Hkv) e.cs = rope[(int64_t)e.pos * (dh >> 1) + c.c];
+        return e;
+    }
+    __device__ __forceinline__ void put(int64_t row, const Col &c, const Early &e, float x, float y) const
+    {
+        if (e.pos < 0) {                                     // skipped
+            if (c.first) atomicOr(flags, FLAG_CACHE_OVERFLOW);
+            return;
+        }
+        const int pos = e.pos, half = dh >> 1;
+        const int64_t s = e.s;
+        x = 0.f + x, y = 0.f + y;
+        if (c.slot < Hq + Hkv) {
+            const float2 z = rotate_pair(c.odd ? y : x, c.odd ? x : y, e.cs);
+            x = c.odd ? z.y : z.x;
+        }
+        float *const dst = c.slot < Hq ? q + row * (int64_t)(Hq * dh) + c.slot * dh
+                         : (c.slot < Hq + Hkv ? kc + ((s * Hkv + (c.slot - Hq)) * crows + pos) * dh
+                                              : vc + ((s * Hkv + (c.slot - Hq - Hkv)) * crows + pos) * dh);
+        dst[c.c + (c.odd ? half : 0)] = x;
+    }
+};
+template <class Epi>
+__device__ __forceinline__ void f32_put(const Epi &epi, int64_t row, const typename Epi::Col &c, const typename Epi::Early &e, float x)
+{
+    float y = 0.f;
+    if constexpr (Epi::pairs) y = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));   // lane ^ 1
+    epi.put(row, c, e, x, y);
+}
 
 // 16 bytes per lane straight into LDS: lane l's piece lands at lds_addr + 16 * l (wave-uniform)
 __device__ __forceinline__ void lds_load16(const float *src, uint32_t lds_addr)
@@ -94,10 +190,9 @@ __device__ __forceinline__ void lds_load16(const float *src, uint32_t lds_addr)
 // reads, 549 us for the first shape above against 606 with three stages and one workgroup. READ_AHEAD (a lone 64 x 64
 // tile per CU): the fragments of the next four k are read before the current ones are multiplied, 54 against 61 us for
 // 100 x 2048 x 2048 (and 616 against 549 us in the 128 x 128 tile, where the second workgroup does it better).
-template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD>
+template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD, class Epi>
 __global__ void __launch_bounds__(256, 2)
-k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, float *__restrict__ C, int64_t ldc, int64_t M, int N, int K,
-               int tiles_m, int tiles_n)
+k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int64_t M, int N, int K, int tiles_m, int tiles_n)
 {
     static_assert((BM / WM) * (BN / WN) == 4, "four waves");
     constexpr int NWN = BN / WN, TM = WM / 32, TN = WN / 32, AP = BM / 32, BP = BN / 32;
@@ -184,24 +279,26 @@ k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, float *__rest
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no LDS-direct load outlives its workgroup
     const int col0 = n0 + wn * WN + frow;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+        if (col0 + 32 * j >= N) continue;                    // (N is even where columns come in pairs)
+        const typename Epi::Col cj = epi.column(col0 + 32 * j);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = m0 + wm * WM + i * 32 + 8 * (r >> 2) + (r & 3) + (hi ? 4 : 0);
-            if (row >= M) continue;
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                if (col0 + 32 * j < N) C[row * ldc + col0 + 32 * j] = acc[i][j][r];
-        }
+            for (int r = 0; r < 16; ++r) {
+                const int64_t row = m0 + wm * WM + i * 32 + 8 * (r >> 2) + (r & 3) + (hi ? 4 : 0);
+                if (row < M) f32_put(epi, row, cj, epi.early(row, cj), acc[i][j][r]);
+            }
+    }
 }
 
 // 32 x 32 tiles of four waves, one 16x16 tile each: a quarter of the tile and of the chain's time per k, for products too
 // small to give every CU a 64 x 64 tile. Pipeline as in k_gemm_tile: four slices of 32 k in flight, the fragments of
 // slice kt + 1 read (4 bytes per lane, conflict-free: 16 rows' chunks fill the 64 banks) while slice kt is multiplied.
 constexpr int F32SMALL_STAGES = 4;
+template <class Epi>
 __global__ void __launch_bounds__(256)
-k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, float *__restrict__ C, int64_t ldc, int64_t M, int N, int K,
-                int tiles_m, int tiles_n)
+k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int64_t M, int N, int K, int tiles_m, int tiles_n)
 {
     constexpr int ST = F32SMALL_STAGES;
     constexpr uint32_t SB = 64 * 128;
@@ -225,6 +322,9 @@ k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, float *__res
     };
     f32x4v_t acc = {0.f, 0.f, 0.f, 0.f};
     const int r16 = lane & 15, g = lane >> 4;                // this lane supplies k = 4c + g of row r16 of its wave's tile
+    const int col = n0 + (wave & 1) * 16 + r16;              // and gets rows row0 .. row0 + 3 of this column
+    const int64_t row0 = m0 + (wave >> 1) * 16 + 4 * g;
+    const bool there = col < N;
     const int ar = (wave >> 1) * 16 + r16, br = (wave & 1) * 16 + r16;
     const int a_frag = ar * 128 + g * 4, b_frag = 4096 + br * 128 + g * 4, asw = (ar >> 1) & 7, bsw = (br >> 1) & 7;
     float a0[8], b0[8], a1[8], b1[8];
@@ -240,6 +340,11 @@ k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, float *__res
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[c], acc, 0, 0, 0);
     };
+    // (ahead of the LDS-direct loads, whose count the waits below know)
+    const typename Epi::Col c = epi.column(there ? col : 0);
+    typename Epi::Early early[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) early[r] = epi.early(row0 + r < M ? row0 + r : M - 1, c);
 #pragma unroll
     for (int s = 0; s < ST; ++s) request(s, s * SB);
     uint32_t cur = 0, nxt = SB;                              // the stages of slices kt and kt + 1
@@ -261,19 +366,17 @@ k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, float *__res
     }
 #undef SOL_F32_SYNC
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no LDS-direct load outlives its workgroup
-    const int col = n0 + (wave & 1) * 16 + r16;
+    if (!there) return;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int64_t row = m0 + (wave >> 1) * 16 + 4 * g + r;
-        if (row < M && col < N) C[row * ldc + col] = acc[r];
-    }
+    for (int r = 0; r < 4; ++r)
+        if (row0 + r < M) f32_put(epi, row0 + r, c, early[r], acc[r]);
 }
 
-template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD>
-static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st)
+template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD, class Epi>
+static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, const Epi &epi, int64_t M, int N, int K, hipStream_t st)
 {
     constexpr size_t lds = (size_t)ST * (BM + BN) * 128;
-    auto kern = k_gemm_f32mfma<BM, BN, WM, WN, ST, READ_AHEAD>;
+    auto kern = k_gemm_f32mfma<BM, BN, WM, WN, ST, READ_AHEAD, Epi>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -281,31 +384,63 @@ static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, float *
         attr_done = true;
     }
     const int tm = (int)((M + BM - 1) / BM), tn = (N + BN - 1) / BN, per_xcd = (tm * tn + 7) / 8;
-    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256), lds, st, A, lda, map, C, ldc, M, N, K, tm, tn);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256), lds, st, A, lda, map, epi, M, N, K, tm, tn);
     return true;
 }
 
 // The tile is the one that ends soonest by what was measured at K = 2048 (us; r rounds of one tile on every CU; the 1B
 // layer's widths, 30 to 1018 rows): 32 x 32: 12 + 10.5 r, 64 x 64: 21 + 36 r, 128 x 128: 15 + 134 r.
-bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w0, int n0, const float *w1, int n1, const float *w2, int n2,
-                         int64_t ldw, float *C, int64_t ldc, int64_t M, int K, hipStream_t st)
+template <class Epi>
+static bool launch_f32_product(const float *A, int64_t lda, const FMap &map, const Epi &epi, int64_t M, int64_t N, int K, hipStream_t st)
 {
-    const int64_t N = (int64_t)n0 + n1 + n2;
     auto aligned = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (K < 32 || K % 32 || lda % 4 || ldw % 4 || !aligned(A) || !aligned(w0) || !aligned(w1) || !aligned(w2) ||
-        M > (1ll << 30) || N > (1ll << 30))
+    if (K < 32 || K % 32 || lda % 4 || map.ldw % 4 || !aligned(A) || !aligned(map.base[0]) || !aligned(map.base[1]) ||
+        !aligned(map.base[2]) || M > (1ll << 30) || N > (1ll << 30))
         return false;                                        // 16-byte loads of whole slices
     if (M <= 0 || N <= 0) return true;
-    FMap map{{w0, w1, w2}, {n0, n0 + n1, n0 + n1 + n2}, ldw};
     const int cus = device_cus() > 0 ? device_cus() : 256;
     auto rounds = [&](int b) { return (double)(((M + b - 1) / b * ((N + b - 1) / b) + cus - 1) / cus); };
     if ((M + 31) / 32 * ((N + 31) / 32) > (1ll << 30)) return false;
     const double c32 = 12 + 10.5 * rounds(32), c64 = 21 + 36 * rounds(64), c128 = 15 + 134 * rounds(128);
-    if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, false>(A, lda, map, C, ldc, M, (int)N, K, st);
-    if (c64 <= c32) return launch_f32mfma<64, 64, 32, 32, 3, true>(A, lda, map, C, ldc, M, (int)N, K, st);
+    if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, false>(A, lda, map, epi, M, (int)N, K, st);
+    if (c64 <= c32) return launch_f32mfma<64, 64, 32, 32, 3, true>(A, lda, map, epi, M, (int)N, K, st);
     const int tm = (int)((M + 31) / 32), tn = (int)((N + 31) / 32);
-    hipLaunchKernelGGL(k_gemm_f32small, dim3((tm * tn + 7) / 8 * 8), dim3(256), F32SMALL_STAGES * 64 * 128, st, A, lda, map, C, ldc, M, (int)N, K, tm, tn);
+    hipLaunchKernelGGL(k_gemm_f32small<Epi>, dim3((tm * tn + 7) / 8 * 8), dim3(256), F32SMALL_STAGES * 64 * 128, st, A, lda, map, epi, M, (int)N, K, tm, tn);
     return true;
+}
+
+bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w, int N, int64_t ldw, float *C, int64_t ldc, int64_t M, int K,
+                         hipStream_t st)
+{
+    const FMap map{{w, w, w}, {N, N, N}, ldw, FMAP_STACKED, 0};
+    return launch_f32_product(A, lda, map, F32Store{C, ldc}, M, N, K, st);
+}
+
+// out = x2 + A w^T
+bool launch_gemm_f32_resid(const float *A, const float *w, const float *x2, float *out, int64_t M, int N, int K, hipStream_t st)
+{
+    const FMap map{{w, w, w}, {N, N, N}, K, FMAP_STACKED, 0};
+    return launch_f32_product(A, K, map, F32Resid{x2, out, N}, M, N, K, st);
+}
+
+// a = silu(A wg^T) * (A wu^T)
+bool launch_gemm_f32_silu(const float *A, const float *wg, const float *wu, float *a, int64_t M, int dff, int K, hipStream_t st)
+{
+    const FMap map{{wg, wu, wu}, {0, 0, 0}, K, FMAP_PAIRS, 0};
+    return launch_f32_product(A, K, map, F32Silu{a, dff}, M, 2 * (int64_t)dff, K, st);
+}
+
+// q / k / v, rotary embedding, cache write (cache_rows as for launch_rope_store)
+bool launch_gemm_f32_qkv(const float *A, const float *wq, const float *wk, const float *wv, float *q, float *kc, float *vc,
+                         const float2 *rope, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int K,
+                         int *flags, hipStream_t st, int cache_rows)
+{
+    const int64_t M = (int64_t)n_seq * T;
+    const int nq = Hq * dh, nkv = Hkv * dh;
+    if (dh % 2) return false;
+    const FMap map{{wq, wk, wv}, {nq, nq + nkv, nq + 2 * nkv}, K, FMAP_ROPE, dh};
+    const F32Qkv epi{q, kc, vc, rope, pos0, T, L_max, cache_rows > 0 ? cache_rows : L_max, Hq, Hkv, dh, flags};
+    return launch_f32_product(A, K, map, epi, M, (int64_t)nq + 2 * nkv, K, st);
 }
 
 void launch_gemm_generic(const void *A, int a_dtype, int64_t lda, const void *W, int w_dtype, int64_t ldw, float *C,
@@ -313,7 +448,7 @@ void launch_gemm_generic(const void *A, int a_dtype, int64_t lda, const void *W,
 {
     if (M <= 0 || N <= 0) return;
     if (a_dtype == 0 && w_dtype == 0 &&
-        launch_gemm_f32rows((const float *)A, lda, (const float *)W, N, nullptr, 0, nullptr, 0, ldw, C, ldc, M, K, st))
+        launch_gemm_f32rows((const float *)A, lda, (const float *)W, N, ldw, C, ldc, M, K, st))
         return;
     const dim3 grid((unsigned)((N + GT - 1) / GT), (unsigned)((M + GT - 1) / GT));
     if (a_dtype == 0 && w_dtype == 0)

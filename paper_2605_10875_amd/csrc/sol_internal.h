@@ -79,10 +79,16 @@ void launch_test_quant(const float *z, int rows, int n, const int32_t *bits, int
 void launch_gemm_generic(const void *A, int a_dtype, int64_t lda, const void *W, int w_dtype, int64_t ldw,
                          float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st);
 
-// The same for fp32 operands and up to three stacked weight matrices [n][ldw] (unused ones: nullptr, 0) side by side in
-// C's columns, on the fp32 matrix instructions. False (nothing launched): K no multiple of 32, rows not 16-byte aligned.
-bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w0, int n0, const float *w1, int n1, const float *w2, int n2,
-                         int64_t ldw, float *C, int64_t ldc, int64_t M, int K, hipStream_t st);
+// The same for fp32 operands on the fp32 matrix instructions. False (nothing launched): K no multiple of 32, rows not
+// 16-byte aligned.
+bool launch_gemm_f32rows(const float *A, int64_t lda, const float *w, int N, int64_t ldw, float *C, int64_t ldc, int64_t M, int K,
+                         hipStream_t st);
+// the same products with what follows them in the layer: out = x2 + product; silu(gate) * up; rotary embedding and cache write
+bool launch_gemm_f32_resid(const float *A, const float *w, const float *x2, float *out, int64_t M, int N, int K, hipStream_t st);
+bool launch_gemm_f32_silu(const float *A, const float *wg, const float *wu, float *a, int64_t M, int dff, int K, hipStream_t st);
+bool launch_gemm_f32_qkv(const float *A, const float *wq, const float *wk, const float *wv, float *q, float *kc, float *vc,
+                         const float2 *rope, const int32_t *pos0, int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int K,
+                         int *flags, hipStream_t st, int cache_rows);
 // compute units of the current device, 0 if the query fails
 int device_cus();
 

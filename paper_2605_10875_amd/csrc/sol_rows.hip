@@ -569,8 +569,6 @@ void launch_rope_store(const float *qkv32, void *q, void *k_cache, void *v_cache
 // ------------------------------------------------------------------------------------------------
 // SwiGLU elementwise: a = g * sigmoid(g) * u
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ float silu_mul(float g, float u) { return (g / (1.0f + expf(-g))) * u; }
-
 template <typename T>
 __global__ void k_silu_mul(const float *__restrict__ gu, int nsplit, T *__restrict__ a, int64_t M, int dff)
 {
