@@ -456,17 +456,17 @@ static int attn_stage(sol_ctx *ctx, LayerWs &w, const int32_t *pos0, void *kc, v
 // MLP stage of the layer from its input on: gate / up projections, SiLU(gate)*up, magnitude pruning and the
 // quantiser of the down projection's input, down projection, (quantiser of the MLP output,) residual add.
 // Reads w.h (the MLP input as the projections take it) and w.x2 (fp32 residual after attention), writes w.a and x_out.
+// fused_gu: w.a holds SiLU(gate)*up already.
 static int mlp_stage(sol_ctx *ctx, const sol_layer_weights *lw, LayerWs &w, void *x_out, int64_t M, bool skinny,
-                     hipStream_t st)
+                     hipStream_t st, bool fused_gu = false)
 {
     const sol_model_cfg &g = ctx->cfg;
     const int dt = g.dtype;
     const int d = g.d_model, dff = g.d_ff;
     const uint32_t qs = g.quant_sites;
     const bool mfma = dt == SOL_BF16;
-    bool fused_gu = false;
     int ns_gu = 1;
-    {   // gate / up (+ SiLU(gate)*up when fused)
+    if (!fused_gu) {   // gate / up (+ SiLU(gate)*up when fused)
         STAGE(ctx, ST_GATEUP, st);
         if (skinny && M == 1) fused_gu = launch_gemv_gateup_silu(w.h, lw->w_gate, lw->w_up, w.a, dff, d, st);
         if (fused_gu) {
@@ -536,10 +536,6 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
     const uint32_t qs = g.quant_sites;
 
-    {   // input norm + quantise (linear-input site of q/k/v)
-        STAGE(ctx, ST_NORM_IN, st);
-        launch_rmsnorm_fq(x_in, dt, nullptr, nullptr, lw->w_in_norm, dt, w.h, dt, w.ra, qs & SOL_QS_QKV_IN, M, d, g.rms_eps, st);
-    }
     const bool mfma = dt == SOL_BF16;
     const bool skinny = use_skinny(g, M);                      // decode: HBM-bound GEMMs
     // shared prefix: the own caches hold positions P.. only; their writers get the base minus P rows
@@ -547,8 +543,18 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
     void *kcw = pv ? (void *)((char *)kc - esize(dt) * (size_t)pv->P * dh) : kc;
     void *vcw = pv ? (void *)((char *)vc - esize(dt) * (size_t)pv->P * dh) : vc;
     bool fused_qkv = false;
+    if (skinny && M == 1) {   // one row: norm, quantise, q/k/v, rotary and cache write in one launch
+        STAGE(ctx, ST_QKV, st);
+        const NormIn norm{x_in, lw->w_in_norm, qs & SOL_QS_QKV_IN ? w.ra : nullptr, g.rms_eps};
+        fused_qkv = launch_gemv_qkv_rope(nullptr, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, L_max, Hq, Hkv,
+                                         dh, d, ctx->d_flags, st, crows, &norm);
+    }
+    if (!fused_qkv) {   // input norm + quantise (linear-input site of q/k/v)
+        STAGE(ctx, ST_NORM_IN, st);
+        launch_rmsnorm_fq(x_in, dt, nullptr, nullptr, lw->w_in_norm, dt, w.h, dt, w.ra, qs & SOL_QS_QKV_IN, M, d, g.rms_eps, st);
+    }
     int ns_qkv = 1;
-    {   // q/k/v projections (+ rotary and cache write when fused)
+    if (!fused_qkv) {   // q/k/v projections (+ rotary and cache write when fused)
         STAGE(ctx, ST_QKV, st);
         if (skinny && M == 1)
             fused_qkv = launch_gemv_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, L_max, Hq, Hkv,
@@ -597,7 +603,13 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
             if (!fused_o) launch_gemm_generic(w.qb, dt, nq, lw->wo, dt, nq, w.big32, d, M, d, nq, st);
         }
     }
-    {   // post norm (+ pruning at the MLP-input site) + quantise (gate/up input)
+    bool fused_gu = false;
+    if (fused_o && skinny && g.prune_site != 1) {   // one row: post norm, quantise, gate / up and SiLU * up in one launch
+        STAGE(ctx, ST_GATEUP, st);
+        const NormIn norm{w.x2, lw->w_post_norm, qs & SOL_QS_GATEUP_IN ? w.ra : nullptr, g.rms_eps};
+        fused_gu = launch_gemv_gateup_silu(nullptr, lw->w_gate, lw->w_up, w.a, g.d_ff, d, st, &norm);
+    }
+    if (!fused_gu) {   // post norm (+ pruning at the MLP-input site) + quantise (gate/up input)
         STAGE(ctx, ST_NORM_POST, st);
         bool prune_in = g.prune_site == 1;
         if (prune_in) {                              // one kernel when the wave-per-row norm covers the shape
@@ -620,7 +632,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
             launch_fq_rows(w.hn32, w.h, dt, w.ra, false, M, d, st);
         }
     }
-    if (int rc = mlp_stage(ctx, lw, w, x_out, M, skinny, st)) return rc;
+    if (int rc = mlp_stage(ctx, lw, w, x_out, M, skinny, st, fused_gu)) return rc;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, SOL_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return SOL_OK;

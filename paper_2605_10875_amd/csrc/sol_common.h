@@ -436,6 +436,44 @@ __device__ __forceinline__ float fq_code(float z, float s, float qmax)
     return c;
 }
 
+// RMS norm and fake-quantiser of a row that one wave holds, lane l with elements 512 c + 8 l .. + 7 of chunk c: one order of
+// sums for every kernel that normalises rows this way. wt(c): the norm's weights of the lane's eight elements, bf16.
+typedef uint32_t u32x4_w __attribute__((ext_vector_type(4)));
+typedef float f32x4_w __attribute__((ext_vector_type(4)));
+template <int CH, class W> __device__ __forceinline__ float wave_norm_row(float (&v)[CH][8], W wt, float eps)
+{
+    float ss = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += v[c][e] * v[c][e];
+    ss = wave_sum_dpp(ss);
+    const float rinv = 1.0f / sqrtf(ss / (float)(CH * 512) + eps);
+    float amax = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const u32x4_w t = wt(c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[c][2 * e] = v[c][2 * e] * rinv * __uint_as_float(t[e] << 16);
+            v[c][2 * e + 1] = v[c][2 * e + 1] * rinv * __uint_as_float(t[e] & 0xFFFF0000u);
+            amax = fmaxf(amax, fmaxf(fabsf(v[c][2 * e]), fabsf(v[c][2 * e + 1])));
+        }
+    }
+    return amax;                                             // of this lane
+}
+template <int CH> __device__ __forceinline__ void wave_fq_row(float (&v)[CH][8], float amax, int bits)
+{
+    if (bits >= 16) return;
+    amax = __uint_as_float(wave_max_u32(__float_as_uint(amax)));         // non-negative floats order like their bits
+    if (!(amax > 0.f)) return;
+    const float qmax = fq_qmax(bits), s = amax / qmax;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[c][e] = fq_code(v[c][e], s, qmax) * s;
+}
+
 __device__ __forceinline__ int budget_ceil(uint32_t num, uint32_t den, int n)
 {
     const unsigned long long x = (unsigned long long)num * (unsigned long long)n + den - 1ull;

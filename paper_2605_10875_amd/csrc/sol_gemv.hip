@@ -36,6 +36,7 @@ struct GemvArgs {
     const int32_t *pos0;
     int L_max, crows, Hq, Hkv, dh;
     int *flags;
+    NormIn norm;                   // norm.x set: x is the RMS norm, quantised, of that row
 };
 
 // The matrix of a 32x32x16 MFMA holds 32 (weight row, split) pairs as its rows and the activations of the pairs' splits as
@@ -46,10 +47,16 @@ struct GemvArgs {
 // them, or one in two matrices. Two blocks' loads (one with two matrices) are in flight while one is multiplied: 15.5 -> 14.8 us
 // for gate / up of the 1B shape against one block. More units per wave (two matrices for every SP) took 16.0 us there, and
 // activations from memory for every SP 18.3.
-template <int MODE, int SP>
+// NCH > 0: the activations are the RMS norm (and fake-quantiser) of a row of NCH * 512, bf16 for q / k / v and fp32 for gate /
+// up. Every wave normalises the whole row, in the order of k_rmsnorm_fq_wave and with its bits, and brings every nw-th chunk
+// of it to the LDS. The row is requested before the weights (loads return in order), whose first blocks arrive meanwhile.
+// The norm's own kernels took 2.5 and 3.1 us per layer for a row of 2048: a decode step of the 1B model, 1307 -> 1252 us.
+template <int MODE, int SP, int NCH>
 __global__ void __launch_bounds__(256)
 k_gemv(GemvArgs a)
 {
+    constexpr int NC = NCH > 0 ? NCH : 1, NP = MODE == GV_SILU ? 2 : 1;      // 16-byte pieces of the row per chunk and lane
+    static_assert(NCH == 0 || (SP < 32 && (MODE == GV_QKV || MODE == GV_SILU)), "the normalised row goes through the LDS");
     constexpr bool XD = SP == 32;                            // activations straight from memory, each piece once per wave
     constexpr int NT = XD ? 2 : 1, UW = 16 * NT / SP;        // matrices and units of a wave
     constexpr int ND = XD ? 2 : 3;                           // blocks in registers
@@ -79,6 +86,19 @@ k_gemv(GemvArgs a)
             row[t] += off;
         }
     }
+    u32x4_w nx[NC * NP], nwt[NC];                            // the row to normalise, raw, and the norm's weights
+    int nbits = 16;
+    if constexpr (NCH > 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                nx[c * NP + p] = *reinterpret_cast<const u32x4_w *>((const unsigned char *)a.norm.x + (size_t)(c * 64 + lane) * 16 * NP + p * 16);
+            nwt[c] = *reinterpret_cast<const u32x4_w *>((const bf16_t *)a.norm.w + c * 512 + lane * 8);
+        }
+        if (a.norm.ra) nbits = a.norm.ra[0].bits;
+        __builtin_amdgcn_sched_barrier(0);
+    }
     const int nblk = a.kps / 64;
     struct Set { u32x4_v w[NT][4], x[XD ? 4 : 1]; } set[ND];         // blocks in flight
     const bf16_t *const xg = a.x + (r % SP < a.splits ? r % SP : a.splits - 1) * a.kps + h * 32;
@@ -93,6 +113,7 @@ k_gemv(GemvArgs a)
 #pragma unroll
     for (int d = 0; d + 1 < ND; ++d)
         if (d < nblk) load(d, set[d]);
+    if constexpr (NCH > 0) __builtin_amdgcn_sched_barrier(0);
     // what the outputs of this lane's unit will need
     const int u = u0 + lane;
     const bool mine = lane < UW && u < a.units;
@@ -118,10 +139,31 @@ k_gemv(GemvArgs a)
     }
     if (!XD) {
         const int pps = a.kps / 8;                           // pieces per split
-        for (int i = tid; i < a.K / 8; i += blockDim.x) {
+        auto slot = [&](int i) {                             // of piece i in the LDS
             const int sp = i / pps, p = i - sp * pps;        // p = block * 8 + h * 4 + j
-            *reinterpret_cast<u32x4_v *>(xs + (size_t)((((p >> 3) * 4 + (p & 3)) * 2 + ((p >> 2) & 1)) * SP + sp) * 16) =
-                *reinterpret_cast<const u32x4_v *>(a.x + (int64_t)i * 8);
+            return reinterpret_cast<u32x4_v *>(xs + (size_t)((((p >> 3) * 4 + (p & 3)) * 2 + ((p >> 2) & 1)) * SP + sp) * 16);
+        };
+        if constexpr (NCH > 0) {
+            float v[NC][8];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (NP == 2) v[c][e] = __uint_as_float(nx[c * NP + (e >> 2)][e & 3]);
+                    else v[c][e] = __uint_as_float(e & 1 ? nx[c][e >> 1] & 0xFFFF0000u : nx[c][e >> 1] << 16);
+                }
+            const float amax = wave_norm_row<NC>(v, [&](int c) { return nwt[c]; }, a.norm.eps);
+            wave_fq_row<NC>(v, amax, nbits);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (c % nw != w) continue;
+                u32x4_v o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = pack_bf16x2(v[c][2 * e], v[c][2 * e + 1]);
+                *slot(c * 64 + lane) = o;
+            }
+        } else {
+            for (int i = tid; i < a.K / 8; i += blockDim.x) *slot(i) = *reinterpret_cast<const u32x4_v *>(a.x + (int64_t)i * 8);
         }
         __syncthreads();
     }
@@ -188,7 +230,7 @@ k_gemv(GemvArgs a)
     }
 }
 
-template <int MODE, int SP>
+template <int MODE, int SP, int NCH>
 static bool launch_gemv_sp(const GemvArgs &a, hipStream_t st)
 {
     const size_t lds = SP == 32 ? 0 : 2 * (size_t)a.kps * SP;
@@ -196,13 +238,13 @@ static bool launch_gemv_sp(const GemvArgs &a, hipStream_t st)
     constexpr int UW = SP == 32 ? 1 : 16 / SP;               // as in the kernel
     const int waves = (a.units + UW - 1) / UW, cus = device_cus() > 0 ? device_cus() : 256;
     const int nw = waves >= 4 * cus ? 4 : (waves + cus - 1) / cus;   // up to four waves in a workgroup, all CUs first
-    hipLaunchKernelGGL((k_gemv<MODE, SP>), dim3((unsigned)((waves + nw - 1) / nw)), dim3(64 * nw), lds, st, a);
+    hipLaunchKernelGGL((k_gemv<MODE, SP, NCH>), dim3((unsigned)((waves + nw - 1) / nw)), dim3(64 * nw), lds, st, a);
     return true;
 }
 
 // Nv: the width that the K-split kernel would be called with (all stacked maps)
-template <int MODE>
-static bool launch_gemv(GemvArgs a, int Nv, hipStream_t st)
+template <int MODE, int NCH>
+static bool launch_gemv_ch(GemvArgs a, int Nv, hipStream_t st)
 {
     if (Nv <= 0 || Nv % 4 || a.K < 64 || a.K % 64) return false;
     a.units = Nv / 2;
@@ -210,26 +252,39 @@ static bool launch_gemv(GemvArgs a, int Nv, hipStream_t st)
     if (a.K % a.splits) return false;
     a.kps = a.K / a.splits;
     if (a.kps % 64) return false;
-    if (a.splits <= 2) return launch_gemv_sp<MODE, 2>(a, st);
-    if (a.splits <= 4) return launch_gemv_sp<MODE, 4>(a, st);
-    if (a.splits <= 8) return launch_gemv_sp<MODE, 8>(a, st);
-    if (a.splits <= 16) return launch_gemv_sp<MODE, 16>(a, st);
-    return a.splits <= 32 && launch_gemv_sp<MODE, 32>(a, st);
+    if (a.splits <= 2) return launch_gemv_sp<MODE, 2, NCH>(a, st);
+    if (a.splits <= 4) return launch_gemv_sp<MODE, 4, NCH>(a, st);
+    if (a.splits <= 8) return launch_gemv_sp<MODE, 8, NCH>(a, st);
+    if (a.splits <= 16) return launch_gemv_sp<MODE, 16, NCH>(a, st);
+    if constexpr (NCH == 0) return a.splits <= 32 && launch_gemv_sp<MODE, 32, 0>(a, st);
+    return false;                                            // (32 splits take the activations from memory)
+}
+
+template <int MODE>
+static bool launch_gemv(const GemvArgs &a, int Nv, hipStream_t st)
+{
+    if (!a.norm.x) return launch_gemv_ch<MODE, 0>(a, Nv, st);
+    if constexpr (MODE == GV_QKV || MODE == GV_SILU) {       // the widths of k_rmsnorm_fq_wave
+        if (a.K == 2048) return launch_gemv_ch<MODE, 4>(a, Nv, st);
+        if (a.K == 4096) return launch_gemv_ch<MODE, 8>(a, Nv, st);
+    }
+    return false;
 }
 
 bool launch_gemv_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
                           const float2 *rope, const int32_t *pos0, int L_max, int Hq, int Hkv, int dh, int d,
-                          int *flags, hipStream_t st, int cache_rows)
+                          int *flags, hipStream_t st, int cache_rows, const NormIn *norm)
 {
     const GemvArgs a{(const bf16_t *)h, d, (const bf16_t *)wq, (const bf16_t *)wk, (const bf16_t *)wv, q, nullptr, 0, 0, 0,
-                     (bf16_t *)kc, (bf16_t *)vc, rope, pos0, L_max, cache_rows > 0 ? cache_rows : L_max, Hq, Hkv, dh, flags};
+                     (bf16_t *)kc, (bf16_t *)vc, rope, pos0, L_max, cache_rows > 0 ? cache_rows : L_max, Hq, Hkv, dh, flags,
+                     norm ? *norm : NormIn{}};
     return dh % 2 == 0 && launch_gemv<GV_QKV>(a, (Hq + 2 * Hkv) * dh, st);
 }
 
 static GemvArgs plain_args(const void *x, int K, const void *w0, const void *w1, void *out, const void *aux)
 {
     return GemvArgs{(const bf16_t *)x, K, (const bf16_t *)w0, (const bf16_t *)w1, nullptr, out, aux, 0, 0, 0,
-                    nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, nullptr};
+                    nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, nullptr, NormIn{}};
 }
 
 bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, float *out, int N, int K, hipStream_t st)
@@ -237,9 +292,11 @@ bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, floa
     return launch_gemv<GV_RESID_F32>(plain_args(a, K, w, nullptr, out, resid), N, st);
 }
 
-bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int dff, int d, hipStream_t st)
+bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int dff, int d, hipStream_t st, const NormIn *norm)
 {
-    return launch_gemv<GV_SILU>(plain_args(h, d, wg, wu, a, nullptr), 2 * dff, st);
+    GemvArgs g = plain_args(h, d, wg, wu, a, nullptr);
+    if (norm) g.norm = *norm;
+    return launch_gemv<GV_SILU>(g, 2 * dff, st);
 }
 
 bool launch_gemv_resid_out(const void *a, const void *w, const float *x2, void *out, int N, int K, hipStream_t st)

@@ -132,11 +132,19 @@ int skinny_splits(int M, int Nv, int K);
 // ---- linear maps of one row with what follows them (sol_gemv.hip) --------------------------
 // One bf16 row, with the sums of launch_gemm_skinny and skinny_splits(1, ..); false (nothing launched) beyond 32 splits or 62 KB
 // of activations. Arguments as the MFMA launchers of the same names; no scratch. launch_gemv_f32: C [N].
+// norm: the activations are that row's RMS norm (quantised where norm->ra is set) instead of h; K 2048 or 4096.
+struct NormIn {
+    const void *x = nullptr;       // q / k / v: bf16 [K], gate / up: fp32 [K]
+    const void *w = nullptr;       // bf16 [K]
+    const RowAct *ra = nullptr;
+    float eps = 0.f;
+};
 bool launch_gemv_qkv_rope(const void *h, const void *wq, const void *wk, const void *wv, void *q, void *kc, void *vc,
                           const float2 *rope, const int32_t *pos0, int L_max, int Hq, int Hkv, int dh, int d,
-                          int *flags, hipStream_t st, int cache_rows = 0);
+                          int *flags, hipStream_t st, int cache_rows = 0, const NormIn *norm = nullptr);
 bool launch_gemv_resid_f32(const void *a, const void *w, const void *resid, float *out, int N, int K, hipStream_t st);
-bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int dff, int d, hipStream_t st);
+bool launch_gemv_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int dff, int d, hipStream_t st,
+                              const NormIn *norm = nullptr);
 bool launch_gemv_resid_out(const void *a, const void *w, const float *x2, void *out, int N, int K, hipStream_t st);
 bool launch_gemv_f32(const void *a, const void *w, float *C, int N, int K, hipStream_t st);
 

@@ -141,8 +141,6 @@ k_rmsnorm_fq(const TX *__restrict__ x, const float *__restrict__ add, int nsplit
 // One wave per row, the row in registers (d = CH * 512: lane l holds elements [c*512 + 8*l, +8) of every chunk
 // c), 16-byte accesses, reductions on DPP: the layer's bf16 pass, where x is bf16 (layer input) or fp32 (the
 // residual stream inside the layer), the gain and the output are bf16 and there is nothing to add.
-typedef uint32_t u32x4_w __attribute__((ext_vector_type(4)));
-typedef float f32x4_w __attribute__((ext_vector_type(4)));
 
 // Keeps the m entries of largest magnitude of a row held by one wave (lane l holds elements
 // (c * 64 + l) * 8 .. + 8 of chunk c) and zeroes the rest; equal magnitudes go to the lower channel.
@@ -264,39 +262,13 @@ k_rmsnorm_fq_wave(const TX *__restrict__ x, const float *__restrict__ add, int n
             *reinterpret_cast<f32x4_w *>(xp + 4) = f32x4_w{v[c][4], v[c][5], v[c][6], v[c][7]};
         }
     }
-    float ss = 0.f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ss += v[c][e] * v[c][e];
-    ss = wave_sum_dpp(ss);
-    const float rinv = 1.0f / sqrtf(ss / (float)D + eps);
-    float amax = 0.f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const u32x4_w t = *reinterpret_cast<const u32x4_w *>(w + c * 512 + lane * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v[c][2 * e] = v[c][2 * e] * rinv * __uint_as_float(t[e] << 16);
-            v[c][2 * e + 1] = v[c][2 * e + 1] * rinv * __uint_as_float(t[e] & 0xFFFF0000u);
-            amax = fmaxf(amax, fmaxf(fabsf(v[c][2 * e]), fabsf(v[c][2 * e + 1])));
-        }
-    }
+    const float amax = wave_norm_row<CH>(
+        v, [&](int c) { return *reinterpret_cast<const u32x4_w *>(w + c * 512 + lane * 8); }, eps);
     if (prune) {                                             // pruning at the MLP input: ra.m of the D channels stay
         const int m = __builtin_amdgcn_readfirstlane(ra[r].m);
         if (m < D) wave_keep_topm<CH>(v, m, lane);           // (the largest magnitude stays, so amax is unchanged)
     }
-    const int bits = (quant && ra) ? ra[r].bits : 16;
-    if (bits < 16) {
-        amax = __uint_as_float(wave_max_u32(__float_as_uint(amax)));     // non-negative floats order like their bits
-        if (amax > 0.f) {
-            const float qmax = fq_qmax(bits), s = amax / qmax;
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[c][e] = fq_code(v[c][e], s, qmax) * s;
-        }
-    }
+    wave_fq_row<CH>(v, amax, (quant && ra) ? ra[r].bits : 16);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         u32x4_w o;

@@ -86,3 +86,12 @@ def test_a_row_alone_has_the_bits_it_has_among_others(shape, opts):
             for a, b in zip(alone, among[m]):
                 assert torch.equal(a[0], b[i]), (i, m)
     assert ctx.device_status() == sol.OK
+
+
+# widths whose norm is done inside the maps (2048, 4096) with quantising actions: gate / up over 4, 2 and 16 splits with a last
+# workgroup that is not full, q / k / v over 16, 8 and 32 splits (these take the norm's own kernel); and without quantisers there
+@pytest.mark.parametrize("opts", [{}, dict(quant_sites=sol.QS_MLP_OUT)], ids=["default", "no_input_sites"])
+@pytest.mark.parametrize("shape", [synth.LLAMA_1B, synth.LLAMA_8B, synth.ModelShape(2048, 8, 2, 64, 1600)], ids=["1b", "8b", "narrow"])
+def test_a_row_alone_is_normalised_and_quantised_as_among_others(shape, opts, monkeypatch):
+    monkeypatch.setitem(globals(), "TABLE", synth.action_table((0.5, 1.0), (0.0, 0.5), (4, 8, 16)))
+    test_a_row_alone_has_the_bits_it_has_among_others(shape, opts)
