@@ -401,11 +401,13 @@ k_row_positions(const int32_t *__restrict__ pos0, int64_t M, int Tn, int L_max, 
 // exp(logit - maximum); k_nll_finish_cols folds the tiles of a token into  logsumexp(logits) - logits[target]
 // (Method, Eq. 1, negated), the target's logit coming from k_target_logit.
 // target token of every row (teacher-forced rows (b, g, t) share the targets of input b when broadcast_g)
+// and clears the n_pad pieces of 16 bytes behind the hidden states' last row (a launch less for every call whose rows are no whole tiles)
 __global__ void __launch_bounds__(256)
 k_row_targets(const int32_t *__restrict__ targets, int64_t M, int G, int Tn, int broadcast_g, int V, int32_t *__restrict__ row_tgt,
-              int *__restrict__ flags)
+              int *__restrict__ flags, u32x4_t *__restrict__ pad, int64_t n_pad)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = r; i < n_pad; i += (int64_t)gridDim.x * 256) pad[i] = u32x4_t{0u, 0u, 0u, 0u};
     if (r >= M) return;
     const int64_t ti = broadcast_g ? (r / ((int64_t)G * Tn)) * Tn + (r % Tn) : r;
     int tg = targets[ti];
@@ -964,9 +966,13 @@ k_gemm_tile(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t m_firs
     }
 #undef SOL_TILE_SYNC
     vm_wait<0>();                                           // no LDS-direct load outlives its workgroup
-    const int64_t row_w = m0 + wm * WM + 4 * (lane >> 5);
-    if (m0 + BM <= M) gemm_epilogue<true, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
-    else gemm_epilogue<false, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
+    if constexpr (epi_whole_tile<Epi>::value) {             // (the launcher admits whole tiles only)
+        epi.template tile<TM, TN>(acc, m0 + wm * WM, n0 + wn * WN, lane);
+    } else {
+        const int64_t row_w = m0 + wm * WM + 4 * (lane >> 5);
+        if (m0 + BM <= M) gemm_epilogue<true, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
+        else gemm_epilogue<false, TM, TN>(acc, epi, row_w, M, n0 + wn * WN, lane & 31);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1233,18 +1239,25 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
                      float *nll, void *scratch, int64_t M, int V, int K, int *flags, hipStream_t st)
 {
     if (M <= 0) return true;
-    const int64_t Mp = nll_pad_rows(M);
+    // A decode step's few tokens take tiles of 32 or 64 columns, two workgroups per CU: with 256 columns of padding the matrix
+    // cores need as long as HBM. The partial results are those of the large tiles bit for bit.
+    // 128256 entries of 2048, one token: 133 -> 109 us (4.8 TB/s); a 1B decode step of 1 sequence 1198 -> 1165, of 64 4599 -> 4553.
+    const int64_t Mp = M <= 32 ? 32 : M <= 64 ? 64 : nll_pad_rows(M);
     if (V % 256 || K % (2 * BK) || K < 2 * BK || Mp >= (1ll << 31)) return false;
     const int n_wt = V / SOL_WN;
     float2 *part = (float2 *)scratch;
     float *tgt_logit = (float *)(part + (size_t)Mp * n_wt);
     int32_t *row_tgt = (int32_t *)(tgt_logit + Mp);
-    hipLaunchKernelGGL(k_row_targets, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, targets, M, G, T,
-                       broadcast_g ? 1 : 0, V, row_tgt, flags);
-    if (Mp > M) launch_fill_i32((int32_t *)((bf16_t *)hf + M * K), 0, (Mp - M) * K / 2, st);   // K is even
+    const int64_t n_pad = (Mp - M) * K / 8, row_wgs = (M + 255) / 256, pad_wgs = (n_pad + 255) / 256;
+    hipLaunchKernelGGL(k_row_targets, dim3((unsigned)(row_wgs > pad_wgs ? row_wgs : pad_wgs)), dim3(256), 0, st, targets, M, G, T,
+                       broadcast_g ? 1 : 0, V, row_tgt, flags, (u32x4_t *)((bf16_t *)hf + M * K), n_pad);
     const BMap bt = plain_map(hf, (int)Mp, K);
     const EpiNllCols epc{part, Mp};
-    if (!launch_mfma<SOL_TILE>((const bf16_t *)lm_head, K, bt, V, (int)Mp, K, epc, st)) return false;
+    const bf16_t *const head = (const bf16_t *)lm_head;
+    if (!(Mp == 32 ? launch_tile<256, 32, 128, 32, 2>(head, K, bt, 0, V, (int)Mp, K, epc, st)
+          : Mp == 64 ? launch_tile<256, 64, 128, 32, 2>(head, K, bt, 0, V, (int)Mp, K, epc, st)
+                     : launch_mfma<SOL_TILE>(head, K, bt, V, (int)Mp, K, epc, st)))
+        return false;
     hipLaunchKernelGGL(k_target_logit, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const bf16_t *)hf,
                        (const bf16_t *)lm_head, row_tgt, M, K, tgt_logit);
     hipLaunchKernelGGL(k_nll_finish_cols, dim3((unsigned)((M + 31) / 32)), dim3(1024), 0, st, part, tgt_logit, n_wt,

@@ -64,3 +64,32 @@ def test_fold_of_the_tiles_is_accurate_to_fp32(vocab):
     # alone is 3.8e-7 off on average.
     assert err.max() < 8.5e-7, err
     assert err.mean() < 2e-7, err
+
+
+# tiles of 32, 64 and 256 columns: a token's partial results are the same chains and sums in all of them
+@pytest.mark.parametrize("d,vocab", [(256, 256), (640, 1280), (2048, 128256)])
+def test_the_head_of_few_tokens_has_the_bits_of_the_large_tiles(d, vocab):
+    shape = synth.ModelShape(d, 4, 2, 64, 512, 1, vocab)
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    z = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    layer = dict(wq=z(256, d), wk=z(128, d), wv=z(128, d), wo=z(d, 256), w_gate=z(512, d), w_up=z(512, d), w_down=z(d, 512),
+                 w_in_norm=z(d) + 1, w_post_norm=z(d) + 1)          # hands the embedding on
+    head = dict(embed=r(vocab, d), w_final_norm=r(d), lm_head=r(vocab, d) * d ** -0.5)
+    tokens, targets = (torch.randint(0, vocab, (1, 70), generator=g, device="cuda", dtype=torch.int32) for _ in range(2))
+    ctx = sol.Sol(shape, [synth.DENSE_ACTION], max_positions=70)
+
+    def nll(n):
+        return ctx.schedule_loglik([layer], head, tokens[:, :n].contiguous(), targets[:, :n].contiguous(),
+                                   torch.zeros((1, 1, n), dtype=torch.int32, device="cuda")).reshape(-1)
+
+    ref = nll(70)
+    for n in (1, 31, 32, 33, 63, 64, 65):
+        assert torch.equal(nll(n), ref[:n]), n
+    assert ctx.device_status() == sol.OK
+    x = head["embed"][tokens[0].long()].double()                    # all 70 rows, in 64 bits; the normalised row rounds to bf16
+    h = (x * (x.square().mean(1, keepdim=True) + 1e-5).rsqrt() * head["w_final_norm"].double()).to(torch.bfloat16).double()
+    logits = h @ head["lm_head"].double().T
+    want = torch.logsumexp(logits, 1) - logits.gather(1, targets[0].long()[:, None])[:, 0]
+    # logits are sums of d products, of about one in all: 2^-24 sqrt(d) of them by rounding, and 2^-9 of the row where a rounding of h flips
+    assert (ref.double() - want).abs().max() < 1e-3
