@@ -2015,7 +2015,8 @@ k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, c
 // It pays while few items leave most CUs of the one-workgroup-per-item kernel idle and their rows are long enough for that
 // kernel's latency to show. What a row holds is not known here, only what its cache can hold: rows of few keys pay for the two
 // launches more and the wider fold. Per layer of a graph-replayed step, caches of 8192 positions (us, one workgroup per item ->
-// split, at 300 / 1000 / 2000 / 8000 keys): 1B shape, B = 1: 73 -> 75, 80 -> 76, 92 -> 77, 131 -> 87; B = 4: 95 -> 100,
+// split, at 300 / 1000 / 2000 / 8000 keys; since the norms went into the maps one sequence takes 3 to 4 less on both sides): 1B
+// shape, B = 1: 73 -> 75, 80 -> 76, 92 -> 77, 131 -> 87; B = 4: 95 -> 100,
 // 102 -> 102, 116 -> 106, 154 -> 119; 8B shape, B = 1: 126 -> 129, 136 -> 131, 152 -> 132, 227 -> 144; B = 4: 153 -> 163,
 // 166 -> 167, 184 -> 170, 259 -> 190. Not taken: 1B, B = 8: 97 -> 108, 105 -> 110, 117 -> 114, 157 -> 133; B = 12: 100 -> 118,
 // 107 -> 120, 120 -> 127, 159 -> 156; 8B, B = 8: 156 -> 174, 168 -> 179, 190 -> 188, 263 -> 226. So the line is drawn at 32

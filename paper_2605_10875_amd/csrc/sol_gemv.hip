@@ -1,12 +1,14 @@
 // Linear maps of a decode step with one row. A wave ends with finished outputs, so that what follows the product (rotary
-// embedding and cache write, residual, SiLU(gate)*up) is done where the sum is: no partial sums in memory and four launches
-// per layer less than with the K-split kernel (k_gemm_skinny, sol_gemm_mfma.hip), whose epilogues are kernels of their own.
+// embedding and cache write, residual, SiLU(gate)*up) is done where the sum is, and the norms where their result is read: no
+// partial sums in memory and six launches per layer less than with the K-split kernel (k_gemm_skinny, sol_gemm_mfma.hip), whose
+// epilogues are kernels of their own.
 // The sums are those of that kernel, bit for bit: K is cut into the same splits, a split is the same chain of MFMAs, and the
 // splits are added in order, so that a sequence decoded alone has the results it has among others.
 // Bound: HBM (weights once) for the wide maps, launch and load latency for the narrow ones. A layer of a graph-replayed decode
-// step with a cache of 300 keys (us, K-split kernel -> here): 1B shape 80.2 -> 60.7, 8B shape 133.9 -> 117.6; gate / up of the
-// 1B shape: 14.8 us, 4.5 TB/s. (One fmaf chain per row took 58.7 and 113.3, but then a row rounded unlike the same row in a
-// batch.) More rows stay with the K-split kernel.
+// step with a cache of 300 keys (us, K-split kernel -> here): 1B shape 80.2 -> 60.7, 8B shape 133.9 -> 117.6, both before the
+// norms came here (3 to 4 less); gate / up of the 1B shape: 14.8 us, 4.5 TB/s, 15.5 with its norm. (One fmaf chain per row took
+// 58.7 and 113.3, but then a row rounded unlike the same row in a batch. Four blocks in registers in place of two or three: 1120 ->
+// 1129 us for the 1B step.) More rows stay with the K-split kernel.
 #include "sol_internal.h"
 
 namespace sol {
