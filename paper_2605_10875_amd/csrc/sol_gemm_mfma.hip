@@ -1241,7 +1241,8 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
     if (M <= 0) return true;
     // A decode step's few tokens take tiles of 32 or 64 columns, two workgroups per CU: with 256 columns of padding the matrix
     // cores need as long as HBM. The partial results are those of the large tiles bit for bit.
-    // 128256 entries of 2048, one token: 133 -> 109 us (4.8 TB/s); a 1B decode step of 1 sequence 1198 -> 1165, of 64 4599 -> 4553.
+    // 128256 entries of 2048, one token: 133 -> 109 .. 123 us on two cards; a 1B decode step of 1 sequence 1198 -> 1165, of 64
+    // 4599 -> 4553.
     const int64_t Mp = M <= 32 ? 32 : M <= 64 ? 64 : nll_pad_rows(M);
     if (V % 256 || K % (2 * BK) || K < 2 * BK || Mp >= (1ll << 31)) return false;
     const int n_wt = V / SOL_WN;
