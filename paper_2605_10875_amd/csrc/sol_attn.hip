@@ -384,10 +384,6 @@ template <class T> __device__ __forceinline__ void swap_lanes16(T &a, T &b)     
     const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
     a = __builtin_bit_cast(T, (uint32_t)r[0]), b = __builtin_bit_cast(T, (uint32_t)r[1]);
 }
-__device__ __forceinline__ void set_lane(int &v, int x, int lane_imm)   // v of lane lane_imm (a constant) = x (uniform)
-{
-    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(lane_imm));
-}
 struct OpMaxF { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fmaxf(a, b); } };
 struct OpMinF { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fminf(a, b); } };
 struct OpAddI { __device__ __forceinline__ int operator()(int a, int b) const { return a + b; } };
@@ -597,7 +593,7 @@ __device__ __forceinline__ float wave_search_rows(const float (&key)[R][SLOTS], 
                 if (n_ge > (float)br) {                  // more scores equal to the threshold than the budget takes
                     const int n_gt = (int)wave_sum_dpp((float)wave_count_ge_s<SLOTS>(key[r], ng, fn));
                     const int js = wave_tie_last<SLOTS>(key[r], nr, ft, br - n_gt, lane);
-                    set_lane(jstar, js, r * W);
+                    jstar = lane == r * W ? js : jstar;
                 }
             }
     }
