@@ -402,8 +402,10 @@ class Sol:
         Returns dict of device tensors: avg [B][G][3], penalty [B][G], returns, signal, adv [B][G][T]."""
         B, G, T = nll.shape
         assert nll.dtype == torch.float32 and nll.is_contiguous() and targets.dtype == torch.float32
-        out = {"avg": nll.new_empty((B, G, 3)), "penalty": nll.new_empty((B, G)), "returns": torch.empty_like(nll),
-               "signal": torch.empty_like(nll), "adv": torch.empty_like(nll)}
+        # made after nll where that lies on the current device (fewer dispatcher calls); it may also be pinned host memory
+        like = nll if nll.get_device() == torch.cuda.current_device() else torch.empty(0, dtype=torch.float32, device="cuda")
+        out = {k: like.new_empty(sh) for k, sh in (("avg", (B, G, 3)), ("penalty", (B, G)), ("returns", (B, G, T)),
+                                                   ("signal", (B, G, T)), ("adv", (B, G, T)))}
         rc = RewardCfg(float(alpha[0]), float(alpha[1]), float(alpha[2]), float(tau), float(gamma), float(eps))
         need = workspace_bytes(self.cfg, OP_REWARD, B, T, 0)
         ws = torch.empty(need, dtype=torch.uint8, device="cuda")

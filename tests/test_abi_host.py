@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2605_10875_amd import sol, synth
 
@@ -130,3 +131,20 @@ def test_a_decode_workspace_serves_smaller_batches(shape):
     for L in (1024, 1536, 8192):
         need = [sol.workspace_bytes(sol.make_cfg(shape, sol.BF16, 9216), sol.OP_DECODE_STEP, B, 1, L) for B in range(1, 65)]
         assert need == sorted(need)
+
+
+def test_reward_outputs_lie_on_the_device_when_nll_does_not(monkeypatch):
+    """nll may be pinned host memory, which kernels read; the outputs are the device's all the same. Without a GPU: what is
+    asked of "cuda" comes back as a tensor without storage, and the library is a stub that takes the arguments."""
+    empty = torch.empty
+    monkeypatch.setattr(sol.torch, "empty", lambda *a, device=None, **k: empty(*a, device="meta" if device == "cuda" else device, **k))
+    monkeypatch.setattr(sol.torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(sol, "_i32", lambda t: t)
+    monkeypatch.setattr(sol, "_stream", lambda s: None)
+    ctx = object.__new__(sol.Sol)
+    ctx.cfg, ctx.handle = sol.make_cfg(synth.TINY, sol.F32, 16), C.c_void_p()
+    ctx.L = type("Stub", (), {"sol_reward_advantages": staticmethod(lambda *a: 0)})()
+    out = ctx.reward_advantages(torch.zeros(1, 2, 5), torch.zeros(1, 2, 5, dtype=torch.int32), torch.ones(1, 3), (1, 1, 1), 0.0, 0.9)
+    assert {k: (v.device.type, v.dtype, tuple(v.shape)) for k, v in out.items()} == {
+        k: ("meta", torch.float32, sh) for k, sh in (("avg", (1, 2, 3)), ("penalty", (1, 2)), ("returns", (1, 2, 5)),
+                                                     ("signal", (1, 2, 5)), ("adv", (1, 2, 5)))}

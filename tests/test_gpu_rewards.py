@@ -63,3 +63,16 @@ def test_reward_flags_an_action_outside_the_table_and_rejects_bad_settings():
     with pytest.raises(sol.SolError):
         ctx.reward_advantages(dev(nll, sol.F32), dev(ids), dev(targets, sol.F32), (-1, 1, 1), 0.0, 0.85)
     ctx.close()
+
+
+def test_reward_of_likelihoods_in_pinned_host_memory():
+    nll, ids, targets, _ = _case(2, 3, 33, 7200, False)
+    ctx = sol.Sol(synth.TINY, TABLE, dtype=sol.F32, max_positions=16)
+    pinned = torch.empty(nll.shape, dtype=torch.float32, pin_memory=True)
+    pinned.copy_(torch.from_numpy(nll))
+    args = (dev(ids), dev(targets, sol.F32), (1, 1, 1), 0.0, 0.85)
+    here, there = ctx.reward_advantages(dev(nll, sol.F32), *args), ctx.reward_advantages(pinned, *args)
+    assert ctx.device_status() == sol.OK
+    ctx.close()
+    for k in here:
+        assert there[k].is_cuda and torch.equal(here[k], there[k])
