@@ -116,16 +116,20 @@ k_reward_rows(const float *__restrict__ nll, const int32_t *__restrict__ ids, co
         if (pen_out) pen_out[(int64_t)b * K + k] = pen;
     }
     // ---- return-to-go ---------------------------------------------------------------------------
-    double gp[10];                                                  // gamma^(RW_STEPS * 2^i)
+    // weights stay above zero (gamma is, gamma^512 need not be): an infinite NLL makes every return before it infinite, and
+    // what a weight of 2^-1022 adds to a finite one is far below its last place
+    constexpr double W_MIN = 0x1p-1022;
+    double gp[7];                                                   // gamma^(RW_STEPS * 2^i)
     {
         double g = (double)rc.gamma;
         for (int i = 1; i < RW_STEPS; i <<= 1) g *= g;
 #pragma unroll
-        for (int i = 0; i < 10; ++i) { gp[i] = g; g *= g; }
+        for (int i = 0; i < 7; ++i) { gp[i] = fmax(g, W_MIN); g *= g; }
     }
     double tail = 1.0;                                              // gamma^(steps of the lanes behind this one)
 #pragma unroll
     for (int i = 0; i < 6; ++i) tail *= ((63 - lane) >> i) & 1 ? gp[i] : 1.0;
+    tail = fmax(tail, W_MIN);
     double behind = 0.0;                                            // return-to-go at the first step behind the tile
     for (int tile = n_tiles - 1; tile >= 0; --tile) {
         if (tile < n_tiles - 1) load_tile(tile);

@@ -76,3 +76,18 @@ def test_reward_of_likelihoods_in_pinned_host_memory():
     ctx.close()
     for k in here:
         assert there[k].is_cuda and torch.equal(here[k], there[k])
+
+
+@pytest.mark.parametrize("gamma", [0.99, 0.2, 0.05, 1e-3])
+def test_an_infinite_likelihood_makes_every_return_before_it_infinite(gamma):
+    """also where gamma to the distance is zero in 64 bits (0.2 ** 512)"""
+    T = 2300
+    nll, ids, targets, _ = _case(1, 3, T, 7300, False)
+    nll[0, 1, 2047] = nll[0, 2, 100] = np.inf
+    nll[0, 2, T - 1] = -np.inf
+    ref = oracle.reward_advantages(nll, ids, TABLE, targets, (0, 0, 0), 0.0, gamma)["returns"]
+    ctx = sol.Sol(synth.TINY, TABLE, dtype=sol.F32, max_positions=16)
+    got = host(ctx.reward_advantages(dev(nll, sol.F32), dev(ids), dev(targets, sol.F32), (0, 0, 0), 0.0, gamma)["returns"])
+    assert ctx.device_status() == sol.OK
+    ctx.close()
+    np.testing.assert_allclose(got, ref, rtol=1e-5, atol=1e-5 * np.abs(ref[np.isfinite(ref)]).max())
