@@ -1214,7 +1214,7 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
     // A workgroup takes query blocks n_qb - 1 - x and x: every workgroup streams the same number of causal keys.
     // With one block per workgroup the lifetimes differ by a factor of up to n_qb, and slots freed by the short
     // workgroups of a launch were seen to stay empty until the long ones around them had ended.
-    // A grid of one workgroup per block: no partners (few blocks: every CU gets one at most, see pv_split).
+    // A grid of one workgroup per block: no partners (all of them are resident at once, see pv_split).
     const int n_qb = (Tn + QT - 1) / QT;
     const bool alone = (int)gridDim.x >= n_qb;
     for (int pass = 0; pass < 2; ++pass) {
@@ -2643,21 +2643,28 @@ static bool launch_attn_select_t(const void *q, const void *kc, SelRow *sel, con
 }
 
 // How the softmax V kernels deal a sequence's query rows to workgroups: tiles of 16 rows per workgroup and block, workgroups
-// per (sequence, KV head). Two tiles per block share the K and V reads from LDS, and a workgroup takes a late and an early block
-// so that all of them last equally long: the better one as soon as such workgroups fill the chip (one round of `slots`). With
-// fewer, blocks of one tile, and as long as these do not fill the chip either, one block per workgroup. 1B shape, us, pairs
-// of two tiles / pairs of one / one: 333 rows 21 / 12 / 10; 2 x 700 rows 32 / 24 / 22; 3 x 1000 rows 54 / 44 / 43; 8 x 250 rows
-// 20 / 14 / 16; page rule, 14 x 437 rows 63 / 53 / 55; 16 x 2048 rows 560 / 640 / 660; refresh of 8 x 64 rows 129 / 83 / 47; 8B
+// per (sequence, KV head). A block of two tiles reads K and V once for 32 rows, and a workgroup that takes a late and an early
+// block lasts as long as the others: the better one as soon as such workgroups take 3/5 of the chip's slots (all of them where
+// no keys lie before the rows and the head size is 64: an early block then costs little). Fewer leave CUs without work; so
+// blocks of one tile, one per workgroup while all of these are resident at once, else a late and an early one, unless that is no
+// larger a grid than two tiles make (17 .. 32 rows: two sweeps of the keys instead of one, and nothing for it). Slots: resident
+// workgroups of one-tile blocks. Timed for 3430 layers of 1 .. 128 sequences, 17 .. 1000 rows, 0 .. 3000 keys before them, 1 .. 8
+// heads per group, both rules and dense: 9 % less than with two tiles always (geometric mean of the calls), 10 slower by
+// 1 to 3 %. With the line at all slots throughout, 196 were slower, by up to 9 %. A layer under the page rule, 64 x 32 rows behind 3000
+// keys, 1B shape, us: two tiles 622, pairs of one 667, one per workgroup (more than the slots) 611.
+// 1B shape, us of the kernel, pairs of two tiles / pairs of one / one: 333 rows 21 / 12 / 10; 2 x 700 rows 32 / 24 / 22; 8 x 250
+// rows 20 / 14 / 16; page rule, 14 x 437 rows 63 / 53 / 55; 16 x 2048 rows 560 / 640 / 660; refresh of 8 x 64 rows 129 / 83 / 47; 8B
 // shape: 333 rows 21 / 17 / 14, page rule, 3 x 1777 rows 260 / 283 / 307.
 struct PvSplit { int tiles, grid; };
-static PvSplit pv_split(int T, int64_t groups, int dh, int G)
+static PvSplit pv_split(int T, int L_max, int64_t groups, int dh, int G)
 {
     if (T <= 16) return PvSplit{1, 1};
     const int cus = device_cus() > 0 ? device_cus() : 256;
-    const int64_t slots = (int64_t)cus * (dh == 64 ? 4 : 2) / (G == 8 ? 2 : 1);      // resident workgroups (registers, LDS)
-    const int pairs = ((T + 31) / 32 + 1) / 2, blocks = (T + 15) / 16;
-    if (pairs * groups >= slots) return PvSplit{2, pairs};
-    return PvSplit{1, blocks * groups < slots ? blocks : (blocks + 1) / 2};
+    const int64_t slots = (int64_t)cus * (dh == 64 ? 4 : 2) / (G == 8 ? 2 : 1);      // (registers, LDS)
+    const int pairs = ((T + 31) / 32 + 1) / 2, blocks = (T + 15) / 16, halves = (blocks + 1) / 2;
+    if (blocks * groups < slots) return PvSplit{1, blocks};
+    const int64_t line = L_max <= T && dh == 64 ? slots : slots * 3 / 5;
+    return pairs * groups >= line || halves <= pairs ? PvSplit{2, pairs} : PvSplit{1, halves};
 }
 
 template <int DH, int G, bool PRE = false>
@@ -2675,7 +2682,7 @@ static bool launch_attn_pv_t(const void *q, const void *kc, const void *vc, cons
             return false;
         attr_done = true;
     }
-    const PvSplit sp = pv_split(Tn, (int64_t)n_seq * Hkv, DH, G);
+    const PvSplit sp = pv_split(Tn, L_max, (int64_t)n_seq * Hkv, DH, G);
     if (sp.tiles == 1)                                       // one tile of 16 query rows per workgroup
         hipLaunchKernelGGL((k_attn_pv<DH, G, PRE, 1>), dim3(sp.grid, Hkv, n_seq), dim3(G * 64), lds, st, (const bf16_t *)q,
                            (const bf16_t *)kc, (const bf16_t *)vc, sel, o32, pos0, Tn, L_max, Hq, Hkv,
@@ -3268,7 +3275,7 @@ static bool launch_attn_tile_pages_t(const void *q, const void *kc, const void *
                            Hkv, scale, log2S, opt.n_sink, opt.n_window, pv);                                  \
         return true;                                                                                                 \
     }
-    const PvSplit sp = pv_split(T, (int64_t)n_seq * Hkv, DH, G);
+    const PvSplit sp = pv_split(T, L_max, (int64_t)n_seq * Hkv, DH, G);
     if (sp.tiles == 1) {                                     // one tile of 16 query rows per workgroup
         if (G == 1) SOL_PVP(1, 1)
         if (G == 2) SOL_PVP(2, 1)
@@ -3304,7 +3311,7 @@ bool launch_attn_tile_dense(const void *q, const void *k_cache, const void *v_ca
                            L_max, Hq, Hkv, scale, 6, 0, 0, PrefixView());                                     \
         return true;                                                                                                 \
     }
-    const PvSplit sp = pv_split(T, (int64_t)n_seq * Hkv, dh, G);
+    const PvSplit sp = pv_split(T, L_max, (int64_t)n_seq * Hkv, dh, G);
 #define SOL_PVD(DH_, G_) { if (sp.tiles == 1) SOL_PVD2(DH_, G_, 1) SOL_PVD2(DH_, G_, 2) }
     if (dh == 64) {
         if (G == 1) SOL_PVD(64, 1)

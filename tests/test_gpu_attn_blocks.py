@@ -69,6 +69,28 @@ def test_a_sequence_has_the_bits_it_has_among_others(dh, rule):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [17, 33, 64])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("rule", [{}, sol.PAPER_PRESET], ids=["topk", "pages"])
+def test_rows_behind_a_past_have_the_bits_they_have_among_others(dh, rule, T):
+    """1, 40, 80 and 150 sequences of two to four 16-row blocks behind 300 keys: every way the blocks are dealt to workgroups"""
+    g = torch.Generator(device="cuda").manual_seed(dh + T)
+    past, Hq, Hkv = 300, 16, 4
+    shape = synth.ModelShape(d_model=256, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=256, n_layers=1, vocab=100)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()  # noqa: E731
+    q, kc, vc = rnd(1, T, Hq * dh), rnd(1, Hkv, past + T, dh), rnd(1, Hkv, past + T, dh)
+    ids = torch.randint(0, len(TABLE), (1, T), generator=g, device="cuda", dtype=torch.int32)
+    pos0 = torch.full((1,), past, dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, TABLE, dtype=sol.BF16, max_positions=past + T, **rule)
+    want = ctx.test_attention_stage(q, ids, kc, vc, pos0=pos0)
+    for n in (40, 80, 150):
+        many = lambda t: t.expand(n, *t.shape[1:]).contiguous()  # noqa: E731
+        got = ctx.test_attention_stage(many(q), many(ids), many(kc), many(vc), pos0=many(pos0))
+        assert torch.equal(got, many(want)), n
+    assert ctx.device_status() == sol.OK
+    ctx.close()
+
+
 def _attend64(q, k, v, pos, budget):
     """q [T][dh] at positions pos, k and v [L][dh]: softmax over the `budget` largest causal scores, in 64 bits"""
     x = q.double() @ k.double().t().contiguous() / q.shape[-1] ** 0.5
