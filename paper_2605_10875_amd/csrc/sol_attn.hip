@@ -272,7 +272,7 @@ bool launch_attn_rows(const void *q, const void *k_cache, const void *v_cache, i
 {
     if ((int64_t)n_seq * T <= 0) return true;
     if (opt.page < 1 || opt.n_sink < 0 || opt.n_window < 0) return false;
-    if (dtype == 0 && opt.page == 1 && opt.n_sink == 0 && opt.n_window == 0 &&
+    if (dtype == 0 && opt.plain() &&
         launch_attn_f32((const float *)q, (const float *)k_cache, (const float *)v_cache, o32, ra, pos0, n_seq, T, L_max, Hq, Hkv, dh, flags, st))
         return true;
     const int vec = dtype == 0 ? 4 : 8;
@@ -1095,11 +1095,19 @@ k_attn_f32(const float *__restrict__ q, const float *__restrict__ kc, const floa
 }
 
 // Passes of 16 rows per sequence or more on caches of at most 1024 positions: fewer rows leave most of a block's 16 columns
-// empty, longer rows do not fit the search's registers; both stay with k_attn_rows.
+// empty, longer rows do not fit the search's registers (and what a row holds is not known here, only what its cache can hold);
+// both stay with k_attn_rows. So do small passes of models with fewer than four heads per group, whose workgroups there have one or two
+// short rows each and fit the chip together: a layer's call over one sequence of 4 heads of 64, us, k_attn_rows / here, 16 rows
+// 57 / 62, 128 rows 64 / 68, 250 rows 73 / 72, 16 rows behind 368 keys 72 / 71; 4 x 128 rows 81 / 79; 32 x 16 rows 75 / 76, 128 x 16
+// rows 137 / 122; 16 heads, 64 rows 69 / 73, 2 x 128 rows 93 / 85; 4 heads in 2 groups of 128, 16 rows 64 / 66, 128 rows 77 / 72. With
+// four heads per group (32 heads of 64) 16 rows 86 / 82, 16 rows behind 900 keys 141 / 103.
 static bool launch_attn_f32(const float *q, const float *kc, const float *vc, float *o32, const RowAct *ra, const int32_t *pos0,
                             int n_seq, int T, int L_max, int Hq, int Hkv, int dh, int *flags, hipStream_t st)
 {
     if ((dh != 64 && dh != 128) || T < 16 || L_max > 1024 || Hkv <= 0 || Hq % Hkv || Hq > 65535 || n_seq > 65535) return false;
+    const int heads = Hq / Hkv % 4 == 0 ? 4 : Hq / Hkv % 2 == 0 ? 2 : 1, keys = pos0 ? L_max : T;   // k_attn_rows: heads per workgroup
+    const int64_t rows = (int64_t)n_seq * T * Hq;
+    if (heads < 4 && keys * heads * dh <= 24576 && rows <= 2048 && rows * keys * heads <= 163840) return false;
     const int LS = (L_max + 255) / 256 * 256 + 4;          // row stride = 4 mod 64 floats
     const size_t lds = ((size_t)16 * LS + 4 * 16 * dh) * 4;
     auto kern = dh == 64 ? k_attn_f32<64> : k_attn_f32<128>;

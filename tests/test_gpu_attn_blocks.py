@@ -140,3 +140,10 @@ def test_fp32_attention_of_blocks_of_rows(dh, Hq, Hkv, T, last):
     assert torch.equal(a[1], b[1])
     assert ctx.device_status() == sol.OK
     ctx.close()
+
+
+@pytest.mark.parametrize("last", [16, 17, 31, 64, 255])
+@pytest.mark.parametrize("dh,Hq,Hkv,T", [(64, 4, 1, 16), (128, 8, 2, 33)])
+def test_fp32_attention_of_blocks_of_short_rows(dh, Hq, Hkv, T, last):
+    """as above for short rows, at the heads per group (four) where no pass of 16 rows or more goes to the kernel per row"""
+    test_fp32_attention_of_blocks_of_rows(dh, Hq, Hkv, T, last)
