@@ -402,10 +402,9 @@ class Sol:
         Returns dict of device tensors: avg [B][G][3], penalty [B][G], returns, signal, adv [B][G][T]."""
         B, G, T = nll.shape
         assert nll.dtype == torch.float32 and nll.is_contiguous() and targets.dtype == torch.float32
-        # made after nll where that lies on the current device (fewer dispatcher calls); it may also be pinned host memory
-        like = nll if nll.get_device() == torch.cuda.current_device() else torch.empty(0, dtype=torch.float32, device="cuda")
-        out = {k: like.new_empty(sh) for k, sh in (("avg", (B, G, 3)), ("penalty", (B, G)), ("returns", (B, G, T)),
-                                                   ("signal", (B, G, T)), ("adv", (B, G, T)))}
+        like = nll if nll.is_cuda else torch.empty((B, G, T), dtype=torch.float32, device="cuda")   # (pinned host memory)
+        out = {"avg": like.new_empty((B, G, 3)), "penalty": like.new_empty((B, G)), "returns": torch.empty_like(like),
+               "signal": torch.empty_like(like), "adv": torch.empty_like(like)}
         rc = RewardCfg(float(alpha[0]), float(alpha[1]), float(alpha[2]), float(tau), float(gamma), float(eps))
         need = workspace_bytes(self.cfg, OP_REWARD, B, T, 0)
         ws = torch.empty(need, dtype=torch.uint8, device="cuda")
