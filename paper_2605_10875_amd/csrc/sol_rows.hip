@@ -652,11 +652,10 @@ struct PruneSearch {
     {
         return __builtin_amdgcn_logf((c + 0.5f) * __builtin_amdgcn_rcpf(n1 - c));
     }
-    __device__ __forceinline__ void clamp_mid(float x)
+    __device__ __forceinline__ void clamp_mid(float x)       // clamped as a float: x may lie outside every integer's range, or be a NaN
     {
-        const int k = (int)x;                                // out of range or NaN: saturates, and is clamped
-        mid = (uint32_t)(k < (int)lo + 1 ? (int)lo + 1 : (k > (int)hi ? (int)hi : k));
-        mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)mid);
+        x = __builtin_fminf(__builtin_fmaxf(x, (float)(lo + 1u)), (float)hi);
+        mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
     }
     static __device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
     // D keys up to kmax > 0, m of them wanted (0 < m < D), mean magnitude of a sample

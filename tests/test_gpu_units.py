@@ -165,6 +165,30 @@ def test_prune_search_at_extreme_ranks_and_rows(n, rows):
         assert np.array_equal(out[r], want), (r, m[r], np.flatnonzero(out[r] != want)[:8])
 
 
+@pytest.mark.parametrize("n,rows", [(2048, 24), (8192, 600), (11264, 600), (14336, 24)])
+def test_prune_search_with_infinities_and_nans(n, rows):
+    """rows whose mean, and with it the first pivots, is infinite or a NaN: magnitudes rank by their bit patterns, a NaN above
+    an infinity, equal ones by channel"""
+    rng = np.random.default_rng(n)
+    t = torch.from_numpy(rng.standard_normal((rows, n)).astype(np.float32)).to(torch.bfloat16)
+    t[0::6, 5] = torch.inf
+    t[1::6, 8::3] = -torch.inf
+    t[2::6, n - 1] = torch.nan
+    t[3::6, :] = torch.nan
+    t[4::6, ::2] = torch.inf
+    t[4::6, 1::4] = torch.nan
+    t[5::6, :] *= 2.0 ** 120                                          # the mean overflows, no value does
+    t[5::6, :] = torch.nan_to_num(t[5::6, :] * 64.0)
+    m = np.array([(1, 2, n - 1, n // 2, n // 3, n // 16, 7)[(r // 6) % 7] for r in range(rows)], np.int32)
+    words = t.view(torch.int16).numpy()
+    got = sol.prune_quant(t.cuda(), dev(m), dev(np.full(rows, 16, np.int32))).view(torch.int16).cpu().numpy()
+    for r in range(rows):
+        order = np.argsort(-(words[r].astype(np.int32) & 0x7FFF), kind="stable")
+        want = np.zeros(n, np.int16)
+        want[order[:m[r]]] = words[r][order[:m[r]]]
+        assert np.array_equal(got[r], want), (r, m[r], np.flatnonzero(got[r] != want)[:8])
+
+
 def test_quant_codes_worked_examples():
     with open(os.path.join(GOLDEN, "fake_quant_worked.txt")) as f:
         for line in f:
