@@ -856,14 +856,17 @@ bool launch_test_attn_threshold(const float *scores, int rows, int n_cols, const
                                 uint8_t *keep_out, hipStream_t st)
 {
     if (n_cols > 4096) return false;
-#define SOL_TSEL(SL, R_)                                                                                             \
-    hipLaunchKernelGGL((k_test_select_rows<SL, R_>), dim3((rows + R_ - 1) / R_), dim3(64), (size_t)(R_) * (SL) * 64 * 4, st, \
-                       scores, rows, n_cols, n_valid, k, keep_out)
-    if (n_cols <= 256) SOL_TSEL(4, 4);                       // the variants of launch_attn_tile
-    else if (n_cols <= 1024) SOL_TSEL(16, 4);
-    else if (n_cols <= 1280) SOL_TSEL(20, 2);
-    else if (n_cols <= 2048) SOL_TSEL(32, 2);
-    else SOL_TSEL(64, 2);
+    // the variants of k_attn_select, by columns; up to 1024 both widths of a wave, four rows for the first half of the rows
+    const int half = n_cols <= 1024 ? (rows + 1) / 2 : 0;
+#define SOL_TSEL(SL, R_, R0, COUNT)                                                                                  \
+    if ((COUNT) > 0)                                                                                                 \
+        hipLaunchKernelGGL((k_test_select_rows<SL, R_>), dim3(((COUNT) + R_ - 1) / R_), dim3(64), (size_t)(R_) * (SL) * 64 * 4, st, \
+                           scores + (int64_t)(R0) * n_cols, COUNT, n_cols, n_valid + (R0), k + (R0), keep_out + (int64_t)(R0) * n_cols)
+    if (n_cols <= 256) { SOL_TSEL(4, 4, 0, half); SOL_TSEL(4, 2, half, rows - half); }
+    else if (n_cols <= 1024) { SOL_TSEL(16, 4, 0, half); SOL_TSEL(16, 2, half, rows - half); }
+    else if (n_cols <= 1280) { SOL_TSEL(20, 2, 0, rows); }
+    else if (n_cols <= 2048) { SOL_TSEL(32, 2, 0, rows); }
+    else { SOL_TSEL(64, 2, 0, rows); }
 #undef SOL_TSEL
     return true;
 }

@@ -4,6 +4,7 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2605_10875_amd import sol, synth
@@ -118,3 +119,56 @@ def test_reading_the_prefix_in_place_equals_working_on_copies(preset, P):
     ctx.close()
     assert np.isfinite(outs[0]).all() and np.array_equal(outs[0], outs[1])
     assert sizes[0] < sizes[1], sizes          # the in-place layout was the one that ran: no per-schedule prefix copies
+
+
+HEADS128 = synth.ModelShape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=512, n_layers=1, vocab=512)
+HEADS64 = synth.ModelShape(d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=64, d_ff=512, n_layers=1, vocab=512)
+
+
+def _in_place_equals_copies(shape, B, K, P, T, seed):
+    table = synth.action_table((0.125, 0.5, 0.9, 1.0), (0.0, 0.75), (6, 16))
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").mul_(0.05).bfloat16()  # noqa: E731
+    ints = lambda hi, *s: torch.randint(0, hi, s, generator=g, device="cuda", dtype=torch.int32)  # noqa: E731
+    d, nq, nkv, ff = shape.d_model, shape.n_q_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim, shape.d_ff
+    w = dict(w_in_norm=rnd(d) + 1, wq=rnd(nq, d), wk=rnd(nkv, d), wv=rnd(nkv, d), wo=rnd(d, nq), w_post_norm=rnd(d) + 1,
+             w_gate=rnd(ff, d), w_up=rnd(ff, d), w_down=rnd(d, ff))
+    head = dict(embed=rnd(shape.vocab, d), w_final_norm=rnd(d) + 1, lm_head=rnd(shape.vocab, d))
+    args = ([w], head, ints(shape.vocab, B, P), ints(shape.vocab, B, T), ints(shape.vocab, B, T), ints(len(table), B, K, T))
+    ctx = sol.Sol(shape, table, dtype=sol.BF16, max_positions=P + T)
+    here, copies = (ctx.episode_loglik(*args, force_copies=f) for f in (False, True))
+    assert ctx.device_status() == sol.OK
+    small, large = (int(f(ctx.cfg, B, K, P, T)) for f in (ctx.L.sol_episode_workspace_bytes, ctx.L.sol_test_episode_copies_workspace_bytes))
+    ctx.close()
+    assert torch.isfinite(here).all() and torch.equal(here, copies)
+    return small, large
+
+
+@pytest.mark.parametrize("P,T", [(192, 24), (960, 40), (1216, 24), (1280, 17), (1984, 64), (2048, 24), (2112, 40), (4032, 33)])
+@pytest.mark.parametrize("shape", [HEADS64, HEADS128], ids=["64", "128"])
+def test_every_row_length_of_the_prefix_read_in_place(shape, P, T):
+    """each class of the threshold kernel on a shared prefix (256, 1024, 1280, 2048 and 4096 keys), blocks of 16 rows with a
+    rest: the bits of the kernels of one cache per sequence"""
+    small, large = _in_place_equals_copies(shape, 2, 3, P, T, P + T)
+    assert small < large                           # the in-place layout was the one that ran: no prefix copies per schedule
+
+
+@pytest.mark.parametrize("P", [1216, 1984, 2112])
+@pytest.mark.parametrize("shape", [HEADS64, HEADS128], ids=["64", "128"])
+def test_a_prefix_whose_copy_in_operand_order_is_out_of_reach(shape, P):
+    """sizes at which the schedules' own caches lie less than 2^32 bytes behind the prefix caches, but more than that behind
+    the copy of the prefix keys in the matrix instruction's order (the prefix's hidden states lie between the two): the
+    threshold kernel reads the prefix cache itself"""
+    shape, T = dataclasses.replace(shape, d_model=4096), 17
+    cfg = sol.make_cfg(shape, sol.BF16, P + T)
+    B = -(-10 ** 9 // (4 * P * shape.d_model))
+    hidden = 2 * 2 * B * P * shape.d_model                            # two buffers of the prefix's hidden states
+
+    def reach(K):                                                     # both prefix caches, the steps' workspace and hidden states
+        return (2 * 2 * B * shape.n_kv_heads * P * shape.head_dim + sol.workspace_bytes(cfg, sol.OP_LAYER_FORWARD, B * K, T, T)
+                + 3 * 2 * B * K * T * shape.d_model)
+
+    K = max(k for k in range(1, 200) if reach(k) < 4 * 10 ** 9)
+    assert reach(K) < 0.95 * 2 ** 32 and reach(K) + hidden > 1.05 * 2 ** 32, (K, reach(K), hidden)
+    small, large = _in_place_equals_copies(shape, B, K, P, T, P)
+    assert small < large

@@ -91,3 +91,22 @@ def test_an_infinite_likelihood_makes_every_return_before_it_infinite(gamma):
     assert ctx.device_status() == sol.OK
     ctx.close()
     np.testing.assert_allclose(got, ref, rtol=1e-5, atol=1e-5 * np.abs(ref[np.isfinite(ref)]).max())
+
+
+@pytest.mark.parametrize("n_actions", [512, 513])
+def test_reward_with_as_many_actions_as_the_table_on_the_chip_holds_and_one_more(n_actions):
+    rng = np.random.default_rng(n_actions)
+    table = [synth.DENSE_ACTION] + [(int(a), 1000, int(b), 900, int(c)) for a, b, c in
+                                    zip(rng.integers(1, 1001, n_actions - 1), rng.integers(1, 901, n_actions - 1), rng.integers(4, 17, n_actions - 1))]
+    nll, _, targets, eff = _case(2, 3, 700, 7400 + n_actions, True)
+    eff[0] = 1
+    ids = rng.integers(0, n_actions, nll.shape).astype(np.int32)
+    ids[:, :, ::50] = n_actions - 1
+    ref = oracle.reward_advantages(nll, ids, table, targets, (3.0, 2.0, 5.0), 0.05, 0.9, eff=eff)
+    ctx = sol.Sol(synth.TINY, table, dtype=sol.F32, max_positions=16)
+    out = ctx.reward_advantages(dev(nll, sol.F32), dev(ids), dev(targets, sol.F32), (3.0, 2.0, 5.0), 0.05, 0.9, eff=dev(eff))
+    assert ctx.device_status() == sol.OK
+    ctx.close()
+    np.testing.assert_allclose(host(out["avg"]), ref["avg"], rtol=0, atol=2e-7)             # as test_reward_advantages
+    np.testing.assert_allclose(host(out["penalty"]), ref["penalty"], rtol=1e-4, atol=1e-7)
+    assert np.abs(host(out["adv"]) - ref["adv"]).max() < 1e-4

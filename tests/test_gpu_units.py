@@ -78,6 +78,25 @@ def test_attn_threshold_stage_bit_exact(n, kind):
         assert np.array_equal(keep[r], want), (r, n_valid[r], k[r])
 
 
+@pytest.mark.parametrize("n", [1, 64, 255, 256, 257, 700, 1023, 1024])
+@pytest.mark.parametrize("kind", ["normal", "ties", "const", "wide", "heavy", "signed0"])
+def test_attn_threshold_of_two_and_of_four_rows_per_wave(n, kind):
+    """rows of up to 1024 keys are searched four to a wave or two, by head size and cache layout; the hook takes four for the
+    first half of the rows and two for the second: the same rows in both halves"""
+    rng = np.random.default_rng(n * 13 + len(kind))
+    rows = 18                                                         # the last waves of both halves are not full
+    s = _rows(rng, rows, n, kind)
+    n_valid = rng.integers(1, n + 1, rows).astype(np.int32)
+    n_valid[::3] = n
+    k = np.array([rng.integers(1, nv + 1) for nv in n_valid], np.int32)
+    twice = lambda a: np.concatenate([a, a])  # noqa: E731
+    keep = host(sol.attn_threshold(dev(twice(s)), dev(twice(n_valid)), dev(twice(k)))).astype(np.uint8)
+    for r in range(rows):
+        want = np.zeros(n, np.uint8)
+        want[:n_valid[r]] = oracle.select_keys(s[r, :n_valid[r]], int(k[r]))
+        assert np.array_equal(keep[r], want) and np.array_equal(keep[rows + r], want), (r, n_valid[r], k[r])
+
+
 def test_attn_threshold_stage_rejects_long_rows():
     s = torch.zeros((1, 4097), dtype=torch.float32, device="cuda")
     one = torch.ones(1, dtype=torch.int32, device="cuda")
