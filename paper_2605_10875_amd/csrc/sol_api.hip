@@ -60,6 +60,7 @@ struct StageTimer {
         (void)hipEventRecord(c->ev[2 * c->ev_used + 1], st);
         c->ev_used++;
     }
+    void drop() { on = false; }                          // nothing was launched after all
 };
 #define STAGE(ctx, id, st) StageTimer stage_timer_##id(ctx, id, st)
 
@@ -548,6 +549,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
         const NormIn norm{x_in, lw->w_in_norm, qs & SOL_QS_QKV_IN ? w.ra : nullptr, g.rms_eps};
         fused_qkv = launch_gemv_qkv_rope(nullptr, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, L_max, Hq, Hkv,
                                          dh, d, ctx->d_flags, st, crows, &norm);
+        if (!fused_qkv) stage_timer_ST_QKV.drop();
     }
     if (!fused_qkv) {   // input norm + quantise (linear-input site of q/k/v)
         STAGE(ctx, ST_NORM_IN, st);
@@ -608,6 +610,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
         STAGE(ctx, ST_GATEUP, st);
         const NormIn norm{w.x2, lw->w_post_norm, qs & SOL_QS_GATEUP_IN ? w.ra : nullptr, g.rms_eps};
         fused_gu = launch_gemv_gateup_silu(nullptr, lw->w_gate, lw->w_up, w.a, g.d_ff, d, st, &norm);
+        if (!fused_gu) stage_timer_ST_GATEUP.drop();
     }
     if (!fused_gu) {   // post norm (+ pruning at the MLP-input site) + quantise (gate/up input)
         STAGE(ctx, ST_NORM_POST, st);

@@ -95,3 +95,21 @@ def test_a_row_alone_has_the_bits_it_has_among_others(shape, opts):
 def test_a_row_alone_is_normalised_and_quantised_as_among_others(shape, opts, monkeypatch):
     monkeypatch.setitem(globals(), "TABLE", synth.action_table((0.5, 1.0), (0.0, 0.5), (4, 8, 16)))
     test_a_row_alone_has_the_bits_it_has_among_others(shape, opts)
+
+
+# a width without the norm in the maps, one where q / k / v has 32 splits and takes the norm's own kernel, both norms inside
+@pytest.mark.parametrize("shape", [synth.ModelShape(1024, 4, 1, 64, 512), synth.ModelShape(2048, 8, 2, 64, 1600), synth.LLAMA_1B],
+                         ids=["1024", "narrow", "1b"])
+def test_each_stage_of_a_row_alone_is_recorded_once(shape):
+    d, nq, nkv, ff = shape.d_model, shape.n_q_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim, shape.d_ff
+    w = {k: torch.zeros(size, dtype=torch.bfloat16, device="cuda") for k, size in dict(
+        w_in_norm=(d,), wq=(nq, d), wk=(nkv, d), wv=(nkv, d), wo=(d, nq), w_post_norm=(d,), w_gate=(ff, d), w_up=(ff, d), w_down=(d, ff)).items()}
+    x, cache = torch.ones((1, 1, d), dtype=torch.bfloat16, device="cuda"), torch.zeros((1, shape.n_kv_heads, 8, shape.head_dim), dtype=torch.bfloat16, device="cuda")
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, TABLE, max_positions=8)
+    ctx.profile_enable(64)
+    ctx.layer_forward(w, x, one.view(1, 1), cache, cache.clone(), pos0=one)
+    calls = {k: v[1] for k, v in ctx.profile_read().items()}
+    assert ctx.device_status() == sol.OK
+    ctx.close()
+    assert calls["qkv_gemm"] == calls["gate_up_gemm"] == 1 and max(calls.values()) == 1, calls
