@@ -62,14 +62,16 @@ def copy_calibration():
 
 
 def kernel_sources_digest():
-    """Digest of the kernel sources: counters collected for other sources than the ones that run are not quoted."""
+    """Digest of the kernel sources, comments aside: counters collected for other sources than the ones that run are not quoted."""
     import glob
     import hashlib
     import os
+    import re
     h = hashlib.sha1()
     root = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2605_10875_amd", "csrc")
     for p in sorted(glob.glob(os.path.join(root, "*.hip")) + glob.glob(os.path.join(root, "*.h"))):
-        h.update(open(p, "rb").read())
+        code = re.sub(r"//[^\n]*|/\*.*?\*/", " ", open(p).read(), flags=re.S)
+        h.update(" ".join(code.split()).encode())
     return h.hexdigest()[:16]
 
 

@@ -314,12 +314,12 @@ typedef float f32x4_a __attribute__((ext_vector_type(4)));
 // =================================================================================================
 // Batched bf16 attention in two kernels.
 //
-//   k_attn_select   per (sequence, query head, BQ query rows): all causal scores of the rows by MFMA into
-//                   LDS as fp32, then per row the row maximum and -- when the budget is below the row
-//                   length -- the exact threshold of the b largest scores (two or four rows per wave).
+//   k_attn_select   per (sequence, query head, 16 or 32 query rows): all causal scores of the rows by MFMA
+//                   through LDS into registers as fp32, then per row the row maximum and -- when the budget is
+//                   below the row length -- the exact threshold of the b largest scores (two or four rows per wave).
 //                   Output per (row, head): { thr, max, jstar }: a key is kept iff
 //                   s > thr  or  (s == thr and key index <= jstar).
-//   k_attn_pv       per (sequence, KV head, 32 query rows), one wave per query head of the group: streams
+//   k_attn_pv       per (sequence, KV head, 16 or 32 query rows), one wave per query head of the group: streams
 //                   K and V^T chunks through LDS once for all heads of the group, recomputes the scores
 //                   with the same MFMA sequence (bit-identical to the first kernel's), applies the
 //                   threshold, and accumulates softmax numerators times V flash-style with scores and
@@ -505,7 +505,10 @@ __device__ __forceinline__ int wave_count_ge_s(const float (&key)[SLOTS], int ng
 // rows), with the Illinois correction (an end that stays put is scaled by a half), and from the 13th step on the middle
 // of the bracket in key space, which bounds the worst case. Every pivot is clamped into the open bracket, so every step
 // shrinks it. In a simulation 4.5 steps on normal rows of 512 .. 3072 scores, 6 on heavy-tailed ones, where regula falsi
-// from the row's extremes takes 6.4 and 7.5.
+// from the row's extremes takes 6.4 and 7.5. The attention stage on other rows, against that on normal ones (4 x 4096 tokens,
+// head size 64, 1802 us): a common shift 1.01, keys that grow with the position 1.07, four keys 20 times the others 1.09, a
+// third of them shifted along the query 1.08, norms spread by e 1.17, 16 clusters 1.44, 64 distinct keys (all ties) 2.37; with regula
+// falsi from the extremes 1.01, 1.08, 1.13, 1.00, 1.16, 1.38, 2.23 (of 2719 us).
 template <int R, int SLOTS>
 __device__ __forceinline__ float wave_search_rows(const float (&key)[R][SLOTS], int ng, int n, int b, bool open, float fmx,
                                                   float fmn, float s1, float s2, int lane, int &jstar)
@@ -3155,13 +3158,12 @@ bool launch_attn_tile(const void *q, const void *k_cache, const void *v_cache, v
     if ((dh != 64 && dh != 128) || L_max > 4096 || T < 16 || G * Hkv != Hq || (G != 1 && G != 2 && G != 4 && G != 8))
         return false;
     SelRow *sel = (SelRow *)sel_ws;
-    // K in MFMA operand order for the threshold kernel, which reads all causal keys once per block of 8 or 16 query rows
+    // K in MFMA operand order for the threshold kernel, which reads all causal keys once per block of 16 or 32 query rows
     // (up to 256 keys the copy does not pay)
     const bool frag = L_max > 256;
     if (frag && !launch_attn_frag_k(k_cache, kfr, pos0, n_seq, T, L_max, Hkv, dh, st)) return false;
-    // score rows of a workgroup stay in LDS: 16 rows x 1024 keys (66 KB) lets two workgroups share a CU. A launch per
-    // class of row lengths: the rows of a long sequence that see at most 1024 (2048) keys go to the variant for that
-    // length, with its larger blocks and higher occupancy, not to the one the sequence's last row needs.
+    // A launch per class of row lengths: the rows of a long sequence that see at most 1024 (2048) keys go to the variant for
+    // that length, whose rows take fewer registers, not to the one the sequence's last row needs.
     bool ok;
 #define SOL_SEL2(SL, DH_, R, U, NS, SC, KF, LO, HI)                                                                  \
     launch_attn_select_t<SL, DH_, R, U, NS, SC, false, KF>(q, KF ? kfr : k_cache, sel, ra, pos0, n_seq, T, L_max, Hq, Hkv, st, PrefixView(), LO, HI)

@@ -223,7 +223,7 @@ k_gemv(GemvArgs a)
         st(dst + c, y[0]);
         st(dst + c + half, y[1]);
     } else if (MODE == GV_SILU) {
-        st((bf16_t *)a.out + u, (y[0] / (1.0f + expf(-y[0]))) * y[1]);
+        st((bf16_t *)a.out + u, silu_mul(y[0], y[1]));
     } else if (MODE == GV_RESID_OUT) {
         *reinterpret_cast<uint32_t *>((bf16_t *)a.out + 2 * u) = pack_bf16x2(res.x + y[0], res.y + y[1]);
     } else {                                                 // (GV_F32: the products themselves)

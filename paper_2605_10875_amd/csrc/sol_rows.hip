@@ -640,7 +640,11 @@ typedef short i16x2_r __attribute__((ext_vector_type(2)));
 // long so that they bracket the rank; then regula falsi on t over the key, which is close to log2 of the value, with the
 // Illinois correction, and from the 11th step on the middle. Every pivot is clamped into (lo, hi]. In a simulation 3.8 passes on
 // SiLU(g) * u with unit-variance g and u, 4 to 6 on narrower, wider and mixed ones; regula falsi between 0 and the
-// maximum in the value domain takes 9 to 16.
+// maximum in the value domain takes 9 to 16. Measured, 16384 rows of 8192, kept quarter / half / three quarters, us, that search /
+// this: SiLU(g) * u 150 / 110, 148 / 107, 150 / 108; normal 147 / 116, 148 / 116, 149 / 116; log-normal scales 165 / 131, 157 / 131,
+// 150 / 120; one channel 3000 times the others 180 / 109, 161 / 108, 153 / 107. Where the rank falls into a gap of the values the curve
+// leads astray: half of the channels 0 and half kept 193 / 203, a half of them 100 times the other 151 / 148 (rows of 2048: 43 / 46);
+// and rows of nearly one value (1 +- 1 %) have a spread of a few keys only: 147 / 140, rows of 14336 200 / 253.
 template <int D>
 struct PruneSearch {
     static constexpr float n1 = (float)D + 0.5f;

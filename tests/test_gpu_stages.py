@@ -52,7 +52,7 @@ HD128 = synth.ModelShape(d_model=256, n_q_heads=4, n_kv_heads=1, head_dim=128, d
 HD128_G8 = synth.ModelShape(d_model=256, n_q_heads=8, n_kv_heads=1, head_dim=128, d_ff=512, n_layers=1, vocab=100)
 
 
-# T picks the variant of the threshold kernel: <= 256, <= 1024, <= 1280, <= 2048, <= 4096 keys
+# T picks the variants of the threshold kernel: <= 256, <= 1024, <= 2048, <= 4096 keys
 @pytest.mark.parametrize("shape,n_seq,T", [
     (HD64, 3, 70), (HD64, 2, 300), (HD64, 1, 1100), (HD64, 1, 1500), (HD64, 1, 2100),
     (HD128, 3, 72), (HD128, 2, 300), (HD128, 1, 1100), (HD128, 1, 1500), (HD128, 1, 2100), (HD128, 1, 4096),
