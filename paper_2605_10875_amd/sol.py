@@ -76,7 +76,7 @@ def lib_path():
 
 def lib():
     """Loads libsol.so, building it first only if it has never been built. A library older than its sources is
-    still loaded (a GPU machine runs what was built beforehand) but reported, so that stale results are not mistaken
+    still loaded (where there is no compiler, what was built beforehand runs) but reported, so that stale results are not mistaken
     for current ones."""
     global _lib
     if _lib is None:
