@@ -1,24 +1,20 @@
-// bf16 MFMA GEMM for gfx950 with fused epilogues:  C[M][Nv] = A[M][K] * Wv[Nv][K]^T, fp32 accumulate.
+// bf16 MFMA GEMMs for gfx950 with fused epilogues:  C[M][Nv] = A[M][K] * Wv[Nv][K]^T, fp32 accumulate.
 //
-// Both operands are K-contiguous, which is the layout v_mfma_f32_32x32x16_bf16 wants for A and B
+// Both operands are K-contiguous, which is the layout the matrix instructions want for A and B
 // alike (each lane supplies 8 consecutive k of one row / one column). "Nv" is a virtual column
 // space: a column maps to a row of one of up to three weight matrices (q|k|v stacked, or gate and
-// up interleaved in 64-column halves so that SiLU(gate)*up is formed inside one wave tile).
+// up interleaved in pieces of 32 columns so that SiLU(gate)*up is formed inside one wave tile).
 //
-// Tiling: workgroup tile BM x BN, K step 64; waves in a (BM/WM) x (BN/WN) grid, each wave owning
-// WM x WN = (WM/32) x (WN/32) MFMA tiles of 32x32 in accumulator registers. A and B K-slices go
-// from global memory straight into LDS (LDS-direct loads; two stages, XOR-swizzled 16-byte chunks
-// so that the 128-bit fragment reads are bank-conflict free): the slice after next is requested
-// while the MFMAs of the current slice's last k-group issue. Workgroups are mapped to tiles
+// k_gemm_mfma: 256 x 256 tiles for whole rounds of the chip; k_gemm_tile: smaller tiles for few rows. A and B K-slices
+// of 64 go from global memory straight into LDS (LDS-direct loads, XOR-swizzled 16-byte chunks so that the 128-bit fragment
+// reads are bank-conflict free). Workgroups are mapped to tiles
 // XCD-aware: each of the 8 XCDs walks its own contiguous band of the tile grid in groups of
 // GROUP_M tile rows, so the tiles resident on an XCD at any time share A rows and B columns in
-// that XCD's L2; with several tiles per CU one persistent workgroup per CU walks its share of the
-// band and the load pipeline runs across tile boundaries.
-//
-// Epilogue: functors consume the accumulators in their MFMA register layout, two rows at a time
-// (rotary + cache write, residual add, SiLU(gate)*up, plain store); bf16 outputs are paired up across
-// neighbouring lanes into 4-byte stores.
+// that XCD's L2.
 #include "sol_internal.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace sol {
 
@@ -84,7 +80,6 @@ __device__ __forceinline__ void store_bf16_rows2(bf16_t *p0, bf16_t *p1, bool ok
 struct NoAux {};
 
 struct EpiStoreF32 {
-    static constexpr bool persistent_walk = true;
     float *C; int64_t ldc;
     template <int TN> using Aux = NoAux;
     template <int TN> __device__ __forceinline__ void preload0(int64_t, int64_t, NoAux &) const {}
@@ -106,7 +101,6 @@ template <int TN> struct AuxRows { float a0[TN], a1[TN]; };
 
 // x2 = resid + acc  (fp32 out), resid in bf16
 struct EpiResidF32 {
-    static constexpr bool persistent_walk = false;   // measured: 0.30 -> 0.42 ms for the C2 o-projection under the persistent walk
     const bf16_t *resid; float *out; int64_t ld;
     template <int TN> using Aux = AuxRows<TN>;
     template <int TN> __device__ __forceinline__ void preload0(int64_t, int64_t, AuxRows<TN> &) const {}
@@ -135,7 +129,6 @@ struct EpiResidF32 {
 
 // out = bf16(x2 + acc), x2 in fp32
 struct EpiResidOut {
-    static constexpr bool persistent_walk = true;
     const float *x2; bf16_t *out; int64_t ld;
     template <int TN> using Aux = AuxRows<TN>;
     template <int TN> __device__ __forceinline__ void preload0(int64_t, int64_t, AuxRows<TN> &) const {}
@@ -162,7 +155,6 @@ struct EpiResidOut {
 
 // a = bf16(silu(gate) * up); the wave tile's first WN/2 columns are gate, the rest the matching up
 struct EpiSiluMul {
-    static constexpr bool persistent_walk = true;
     bf16_t *a; int64_t ld;   // [M][d_ff]
     template <int TN> using Aux = NoAux;
     template <int TN> __device__ __forceinline__ void preload0(int64_t, int64_t, NoAux &) const {}
@@ -201,12 +193,9 @@ template <int TN> struct AuxRope { float2 t0[TN], t1[TN]; int2 sp0, sp1; };
 
 template <int DHT>                                      // head size: 64 or 128
 struct EpiQkvRope {
-    static constexpr bool persistent_walk = true;
     bf16_t *q, *kc, *vc;
     const float2 *rope; const int2 *row_sp;
     int L_max, Hq, Hkv;
-    const int *only_if_flagged;                          // not null: the kernel runs only if a sequence has been flagged (see EpiQkvRopeTile)
-    __device__ __forceinline__ bool run() const { return !only_if_flagged || (*only_if_flagged & FLAG_CACHE_OVERFLOW) != 0; }
     template <int TN> using Aux = AuxRope<TN>;
     template <int TN> __device__ __forceinline__ void preload0(int64_t row0, int64_t row1, AuxRope<TN> &x) const
     {
@@ -265,125 +254,6 @@ struct EpiQkvRope {
     }
 };
 
-// The same epilogue for whole wave tiles whose 128 consecutive rows touch at most two sequences (Tn >= 128, M a
-// multiple of the tile height). EpiQkvRope reads a row's (sequence, position) and then, at an address that depends on
-// it, its cos / sin pairs: two exposed load latencies per block of 32 rows, about 16 us per tile under the GEMM's own
-// traffic, as long as the MFMA part of a K = 2048 tile. Here the positions come from arithmetic on the tile's first
-// row (two scalar loads of pos0 per tile), so every table load can be issued at once, and they run two groups of four
-// rows ahead of the rotation and the stores. Values and destinations are those of EpiQkvRope.
-template <int DHT>
-struct EpiQkvRopeTile {
-    static constexpr bool persistent_walk = false;       // inside the persistent walk, next to the held fragments, it spills
-    static constexpr bool whole_tile = true;
-    bf16_t *q, *kc, *vc;
-    const float2 *rope; const int32_t *pos0;
-    int Tn, L_max, Hq, Hkv, n_seq;                       // L_max: rows of a cache slab
-    const int *flags;
-    // flags not null: the kernel runs only while no sequence of the call has been flagged (k_row_positions, just before
-    // it, flags those that do not fit their cache): then every store is unconditional. Otherwise the launcher's second
-    // kernel, with EpiQkvRope and its per-row predicates, does the work (both versions in one kernel spill the
-    // accumulators). Without per-sequence start positions the host has checked that T rows fit: flags is null.
-    __device__ __forceinline__ bool run() const { return !flags || (*flags & FLAG_CACHE_OVERFLOW) == 0; }
-    template <int TM, int TN>
-    __device__ __forceinline__ void tile(const floatx16_t (&acc)[TM][TN], int64_t row_w, int vcol_w, int lane) const
-    {
-        // the wave tile's corner is the same in every lane; said so, what follows from it (segment, bases, positions)
-        // stays in scalar registers and the segment tests become branches instead of selects per value
-        const int vcol_u = __builtin_amdgcn_readfirstlane(vcol_w);
-        const int64_t row_u = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(row_w >> 32)) << 32) |
-                                        (uint32_t)__builtin_amdgcn_readfirstlane((int)row_w));
-        // rows row_u + k, k < 128: sequence s0 up to its end, then s0 + 1
-        const int s0 = (int)(row_u / Tn), t0 = (int)(row_u - (int64_t)s0 * Tn);
-        const int pa = pos0 ? pos0[s0] : 0;
-        const int pb = (pos0 && s0 + 1 < n_seq) ? pos0[s0 + 1] : 0;
-        tile_rows<TM, TN>(acc, row_u, vcol_u, lane, s0, t0, pa, pb);
-    }
-    // Destinations are a uniform base per 32-column tile plus a 32-bit byte offset per lane. Of a pair of rows a lane
-    // stores one (even columns the first, odd columns the second: two bf16 of that row, its own and its neighbour's),
-    // so it needs the destination of that row only; the cos / sin pairs it needs for both.
-    template <int TM, int TN>
-    __device__ __forceinline__ void tile_rows(const floatx16_t (&acc)[TM][TN], int64_t row_w, int vcol_w, int lane, int s0,
-                                              int t0, int pa, int pb) const
-    {
-        constexpr int dh = DHT, half = DHT / 2, ND = DHT / 64;   // ND: table columns a lane needs per row (c, c + 32, ..)
-        static_assert(TN * 32 == 128 && TM * 32 == 128, "128 x 128 wave tiles");
-        const int c = lane & 31, rg = lane >> 5;
-        const bool odd = (c & 1) != 0;
-        const int nq = Hq * dh, nkv = Hkv * dh;
-        const int seg = vcol_w < nq ? 0 : (vcol_w < nq + nkv ? 1 : 2);        // the wave tile lies inside one of q / k / v
-        const int w0 = vcol_w - (seg == 0 ? 0 : (seg == 1 ? nq : nq + nkv));  // column inside the segment
-        const int hd = w0 / dh, wi = w0 - hd * dh;
-        const int hstep = (seg == 0 || dh >= TN * 32) ? 0 : (int)((int64_t)L_max * dh) - dh;   // next head inside the tile (dh = 64)
-        // row k of the tile lies (k < kx ? ca : cb) + k rows of rs bytes behind `base` (q: the tile's first row; caches:
-        // the slab of (s0, head hd), that of s0 + 1 being Hkv * L_max rows further on)
-        const int kx = Tn - t0;
-        char *base;
-        int ca, cb;
-        uint32_t rs;
-        if (seg == 0) { base = reinterpret_cast<char *>(q + row_w * (int64_t)nq + w0); ca = cb = 0; rs = (uint32_t)nq * 2u; }
-        else {
-            base = reinterpret_cast<char *>((seg == 1 ? kc : vc) + ((int64_t)s0 * Hkv + hd) * (int64_t)L_max * dh + wi);
-            ca = pa + t0; cb = Hkv * L_max + pb - kx; rs = (uint32_t)dh * 2u;
-        }
-        char *bj[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bj[j] = base + (32 * j + ((32 * j) / dh) * hstep) * 2;
-        const uint32_t lane_col = (uint32_t)(c - (odd ? 1 : 0)) * 2u;
-        const int ta = pa + t0, tb = pb - kx;                    // position of row k: (k < kx ? ta : tb) + k
-        const char *const tbase = reinterpret_cast<const char *>(rope);
-        constexpr int NCH = TM * 4;                              // groups of four rows (registers 4g .. 4g + 3 of block i)
-        float2 cs[3][4][ND];
-        auto load_group = [&](int n, float2 (&x)[4][ND]) {
-            if (seg < 2) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = (n >> 2) * 32 + 8 * (n & 3) + 4 * rg + e;
-                    const bool a = k < kx;
-                    const int pos = (a ? ta : tb) + k;
-                    const uint32_t to = ((uint32_t)pos * (uint32_t)half + (uint32_t)c) * 8u;
-#pragma unroll
-                    for (int dd = 0; dd < ND; ++dd) x[e][dd] = *reinterpret_cast<const float2 *>(tbase + to + dd * 256);
-                }
-            }
-        };
-        load_group(0, cs[0]);
-        load_group(1, cs[1]);
-#pragma unroll
-        for (int n = 0; n < NCH; ++n) {
-            if (n + 2 < NCH) load_group(n + 2, cs[(n + 2) % 3]);
-            const int i = n >> 2, g4 = n & 3;
-#pragma unroll
-            for (int e = 0; e < 4; e += 2) {                     // rows in pairs
-                const int ko = i * 32 + 8 * g4 + 4 * rg + e + (odd ? 1 : 0);   // the row of the pair this lane stores
-                const bool a = ko < kx;
-                const uint32_t roff = (uint32_t)((a ? ca : cb) + ko) * rs + lane_col;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int r = 4 * g4 + e;
-                    float o0 = acc[i][j][r], o1 = acc[i][j][r + 1];
-                    if (seg < 2) {                               // q or k: rotate
-                        const int cj0 = (32 * j) & (dh - 1);     // the tile's first column inside its head
-                        const bool lo = cj0 < half;
-                        const int jp = lo ? j + half / 32 : j - half / 32;   // tile of the partner column
-                        const int dd = (cj0 & (half - 1)) / 32;
-                        const float y0 = acc[i][jp][r], y1 = acc[i][jp][r + 1];
-                        const float2 a0 = cs[n % 3][e][dd], a1 = cs[n % 3][e + 1][dd];
-                        o0 = rotated(o0, y0, a0, lo);
-                        o1 = rotated(o1, y1, a1, lo);
-                    }
-                    // the neighbour's values of both rows (lanes c ^ 1); even columns store (own, neighbour's) of the
-                    // first row, odd columns (neighbour's, own) of the second
-                    const float n0 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, o0), 0xB1, 0xF, 0xF, false));
-                    const float n1 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, o1), 0xB1, 0xF, 0xF, false));
-                    const uint32_t pk = pack_bf16x2(odd ? n1 : o0, odd ? o1 : n0);
-                    *reinterpret_cast<uint32_t *>(bj[j] + roff) = pk;
-                }
-                __builtin_amdgcn_sched_barrier(0);               // one pair at a time: hoisted accumulator reads would spill
-            }
-        }
-    }
-};
-
 // row -> (sequence, absolute position), position -1 (and the overflow flag) if the sequence does not fit
 __global__ void __launch_bounds__(256)
 k_row_positions(const int32_t *__restrict__ pos0, int64_t M, int Tn, int L_max, int2 *__restrict__ row_sp, int *flags)
@@ -433,7 +303,6 @@ __device__ __forceinline__ float swap_halves(float v, int lane)
     return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, __builtin_bit_cast(int, v)));
 }
 struct EpiNllCols {
-    static constexpr bool persistent_walk = true;
     static constexpr bool whole_tile = true;
     float2 *part;               // [V / 128][Mp]
     int64_t M;                  // Mp: tokens, padded to the tile
@@ -451,16 +320,21 @@ struct EpiNllCols {
                 for (int r = 0; r < 16; ++r) m = fmaxf(m, acc[i][j][r]);
             m = fmaxf(m, swap_halves(m, lane));
             const float ml = m * LOG2E;
-            float s0 = 0.f, s1 = 0.f;
+            float q4[4];                                          // rows 8q .. 8q + 7 of every 32: this lane's half, then both
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int q = 0; q < 4; ++q) {
+                float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], LOG2E, -ml));
-                    s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r + 1], LOG2E, -ml));
-                }
-            float se = s0 + s1;
-            se += swap_halves(se, lane);
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int r = 4 * q; r < 4 * q + 4; r += 2) {
+                        s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], LOG2E, -ml));
+                        s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r + 1], LOG2E, -ml));
+                    }
+                const float own = s0 + s1;
+                q4[q] = own + swap_halves(own, lane);
+            }
+            const float se = (q4[0] + q4[1]) + (q4[2] + q4[3]);
             if (lane < 32) dst[32 * j] = make_float2(m, se);
         }
     }
@@ -555,8 +429,6 @@ k_nll_finish_cols(const float2 *__restrict__ part, const float *__restrict__ tgt
 // Register r of accumulator tile (i, j) is row 32*i + 8*(r/4) + 4*(lane/32) + r%4, column 32*j + lane%32
 // of the wave tile (row_w already holds the wave tile's first row + 4*(lane/32)). Per 32-row tile all
 // global reads of the epilogue are issued first, then the row pairs are combined and stored.
-template <class E, class = void> struct epi_gated { static constexpr bool value = false; };
-template <class E> struct epi_gated<E, decltype((void)&E::run)> { static constexpr bool value = true; };
 template <class E, class = void> struct epi_whole_tile { static constexpr bool value = false; };
 template <class E> struct epi_whole_tile<E, decltype((void)E::whole_tile)> { static constexpr bool value = E::whole_tile; };
 
@@ -603,6 +475,11 @@ __device__ __forceinline__ void dtl16(const bf16_t *base, uint32_t byte_off, uin
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
+// the same with the LDS address as a base and a constant: nothing for the compiler to keep 32 sums of in scalar registers
+template <int C> __device__ __forceinline__ void dtl16c(const bf16_t *base, uint32_t byte_off, uint32_t lds_base)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_base), "n"(C) : "memory", "m0", "scc");
+}
 // s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, the expcnt and lgkmcnt fields at "no wait")
 template <int N> __device__ __forceinline__ void vm_wait()
 {
@@ -610,251 +487,457 @@ template <int N> __device__ __forceinline__ void vm_wait()
     __builtin_amdgcn_s_waitcnt(((N >> 4) << 14) | 0x0F70 | (N & 15));
 }
 
-// EpiResidF32 for whole tiles of a kernel that is not persistent (its two LDS stages are dead once the K loop is
-// over). In the accumulator layout a lane holds one column of four consecutive rows, so the plain epilogue issues a
-// 4-byte store and a 2-byte residual load per element: 1024 store and 1024 load instructions per tile through the
-// CU's one memory pipeline, which takes them at a few tens of cycles each whatever their size. Here the wave passes
-// its tile, 64 rows at a time, through its own quarter of the LDS and takes it back row-wise: a lane then owns four
-// consecutive columns of a row, reads the residual as 8 bytes and stores 16 (two whole 512-byte rows of the wave tile
-// per instruction): 64 + 64 instructions per wave tile instead of 256 + 256. Same values as EpiResidF32.
-struct EpiResidF32Tile {
-    static constexpr bool persistent_walk = false;
-    static constexpr bool whole_tile = true;
-    const bf16_t *resid; float *out; int64_t ld;
-    template <int TM, int TN>
-    __device__ __forceinline__ void tile(const floatx16_t (&acc)[TM][TN], int64_t row_w, int vcol_w, int lane) const
+// ------------------------------------------------------------------------------------------------
+// 256 x 256 tiles: 4 waves, one per SIMD, each with 128 weight rows x 128 tokens of the product on v_mfma_f32_16x16x32_bf16
+// (its sums are those of two 32x32x16 instructions bit for bit, so the tile does not show in the results). The weights are the
+// instruction's first operand: a lane's four results are then consecutive columns of one token's output row.
+//
+// Bound: the power the chip grants its matrix cores. With normally distributed operands a loop of nothing but 32x32x16
+// instructions reaches 1.78 PFLOP/s (2.46 on zeros), of 16x16x32 2.06: they move fewer accumulator bits per product.
+// A step (64 of K) goes through the four quadrants of the wave tile: (top, left), (top, right), (bottom, right), (bottom,
+// left), each 32 instructions, and reads one half of an operand from the LDS per quadrant, for the next one. So every half
+// of a slice is read out during ONE quadrant, and the LDS-direct requests of slice kt + 2 go into it from the barrier that
+// follows, two barriers per step: a request has 1 to 1.5 steps to arrive, where the whole-slice order of the kernel before this
+// one (fragments two k-groups ahead, one barrier) left it 0.5 to 1.
+// 32768 rows, epilogue included, us, that kernel -> this one, normal data: 1B shape gate / up 1627 -> 1437, down 823 -> 738, o 264 -> 245,
+// q/k/v 371 -> 334, head 12300 -> 11665; 8B shape gate / up 5441 -> 4877, down 2930 -> 2504. Without an epilogue gate / up is 1320 (1.67
+// PFLOP/s; 980 us, 2.24 PFLOP/s, on zeros): SiLU and the head's exponentials cost what they take to issue (3.7 and 4.1 us per tile
+// of 42), the residual epilogues what a round's 98 MB take at the rate of a copy (all CUs store at once; letting the stores
+// drain behind another step changes nothing).
+//
+// The 256 accumulator registers of a lane are a[0:255], named in the instructions' text: left to the register allocator, 64
+// groups of four that fill the file exactly are moved about between steps (0.8 PFLOP/s). The compiler must not use that
+// half of the register file in this kernel for anything else; ACC_ALL among the clobbers of every barrier keeps it from values that live
+// long, and tests/test_isa_waits.py looks for any other use in the disassembly. Wait states between the last matrix instruction and the first
+// read of its result are the kernel's own business too (acc_settle).
+// ------------------------------------------------------------------------------------------------
+#define SOL_A4(x) "a" #x "0", "a" #x "1", "a" #x "2", "a" #x "3", "a" #x "4", "a" #x "5", "a" #x "6", "a" #x "7", "a" #x "8", "a" #x "9"
+#define SOL_ACC_ALL                                                                                                             \
+    "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", SOL_A4(1), SOL_A4(2), SOL_A4(3), SOL_A4(4), SOL_A4(5), SOL_A4(6),   \
+    SOL_A4(7), SOL_A4(8), SOL_A4(9), SOL_A4(10), SOL_A4(11), SOL_A4(12), SOL_A4(13), SOL_A4(14), SOL_A4(15), SOL_A4(16), SOL_A4(17), \
+    SOL_A4(18), SOL_A4(19), SOL_A4(20), SOL_A4(21), SOL_A4(22), SOL_A4(23), SOL_A4(24), "a250", "a251", "a252", "a253", "a254", "a255"
+
+// accumulator tile at a[R:R+3] = (FIRST ? 0 : itself) + x * y
+template <int R, bool FIRST> __device__ __forceinline__ void acc_mma(const bf16x8_t &x, const bf16x8_t &y)
+{
+    if constexpr (FIRST) asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, 0" ::"v"(x), "v"(y), "n"(R), "n"(R + 3));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(x), "v"(y), "n"(R), "n"(R + 3));
+}
+// the last matrix instruction's results may be read (18 wait states at most)
+__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+template <int R> __device__ __forceinline__ f32x4_t acc_read()
+{
+    float a, b, c, d;
+    asm volatile("v_accvgpr_read_b32 %0, a[%4]\n\tv_accvgpr_read_b32 %1, a[%5]\n\tv_accvgpr_read_b32 %2, a[%6]\n\tv_accvgpr_read_b32 %3, a[%7]"
+                 : "=v"(a), "=v"(b), "=v"(c), "=v"(d) : "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3));
+    return f32x4_t{a, b, c, d};
+}
+template <int... I, class F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_(std::make_integer_sequence<int, N>{}, f); }
+
+// ------------------------------------------------------------------------------------------------
+// Epilogues of k_gemm_mfma. A lane holds, for token 16 t + lane % 16 of its wave tile's 128 (t < 8) and g = lane / 16, the columns
+// 32 p + 8 g .. + 7 (p < 4) of the wave tile's 128: 16 bytes of a bf16 row. Parts of an epilogue (row: an existing token, col0:
+// the wave tile's first virtual column):
+//   place(row[8], p)               what is known of the lane's eight tokens before anything else
+//   fetch(row, p, col0, g, aux)    reads what a token's piece needs, AHEAD tokens ahead of
+//   put(row, ok, p, col0, g, v, aux)   which combines and stores it (ok: the token exists)
+// The pieces lie in the caller's tensors, which are aligned to their elements only: AnyVec.
+// ------------------------------------------------------------------------------------------------
+typedef u32x4_t AnyU4 __attribute__((aligned(2)));
+typedef f32x4_t AnyF4 __attribute__((aligned(4)));
+struct NoPlace {};
+struct EpiTokens {                                          // what most epilogues have in common
+    static constexpr bool weight_rows = false;              // tiles are walked in bands of tokens (or of weight rows)
+    static constexpr int AHEAD = 2;
+    typedef NoPlace Place;
+    struct Aux {};
+    __device__ __forceinline__ void place(const uint32_t (&)[8], NoPlace (&)[8]) const {}
+    template <class A> __device__ __forceinline__ void fetch(uint32_t, const NoPlace &, int, int, A &) const {}
+};
+__device__ __forceinline__ u32x4_t pack8(const float (&v)[8])
+{
+    return u32x4_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+}
+
+struct EpiStoreF32x8 : EpiTokens {
+    float *C; int64_t ldc;
+    EpiStoreF32x8(float *c, int64_t l) : C(c), ldc(l) {}
+    __device__ __forceinline__ void put(uint32_t row, bool ok, const NoPlace &, int col0, int g, const float (&v)[4][8], const Aux &) const
     {
-        static_assert(TM * 32 == 128 && TN * 32 == 128, "128 x 128 wave tiles: 64 rows of fp32 fill the wave's 32 KB");
-        extern __shared__ __align__(16) unsigned char lds_all[];          // the kernel's dynamic segment (128 KB)
-        const int vcol_u = __builtin_amdgcn_readfirstlane(vcol_w);
-        const int64_t row_u = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(row_w >> 32)) << 32) |
-                                        (uint32_t)__builtin_amdgcn_readfirstlane((int)row_w));
-        const int wave_u = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const int c = lane & 31, rg = lane >> 5;
-        unsigned char *const lw = lds_all + (uint32_t)wave_u * 32768u;    // [64 rows][128 fp32]
-        const char *const rbase = reinterpret_cast<const char *>(resid + row_u * ld + vcol_u);
-        char *const obase = reinterpret_cast<char *>(out + row_u * ld + vcol_u);
-        const uint32_t ld_u = (uint32_t)ld;                      // a wave tile spans 128 rows: offsets far below 2^32
-        // row-wise pass: instruction t of a half covers rows 2t and 2t + 1; this lane: row 2t + rg, columns 4c .. 4c + 3
-        const uint32_t el0 = (uint32_t)rg * ld_u + (uint32_t)c * 4u;
+        float *const o = C + row * ldc + col0 + 8 * g;
+        if (!ok) return;
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            u32x2_t rv[32];                                      // the half's residual, requested before the LDS round trip
+        for (int p = 0; p < 4; ++p)
 #pragma unroll
-            for (int t = 0; t < 32; ++t)
-                rv[t] = *reinterpret_cast<const u32x2_t *>(rbase + (el0 + (uint32_t)(hf * 64 + 2 * t) * ld_u) * 2u);
+            for (int h = 0; h < 2; ++h)
+                *reinterpret_cast<AnyF4 *>(o + 32 * p + 4 * h) = f32x4_t{v[p][4 * h], v[p][4 * h + 1], v[p][4 * h + 2], v[p][4 * h + 3]};
+    }
+};
+
+struct EpiResidF32x8 : EpiTokens {                          // EpiResidF32
+    const bf16_t *resid; float *out; int64_t ld;
+    EpiResidF32x8(const bf16_t *r, float *o, int64_t l) : resid(r), out(o), ld(l) {}
+    struct Aux { u32x4_t r[4]; };
+    __device__ __forceinline__ void fetch(uint32_t row, const NoPlace &, int col0, int g, Aux &x) const
+    {
+        const bf16_t *const r = resid + row * ld + col0 + 8 * g;
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
+        for (int p = 0; p < 4; ++p) x.r[p] = *reinterpret_cast<const AnyU4 *>(r + 32 * p);
+    }
+    __device__ __forceinline__ void put(uint32_t row, bool ok, const NoPlace &, int col0, int g, const float (&v)[4][8], const Aux &x) const
+    {
+        float *const o = out + row * ld + col0 + 8 * g;
+        if (!ok) return;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int k = ii * 32 + 8 * (r >> 2) + (r & 3);   // row of the half, less the lane's 4 * rg
+        for (int p = 0; p < 4; ++p)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        *reinterpret_cast<float *>(lw + (uint32_t)(k + 4 * rg) * 512u + (uint32_t)(c + 32 * j) * 4u) = acc[hf * 2 + ii][j][r];
+            for (int h = 0; h < 2; ++h) {
+                f32x4_t y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t w = x.r[p][2 * h + (e >> 1)];
+                    y[e] = v[p][4 * h + e] + __uint_as_float((e & 1) ? w & 0xFFFF0000u : w << 16);
                 }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes, read back by the wave: no barrier
-#pragma unroll
-            for (int t = 0; t < 32; ++t) {
-                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(lw + (uint32_t)(2 * t + rg) * 512u + (uint32_t)c * 16u);
-                const f32x4_t o = {v[0] + __uint_as_float(rv[t][0] << 16), v[1] + __uint_as_float(rv[t][0] & 0xFFFF0000u),
-                                   v[2] + __uint_as_float(rv[t][1] << 16), v[3] + __uint_as_float(rv[t][1] & 0xFFFF0000u)};
-                *reinterpret_cast<f32x4_t *>(obase + (el0 + (uint32_t)(hf * 64 + 2 * t) * ld_u) * 4u) = o;
+                *reinterpret_cast<f32x4_t *>(o + 32 * p + 4 * h) = y;
             }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are over before the next half overwrites the rows
+    }
+};
+
+struct EpiResidOut8 : EpiTokens {                           // EpiResidOut
+    const float *x2; bf16_t *out; int64_t ld;
+    EpiResidOut8(const float *x, bf16_t *o, int64_t l) : x2(x), out(o), ld(l) {}
+    struct Aux { f32x4_t r[4][2]; };
+    __device__ __forceinline__ void fetch(uint32_t row, const NoPlace &, int col0, int g, Aux &x) const
+    {
+        const float *const r = x2 + row * ld + col0 + 8 * g;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) x.r[p][h] = *reinterpret_cast<const AnyF4 *>(r + 32 * p + 4 * h);
+    }
+    __device__ __forceinline__ void put(uint32_t row, bool ok, const NoPlace &, int col0, int g, const float (&v)[4][8], const Aux &x) const
+    {
+        bf16_t *const o = out + row * ld + col0 + 8 * g;
+        if (!ok) return;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            float y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = v[p][e] + x.r[p][e >> 2][e & 3];
+            *reinterpret_cast<AnyU4 *>(o + 32 * p) = pack8(y);
         }
     }
 };
 
-// PERSIST: one workgroup per CU walks every tile of its slot in the XCD's band (tile index + workgroups per XCD) and
-// the pipeline runs across the tile boundary: the last two K steps of a tile request the first two slices of the next
-// one, so only a workgroup's first tile starts cold. (The pipeline's state between steps is LDS only, no registers,
-// so the epilogue in between costs it nothing.)
-template <int BM, int BN, int WM, int WN, class Epi, bool PERSIST>
-__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_gemm_mfma(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t M, int Nv, int K, int tiles_m, int tiles_n,
-            Epi epi)
-{
-    constexpr int NWM = BM / WM, NWN = BN / WN, NT = NWM * NWN * 64;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int ROWS_PER_PASS = NT / 8;                 // 8 threads (16-byte chunks) per 128-byte row
-    constexpr int A_PASSES = BM / ROWS_PER_PASS, B_PASSES = BN / ROWS_PER_PASS;
-    static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "tile / thread mismatch");
-    extern __shared__ __align__(16) unsigned char lds[];
-
-    if constexpr (epi_gated<Epi>::value) {
-        if (!epi.run()) return;                            // the whole grid, before any barrier
+struct EpiSiluMul8 : EpiTokens {                            // EpiSiluMul; gate in pieces 0 and 2, up in 1 and 3
+    bf16_t *a; int64_t ld;
+    EpiSiluMul8(bf16_t *a_, int64_t l) : a(a_), ld(l) {}
+    __device__ __forceinline__ void put(uint32_t row, bool ok, const NoPlace &, int col0, int g, const float (&v)[4][8], const Aux &) const
+    {
+        bf16_t *const o = a + row * ld + col0 / 2 + 8 * g;
+        u32x4_t y[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            float z[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) z[e] = EpiSiluMul::silu_mul(v[2 * p][e], v[2 * p + 1][e]);
+            y[p] = pack8(z);
+        }
+        if (!ok) return;
+        *reinterpret_cast<u32x4_t *>(o) = y[0];
+        *reinterpret_cast<u32x4_t *>(o + 32) = y[1];
     }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / NWN, wn = wave - wm * NWN;
+};
+
+// EpiQkvRope with the rows' positions by arithmetic: a row's sequence that does not fit its cache is flagged and not stored.
+template <int DHT>
+struct EpiQkvRope8 : EpiTokens {
+    static constexpr int ND = DHT / 64;                     // pieces of cos / sin that a token needs
+    static constexpr int AHEAD = DHT == 64 ? 2 : 1;         // (three sets of two pieces spill)
+    bf16_t *q, *kc, *vc;
+    const float2 *rope; const int32_t *pos0;
+    int Tn, L_max, crows, Hq, Hkv;                          // crows: rows of a cache slab
+    int *flags;
+    EpiQkvRope8(bf16_t *q_, bf16_t *k, bf16_t *v, const float2 *r, const int32_t *p0, int T, int L, int c, int hq, int hkv, int *f)
+        : q(q_), kc(k), vc(v), rope(r), pos0(p0), Tn(T), L_max(L), crows(c), Hq(hq), Hkv(hkv), flags(f) {}
+    struct Place { int s, pos; };                           // pos < 0: not stored
+    struct Aux { f32x4_t cs[ND][4]; };
+    __device__ __forceinline__ void place(const uint32_t (&row)[8], Place (&pl)[8]) const
+    {
+        int p0[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            pl[t].s = (int)(row[t] / (uint32_t)Tn);
+            p0[t] = pos0 ? pos0[pl[t].s] : 0;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const bool bad = p0[t] < 0 || p0[t] + Tn > L_max;
+            if (bad) atomicOr(flags, FLAG_CACHE_OVERFLOW);
+            pl[t].pos = bad ? -1 : p0[t] + (int)(row[t] - (uint32_t)pl[t].s * (uint32_t)Tn);
+        }
+    }
+    __device__ __forceinline__ void fetch(uint32_t, const Place &pl, int col0, int g, Aux &x) const
+    {
+        if (col0 >= (Hq + Hkv) * DHT) return;               // v
+        const float *const r = reinterpret_cast<const float *>(rope + (int64_t)(pl.pos < 0 ? 0 : pl.pos) * (DHT / 2)) + 16 * g;
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) x.cs[d][h] = *reinterpret_cast<const f32x4_t *>(r + 64 * d + 4 * h);
+    }
+    __device__ __forceinline__ void put(uint32_t row, bool ok, const Place &pl, int col0, int g, const float (&v)[4][8], const Aux &x) const
+    {
+        constexpr int dh = DHT;
+        const int nq = Hq * dh, nkv = Hkv * dh;
+        const int seg = col0 < nq ? 0 : (col0 < nq + nkv ? 1 : 2);            // the wave tile lies inside one of q / k / v
+        const int w0 = col0 - (seg == 0 ? 0 : (seg == 1 ? nq : nq + nkv));
+        bf16_t *d;                                          // piece 0's destination
+        int64_t up;                                         // elements from pieces 0, 1 to 2, 3
+        if (seg == 0) { d = q + row * (int64_t)nq + w0; up = 64; }
+        else {
+            d = (seg == 1 ? kc : vc) + (((int64_t)pl.s * Hkv + w0 / dh) * crows + pl.pos) * dh;
+            up = dh == 64 ? (int64_t)crows * 64 : 64;
+        }
+        d += 8 * g;
+        u32x4_t y[4];
+        if (seg == 2) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) y[p] = pack8(v[p]);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const bool lo = (p & ND) == 0;              // lower half of its head; the partner is ND pieces on
+                const int cd = p & (ND - 1);
+                float z[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    z[e] = rotated(v[p][e], v[p ^ ND][e], make_float2(x.cs[cd][e >> 1][2 * (e & 1)], x.cs[cd][e >> 1][2 * (e & 1) + 1]), lo);
+                y[p] = pack8(z);
+            }
+        }
+        if (!ok || pl.pos < 0) return;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) *reinterpret_cast<AnyU4 *>(d + (p >> 1) * up + 32 * (p & 1)) = y[p];
+    }
+};
+
+// EpiNllCols: the partial results of the wave tile's 128 vocabulary entries. A lane holds rows 8g .. 8g + 7 of every 32; the sums
+// run in that epilogue's order.
+struct EpiNllCols8 {
+    static constexpr bool weight_rows = true;
+    float2 *part;                                           // [V / 128][Mp]
+    int64_t Mp;
+};
+__device__ __forceinline__ float lane_xor(float v, int lane, int x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((lane ^ x) << 2, __builtin_bit_cast(int, v)));
+}
+
+template <class Epi>
+__device__ __forceinline__ void tile_epilogue(const Epi &epi, int64_t m_w, int64_t M, int col0, int lane)
+{
+    const int g = lane >> 4;
+    uint32_t row[8];
+    bool ok[8];
+    typename Epi::Place pl[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int64_t r = m_w + 16 * t + (lane & 15);
+        ok[t] = r < M;
+        row[t] = (uint32_t)(ok[t] ? r : M - 1);
+    }
+    epi.place(row, pl);
+    typename Epi::Aux aux[Epi::AHEAD + 1];
+#pragma unroll
+    for (int t = 0; t < Epi::AHEAD; ++t) epi.fetch(row[t], pl[t], col0, g, aux[t]);
+    static_for<8>([&](auto t_) {
+        constexpr int t = t_;
+        if constexpr (t + Epi::AHEAD < 8) epi.fetch(row[t + Epi::AHEAD], pl[t + Epi::AHEAD], col0, g, aux[(t + Epi::AHEAD) % (Epi::AHEAD + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+        float v[4][8];
+        static_for<8>([&](auto i_) {
+            constexpr int i = i_;
+            const f32x4_t a = acc_read<4 * (8 * i + t)>();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[i >> 1][4 * (i & 1) + e] = a[e];
+        });
+        epi.put(row[t], ok[t], pl[t], col0, g, v, aux[t % (Epi::AHEAD + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+__device__ __forceinline__ void tile_epilogue(const EpiNllCols8 &epi, int64_t m_w, int64_t, int col0, int lane)
+{
+    constexpr float LOG2E = 1.44269504088896341f;
+    float2 *const dst = epi.part + (int64_t)(col0 / 128) * epi.Mp + m_w + (lane & 15);
+    static_for<8>([&](auto t_) {
+        constexpr int t = t_;
+        f32x4_t v[8];
+        static_for<8>([&](auto i_) { v[i_] = acc_read<4 * (8 * i_ + t)>(); });
+        float m = v[0][0];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m = fmaxf(m, v[i][e]);
+        m = fmaxf(m, lane_xor(m, lane, 16));
+        m = fmaxf(m, lane_xor(m, lane, 32));
+        const float ml = m * LOG2E;
+        float h[2];                                         // rows with bit 2 clear, set
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+            for (int i = b; i < 8; i += 2)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(v[i][e], LOG2E, -ml));
+                    s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(v[i][e + 1], LOG2E, -ml));
+                }
+            h[b] = s0 + s1;
+        }
+        float se = h[0] + h[1];
+        se += lane_xor(se, lane, 16);
+        se += lane_xor(se, lane, 32);
+        if (lane < 16) dst[16 * t] = make_float2(m, se);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+template <class Epi>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_gemm_mfma(const bf16_t *__restrict__ X, BMap bmap, int64_t M, int K, int tiles_r, int tiles_c, Epi epi)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int SB = 65536;                               // a stage: 256 weight rows, 256 token rows of 128 bytes
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ww = wave >> 1, wt = wave & 1;                // this wave's half of the weight rows, of the tokens
 
     // ---- XCD-aware tile mapping: workgroup b runs on XCD b % 8; XCD x owns a contiguous band ----
-    const int n_tiles = tiles_m * tiles_n;
-    const int per_xcd = (n_tiles + 7) / 8;
+    const int n_tiles = tiles_r * tiles_c, per_xcd = (n_tiles + 7) / 8;
     const int band_end = ((int)(blockIdx.x & 7) + 1) * per_xcd < n_tiles ? ((int)(blockIdx.x & 7) + 1) * per_xcd : n_tiles;
-    const int lin_step = (int)(gridDim.x >> 3);             // PERSIST: workgroups per XCD
+    const int lin_step = (int)(gridDim.x >> 3);
     int lin = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (lin >= band_end) return;
-    const int group_sz = GROUP_M * tiles_n;
+    const int group_sz = GROUP_M * tiles_c;
 
-    // ---- per-thread global sources and LDS destinations of the staged K slices ----
-    // A pass covers ROWS_PER_PASS rows (8 threads x 16 bytes per 128-byte row). Sources are wave-uniform
-    // bases (scalar registers) plus one 32-bit lane offset each; the LDS swizzle does not depend on the
-    // pass (ROWS_PER_PASS is a multiple of 16), so one destination offset serves all passes.
-    static_assert(ROWS_PER_PASS % 16 == 0, "swizzle must repeat from pass to pass");
-    const int chunk = tid & 7, r_in_pass = tid >> 3;
-    const bf16_t *a_base;                                   // uniform
-    uint32_t a_off[A_PASSES];
-    const bf16_t *b_base[B_PASSES];                         // uniform: first weight row of each pass
-    // sources of tile LIN_, its first row and first virtual column
-#define SOL_TILE_SRC(LIN_, M0_, N0_)                                                                       \
-    {                                                                                                      \
-        const int grp_ = (LIN_) / group_sz, in_grp_ = (LIN_) - grp_ * group_sz;                            \
-        const int rows_here_ = (tiles_m - grp_ * GROUP_M) < GROUP_M ? (tiles_m - grp_ * GROUP_M) : GROUP_M; \
-        M0_ = (int64_t)(grp_ * GROUP_M + in_grp_ % rows_here_) * BM;                                       \
-        N0_ = (in_grp_ / rows_here_) * BN;                                                                 \
-        a_base = A + M0_ * lda;                                                                            \
-        _Pragma("unroll") for (int p = 0; p < A_PASSES; ++p) {                                             \
-            int64_t rl = p * ROWS_PER_PASS + r_in_pass;                                                    \
-            if (M0_ + rl >= M) rl = M - 1 - M0_;   /* ragged last tile: re-read the last row, never stored */ \
-            a_off[p] = ((uint32_t)(rl * lda) + (uint32_t)((chunk ^ SOL_SWZ(r_in_pass)) * 8)) * 2u;   /* bytes; lane = LDS slot */ \
-        }                                                                                                  \
-        _Pragma("unroll") for (int p = 0; p < B_PASSES; ++p) b_base[p] = bmap.row(N0_ + p * ROWS_PER_PASS); \
-    }
-    int64_t m0, m0_next = 0;
-    int n0, n0_next = 0;
-    SOL_TILE_SRC(lin, m0, n0);
-    const uint32_t b_off = ((uint32_t)r_in_pass * (uint32_t)bmap.ld + (uint32_t)((chunk ^ SOL_SWZ(r_in_pass)) * 8)) * 2u;
-
-    floatx16_t acc[TM][TN];
-#define SOL_ACC_ZERO                                                                                       \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) _Pragma("unroll") for (int j = 0; j < TN; ++j)          \
-        _Pragma("unroll") for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    SOL_ACC_ZERO;
-
-    // Two LDS stages filled by LDS-direct loads: slice kt+2 is requested into the stage of slice kt right after the
-    // barrier that ends the reads of slice kt, and must have landed by the next step's barrier.
-    bf16x8_t fa0[TM], fb0[TN], fa1[TM], fb1[TN], fa2[TM], fb2[TN], fa3[TM], fb3[TN];   // one set per k-group of a step
-    const int KT = K / BK;
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int frow = lane & 31, fk = lane >> 5, fsw = SOL_SWZ(frow);
-    const int a_frag0 = (wm * WM + frow) * 128;
-    const int b_frag0 = BM * 128 + (wn * WN + frow) * 128;
-#define SOL_F_READ(FA, FB, STAGE_, KK_)                                                                    \
-    {                                                                                                      \
-        const int coff = ((((KK_) * 2 + fk) ^ fsw) << 4);                                                  \
-        _Pragma("unroll") for (int i = 0; i < TM; ++i) FA[i] = __builtin_bit_cast(                         \
-            bf16x8_t, *reinterpret_cast<const u32x4_t *>((STAGE_) + a_frag0 + i * 32 * 128 + coff));       \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) FB[j] = __builtin_bit_cast(                         \
-            bf16x8_t, *reinterpret_cast<const u32x4_t *>((STAGE_) + b_frag0 + j * 32 * 128 + coff));       \
-    }
-#define SOL_MMA(FA, FB)                                                                                    \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) _Pragma("unroll") for (int j = 0; j < TN; ++j)          \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(FA[i], FB[j], acc[i][j], 0, 0, 0);
-#define SOL_FENCE __builtin_amdgcn_sched_barrier(0)
-#define SOL_ORDER_RM                                                                                       \
-    _Pragma("unroll") for (int i_ = 0; i_ < TM + TN; ++i_) {                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                 \
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                 \
-    }                                                                                                      \
-    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - (TM + TN), 0);
-    // all passes of slice KT_ into the stage at LDS byte offset STG_
-#define SOL_DTL_ONE(P_, KT_, STG_)                                                                         \
-    {                                                                                                      \
-        const int koff_ = ((KT_) < KT ? (KT_) : KT - 1) * BK;                                              \
-        if ((P_) < A_PASSES) dtl16(a_base + koff_, a_off[(P_)], (uint32_t)((STG_) + (P_) * ROWS_PER_PASS * 128 + wave_u * 1024)); \
-        else dtl16(b_base[(P_) - A_PASSES] + koff_, b_off, (uint32_t)((STG_) + BM * 128 + ((P_) - A_PASSES) * ROWS_PER_PASS * 128 + wave_u * 1024)); \
-    }
-    static_assert(TM * TN == A_PASSES + B_PASSES && ROWS_PER_PASS == 32, "one LDS-direct load per MFMA of a k-group");
-    // one k-group of the second half of a step, in issue order: behind each MFMA one fragment read (the first TM + TN
-    // MFMAs: k-group KK_ of the next slice into the set (FRA, FRB)) and behind every second MFMA one LDS-direct
-    // request (passes P0_ .. P0_ + 7 of slice KT_LOAD_ into the stage that was just read out)
-#define SOL_MMA_DTL(FA, FB, FRA, FRB, STG_, KK_, P0_, KT_LOAD_, CURO_)                                     \
-    {                                                                                                      \
-        const int coff_ = ((((KK_) * 2 + fk) ^ fsw) << 4);                                                 \
-        _Pragma("unroll") for (int m = 0; m < TM * TN; ++m) {                                              \
-            acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(FA[m / TN], FB[m % TN],          \
-                                                                         acc[m / TN][m % TN], 0, 0, 0);    \
-            if (m < TM) FRA[m] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(          \
-                            (STG_) + a_frag0 + m * 32 * 128 + coff_));                                     \
-            else if (m < TM + TN) FRB[m - TM] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>( \
-                            (STG_) + b_frag0 + (m - TM) * 32 * 128 + coff_));                              \
-            if (m & 1) SOL_DTL_ONE((P0_) + m / 2, KT_LOAD_, CURO_);                                        \
-            SOL_FENCE;                                                                                     \
-        }                                                                                                  \
-    }
-    // One step. Fragments are read two k-groups ahead (four register sets), so the reads of the current stage are
-    // over after the second k-group: the barrier sits there, and the second half of the step requests slice
-    // KT_LOAD_ into the stage just read out (CURO_ = its LDS byte offset) while it reads the first two k-groups of
-    // the next stage. The requests of the previous step must have landed before the barrier publishes their stage.
-#define SOL_STEP(CUR_, NXT_, CURO_, KT_LOAD_)                                                              \
-    SOL_F_READ(fa2, fb2, CUR_, 2); SOL_MMA(fa0, fb0); SOL_ORDER_RM; SOL_FENCE;                             \
-    SOL_F_READ(fa3, fb3, CUR_, 3); SOL_MMA(fa1, fb1); SOL_ORDER_RM; SOL_FENCE;                             \
-    vm_wait<0>();                                                                                          \
-    __syncthreads();                                                                                       \
-    SOL_FENCE;                                                                                             \
-    SOL_MMA_DTL(fa2, fb2, fa0, fb0, NXT_, 0, 0, KT_LOAD_, CURO_);                                          \
-    SOL_MMA_DTL(fa3, fb3, fa1, fb1, NXT_, 1, (A_PASSES + B_PASSES) / 2, KT_LOAD_, CURO_);
-
-    constexpr int STAGE_BYTES2 = (BM + BN) * 128;
-    unsigned char *const stage0 = lds, *const stage1 = lds + STAGE_BYTES2;
+    // ---- sources of the staged K slices: uniform bases, per-lane byte offsets ----
+    const int64_t ld = bmap.ld;                             // of weights and tokens alike
+    const int64_t w_mid = (bmap.mode == 0 ? 64 : 32) * ld;  // rows of piece p + 2 behind piece p
+    const int chunk = tid & 7, rip = tid >> 3;              // this thread's 16-byte piece and row of a pass of 32 rows
+    const uint32_t w_off0 = ((uint32_t)rip * (uint32_t)ld + (uint32_t)((chunk ^ (((rip >> 1) & 1) | ((rip >> 3) << 1))) * 8)) * 2u;
+    const uint32_t w_off1 = w_off0 + (uint32_t)(2 * w_mid) * 2u;
+    const uint32_t x_chunk = (uint32_t)((chunk ^ ((rip >> 1) & 7)) * 8);
+    uint32_t x_off[8];
+    const bf16_t *we, *wo, *we2, *wo2, *xb;                 // of the slice being requested: pieces 0, 1, 2, 3 (4 .. 7 at w_off1), tokens
+    int64_t m0, m0_next;
+    int n0, n0_next;
+    auto tile_src = [&](int l, int64_t &m, int &n) {
+        const int grp = l / group_sz, in_grp = l - grp * group_sz;
+        const int rows_here = (tiles_r - grp * GROUP_M) < GROUP_M ? (tiles_r - grp * GROUP_M) : GROUP_M;
+        const int tr = grp * GROUP_M + in_grp % rows_here, tc = in_grp / rows_here;
+        m = (int64_t)(Epi::weight_rows ? tc : tr) * 256;
+        n = (Epi::weight_rows ? tr : tc) * 256;
+        we = bmap.row(n);
+        wo = bmap.row(n + 32);
+        we2 = we + w_mid;
+        wo2 = wo + w_mid;
+        xb = X + m * ld;
 #pragma unroll
-    for (int p = 0; p < A_PASSES + B_PASSES; ++p) SOL_DTL_ONE(p, 0, 0);
-#pragma unroll
-    for (int p = 0; p < A_PASSES + B_PASSES; ++p) SOL_DTL_ONE(p, 1, STAGE_BYTES2);
-    vm_wait<0>();
-    __syncthreads();
-    SOL_F_READ(fa0, fb0, stage0, 0);
-    SOL_F_READ(fa1, fb1, stage0, 1);
-    const int vcol_w = wn * WN;
-    const int64_t row_w = wm * WM + 4 * (lane >> 5);
-    if constexpr (!PERSIST) {
-        for (int kt = 0; kt < KT; kt += 2) {                // KT is even (K is a multiple of 128)
-            SOL_STEP(stage0, stage1, 0, kt + 2);
-            SOL_STEP(stage1, stage0, STAGE_BYTES2, kt + 3);
+        for (int p = 0; p < 8; ++p) {
+            int64_t r = p * 32 + rip;
+            if (m + r >= M) r = M - 1 - m;                  // ragged last tile: re-read the last row, never stored
+            x_off[p] = ((uint32_t)(r * ld) + x_chunk) * 2u;
         }
-        vm_wait<0>();
-        __syncthreads();
-    } else {
-        for (;;) {
-            const bool more = lin + lin_step < band_end;
-            for (int kt = 0; kt < KT - 2; kt += 2) {
-                SOL_STEP(stage0, stage1, 0, kt + 2);
-                SOL_STEP(stage1, stage0, STAGE_BYTES2, kt + 3);
-            }
-            // the last two steps request slices 0 and 1 of the next tile (of this tile again after the last one:
-            // never used)
-            SOL_TILE_SRC(more ? lin + lin_step : lin, m0_next, n0_next);
-            SOL_STEP(stage0, stage1, 0, 0);
-            SOL_STEP(stage1, stage0, STAGE_BYTES2, 1);
-            // stage 0 holds the next tile's slice 0 and its first fragments are in registers; slice 1 is on its way
-            // into stage 1 and is waited for in the next tile's first step
-            if constexpr (epi_whole_tile<Epi>::value) epi.template tile<TM, TN>(acc, m0 + wm * WM, n0 + vcol_w, lane);
-            else gemm_epilogue<true, TM, TN>(acc, epi, m0 + row_w, M, n0 + vcol_w, lane & 31);   // M % BM == 0 (launcher): with
-            if (!more) break;                               // both epilogue versions in the loop the compiler spills the accumulators
-            SOL_ACC_ZERO;
-            lin += lin_step; m0 = m0_next; n0 = n0_next;
-        }
-        vm_wait<0>();                                       // no LDS-direct load outlives its workgroup
-        return;
+    };
+    // request R of a slice into stage STG: 0..3 the weights' top halves (rows 0..63 of each wave's 128), 4..7 the tokens' left
+    // halves, 8..11 right, 12..15 bottom
+    const uint32_t wave_lds = (uint32_t)wave * 1024u;
+    auto request = [&](auto r_, auto stg_) {
+        constexpr int R = r_, q = R & 3, p = (q & 1) + 4 * (q >> 1) + (R >= 8 ? 2 : 0), at = (int)stg_ + p * 4096;
+        if constexpr (R < 4) dtl16c<at>(q & 1 ? wo : we, q >> 1 ? w_off1 : w_off0, wave_lds);
+        else if constexpr (R >= 12) dtl16c<at>(q & 1 ? wo2 : we2, q >> 1 ? w_off1 : w_off0, wave_lds);
+        else dtl16c<at + 32768>(xb, x_off[p], wave_lds);
+    };
+    auto next_slice = [&] { we += BK; wo += BK; we2 += BK; wo2 += BK; xb += BK; };
+
+    // ---- fragments. Weight rows are dealt to the 16 rows of instruction tiles 2p and 2p + 1 so that a lane's results of the
+    // two are eight consecutive columns: lane (m, g) reads row 32p + 8 (m / 4) + 4 e + m % 4 of tile 2p + e ----
+    const int m16 = lane & 15, g = lane >> 4;
+    const uint32_t w_row = (uint32_t)(ww * 128 + 8 * (m16 >> 2) + (m16 & 3)) * 128, w_swz = (uint32_t)(((m16 >> 1) & 1) | ((m16 >> 2) << 1));
+    const uint32_t x_row = (uint32_t)(256 + wt * 128 + m16) * 128, x_swz = (uint32_t)((m16 >> 1) & 7);
+    const uint32_t w_at[2] = {w_row + (((uint32_t)g ^ w_swz) << 4), w_row + (((uint32_t)(g + 4) ^ w_swz) << 4)};
+    const uint32_t x_at[2] = {x_row + (((uint32_t)g ^ x_swz) << 4), x_row + (((uint32_t)(g + 4) ^ x_swz) << 4)};
+    typedef bf16x8_t Half[2][4];                            // half an operand of a step: [32 of K][16 rows]
+    auto read_w = [&](Half &d, auto f_, int half, int stg) {
+        constexpr int f = f_;
+        d[f >> 2][f & 3] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(
+                                                            lds + stg + w_at[f >> 2] + (half * 64 + ((f & 3) >> 1) * 32 + (f & 1) * 4) * 128));
+    };
+    auto read_x = [&](Half &d, auto f_, int half, int stg) {
+        constexpr int f = f_;
+        d[f >> 2][f & 3] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(lds + stg + x_at[f >> 2] + (half * 64 + (f & 3) * 16) * 128));
+    };
+    // One quadrant: 32 instructions in the order that changes one operand at a time; behind them 8 fragment reads (the first
+    // 16) and 4 requests.
+#define SOL_QUAD(FIRST_, W_, X_, HW_, HX_, READ_, RD_, RHALF_, RSTG_, REQ0_, STG_)                                        \
+    static_for<32>([&](auto m_) {                                                                                              \
+        constexpr int m = m_, kg = m >> 4, i = (m >> 2) & 3, j = (i & 1) ? 3 - (m & 3) : (m & 3);                                \
+        acc_mma<4 * (8 * (HW_ * 4 + i) + HX_ * 4 + j), FIRST_ && kg == 0>(W_[kg][i], X_[kg][j]);                                 \
+        if constexpr ((m & 1) == 0 && m < 16) READ_(RD_, std::integral_constant<int, m / 2>{}, RHALF_, RSTG_);                   \
+        if constexpr ((m & 7) == 1) request(std::integral_constant<int, REQ0_ + m / 8>{}, std::integral_constant<int, STG_>{});                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                                     \
+    });
+    // The 16 youngest requests are those of the last two half steps: what the half step after the barrier reads has landed. The
+    // wave's own reads of the halves that will be overwritten are over (lgkmcnt).
+#define SOL_SYNC                                                                                                               \
+    asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory", SOL_ACC_ALL);                                      \
+    __builtin_amdgcn_sched_barrier(0);
+    // One step of the slice in stage CS_, the next in NS_; XL_ holds its left tokens, XR_ is free. Requests: slice + 2 into CS_.
+#define SOL_STEP(FIRST_, XL_, XR_, CS_, NS_)                                                                             \
+    SOL_QUAD(FIRST_, wtop, XL_, 0, 0, read_x, XR_, 1, CS_, 0, CS_)                                                       \
+    SOL_QUAD(FIRST_, wtop, XR_, 0, 1, read_w, wbot, 1, CS_, 4, CS_)                                                      \
+    SOL_SYNC                                                                                                                   \
+    SOL_QUAD(FIRST_, wbot, XR_, 1, 1, read_w, wtop, 0, NS_, 8, CS_)                                                      \
+    SOL_QUAD(FIRST_, wbot, XL_, 1, 0, read_x, XR_, 0, NS_, 12, CS_)                                                      \
+    SOL_SYNC
+    // Two steps; the requests of a tile's last two are the first two slices of the next tile (of this one again after the last
+    // tile: never used), so only a workgroup's first tile starts cold.
+#define SOL_PAIR(FIRST_, KT_)                                                                                                  \
+    {                                                                                                                          \
+        if ((KT_) == KT - 2) tile_src(more ? lin + lin_step : lin, m0_next, n0_next);                                           \
+        else next_slice();                                                                                                     \
+        SOL_STEP(FIRST_, xa, xc, 0, SB)                                                                                         \
+        next_slice();                                                                                                          \
+        SOL_STEP(false, xc, xa, SB, 0)                                                                                          \
     }
-#undef SOL_F_READ
-#undef SOL_MMA
+    Half wtop, wbot, xa, xc;
+    const int KT = K / BK;                                  // even (K is a multiple of 128)
+    tile_src(lin, m0, n0);
+    static_for<16>([&](auto r) { request(r, std::integral_constant<int, 0>{}); });
+    next_slice();
+    static_for<16>([&](auto r) { request(r, std::integral_constant<int, SB>{}); });
+    SOL_SYNC
+    static_for<8>([&](auto f) { read_w(wtop, f, 0, 0); read_x(xa, f, 0, 0); });
+    SOL_SYNC
+    for (;;) {
+        const bool more = lin + lin_step < band_end;
+        SOL_PAIR(true, 0)
+        for (int kt = 2; kt < KT; kt += 2) SOL_PAIR(false, kt)
+        acc_settle();
+        tile_epilogue(epi, m0 + wt * 128, M, n0 + ww * 128, lane);
+        if (!more) break;
+        lin += lin_step; m0 = m0_next; n0 = n0_next;
+    }
+#undef SOL_PAIR
 #undef SOL_STEP
-#undef SOL_MMA_DTL
-#undef SOL_ORDER_RM
-#undef SOL_FENCE
-#undef SOL_DTL_ONE
-#undef SOL_TILE_SRC
-#undef SOL_ACC_ZERO
-
-    // ---- epilogue straight from the accumulators (tiles that lie wholly inside the matrix take the
-    // version without row checks) ----
-    if constexpr (epi_whole_tile<Epi>::value) {             // (the launcher admits whole tiles only)
-        epi.template tile<TM, TN>(acc, m0 + wm * WM, n0 + vcol_w, lane);
-    } else {
-        if (m0 + BM <= M) gemm_epilogue<true, TM, TN>(acc, epi, m0 + row_w, M, n0 + vcol_w, lane & 31);
-        else gemm_epilogue<false, TM, TN>(acc, epi, m0 + row_w, M, n0 + vcol_w, lane & 31);
-    }
+#undef SOL_SYNC
+#undef SOL_QUAD
+    vm_wait<0>();                                           // no LDS-direct load outlives its workgroup
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -862,8 +945,8 @@ k_gemm_mfma(const bf16_t *__restrict__ A, int64_t lda, BMap bmap, int64_t M, int
 // most one workgroup. ST LDS stages filled by LDS-direct loads, so that ST slices are in flight. A step reads the fragments
 // of slice kt + 1 and multiplies slice kt; their order is the compiler's, which keeps only part of the next slice's fragments
 // in registers (61 to 91 for the 32 x 32 and 32 x 64 wave tiles). Bound: a step's time goes with its bytes, 0.19 us per slice
-// of a 64 x 64 tile (16 KB) and 0.39 us of 128 x 128 (32 KB), about 85 GB/s for one CU alone. Every output is the chain of
-// 32x32x16 MFMAs over k that k_gemm_mfma runs, so the tile does not show in the results (bit for bit).
+// of a 64 x 64 tile (16 KB) and 0.39 us of 128 x 128 (32 KB), about 85 GB/s for one CU alone. Every output is a
+// chain of 32x32x16 MFMAs over k, two of which are one 16x16x32 of k_gemm_mfma bit for bit: the tile does not show in the results.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, int ST, class Epi>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
@@ -992,53 +1075,28 @@ int device_cus()
     return cus[dev];
 }
 
-#ifndef SOL_GEMM_PERSIST
-#define SOL_GEMM_PERSIST 1
-#endif
-
-template <int BM, int BN, int WM, int WN, class Epi>
-static bool launch_mfma(const bf16_t *A, int64_t lda, const BMap &bmap, int64_t M, int Nv, int K, const Epi &epi,
-                        hipStream_t st)
+// M tokens [M][K] times the weight rows of bmap, 256 x 256 tiles: one workgroup per CU (CUs / 8 per XCD) walks its share
+template <class Epi>
+static bool launch_mfma(const bf16_t *X, const BMap &bmap, int64_t M, int Nv, int K, const Epi &epi, hipStream_t st)
 {
     if (M <= 0) return true;
-    if (Nv % BN || K % (2 * BK) || K < 2 * BK) return false;
-    constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    constexpr size_t lds = 2 * (size_t)(BM + BN) * 128;
-    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = Nv / BN;
-    const int n_tiles = tiles_m * tiles_n;
-    const int per_xcd = (n_tiles + 7) / 8;
-    if constexpr (SOL_GEMM_PERSIST && Epi::persistent_walk) {
-        // several tiles per CU and no ragged tile: the persistent walk, one workgroup per CU (CUs / 8 per XCD)
-        const int wg_xcd = device_cus() / 8;
-        if (wg_xcd > 0 && per_xcd > wg_xcd && M % BM == 0) {
-            auto kern = k_gemm_mfma<BM, BN, WM, WN, Epi, true>;
-            static bool attr_done = false;
-            if (!attr_done) {
-                if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)lds) != hipSuccess) return false;
-                attr_done = true;
-            }
-            hipLaunchKernelGGL(kern, dim3(wg_xcd * 8), dim3(NT), lds, st, A, lda, bmap, M, Nv, K, tiles_m, tiles_n, epi);
-            return true;
-        }
-    }
-    auto kern = k_gemm_mfma<BM, BN, WM, WN, Epi, false>;
+    if (Nv % 256 || K % (2 * BK) || K < 2 * BK || bmap.ld != K || (bmap.mode == 1 && bmap.half != 32)) return false;
+    constexpr size_t lds = 131072;
+    const int tiles_x = (int)((M + 255) / 256), tiles_w = Nv / 256;
+    const int per_xcd = (tiles_x * tiles_w + 7) / 8, wg_xcd = device_cus() / 8;
+    auto kern = k_gemm_mfma<Epi>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess) return false;
         attr_done = true;
     }
-    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(NT), lds, st, A, lda, bmap, M, Nv, K, tiles_m, tiles_n, epi);
+    hipLaunchKernelGGL(kern, dim3((wg_xcd > 0 && wg_xcd < per_xcd ? wg_xcd : per_xcd) * 8), dim3(256), lds, st, X, bmap, M, K,
+                       Epi::weight_rows ? tiles_w : tiles_x, Epi::weight_rows ? tiles_x : tiles_w, epi);
     return true;
 }
 
-// Tile configuration of the fused layer GEMMs: 256 x 256 workgroup tiles, 4 waves (one per SIMD) with
-// 128 x 128 wave tiles: 256 accumulator registers per lane, the smallest LDS read traffic per MFMA
-// (128 KB per K slice), and latency hidden by the software pipeline rather than by a second wave.
-// The q/k/v epilogue needs a whole head (up to 128 columns) inside one wave tile.
-constexpr int SOL_WN = 128;
-#define SOL_TILE 256, 256, 128, SOL_WN
+constexpr int SOL_WN = 128;                                // vocabulary entries of a partial sum of the head
 
 // How the rows of a product are dealt to tiles. Per round of one workgroup on every CU, a 256 x 256 tile per CU costs
 // 1; a grid of one smaller tile per CU at most costs, relative to that (K = 2048 .. 14336, 80 .. 2048 rows, the
@@ -1118,10 +1176,6 @@ static bool launch_small(int cfg, const bf16_t *A, int64_t lda, const BMap &bmap
     }
 }
 
-static bool rope_tile_ok(int T, int L_max, int crows, int Hkv, int dh)
-{
-    return T >= 128 && (int64_t)(Hkv + 1) * crows * dh * 2 < (1ll << 31) && (int64_t)L_max * dh * 4 < (1ll << 31);
-}
 template <int DHT>
 static bool launch_qkv_rope(const bf16_t *h, const BMap &bm, bf16_t *q, bf16_t *kc, bf16_t *vc, const float2 *rope,
                             const int32_t *pos0, int n_seq, int T, int L_max, int crows, int Hq, int Hkv, int d, int *flags,
@@ -1129,25 +1183,15 @@ static bool launch_qkv_rope(const bf16_t *h, const BMap &bm, bf16_t *q, bf16_t *
 {
     const int64_t M = (int64_t)n_seq * T;
     const int N = (Hq + 2 * Hkv) * DHT;
+    if (M >= (1ll << 31)) return false;
     const GemmPlan plan = plan_gemm(M, N);
-    // whole tiles of at most two sequences each: positions by arithmetic (the epilogue's 32-bit byte offsets span two
-    // cache slabs, 128 rows of q, and the cos / sin table); it runs unless k_row_positions has flagged a sequence, in
-    // which case the general kernel behind it does
-    const bool tiles = plan.big > 0 && plan.big % 256 == 0 && rope_tile_ok(T, L_max, crows, Hkv, DHT);
-    const bool sure = pos0 == nullptr && T <= L_max;          // every sequence starts at 0 and fits: nothing to flag
-    int *gate = sure ? nullptr : flags;
-    if (!(tiles && sure && plan.big == M))                    // the rows' (sequence, position) table, and the flags
-        hipLaunchKernelGGL(k_row_positions, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, pos0, M, T, L_max, row_sp, flags);
-    if (tiles) {
-        EpiQkvRopeTile<DHT> te{q, kc, vc, rope, pos0, T, crows, Hq, Hkv, n_seq, gate};
-        if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, te, st)) return false;
-    }
-    if (plan.big > 0 && !(tiles && sure)) {
-        EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, tiles ? flags : nullptr};
-        if (!launch_mfma<SOL_TILE>(h, d, bm, plan.big, N, d, epi, st)) return false;
-    }
+    if (plan.big > 0 &&
+        !launch_mfma(h, bm, plan.big, N, d, EpiQkvRope8<DHT>{q, kc, vc, rope, pos0, T, L_max, crows, Hq, Hkv, flags}, st))
+        return false;
     if (plan.big == M) return true;
-    EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv, nullptr};
+    // the small tiles' table of the rows' (sequence, position), and the flags
+    hipLaunchKernelGGL(k_row_positions, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, pos0, M, T, L_max, row_sp, flags);
+    EpiQkvRope<DHT> epi{q, kc, vc, rope, row_sp, crows, Hq, Hkv};
     return launch_small<DHT>(plan.small, h, d, bm, plan.big, M, N, d, epi, st);
 }
 
@@ -1176,7 +1220,7 @@ static BMap plain_map(const void *w, int N, int K)
     return bm;
 }
 
-// A product over plain weight rows: `big` of the plan with epilogue eb where that part is whole tiles, else e.
+// A product over plain weight rows: `big` of the plan with epilogue eb, the others with e.
 template <class EpiBig, class Epi>
 static bool launch_planned(const void *a, const void *w, int64_t M, int N, int K, const EpiBig &eb, const Epi &e, hipStream_t st)
 {
@@ -1184,18 +1228,14 @@ static bool launch_planned(const void *a, const void *w, int64_t M, int N, int K
     if (N % 256 || K % (2 * BK) || K < 2 * BK) return false;
     const BMap bm = plain_map(w, N, K);
     const GemmPlan plan = plan_gemm(M, N);
-    if (plan.big > 0 && !(plan.big % 256 == 0 ? launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, plan.big, N, K, eb, st)
-                                              : launch_mfma<SOL_TILE>((const bf16_t *)a, K, bm, plan.big, N, K, e, st)))
-        return false;
+    if (plan.big > 0 && !launch_mfma((const bf16_t *)a, bm, plan.big, N, K, eb, st)) return false;
     return plan.big == M || launch_small<32>(plan.small, (const bf16_t *)a, K, bm, plan.big, M, N, K, e, st);
 }
 
 bool launch_gemm_resid_f32(const void *a, const void *w, const void *resid, float *out, int64_t M, int N, int K,
                            hipStream_t st)
 {
-    const EpiResidF32Tile te{(const bf16_t *)resid, out, N};
-    const EpiResidF32 epi{(const bf16_t *)resid, out, N};
-    return launch_planned(a, w, M, N, K, te, epi, st);
+    return launch_planned(a, w, M, N, K, EpiResidF32x8{(const bf16_t *)resid, out, N}, EpiResidF32{(const bf16_t *)resid, out, N}, st);
 }
 
 bool launch_gemm_gateup_silu(const void *h, const void *wg, const void *wu, void *a, int64_t M, int dff, int d,
@@ -1203,30 +1243,25 @@ bool launch_gemm_gateup_silu(const void *h, const void *wg, const void *wu, void
 {
     const int N = 2 * dff;
     if (M <= 0) return true;
-    if (dff % (SOL_WN / 2) || N % 256 || d % (2 * BK) || d < 2 * BK) return false;
+    if (dff % 64 || N % 256 || d % (2 * BK) || d < 2 * BK) return false;
     BMap bm{};
     bm.base[0] = (const bf16_t *)wg; bm.base[1] = (const bf16_t *)wu; bm.mode = 1; bm.ld = d;
-    const EpiSiluMul epi{(bf16_t *)a, dff};
+    bm.half = 32;                                             // gate / up interleaved in pieces of 32 columns
     const GemmPlan plan = plan_gemm(M, N);
-    bm.half = SOL_WN / 2;                                     // gate / up interleaved in halves of a wave tile's columns
-    if (plan.big > 0 && !launch_mfma<SOL_TILE>((const bf16_t *)h, d, bm, plan.big, N, d, epi, st)) return false;
-    bm.half = 32;
-    return plan.big == M || launch_small<64>(plan.small, (const bf16_t *)h, d, bm, plan.big, M, N, d, epi, st);
+    if (plan.big > 0 && !launch_mfma((const bf16_t *)h, bm, plan.big, N, d, EpiSiluMul8{(bf16_t *)a, dff}, st)) return false;
+    return plan.big == M || launch_small<64>(plan.small, (const bf16_t *)h, d, bm, plan.big, M, N, d, EpiSiluMul{(bf16_t *)a, dff}, st);
 }
 
 bool launch_gemm_resid_out(const void *a, const void *w, const float *x2, void *out, int64_t M, int N, int K,
                            hipStream_t st)
 {
-    const EpiResidOut epi{x2, (bf16_t *)out, N};
-    return launch_planned(a, w, M, N, K, epi, epi, st);
+    return launch_planned(a, w, M, N, K, EpiResidOut8{x2, (bf16_t *)out, N}, EpiResidOut{x2, (bf16_t *)out, N}, st);
 }
 
 bool launch_gemm_f32(const void *a, const void *w, float *C, int64_t ldc, int64_t M, int N, int K, hipStream_t st)
 {
-    const EpiStoreF32 epi{C, ldc};
-    return launch_planned(a, w, M, N, K, epi, epi, st);
+    return launch_planned(a, w, M, N, K, EpiStoreF32x8{C, ldc}, EpiStoreF32{C, ldc}, st);
 }
-
 
 static int64_t nll_pad_rows(int64_t M) { return (M + 255) / 256 * 256; }
 int64_t gemm_nll_hf_rows(int64_t M) { return nll_pad_rows(M); }
@@ -1257,7 +1292,7 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
     const bf16_t *const head = (const bf16_t *)lm_head;
     if (!(Mp == 32 ? launch_tile<256, 32, 128, 32, 2>(head, K, bt, 0, V, (int)Mp, K, epc, st)
           : Mp == 64 ? launch_tile<256, 64, 128, 32, 2>(head, K, bt, 0, V, (int)Mp, K, epc, st)
-                     : launch_mfma<SOL_TILE>(head, K, bt, V, (int)Mp, K, epc, st)))
+                     : launch_mfma((const bf16_t *)hf, plain_map(lm_head, V, K), Mp, V, K, EpiNllCols8{part, Mp}, st)))
         return false;
     hipLaunchKernelGGL(k_target_logit, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const bf16_t *)hf,
                        (const bf16_t *)lm_head, row_tgt, M, K, tgt_logit);
