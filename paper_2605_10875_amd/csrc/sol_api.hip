@@ -568,7 +568,7 @@ static int layer_impl(sol_ctx *ctx, const sol_layer_weights *lw, const void *x_i
                 return fail(ctx, SOL_ERR_UNSUPPORTED, "skinny GEMM: unsupported shape");
         } else {
             fused_qkv = mfma && launch_gemm_qkv_rope(w.h, lw->wq, lw->wk, lw->wv, w.qb, kcw, vcw, ctx->d_rope, pos0, n_seq,
-                                                     T, L_max, Hq, Hkv, dh, d, ctx->d_flags, w.big32, st, crows);
+                                                     T, L_max, Hq, Hkv, dh, d, ctx->d_flags, st, crows);
             if (dt == SOL_F32)
                 fused_qkv = launch_gemm_f32_qkv((const float *)w.h, (const float *)lw->wq, (const float *)lw->wk, (const float *)lw->wv,
                                                 (float *)w.qb, (float *)kcw, (float *)vcw, ctx->d_rope, pos0, n_seq, T, L_max, Hq, Hkv,
