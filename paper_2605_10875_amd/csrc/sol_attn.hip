@@ -1382,6 +1382,92 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
     }   // pass
 }
 
+// The search for a decode row's threshold: wave_search_rows for one row whose columns several waves hold, which count between
+// barriers and all run this on the same numbers. Done when exactly b of the n keys are >= thr, or, where ties leave no such
+// pivot, when the bracket has closed on the b-th largest (exact = false). Invariant: count(key >= lo) >= b, count(key >= hi + 1) < b.
+// m1, m2: mean and mean square of a sample of the row. On normal rows 4.5 rounds where regula falsi on the counts from the row's extremes
+// takes 6.4; but the last of them close in on one key, and the slowest of a launch's 32 rows takes 11. So once the bracket holds
+// FEW keys they are gathered in the LDS and ranked there: 2.6 rounds, 4 for the slowest of 32. (Ranked by every wave for itself
+// the 64 comparisons cost as much as the rounds they save: 16 waves share four SIMDs.) k_dec_select at 4096 keys, one sequence:
+// 12.8 -> 8.6 us; a step of 64 sequences of 8192 keys, 1B shape: 4585 -> 4380 us, of 8 of 2048 1873 -> 1757, of one of 4096 1275 -> 1205.
+struct PivotSearch {
+    static constexpr int FEW = 64;
+    uint32_t lo, hi, thr = 0u;
+    bool done = false, exact = true;
+    float flo, fhi, glo, ghi, w_up = 1.0f, w_dn = 1.0f, fp, slope, t_b, nh, bf;
+    int b, clo, chi = 0;                                     // count(key >= lo), count(key > hi)
+    __device__ __forceinline__ PivotSearch(int n, int b_, uint32_t lo_, uint32_t hi_, float m1, float m2)
+        : lo(lo_), hi(hi_), b(b_), clo(n)
+    {
+        const float nf = (float)n;
+        bf = (float)b;
+        nh = nf + 0.5f;
+        t_b = __builtin_amdgcn_logf(bf * __builtin_amdgcn_rcpf((nf - bf) + 1.0f));
+        flo = score_unkey(lo);
+        fhi = score_unkey(hi);
+        const float t_n = __builtin_amdgcn_logf(nh * 2.0f);
+        glo = t_n - t_b;
+        ghi = -t_n - t_b;
+        const float sd = __builtin_amdgcn_sqrtf(__builtin_fmaxf(__builtin_fmaf(-m1, m1, m2), 0.f));
+        const float p = (bf - 0.5f) * __builtin_amdgcn_rcpf(nf);     // upper tail at the threshold
+        const float t = __builtin_amdgcn_sqrtf(-1.3862943611f * __builtin_amdgcn_logf(__builtin_fminf(p, 1.0f - p)));
+        const float num = __builtin_fmaf(__builtin_fmaf(0.010328f, t, 0.802853f), t, 2.515517f);
+        const float den = __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(0.001308f, t, 0.189269f), t, 1.432788f), t, 1.0f);
+        const float z = t - num * __builtin_amdgcn_rcpf(den);
+        fp = __builtin_fmaf(sd, p < 0.5f ? z : -z, m1);
+        slope = sd * 2.5066283f * __builtin_amdgcn_exp2f(0.72134752f * z * z) * __builtin_amdgcn_rcpf(nf);
+    }
+    __device__ __forceinline__ uint32_t pivot(int it) const      // of (lo, hi]
+    {
+        uint32_t mid = score_key(fp);
+        mid = __builtin_elementwise_min(__builtin_elementwise_max(mid, lo + 1u), hi);
+        if (it >= 12) mid = lo + ((hi - lo + 1u) >> 1);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)mid);
+    }
+    __device__ __forceinline__ void count(int it, uint32_t mid, int cnt)
+    {
+        const float cf = (float)cnt, fmid = score_unkey(mid);
+        const float g = __builtin_amdgcn_logf((cf + 0.5f) * __builtin_amdgcn_rcpf(nh - cf)) - t_b;
+        if (cnt == b) { thr = mid; done = true; }
+        else if (cnt > b) {
+            lo = mid; clo = cnt; flo = fmid; glo = g;
+            ghi *= w_up;
+            w_up = 0.5f; w_dn = 1.0f;
+        } else {
+            hi = mid - 1u; chi = cnt; fhi = fmid; ghi = g;
+            glo *= w_dn;
+            w_up = 1.0f; w_dn = 0.5f;
+        }
+        fp = it == 0 ? __builtin_fmaf(cf - bf, slope, fmid) : __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
+    }
+    __device__ __forceinline__ bool few() const { return !done && clo - chi <= FEW; }
+    __device__ __forceinline__ bool open() const { return !done && lo < hi && clo - chi > FEW; }
+};
+// The keys of a bracket that holds few of them, in any order: n_few is 0 before, a barrier follows.
+template <int SLOTS>
+__device__ __forceinline__ void gather_few(const PivotSearch &find, const uint32_t (&key)[SLOTS], uint32_t *cand, int *n_few)
+{
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i)
+        if (key[i] - find.lo <= find.hi - find.lo) {
+            const int at = atomicAdd(n_few, 1);
+            if (at < PivotSearch::FEW) cand[at] = key[i];
+        }
+}
+// The (b - count above the bracket)-th largest of them, and whether it is the last of its value; one wave, cand 0 behind the keys.
+__device__ __forceinline__ uint2 rank_few(const PivotSearch &find, const uint32_t *cand, int lane)
+{
+    const int m = find.clo - find.chi, k = find.b - find.chi;
+    const uint32_t own = cand[lane];
+    int gt = 0;
+    for (int i = 0; i < m; i += 8) {
+        const uint4 c = *reinterpret_cast<const uint4 *>(cand + i), d = *reinterpret_cast<const uint4 *>(cand + i + 4);
+        gt += (c.x > own) + (c.y > own) + (c.z > own) + (c.w > own) + (d.x > own) + (d.y > own) + (d.z > own) + (d.w > own);
+    }
+    const uint32_t thr = wave_min_u32(lane < m && gt < k ? own : 0xFFFFFFFFu);
+    return make_uint2(thr, __popcll(__ballot(lane < m && own >= thr)) == k);
+}
+
 // =================================================================================================
 // Decode attention (one query per sequence, bf16, HBM-bound): one workgroup of 16 waves per
 // (sequence, KV head) serves the HPB = 4 query heads that share that KV head, so K is streamed from
@@ -1389,7 +1475,7 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
 //   1. scores on MFMA: A = a tile of 16 keys (each lane loads 16 contiguous bytes of a K row straight
 //      from global memory, four tiles in flight per wave), B = the query heads as columns; fp32 scores
 //      of all four heads go to LDS.
-//   2. selection: the 4 waves of a head hold a quarter of the row each in registers and bisect the
+//   2. selection: the 4 waves of a head hold a quarter of the row each in registers and search the
 //      key range together, exchanging their ballot counts through LDS once per step.
 //   3. softmax numerators back to LDS, 4. V rows gathered where any head kept the key.
 // =================================================================================================
@@ -1501,6 +1587,10 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
     extern __shared__ __align__(16) float sc[];               // [DEC_HPB][LPAD]; later partial O [DEC_WAVES][HPB][DH]
     __shared__ int s_cnt[2][DEC_WAVES];
     __shared__ uint32_t s_min[DEC_WAVES], s_max[DEC_WAVES];
+    __shared__ float s_s1[DEC_WAVES], s_s2[DEC_WAVES];
+    __shared__ __align__(16) uint32_t s_cand[DEC_HPB][PivotSearch::FEW];
+    __shared__ int s_few[DEC_HPB];
+    __shared__ uint2 s_rank[DEC_HPB];
     __shared__ int s_done[2][DEC_HPB];
     __shared__ int s_gt[DEC_WAVES];
     __shared__ float s_den[DEC_WAVES];
@@ -1519,6 +1609,8 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
         return;
     }
     const int n = p0 + 1;                                      // keys 0..p0 (the new token's key included)
+    const RowAct act = ra[s];
+    const int b = __builtin_amdgcn_readfirstlane(budget_ceil(act.keep_num, act.keep_den, n));   // 64-bit divide runs on the VALU
     const int h0 = kvh * DEC_HPB;
     const bf16_t *kbase = kc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
     const bf16_t *vbase = vc + ((int64_t)s * Hkv + kvh) * (int64_t)L_max * DH;
@@ -1579,6 +1671,7 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
     float *row = sc + head * LPAD + base;
     uint32_t key[SLOTS];                                        // the score itself is recovered from its key
     uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+    float s1 = 0.f, s2 = 0.f;                                  // over every fourth column
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         if (256 * j < n_loc) {
@@ -1590,7 +1683,8 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
                 key[4 * j + e] = kv;
                 kmax = kv > kmax ? kv : kmax;
                 kmin = (valid && kv < kmin) ? kv : kmin;
-            }
+                    if (e == 0 && valid) { s1 += v[0]; s2 = __builtin_fmaf(v[0], v[0], s2); }
+                }
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) key[4 * j + e] = 0u;
@@ -1598,65 +1692,67 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
     }
     kmax = wave_max_u32(kmax);
     kmin = wave_min_u32(kmin);
-    if (lane == 0) { s_max[w] = kmax; s_min[w] = kmin; }
+    if (b < n) {
+        s1 = wave_sum_dpp(s1);
+        s2 = wave_sum_dpp(s2);
+    }
+    if (tid < DEC_HPB) s_few[tid] = 0;
+    if (tid < DEC_HPB * PivotSearch::FEW) s_cand[tid / PivotSearch::FEW][tid % PivotSearch::FEW] = 0u;
+    if (lane == 0) { s_max[w] = kmax; s_min[w] = kmin; s_s1[w] = s1; s_s2[w] = s2; }
     __syncthreads();
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    s1 = s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < DEC_GW; ++i) {
         const uint32_t a = s_min[head * DEC_GW + i], c = s_max[head * DEC_GW + i];
         lo = a < lo ? a : lo;
         hi = c > hi ? c : hi;
+        s1 += s_s1[head * DEC_GW + i];
+        s2 += s_s2[head * DEC_GW + i];
     }
     // values read back from LDS are wave-uniform: move them to scalar registers so that the search
     // below is scalar control flow
     lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
     hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
     const float mx = score_unkey(hi);                          // the head's best score, always kept
-    const RowAct act = ra[s];
-    const int b = __builtin_amdgcn_readfirstlane(budget_ceil(act.keep_num, act.keep_den, n));   // 64-bit divide runs on the VALU
     uint32_t thr = 1u;                                         // budget keeps all: every valid key passes
-    bool done = b >= n, exact = true;
-    // invariant while searching: count(key >= lo) >= b, count(key >= hi + 1) < b. Pivots by regula falsi on
-    // g(x) = count(key >= x) - b + 1/2 in the score domain with the Illinois correction (about 7 counting
-    // rounds, each a workgroup barrier, instead of about 15 for bisection of the key); after 12 rounds, or when
-    // the guess leaves (lo, hi], the midpoint of the key range takes over, which bounds the search.
-    float flo = score_unkey(lo), fhi = score_unkey(hi), glo = (float)(n - b) + 0.5f, ghi = 0.5f - (float)b;
-    int side = 0;
-    for (int it = 0; it < 48; ++it) {
-        const int par = it & 1;
-        uint32_t mid = 0u;
-        if (!done) {
-            const float fp = __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
-            mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fp));
-            if (it >= 12 || !(mid > lo && mid <= hi)) mid = lo + ((hi - lo + 1u) >> 1);
-            const int c = lo < hi ? wave_count_ge<SLOTS>(key, n_loc, mid) : 0;
-            if (lane == 0) s_cnt[par][w] = c;
-        }
-        if (wg == 0 && lane == 0) s_done[par][head] = done || lo >= hi;
-        __syncthreads();
-        if (!done) {
-            if (lo >= hi) { thr = lo; exact = false; done = true; }
-            else {
+    bool exact = true;
+    if (b < n) {                                               // the same for the four heads
+        const float inv = 1.0f / (float)((n + 3) >> 2);
+        PivotSearch find(n, b, lo, hi, s1 * inv, s2 * inv);
+        for (int it = 0; it < 48; ++it) {
+            const int par = it & 1;
+            uint32_t mid = 0u;
+            const bool go = find.open();
+            if (go) {
+                mid = find.pivot(it);
+                const int c = wave_count_ge<SLOTS>(key, n_loc, mid);
+                if (lane == 0) s_cnt[par][w] = c;
+            }
+            if (wg == 0 && lane == 0) s_done[par][head] = !go;
+            __syncthreads();
+            if (go) {
                 int cnt = 0;
 #pragma unroll
                 for (int i = 0; i < DEC_GW; ++i) cnt += s_cnt[par][head * DEC_GW + i];
-                cnt = __builtin_amdgcn_readfirstlane(cnt);
-                const float g = (float)(cnt - b) + 0.5f;
-                if (cnt == b) { thr = mid; done = true; }
-                else if (cnt > b) {
-                    lo = mid; flo = score_unkey(mid); glo = g;
-                    if (side > 0) ghi *= 0.5f;
-                    side = 1;
-                } else {
-                    hi = mid - 1u; fhi = score_unkey(hi); ghi = g;
-                    if (side < 0) glo *= 0.5f;
-                    side = -1;
-                }
+                find.count(it, mid, __builtin_amdgcn_readfirstlane(cnt));
             }
+            const bool all_done =
+                __builtin_amdgcn_readfirstlane(s_done[par][0] & s_done[par][1] & s_done[par][2] & s_done[par][3]) != 0;
+            if (all_done) break;                                   // uniform: every wave reads the same flags
         }
-        const bool all_done =
-            __builtin_amdgcn_readfirstlane(s_done[par][0] & s_done[par][1] & s_done[par][2] & s_done[par][3]) != 0;
-        if (all_done) break;                                   // uniform: every wave reads the same flags
+        const bool few = find.few();
+        if (few) gather_few<SLOTS>(find, key, s_cand[head], &s_few[head]);
+        __syncthreads();
+        if (few && wg == head) {                                   // (these four waves run on different SIMDs)
+            const uint2 r = rank_few(find, s_cand[head], lane);
+            if (lane == 0) s_rank[head] = r;
+        }
+        __syncthreads();
+        if (few) { find.thr = s_rank[head].x; find.exact = s_rank[head].y != 0; }
+        else if (!find.done) { find.thr = find.lo; find.exact = false; }      // the bracket has closed on many equal keys
+        thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)find.thr);
+        exact = __builtin_amdgcn_readfirstlane((int)find.exact) != 0;
     }
     // Ties at the threshold go to the lower columns. Rare for fp32 scores, so the fix-up is a plain
     // loop by the first wave of the head over the row in LDS: tied keys beyond the quota get -inf.
@@ -1743,7 +1839,7 @@ static bool launch_attn_decode_t(const void *q, const void *kc, const void *vc, 
 // =================================================================================================
 // The same attention for few sequences: with B * Hkv items for 256 CUs the one-workgroup-per-item kernel leaves most of
 // the chip idle and takes an item's whole latency (39 us at 4096 keys for any B up to 32). Here an item's keys are
-// spread over workgroups, in three launches (4.0 + 4.7 + 6.9 us there) with the scores between them in global memory (16
+// spread over workgroups, in three launches (4.4 + 8.6 + 7.7 us there, 4.3 + 4.3 + 6.8 where the budget keeps all) with the scores between them in global memory (16
 // bytes per key and KV head against the key's 128 or 256 bytes of K; they stay in the caches). Every sum is made in the
 // order of that kernel, so that a sequence's result does not depend on how many others there are:
 //   k_dec_scores  : scores of DSP_KEYS keys for the 4 heads of a KV group (the MFMA sequence of k_attn_decode)
@@ -1810,6 +1906,10 @@ k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const R
     constexpr int SLICE = SLOTS * 64, NJ = SLOTS / 4;
     __shared__ int s_cnt[2][DSEL_WAVES], s_gt[DSEL_WAVES], s_tie[DSEL_WAVES], s_last;
     __shared__ uint32_t s_min[DSEL_WAVES], s_max[DSEL_WAVES];
+    __shared__ float s_s1[DSEL_WAVES], s_s2[DSEL_WAVES];
+    __shared__ __align__(16) uint32_t s_cand[PivotSearch::FEW];
+    __shared__ int s_few;
+    __shared__ uint2 s_rank;
     __shared__ float s_den[DEC_GW];
     __shared__ __align__(16) float s_p[DSEL_WAVES * SLICE];
     static_assert(DEC_GW * NJU * 256 <= DSEL_WAVES * SLICE, "");
@@ -1821,9 +1921,12 @@ k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const R
     const int n = p0 + 1, base = w * SLICE;
     int n_loc = n - base;
     n_loc = n_loc < 0 ? 0 : (n_loc > SLICE ? SLICE : n_loc); // columns held by this wave
+    const RowAct act = ra[s];
+    const int b = __builtin_amdgcn_readfirstlane(budget_ceil(act.keep_num, act.keep_den, n));
     const float *row = scores + ((int64_t)s * Hq + head) * lpad + base;
     uint32_t key[SLOTS];
     uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+    float s1 = 0.f, s2 = 0.f;                                // over every fourth column
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int c = 256 * j + 4 * lane;
@@ -1836,51 +1939,59 @@ k_dec_select(const float *__restrict__ scores, DecSel *__restrict__ sel, const R
             key[4 * j + e] = kv;
             kmax = kv > kmax ? kv : kmax;
             kmin = (valid && kv < kmin) ? kv : kmin;
+            if (e == 0 && valid) { s1 += v[0]; s2 = __builtin_fmaf(v[0], v[0], s2); }
         }
     }
     kmax = wave_max_u32(kmax);
     kmin = wave_min_u32(kmin);
-    if (lane == 0) { s_max[w] = kmax; s_min[w] = kmin; }
+    if (b < n) {
+        s1 = wave_sum_dpp(s1);
+        s2 = wave_sum_dpp(s2);
+    }
+    if (threadIdx.x == 0) s_few = 0;
+    if (threadIdx.x < PivotSearch::FEW) s_cand[threadIdx.x] = 0u;
+    if (lane == 0) { s_max[w] = kmax; s_min[w] = kmin; s_s1[w] = s1; s_s2[w] = s2; }
     __syncthreads();
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    s1 = s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < DSEL_WAVES; ++i) {
         lo = s_min[i] < lo ? s_min[i] : lo;
         hi = s_max[i] > hi ? s_max[i] : hi;
+        s1 += s_s1[i];
+        s2 += s_s2[i];
     }
     lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
     hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
     const float mx = score_unkey(hi);                        // the head's best score, always kept
-    const RowAct act = ra[s];
-    const int b = __builtin_amdgcn_readfirstlane(budget_ceil(act.keep_num, act.keep_den, n));
-    // the search of k_attn_decode: count(key >= lo) >= b, count(key >= hi + 1) < b; every wave runs the same steps
     uint32_t thr = 1u;                                       // budget keeps all: every valid key passes
-    bool done = b >= n, exact = true;
-    float flo = score_unkey(lo), fhi = score_unkey(hi), glo = (float)(n - b) + 0.5f, ghi = 0.5f - (float)b;
-    int side = 0;
-    for (int it = 0; it < 48 && !done; ++it) {
-        if (lo >= hi) { thr = lo; exact = false; break; }
-        const float fp = __builtin_fmaf(fhi - flo, glo * __builtin_amdgcn_rcpf(glo - ghi), flo);
-        uint32_t mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)score_key(fp));
-        if (it >= 12 || !(mid > lo && mid <= hi)) mid = lo + ((hi - lo + 1u) >> 1);
-        const int c = wave_count_ge<SLOTS>(key, n_loc, mid);
-        if (lane == 0) s_cnt[it & 1][w] = c;
-        __syncthreads();
-        int cnt = 0;
+    bool exact = true;
+    if (b < n) {                                             // every wave runs the same steps
+        const float inv = 1.0f / (float)((n + 3) >> 2);
+        PivotSearch find(n, b, lo, hi, s1 * inv, s2 * inv);
+        for (int it = 0; it < 48 && find.open(); ++it) {
+            const uint32_t mid = find.pivot(it);
+            const int c = wave_count_ge<SLOTS>(key, n_loc, mid);
+            if (lane == 0) s_cnt[it & 1][w] = c;
+            __syncthreads();
+            int cnt = 0;
 #pragma unroll
-        for (int i = 0; i < DSEL_WAVES; ++i) cnt += s_cnt[it & 1][i];
-        cnt = __builtin_amdgcn_readfirstlane(cnt);
-        const float g = (float)(cnt - b) + 0.5f;
-        if (cnt == b) { thr = mid; done = true; }
-        else if (cnt > b) {
-            lo = mid; flo = score_unkey(mid); glo = g;
-            if (side > 0) ghi *= 0.5f;
-            side = 1;
-        } else {
-            hi = mid - 1u; fhi = score_unkey(hi); ghi = g;
-            if (side < 0) glo *= 0.5f;
-            side = -1;
+            for (int i = 0; i < DSEL_WAVES; ++i) cnt += s_cnt[it & 1][i];
+            find.count(it, mid, __builtin_amdgcn_readfirstlane(cnt));
         }
+        if (find.few()) {
+            gather_few<SLOTS>(find, key, s_cand, &s_few);
+            __syncthreads();
+            if (w == 0) {
+                const uint2 r = rank_few(find, s_cand, lane);
+                if (lane == 0) s_rank = r;
+            }
+            __syncthreads();
+            find.thr = s_rank.x;
+            find.exact = s_rank.y != 0;
+        } else if (!find.done) { find.thr = find.lo; find.exact = false; }     // the bracket has closed on many equal keys
+        thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)find.thr);
+        exact = __builtin_amdgcn_readfirstlane((int)find.exact) != 0;
     }
     // ties at the threshold go to the lower columns: the last one kept
     int jstar = 0x7FFFFFFF;

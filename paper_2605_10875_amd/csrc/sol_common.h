@@ -325,6 +325,7 @@ template <int SLOTS>
 __device__ __forceinline__ int wave_count_ge(const uint32_t (&key)[SLOTS], int n, uint32_t pivot)
 {
     pivot = (uint32_t)__builtin_amdgcn_readfirstlane((int)pivot);
+    asm volatile("s_nop 1" : "+s"(pivot));               // mask_ge_u32 reads it two wait states after a vector write at the earliest
     constexpr int NJ = SLOTS / 4;
     const int ng = (n + 255) >> 8;
     if constexpr (NJ <= 4) {
