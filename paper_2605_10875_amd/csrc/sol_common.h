@@ -2,6 +2,8 @@
 // reductions, exact k-th-largest selection (radix select on order-preserving keys) and the
 // per-token fake-quantiser.
 #pragma once
+#include <type_traits>
+#include <utility>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,6 +19,13 @@ struct RowAct {
 };
 
 enum { FLAG_BAD_ACTION = 1, FLAG_CACHE_OVERFLOW = 2, FLAG_BAD_TOKEN = 4 };
+
+// f(0), .., f(N - 1), the arguments integral constants
+template <int... I, class F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_(std::make_integer_sequence<int, N>{}, f); }
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 

@@ -66,10 +66,9 @@ k_gemm_generic(const TA *__restrict__ A, int64_t lda, const TW *__restrict__ W, 
 // at twice the vector pipes' rate and without their LDS reads per product. Bound: the fp32 matrix rate (256 flops per
 // clock and CU) for large products, 125 TFLOP/s reached of 157; the chain over k for small ones: 64 clocks per 2 k in a
 // 32x32 tile, 32 clocks per 4 k in a 16x16 tile.
-// Times with k_gemm_generic -> here: 1018 x 16384 x 2048 2470 -> 549 us, 1018 x 2048 x 8192 1310 -> 326, 512 x 256 x 256
+// Times with k_gemm_generic -> here: 1018 x 16384 x 2048 2470 -> 549 us (551 now with SiLU * up), 1018 x 2048 x 8192 1310 -> 326 (296 now with the residual), 512 x 256 x 256
 // 30 -> 4.8, 512 x 256 x 1024 108 -> 12.
 // ------------------------------------------------------------------------------------------------
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 
 enum { FMAP_STACKED, FMAP_PAIRS, FMAP_ROPE };
@@ -186,17 +185,22 @@ __device__ __forceinline__ void lds_load16(const float *src, uint32_t lds_addr)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr) : "memory", "m0");
 }
 
-// ST stages of 32 k. Two stages (a 128 x 128 tile): two workgroups share a CU and hide each other's barriers and LDS
-// reads, 549 us for the first shape above against 606 with three stages and one workgroup. READ_AHEAD (a lone 64 x 64
-// tile per CU): the fragments of the next four k are read before the current ones are multiplied, 54 against 61 us for
-// 100 x 2048 x 2048 (and 616 against 549 us in the 128 x 128 tile, where the second workgroup does it better).
-template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD, class Epi>
+// ST stages of U slices of 32 k, one barrier per stage. The waves' fragments are read 4 bytes per lane (16 rows' chunks fill the 64
+// banks), CG times 4 k ahead of the matrix instructions that take them, and requests go out behind those; the order is fixed, since left
+// to the compiler the reads sink to their uses. (The kernel before this one read 16 bytes per lane for 32x32x2 instructions and
+// picked each lane half's k by two selects per instruction, behind the reads' full latency.) Bound: the fp32 matrix rate (155
+// TFLOP/s measured, no less on normal data than on zeros); 1018 rows of the 1B shape, us: gate / up 631 -> 551 (124 TFLOP/s), q/k/v
+// 135 -> 124, down 350 -> 296, o 92 -> 78. Two stages of 128 x 128 tiles: two workgroups share a CU and hide each other's barriers.
+// 64 x 64 tiles: with at most two of them per CU, two slices per barrier (down 321 -> 296); where a third finds room beside
+// them, three stages of one (q/k/v, three per CU: 124 against 157).
+template <int BM, int BN, int WM, int WN, int ST, int U, int CG, class Epi>
 __global__ void __launch_bounds__(256, 2)
 k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int64_t M, int N, int K, int tiles_m, int tiles_n)
 {
     static_assert((BM / WM) * (BN / WN) == 4, "four waves");
-    constexpr int NWN = BN / WN, TM = WM / 32, TN = WN / 32, AP = BM / 32, BP = BN / 32;
-    constexpr uint32_t SB = (BM + BN) * 128;                 // a stage: rows of 32 floats, 16-byte chunks XOR-swizzled
+    constexpr int NWN = BN / WN, TM = WM / 16, TN = WN / 16, AP = BM / 32, BP = BN / 32;
+    constexpr int PP = AP + BP, NG = 8 * U / CG, NM = CG * TM * TN, NR = CG * (TM + TN);   // groups of CG * 4 k, their matrix instructions and reads
+    constexpr uint32_t LB = (BM + BN) * 128, SB = U * LB;     // a slice: rows of 32 floats, 16-byte chunks XOR-swizzled; a stage: U slices
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -221,72 +225,62 @@ k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int6
         const int v = n0 + p * 32 + rip;
         bp[p] = map.row(v < N ? v : N - 1) + sw;
     }
-    const int KT = K / 32;
-    auto request = [&](int kt, uint32_t stage) {
-        const int koff = (kt < KT ? kt : KT - 1) * 32;
-#pragma unroll
-        for (int p = 0; p < AP; ++p) lds_load16(ap[p] + koff, stage + (uint32_t)(p * 4096 + wave * 1024));
-#pragma unroll
-        for (int p = 0; p < BP; ++p) lds_load16(bp[p] + koff, stage + (uint32_t)((AP + p) * 4096 + wave * 1024));
+    const int KT = K / (32 * U);
+    auto request = [&](auto p_, int koff, uint32_t stage) {
+        constexpr int u = p_ / PP, p = p_ % PP;
+        const uint32_t to = stage + u * LB + (uint32_t)(p * 4096 + wave * 1024);
+        if constexpr (p < AP) lds_load16(ap[p] + koff + 32 * u, to);
+        else lds_load16(bp[p - AP] + koff + 32 * u, to);
     };
-    f32x16_t acc[TM][TN];
+    f32x4v_t acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+    const int r16 = lane & 15, g = lane >> 4, fsw = (r16 >> 1) & 7;       // this lane supplies k = 4c + g of row r16 of each 16
+    const int a_frag = (wm * WM + r16) * 128 + g * 4, b_frag = (BM + wn * WN + r16) * 128 + g * 4;
+    struct Frags { float a[CG][TM], b[CG][TN]; } f[2];
+    auto read = [&](auto r_, Frags &x, int grp, uint32_t stage) {
+        constexpr int R = r_, c = R / (TM + TN), i = R % (TM + TN);
+        const unsigned char *const st = lds + stage + ((grp * CG + c) >> 3) * LB;
+        const int coff = (((grp * CG + c) & 7) ^ fsw) << 4;
+        if constexpr (i < TM) x.a[c][i] = *reinterpret_cast<const float *>(st + a_frag + i * 2048 + coff);
+        else x.b[c][i - TM] = *reinterpret_cast<const float *>(st + b_frag + (i - TM) * 2048 + coff);
+    };
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    const int frow = lane & 31, fsw = (frow >> 1) & 7;
-    const bool hi = lane >= 32;                              // lanes 0..31 supply the even k of a pair, 32..63 the odd one
-    const int a_frag = (wm * WM + frow) * 128, b_frag = (BM + wn * WN + frow) * 128;
-
-#pragma unroll
-    for (int s = 0; s < ST - 1; ++s) request(s, s * SB);
+    for (int s = 0; s < ST - 1; ++s) static_for<U * PP>([&](auto p) { request(p, (s < KT ? s : KT - 1) * 32 * U, s * SB); });
     uint32_t cur = 0, fre = (ST - 1) * SB;
     for (int kt = 0; kt < KT; ++kt) {
         // slice kt has landed (the ST - 2 younger ones may be in flight), the stage of slice kt - 1 is read out; for all waves
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"((AP + BP) * (ST - 2)) : "memory");
-        request(kt + ST - 1, fre);
-        const unsigned char *const st = lds + cur;
-        f32x4v_t a[2][TM], b[2][TN];                         // fragments of four k
-        auto read = [&](int c, f32x4v_t (&x)[TM], f32x4v_t (&y)[TN]) {
-            const int coff = (c ^ fsw) << 4;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) x[i] = *reinterpret_cast<const f32x4v_t *>(st + a_frag + i * 4096 + coff);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) y[j] = *reinterpret_cast<const f32x4v_t *>(st + b_frag + j * 4096 + coff);
-        };
-        if (READ_AHEAD) read(0, a[0], b[0]);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int u = READ_AHEAD ? c & 1 : 0;
-            if (!READ_AHEAD) read(c, a[0], b[0]);
-            else if (c < 7) read(c + 1, a[u ^ 1], b[u ^ 1]);
-            if constexpr (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int e = 0; e < 4; e += 2)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(hi ? a[u][i][e + 1] : a[u][i][e], hi ? b[u][j][e + 1] : b[u][j][e],
-                                                                         acc[i][j], 0, 0, 0);
-            if constexpr (READ_AHEAD) __builtin_amdgcn_sched_barrier(0);
-        }
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(U * PP * (ST - 2)) : "memory");
+        const int koff = (kt + ST - 1 < KT ? kt + ST - 1 : KT - 1) * 32 * U;
+        static_for<NR>([&](auto r) { read(r, f[0], 0, cur); });
+        static_for<NG>([&](auto g_) {
+            constexpr int grp = g_;
+            static_for<NM>([&](auto m_) {
+                constexpr int m = m_, c = m / (TM * TN), i = m / TN % TM, j = (i & 1) ? TN - 1 - m % TN : m % TN;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[grp & 1].a[c][i], f[grp & 1].b[c][j], acc[i][j], 0, 0, 0);
+                if constexpr (grp + 1 < NG && m < NR) read(m_, f[1 - (grp & 1)], grp + 1, cur);
+                constexpr int q = grp * NM + m;               // the requests: one behind every MPR-th instruction
+                constexpr int MPR = NG * NM / (U * PP);
+                if constexpr (q % MPR == MPR / 2) request(std::integral_constant<int, q / MPR>{}, koff, fre);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
         fre = cur;
         cur = cur + SB == ST * SB ? 0 : cur + SB;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no LDS-direct load outlives its workgroup
-    const int col0 = n0 + wn * WN + frow;
+    const int col0 = n0 + wn * WN + r16;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        if (col0 + 32 * j >= N) continue;                    // (N is even where columns come in pairs)
-        const typename Epi::Col cj = epi.column(col0 + 32 * j);
+        if (col0 + 16 * j >= N) continue;                    // (N is even where columns come in pairs)
+        const typename Epi::Col cj = epi.column(col0 + 16 * j);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * WM + i * 32 + 8 * (r >> 2) + (r & 3) + (hi ? 4 : 0);
+            for (int r = 0; r < 4; ++r) {
+                const int64_t row = m0 + wm * WM + i * 16 + 4 * g + r;
                 if (row < M) f32_put(epi, row, cj, epi.early(row, cj), acc[i][j][r]);
             }
     }
@@ -372,11 +366,11 @@ k_gemm_f32small(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int
         if (row0 + r < M) f32_put(epi, row0 + r, c, early[r], acc[r]);
 }
 
-template <int BM, int BN, int WM, int WN, int ST, bool READ_AHEAD, class Epi>
+template <int BM, int BN, int WM, int WN, int ST, int U, int CG, class Epi>
 static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, const Epi &epi, int64_t M, int N, int K, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)ST * (BM + BN) * 128;
-    auto kern = k_gemm_f32mfma<BM, BN, WM, WN, ST, READ_AHEAD, Epi>;
+    constexpr size_t lds = (size_t)ST * U * (BM + BN) * 128;
+    auto kern = k_gemm_f32mfma<BM, BN, WM, WN, ST, U, CG, Epi>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -402,8 +396,10 @@ static bool launch_f32_product(const float *A, int64_t lda, const FMap &map, con
     auto rounds = [&](int b) { return (double)(((M + b - 1) / b * ((N + b - 1) / b) + cus - 1) / cus); };
     if ((M + 31) / 32 * ((N + 31) / 32) > (1ll << 30)) return false;
     const double c32 = 12 + 10.5 * rounds(32), c64 = 21 + 36 * rounds(64), c128 = 15 + 134 * rounds(128);
-    if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, false>(A, lda, map, epi, M, (int)N, K, st);
-    if (c64 <= c32) return launch_f32mfma<64, 64, 32, 32, 3, true>(A, lda, map, epi, M, (int)N, K, st);
+    if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, 1, 1>(A, lda, map, epi, M, (int)N, K, st);
+    if (c64 <= c32)
+        return rounds(64) <= 2 && K % 64 == 0 ? launch_f32mfma<64, 64, 32, 32, 2, 2, 2>(A, lda, map, epi, M, (int)N, K, st)
+                                              : launch_f32mfma<64, 64, 32, 32, 3, 1, 2>(A, lda, map, epi, M, (int)N, K, st);
     const int tm = (int)((M + 31) / 32), tn = (int)((N + 31) / 32);
     hipLaunchKernelGGL(k_gemm_f32small<Epi>, dim3((tm * tn + 7) / 8 * 8), dim3(256), F32SMALL_STAGES * 64 * 128, st, A, lda, map, epi, M, (int)N, K, tm, tn);
     return true;

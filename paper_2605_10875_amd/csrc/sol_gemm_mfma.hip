@@ -13,9 +13,6 @@
 // that XCD's L2.
 #include "sol_internal.h"
 
-#include <type_traits>
-#include <utility>
-
 namespace sol {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
@@ -233,11 +230,6 @@ template <int R> __device__ __forceinline__ f32x4_t acc_read()
                  : "=v"(a), "=v"(b), "=v"(c), "=v"(d) : "n"(R), "n"(R + 1), "n"(R + 2), "n"(R + 3));
     return f32x4_t{a, b, c, d};
 }
-template <int... I, class F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F &&f)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_(std::make_integer_sequence<int, N>{}, f); }
 
 // ------------------------------------------------------------------------------------------------
 // Epilogues. A lane holds, for token 16 t + lane % 16 of its wave tile (t < TX) and g = lane / 16, the columns
