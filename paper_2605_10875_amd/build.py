@@ -1,11 +1,17 @@
 """Compile the HIP sources under csrc/ for gfx950 into paper_2605_10875_amd/libsol.so.
 
 Each source is compiled to an object file under _build/ (in parallel; an object is reused when it is
-newer than its source and every header, unless force=True), then the objects are linked."""
+newer than its source and every header, unless force=True), then the objects are linked, unless isa.py finds in their
+machine code that the compiler has used registers which a kernel takes for itself."""
 import glob
 import os
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
+
+if __package__:
+    from . import isa
+else:                              # run as a script
+    import isa
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -54,6 +60,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     jobs = max(1, min(len(todo), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
     with ThreadPoolExecutor(jobs) as ex:
         list(ex.map(lambda s: _compile(s, verbose), todo))
+    isa.check_accumulators([_obj(s) for s in sources()])
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + [_obj(s) for s in sources()]
     if verbose:
         print(" ".join(cmd), flush=True)

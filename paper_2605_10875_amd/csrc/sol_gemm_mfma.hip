@@ -205,9 +205,10 @@ template <int N> __device__ __forceinline__ void vm_wait()
 //
 // The 256 accumulator registers of a lane are a[0:255], named in the instructions' text: left to the register allocator, 64
 // groups of four that fill the file exactly are moved about between steps (0.8 PFLOP/s). The compiler must not use that
-// half of the register file in this kernel for anything else; ACC_ALL among the clobbers of every barrier keeps it from values that live
-// long, and tests/test_isa_waits.py looks for any other use in the disassembly. Wait states between the last matrix instruction and the first
-// read of its result are the kernel's own business too (acc_settle).
+// half of the register file in this kernel for anything else. SOL_ACC_ALL among the clobbers of every barrier, of acc_settle and
+// before each token of the epilogue keeps it from values that live longer than that; for the others the build looks in the machine
+// code and fails on any other use (isa.py). Wait states between the last matrix instruction and the first read of its result are
+// the kernel's own business too (acc_settle).
 // ------------------------------------------------------------------------------------------------
 #define SOL_A4(x) "a" #x "0", "a" #x "1", "a" #x "2", "a" #x "3", "a" #x "4", "a" #x "5", "a" #x "6", "a" #x "7", "a" #x "8", "a" #x "9"
 #define SOL_ACC_ALL                                                                                                             \
@@ -222,7 +223,7 @@ template <int R, bool FIRST> __device__ __forceinline__ void acc_mma(const bf16x
     else asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(x), "v"(y), "n"(R), "n"(R + 3));
 }
 // the last matrix instruction's results may be read (18 wait states at most)
-__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory", SOL_ACC_ALL); }
 template <int R> __device__ __forceinline__ f32x4_t acc_read()
 {
     float a, b, c, d;
@@ -668,7 +669,10 @@ k_gemm_mfma(const bf16_t *__restrict__ X, BMap bmap, int64_t m_first, int64_t M,
         SOL_PAIR(true, 0)
         for (int kt = 2; kt < KT; kt += 2) SOL_PAIR(false, kt)
         acc_settle();
-        tile_epilogue<8, XT>(epi, [](auto i, auto t) { return acc_read<4 * (XT * i + t)>(); }, m0 + wt * 16 * XT, M, n0 + ww * 128, lane);
+        tile_epilogue<8, XT>(epi, [](auto i, auto t) {
+            if constexpr (i == 0) asm volatile("" ::: SOL_ACC_ALL);                 // a token's piece of the epilogue
+            return acc_read<4 * (XT * i + t)>();
+        }, m0 + wt * 16 * XT, M, n0 + ww * 128, lane);
         if (!more) break;
         lin += lin_step; m0 = m0_next; n0 = n0_next;
     }
