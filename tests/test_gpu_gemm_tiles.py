@@ -93,3 +93,25 @@ def test_rotated_rows_do_not_depend_on_the_rows_in_the_call():
     assert ctx.device_status() == sol.ERR_CACHE_OVERFLOW
     for a, b, c in zip(flagged, after, whole):
         assert torch.equal(a[rest], c[rest]) and torch.equal(b, c)
+
+
+def test_rows_of_a_wide_layer_do_not_depend_on_the_call():
+    """One sequence of 100 tokens alone and with 1, 2, 3 and 15 others: the 128 x 64 and 128 x 128 tiles of the fused epilogues (gate / up
+    at 100 and 200 rows, q/k/v at 400 and 1600)."""
+    shape, T, n = synth.ModelShape(512, 32, 8, 64, 8192), 100, 16
+    g = torch.Generator(device="cuda").manual_seed(6)
+
+    def rnd(*sz):
+        return torch.randn(sz, generator=g, device="cuda").to(torch.bfloat16)
+
+    w = dict(wq=rnd(2048, 512), wk=rnd(512, 512), wv=rnd(512, 512), wo=rnd(512, 2048), w_gate=rnd(8192, 512), w_up=rnd(8192, 512),
+             w_down=rnd(512, 8192), w_in_norm=rnd(512), w_post_norm=rnd(512))
+    x, ids = rnd(n, T, 512), torch.zeros((n, T), dtype=torch.int32, device="cuda")
+    ctx = sol.Sol(shape, [synth.DENSE_ACTION], max_positions=T)
+    outs = []
+    for m in (1, 2, 3, 4, n):
+        k, v = (torch.zeros((m, 8, T, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        outs.append((ctx.layer_forward(w, x[:m].contiguous(), ids[:m].contiguous(), k, v)[0], k[0], v[0]))
+    assert ctx.device_status() == sol.OK
+    for o in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(o, outs[0]))
