@@ -868,41 +868,40 @@ static bool launch_mfma(const bf16_t *X, const BMap &bmap, int64_t M, int Nv, in
 
 constexpr int SOL_WN = 128;                                // vocabulary entries of a partial sum of the head
 
-// How the rows of a product are dealt to tiles. Per round of one workgroup on every CU, a 256 x 256 tile per CU costs
-// 1 (183 us at K = 8192); a grid of one smaller tile per CU at most costs, relative to that (what a round takes hardly depends on how
-// many CUs it fills):
-//   64 x 64: 0.14   128 x 64: 0.24   128 x 128: 0.36   128 x 256: 0.56
-// (25.5, 43, 66 and 102 us: down projection of the 1B shape, 512, 1024, 2048 and 4096 rows.)
-// The q/k/v map with heads of 128 has 64 x 128 tiles in place of both 64-column ones, and goes by the same costs.
-// So a call takes the smallest tile of which every CU gets at most one; with more rows than that, whole rounds of
-// 256 x 256 tiles first and the smaller tile for the rest where that ends sooner than a last round that is nearly
-// empty. The tile does not show in the results.
+// How the rows of a product are dealt to tiles. A grid of at most one smaller tile per CU takes, in rounds of one 256 x 256 tile on every
+// CU (183 us at K = 8192; what a grid takes hardly depends on how many CUs it fills): 64 x 64 0.14, 128 x 64 0.22, 128 x 128 0.35,
+// 128 x 256 0.56 (25.6, 40, 64 and 102 us: down projection of the 1B shape, 512, 1024, 2048 and 4096 rows). So a call takes the smallest
+// tile of which every CU gets at most one; with more rows than that, whole rounds of 256 x 256 tiles (or whole tile rows) first and the
+// smaller tile for the rest, where that ends sooner than a last round that is nearly empty. Any smaller tile ends sooner than a round and
+// later than none, and rows that fit one tile take the smallest that they fit: no more than that is asked here (REST: with costs of 0.1 to
+// 0.7 in its place, one for each tile, every plan of 1 to 20000 rows and 256 to 32768 columns stays the same). The q/k/v map with
+// heads of 128 has 64 x 128 tiles in place of both 64-column ones (one per CU as well). The tile does not show in the results.
 struct GemmPlan {
     int64_t big;                 // rows [0, big) in 256 x 256 tiles (all rows, or a multiple of 256)
     int small;                   // the others: 0 = 64 x 64, 1 = 128 x 64, 2 = 128 x 128, 3 = 128 x 256
 };
-static double small_tile_cost(int64_t rows, int N, int cus, int &cfg)
+// the smallest tile of which every CU gets at most one, -1 if there is none
+static int small_tile(int64_t rows, int N, int cus)
 {
     static const int bm[4] = {64, 128, 128, 128}, bn[4] = {64, 64, 128, 256};
-    static const double cost[4] = {0.14, 0.24, 0.36, 0.56};
-    for (cfg = 0; cfg < 4; ++cfg)
-        if ((rows + bm[cfg] - 1) / bm[cfg] * (N / bn[cfg]) <= cus) return cost[cfg];
-    return 1e9;
+    for (int cfg = 0; cfg < 4; ++cfg)
+        if ((rows + bm[cfg] - 1) / bm[cfg] * (N / bn[cfg]) <= cus) return cfg;
+    return -1;
 }
 static GemmPlan plan_gemm(int64_t M, int N)
 {
     const int cus = device_cus() > 0 ? device_cus() : 256;
     const int64_t tn = N / 256, whole = M / 256;           // tile columns, whole tile rows
-    const double launch = 0.05;                            // one more kernel
+    const double REST = 0.5;                               // rounds
     GemmPlan best{M, 0};
     double best_cost = (double)(((M + 255) / 256 * tn + cus - 1) / cus);
     const int64_t rounds = whole * tn / cus;               // whole rounds of whole tiles
     const int64_t cand[3] = {0, rounds > 0 ? rounds * cus / tn : 0, whole};
     for (int64_t r : cand) {
         if (r * 256 >= M) continue;
-        int cfg;
-        const double c = (double)((r * tn + cus - 1) / cus) + small_tile_cost(M - r * 256, N, cus, cfg) + (r > 0 ? launch : 0.0);
-        if (c < best_cost) { best_cost = c; best = GemmPlan{r * 256, cfg}; }
+        const int cfg = small_tile(M - r * 256, N, cus);
+        const double c = (double)((r * tn + cus - 1) / cus) + REST;
+        if (cfg >= 0 && c < best_cost) { best_cost = c; best = GemmPlan{r * 256, cfg}; }
     }
     return best;
 }
