@@ -201,6 +201,8 @@ k_gemm_f32mfma(const float *__restrict__ A, int64_t lda, FMap map, Epi epi, int6
     constexpr int NWN = BN / WN, TM = WM / 16, TN = WN / 16, AP = BM / 32, BP = BN / 32;
     constexpr int PP = AP + BP, NG = 8 * U / CG, NM = CG * TM * TN, NR = CG * (TM + TN);   // groups of CG * 4 k, their matrix instructions and reads
     constexpr uint32_t LB = (BM + BN) * 128, SB = U * LB;     // a slice: rows of 32 floats, 16-byte chunks XOR-swizzled; a stage: U slices
+    static_assert(8 * U % CG == 0 && NR <= NM && NG * NM % (U * PP) == 0, "whole groups; a group's instructions cover the next one's reads, all of them the requests");
+    static_assert(ST >= 2 && U * PP * (ST - 2) < 64 && ST * SB <= 163840, "vmcnt counts the loads in flight; the LDS holds them");
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
