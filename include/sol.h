@@ -309,6 +309,12 @@ int sol_profile_read(sol_ctx *ctx, void *stream, int max_stages, const char **na
  * SOL_ERR_WORKSPACE (scratch too small) or SOL_ERR_HIP. */
 int sol_measure_peaks(void *scratch, size_t scratch_bytes, int reps, float *mfma_tflops_out, float *copy_gbs_out,
                       float *read_gbs_out, void *stream);
+/* The rate (TFLOP/s) of register-only loops of bf16 matrix instructions over a 128 x 128 tile per wave, one wave per SIMD, into
+ * tflops_out[4]: 32x32x16 on ones and on normally distributed operands, 16x16x32 on ones and on normally distributed operands. The last
+ * is the instruction and the data of the large bf16 products: what the chip's power leaves of the published peak. scratch: device
+ * memory the caller owns, 1 MiB is enough. `reps` launches of each are timed with events on `stream`; the call synchronises. Status as
+ * sol_measure_peaks. */
+int sol_measure_mfma(void *scratch, size_t scratch_bytes, int reps, float *tflops_out, void *stream);
 
 /* ---- unit hooks: the selection / quantisation device code on caller-supplied fp32 data ----
  * All pointers device; results are exact integer decisions and must match the definitions

@@ -1,5 +1,5 @@
-// Two microbenchmarks that measure what this GPU actually reaches on the two rooflines the path is priced against:
-// a register-only bf16 MFMA loop (no memory traffic at all) and a plain device-to-device copy. The benchmark prints
+// Microbenchmarks that measure what this GPU actually reaches on the two rooflines the path is priced against:
+// register-only bf16 MFMA loops (no memory traffic at all) and a plain device-to-device copy. The benchmark prints
 // them beside the published peaks; nothing on the product path calls them.
 #include "../../include/sol.h"
 
@@ -10,6 +10,7 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // Every wave issues `iters` rounds of eight independent 32x32x16 bf16 MFMAs on registers (eight accumulators, so a
@@ -34,6 +35,71 @@ __global__ __launch_bounds__(256) void k_peak_mfma(float *out, int iters)
     for (int j = 0; j < 8; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) s += acc[j][r];
+    out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+
+// 16 fragments of 8 bf16 for every lane of a wave: normally distributed values (Box and Muller's transform of a hashed index), or ones
+__global__ __launch_bounds__(256) void k_peak_operands(uint32_t *__restrict__ out, bool normal)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;       // two bf16
+    auto hash = [](uint32_t x) { x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; return x ^ (x >> 16); };
+    const float u = ((float)(hash(2 * i) >> 8) + 0.5f) * 0x1p-24f, v = (float)(hash(2 * i + 1) >> 8) * 0x1p-24f;
+    const float r = sqrtf(-2.0f * logf(u));
+    const __bf16 a = (__bf16)(normal ? r * cosf(6.2831853f * v) : 1.0f), b = (__bf16)(normal ? r * sinf(6.2831853f * v) : 1.0f);
+    out[i] = (uint32_t)__builtin_bit_cast(uint16_t, a) | (uint32_t)__builtin_bit_cast(uint16_t, b) << 16;
+}
+// What the matrix cores reach depends on the instruction and on the data, through the power that both take: the products of a
+// 128 x 128 wave tile from operands that are loaded once (256 accumulator registers, one wave per SIMD, as in the large GEMM).
+__global__ __launch_bounds__(256, 1) void k_peak_data32(const bf16x8_t *__restrict__ in, float *__restrict__ out, int iters)
+{
+    const int lane = threadIdx.x & 63;
+    bf16x8_t a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { a[i] = in[i * 64 + lane]; b[i] = in[(8 + i) * 64 + lane]; }
+    f32x16_t acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int t = 0; t < iters; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s += acc[i][j][r];
+    out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+__global__ __launch_bounds__(256, 1) void k_peak_data16(const bf16x8_t *__restrict__ in, float *__restrict__ out, int iters)
+{
+    const int lane = threadIdx.x & 63;
+    bf16x8_t a[8], b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { a[i] = in[i * 64 + lane]; b[i] = in[(8 + i) * 64 + lane]; }
+    f32x4_t acc[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < iters; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += acc[i][j][r];
     out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
@@ -105,6 +171,42 @@ extern "C" int sol_measure_peaks(void *scratch, size_t scratch_bytes, int reps, 
     (void)hipEventRecord(e1, st);
     if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = SOL_ERR_HIP;
     *read_gbs_out = rc ? 0.f : (float)((double)rbytes * reps / (ms * 1e-3) / 1e9);
+    if (hipGetLastError() != hipSuccess) rc = SOL_ERR_HIP;
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    return rc;
+}
+
+extern "C" int sol_measure_mfma(void *scratch, size_t scratch_bytes, int reps, float *tflops_out, void *stream)
+{
+    if (!scratch || !tflops_out || reps <= 0) return SOL_ERR_INVALID_ARG;
+    hipStream_t st = (hipStream_t)stream;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        return SOL_ERR_HIP;
+    constexpr size_t OPERANDS = 16 * 64 * 16;                // bytes
+    if (scratch_bytes < OPERANDS + (size_t)cus * 256 * sizeof(float)) return SOL_ERR_WORKSPACE;
+    hipEvent_t e0, e1;
+    if (hipEventCreate(&e0) != hipSuccess) return SOL_ERR_HIP;
+    if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return SOL_ERR_HIP; }
+    const bf16x8_t *in = (const bf16x8_t *)scratch;
+    float *out = (float *)((char *)scratch + OPERANDS);
+    int rc = SOL_OK;
+    for (int v = 0; v < 4 && rc == SOL_OK; ++v) {            // 32x32x16 on ones, on normal data; 16x16x32 likewise
+        const bool wide = v < 2;
+        const int iters = wide ? 8192 : 4096;                // 1.8 to 2.5 ms per launch
+        auto *const kern = wide ? k_peak_data32 : k_peak_data16;
+        hipLaunchKernelGGL(k_peak_operands, dim3((unsigned)(OPERANDS / 4 / 256)), dim3(256), 0, st, (uint32_t *)scratch, (v & 1) != 0);
+        hipLaunchKernelGGL(kern, dim3(cus), dim3(256), 0, st, in, out, iters);                   // warm-up
+        (void)hipEventRecord(e0, st);
+        for (int r = 0; r < reps; ++r) hipLaunchKernelGGL(kern, dim3(cus), dim3(256), 0, st, in, out, iters);
+        (void)hipEventRecord(e1, st);
+        float ms = 0.f;
+        if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) rc = SOL_ERR_HIP;
+        const double flops = (double)reps * cus * 4.0 * iters * (wide ? 16.0 * 32 * 32 * 16 * 2 : 64.0 * 16 * 16 * 32 * 2);
+        tflops_out[v] = rc ? 0.f : (float)(flops / (ms * 1e-3) / 1e12);
+    }
     if (hipGetLastError() != hipSuccess) rc = SOL_ERR_HIP;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -28,7 +28,7 @@ EXPORTS = ("sol_validate_config", "sol_create", "sol_destroy", "sol_last_error",
            "sol_test_topk_select", "sol_test_prune_mask", "sol_test_prune_quant", "sol_test_quant_codes",
            "sol_test_gemm", "sol_test_attn_threshold", "sol_test_attention_stage", "sol_test_mlp_stage",
            "sol_test_episode_copies_workspace_bytes", "sol_test_episode_loglik_copies",
-           "sol_static_scratch_bytes", "sol_decode_step_static", "sol_measure_peaks")
+           "sol_static_scratch_bytes", "sol_decode_step_static", "sol_measure_peaks", "sol_measure_mfma")
 
 
 class RewardCfg(C.Structure):
@@ -463,6 +463,18 @@ def measure_peaks(scratch_bytes=2 << 30, reps=10, stream=None):
     if rc:
         raise SolError(rc, "sol_measure_peaks")
     return float(tf.value), float(gb.value), float(rd.value)
+
+
+def measure_mfma(reps=40, stream=None):
+    """TFLOP/s of register-only loops of bf16 matrix instructions: 32x32x16 on ones and on normal operands, 16x16x32 likewise."""
+    buf = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    out = (C.c_float * 4)()
+    L = lib()
+    L.sol_measure_mfma.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.POINTER(C.c_float), C.c_void_p]
+    rc = L.sol_measure_mfma(_ptr(buf), buf.numel(), reps, out, _stream(stream))
+    if rc:
+        raise SolError(rc, "sol_measure_mfma")
+    return tuple(float(v) for v in out)
 
 
 def topk_select(scores, n_valid, k, stream=None):

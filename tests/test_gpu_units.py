@@ -225,3 +225,12 @@ def test_empty_inputs_are_no_ops():
     e = torch.zeros(0, dtype=torch.int32, device="cuda")
     assert sol.topk_select(z, e, e).shape == (0, 8)
     assert sol.prune_mask(z, e).shape == (0, 8)
+
+
+def test_rates_of_the_matrix_instructions():
+    """Four rates below the published dense peak; operands that are no constants cost power and never gain."""
+    ones32, normal32, ones16, normal16 = sol.measure_mfma(reps=10)
+    assert all(0.0 < r <= 2600.0 for r in (ones32, normal32, ones16, normal16))
+    assert normal32 <= 1.05 * ones32 and normal16 <= 1.05 * ones16
+    L = sol.lib()
+    assert L.sol_measure_mfma(None, 1 << 20, 1, None, None) == sol.ERR_INVALID_ARG
