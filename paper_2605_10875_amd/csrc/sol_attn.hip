@@ -1385,11 +1385,15 @@ k_attn_pv(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const bf1
 // The search for a decode row's threshold: wave_search_rows for one row whose columns several waves hold, which count between
 // barriers and all run this on the same numbers. Done when exactly b of the n keys are >= thr, or, where ties leave no such
 // pivot, when the bracket has closed on the b-th largest (exact = false). Invariant: count(key >= lo) >= b, count(key >= hi + 1) < b.
-// m1, m2: mean and mean square of a sample of the row. On normal rows 4.5 rounds where regula falsi on the counts from the row's extremes
-// takes 6.4; but the last of them close in on one key, and the slowest of a launch's 32 rows takes 11. So once the bracket holds
-// FEW keys they are gathered in the LDS and ranked there: 2.6 rounds, 4 for the slowest of 32. (Ranked by every wave for itself
-// the 64 comparisons cost as much as the rounds they save: 16 waves share four SIMDs.) k_dec_select at 4096 keys, one sequence:
-// 12.8 -> 8.6 us; a step of 64 sequences of 8192 keys, 1B shape: 4585 -> 4380 us, of 8 of 2048 1873 -> 1757, of one of 4096 1275 -> 1205.
+// m1, m2: mean and mean square of a sample of the row. The first pivot is the normal quantile (Abramowitz and Stegun 26.2.23) of the kept
+// share. On normal rows 4.5 rounds where regula falsi on the counts from the row's extremes takes 6.4; but the last of them close
+// in on one key, and the slowest of a launch's 32 rows takes 11. So once the bracket holds FEW keys they are gathered in the LDS
+// and ranked there: 2.6 rounds, 4 for the slowest of 32. (Ranked by every wave for itself the 64 comparisons cost as much as
+// the rounds they save: 16 waves share four SIMDs.) Skewed rows and rows with outliers take 4 to 8 where that regula falsi took 8 to 21,
+// clusters and magnitudes over a hundred powers of two 15 to 29.
+// us per layer of a replayed 1B step, that search -> this one, at kept shares 1/16, 1/8, 1/4, 1/2 and 1: one sequence of 4096 keys 68.5,
+// 67.1, 66.4, 66.2, 57.3 -> 61.3, 61.6, 61.7, 61.8, 57.5; 8 of 2048 keys 101, 101, 100, 99, 88 -> 93, 93, 94, 94, 88; 64 of 8192 keys 278,
+// 277, 280, 290, 269 -> 256, 258, 266, 279, 268. k_dec_select alone, one sequence of 4096 keys: 12.8 -> 8.6.
 struct PivotSearch {
     static constexpr int FEW = 64;
     uint32_t lo, hi, thr = 0u;
@@ -1683,8 +1687,8 @@ k_attn_decode(const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc, const
                 key[4 * j + e] = kv;
                 kmax = kv > kmax ? kv : kmax;
                 kmin = (valid && kv < kmin) ? kv : kmin;
-                    if (e == 0 && valid) { s1 += v[0]; s2 = __builtin_fmaf(v[0], v[0], s2); }
-                }
+                if (e == 0 && valid) { s1 += v[0]; s2 = __builtin_fmaf(v[0], v[0], s2); }
+            }
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) key[4 * j + e] = 0u;
@@ -2135,13 +2139,13 @@ k_dec_values(const float *__restrict__ scores, const DecSel *__restrict__ sel, c
 // Scratch of the split path for B sequences: scores, selection rows and partial outputs. 0: the shape, or B, is not its.
 // It pays while few items leave most CUs of the one-workgroup-per-item kernel idle and their rows are long enough for that
 // kernel's latency to show. What a row holds is not known here, only what its cache can hold: rows of few keys pay for the two
-// launches more and the wider fold. Per layer of a graph-replayed step, caches of 8192 positions (us, one workgroup per item ->
-// split, at 300 / 1000 / 2000 / 8000 keys; since the norms went into the maps one sequence takes 3 to 4 less on both sides): 1B
-// shape, B = 1: 73 -> 75, 80 -> 76, 92 -> 77, 131 -> 87; B = 4: 95 -> 100,
-// 102 -> 102, 116 -> 106, 154 -> 119; 8B shape, B = 1: 126 -> 129, 136 -> 131, 152 -> 132, 227 -> 144; B = 4: 153 -> 163,
-// 166 -> 167, 184 -> 170, 259 -> 190. Not taken: 1B, B = 8: 97 -> 108, 105 -> 110, 117 -> 114, 157 -> 133; B = 12: 100 -> 118,
-// 107 -> 120, 120 -> 127, 159 -> 156; 8B, B = 8: 156 -> 174, 168 -> 179, 190 -> 188, 263 -> 226. So the line is drawn at 32
-// items, and at twice the keys at which both take the same time (500, 700 and 900 keys at 8, 16 and 32 items). Rows of more
+// launches more and the wider fold. Per layer of a graph-replayed step, caches of 8184 positions (us, one workgroup per item ->
+// split, at 300 / 1000 / 2000 / 8000 keys): 1B shape, B = 1: 63 -> 64, 69 -> 65, 79 -> 66, 115 -> 75; B = 4: 88 -> 93, 94 -> 94, 105 -> 95,
+// 142 -> 107; 8B shape, B = 1: 123 -> 128, 128 -> 124, 145 -> 126, 220 -> 139; B = 4: 157 -> 166, 162 -> 165, 179 -> 169, 256 -> 188. Not
+// taken: 1B, B = 8: 92 -> 101, 97 -> 102, 107 -> 105, 145 -> 124; B = 12: 94 -> 109, 98 -> 110, 109 -> 115, 149 -> 142; 8B, B = 8: 156 ->
+// 174, 162 -> 173, 180 -> 180, 258 -> 218. Both take the same time at 500 and 1000 keys at 8 and 32 items of the 1B shape, at 700 and 1200
+// of the 8B shape: so the line is drawn at 32 items, and at about twice those keys. (At 64 items they meet at 2000 keys and the split loses
+// a tenth on short rows.) Rows of more
 // than 4096 outputs are outside k_fold_fq_rows, and the general quantiser reads the sixteen parts with one workgroup: 64 query
 // heads of 128, 2000 keys, 251 -> 332. (A split by ranges of 256 keys, its partial outputs divided by the denominator, took 2 to
 // 9 us less per layer, but then a step's rounding changed with B.)

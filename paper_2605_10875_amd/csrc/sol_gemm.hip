@@ -61,13 +61,12 @@ k_gemm_generic(const TA *__restrict__ A, int64_t lda, const TW *__restrict__ W, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 operands on the fp32 matrix instructions. Both (32x32x2 and 16x16x4) are fmaf chains over their k in ascending
-// order (subnormals included), so with k walked in order every output is the fmaf chain of k_gemm_generic, bit for bit,
-// at twice the vector pipes' rate and without their LDS reads per product. Bound: the fp32 matrix rate (256 flops per
-// clock and CU) for large products, 125 TFLOP/s reached of 157; the chain over k for small ones: 64 clocks per 2 k in a
-// 32x32 tile, 32 clocks per 4 k in a 16x16 tile.
-// Times with k_gemm_generic -> here: 1018 x 16384 x 2048 2470 -> 549 us (551 now with SiLU * up), 1018 x 2048 x 8192 1310 -> 326 (296 now with the residual), 512 x 256 x 256
-// 30 -> 4.8, 512 x 256 x 1024 108 -> 12.
+// fp32 operands on the fp32 matrix instructions. v_mfma_f32_16x16x4_f32 is an fmaf chain over its k in ascending order
+// (subnormals included), so with k walked in order every output is the fmaf chain of k_gemm_generic, bit for bit,
+// at twice the vector pipes' rate and without their LDS reads per product. Bound: the fp32 matrix rate (155 TFLOP/s measured, 124
+// reached) for large products; the chain over k, 32 clocks per 4 k, for small ones. k_gemm_generic -> here, us: 1018 x 16384 x 2048
+// 2470 -> 551 (with SiLU * up at its end), 1018 x 2048 x 8192 1310 -> 296 (with the residual), 512 x 256 x 256 30 -> 4.8, 512 x 256 x 1024
+// 108 -> 12.
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 

@@ -18,7 +18,6 @@ namespace sol {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));   // native 16-byte vector (stays in registers)
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;               // K step (bf16 elements); one LDS row = 128 bytes = 8 chunks of 16 B
@@ -164,16 +163,11 @@ k_nll_finish_cols(const float2 *__restrict__ part, const float *__restrict__ tgt
 }
 
 // 16 bytes per lane from global memory (wave-uniform base + 32-bit byte offset per lane) straight into LDS: lane l's
-// piece lands at lds_addr + 16 * l (M0 holds the wave's LDS byte address; one wait state between writing M0 and the
-// load). Written as inline assembly because the compiler, which sees an LDS write it cannot place, would wait for
-// the load before the next LDS read of any stage. The kernel therefore owns the waits: vm_wait<0>() before the
-// barrier that publishes a stage, and before a workgroup ends. The kernel must have no static LDS (the dynamic
-// segment then starts at LDS address 0).
-__device__ __forceinline__ void dtl16(const bf16_t *base, uint32_t byte_off, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-// the same with the LDS address as a base and a constant: nothing for the compiler to keep 32 sums of in scalar registers
+// piece lands at lds_base + C + 16 * l (M0 holds the wave's LDS byte address, a base and a constant so that the compiler keeps no 32 sums
+// of them in scalar registers; one wait state between writing M0 and the load). Written as inline assembly because the
+// compiler, which sees an LDS write it cannot place, would wait for the load before the next LDS read of any stage. The kernel
+// therefore owns the waits: before the barrier that publishes a stage, and before a workgroup ends. The kernel must have
+// no static LDS (the dynamic segment then starts at LDS address 0).
 template <int C> __device__ __forceinline__ void dtl16c(const bf16_t *base, uint32_t byte_off, uint32_t lds_base)
 {
     asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_base), "n"(C) : "memory", "m0", "scc");
@@ -190,8 +184,9 @@ template <int N> __device__ __forceinline__ void vm_wait()
 // (its sums are those of two 32x32x16 instructions bit for bit, so the tile does not show in the results). The weights are the
 // instruction's first operand: a lane's four results are then consecutive columns of one token's output row.
 //
-// Bound: the power the chip grants its matrix cores. With normally distributed operands a loop of nothing but 32x32x16
-// instructions reaches 1.78 PFLOP/s (2.46 on zeros), of 16x16x32 2.06: they move fewer accumulator bits per product.
+// Bound: for the most part the power the chip grants its matrix cores. With normally distributed operands a loop of nothing but
+// 32x32x16 instructions reaches 1.78 PFLOP/s (2.4 on ones), of 16x16x32 2.05: they move fewer accumulator bits per product
+// (sol_measure_mfma measures all four). This kernel without an epilogue reaches 1.67 of the 2.05.
 // A step (64 of K) goes through the four quadrants of the wave tile: (top, left), (top, right), (bottom, right), (bottom,
 // left), each 32 instructions, and reads one half of an operand from the LDS per quadrant, for the next one. So every half
 // of a slice is read out during ONE quadrant, and the LDS-direct requests of slice kt + 2 go into it from the barrier that
@@ -239,7 +234,7 @@ template <int R> __device__ __forceinline__ f32x4_t acc_read()
 //   place(row[TX], p)              what is known of the lane's tokens before anything else
 //   fetch(row, p, col0, g, aux)    reads what a token's piece needs, AHEAD tokens ahead of
 //   put(row, ok, p, col0, g, v, aux)   which combines and stores it (ok: the token exists)
-// The pieces lie in the caller's tensors, which are aligned to their elements only: AnyVec.
+// The pieces lie in the caller's tensors, which are aligned to their elements only: AnyU4, AnyF4.
 // ------------------------------------------------------------------------------------------------
 typedef u32x4_t AnyU4 __attribute__((aligned(2)));
 typedef f32x4_t AnyF4 __attribute__((aligned(4)));
@@ -1048,8 +1043,8 @@ bool launch_gemm_nll(void *hf, const void *lm_head, const int32_t *targets, int 
 {
     if (M <= 0) return true;
     // A decode step's few tokens take tiles of 32 or 64 tokens: with 256 columns of padding the matrix cores need as long as HBM. The
-    // partial results are those of the large tiles bit for bit. 128256 entries of 2048, 1 to 32 tokens: 135 us (two workgroups per CU
-    // with half of the stages: 137), 100 tokens (256 columns): 148.
+    // partial results are those of the large tiles bit for bit. 128256 entries of 2048, all four launches: 1 to 64 tokens 134 us (120
+    // of it the product, 4.4 TB/s; two workgroups per CU with half of the stages: 137), 100 tokens (256 columns) 147.
     const int64_t Mp = M <= 32 ? 32 : M <= 64 ? 64 : nll_pad_rows(M);
     if (V % 256 || K % (2 * BK) || K < 2 * BK || Mp >= (1ll << 31)) return false;
     const int n_wt = V / SOL_WN;
