@@ -386,15 +386,17 @@ static bool launch_f32mfma(const float *A, int64_t lda, const FMap &map, const E
 // The tile is the one that ends soonest by what was measured at K = 2048 and 8192 (r: rounds of one tile on every CU; us at K = 2048, 32 to 3000
 // rows of 2048, 3072 and 16384 columns):
 //   32 x 32: 10 + 11.6 r        21 at one round, 33, 43, 54, 68, 80, 91, 103, 118; 195 at 16
-//   64 x 64: 47 (57); 2 + 35 r  46, 72, 106, 138, 178, 208, 249, 282, 384 at 11. Two workgroups of two slices per stage share a CU, or three of
+//   64 x 64: 47; 2 + 35 r       46, 72, 106, 138, 178, 208, 249, 282, 384 at 11. Two workgroups of two slices per stage share a CU, or three of
 //                               one: 72 against 75 at two rounds, 138 - 147 at four; 48 - 46 at one (202 - 175 at K = 8192), 120 - 106 at
 //                               three, level from five on. So two slices at two and four rounds, where K is whole pairs of slices.
-//                               Of a short K one round is worth four of 32 x 32 (57): alone 9.1 - 9.9 us at K = 256, but with SiLU * up at its
-//                               end 12.9 either way, and the quantiser after it 4.6 - 3.7 (4 x 128 tokens of a one-layer model)
+//                               One and two rounds are worth 10 less where K is short or columns come in pairs: alone 9.1 us against 9.9 of
+//                               four rounds of 32 x 32 at K = 256, but with SiLU * up at its end 12.9 either way, and the quantiser after it
+//                               4.6 - 3.7 (4 x 128 tokens of a one-layer model); q/k/v of 300 rows alone 48 - 55, with the rotation
+//                               56.8 - 55.2; gate / up of 70 rows alone 70 - 79, with SiLU * up 78 - 80 and the layer level
 //   128 x 128: 147; 126 r       for an even r, as long for the odd one before it (two share a CU): 250 at two, 498 at three, 508 at four
 // So: 32 x 32 for up to three rounds of it (and five: 68 against 72), 64 x 64 up to four of its own and wherever its share of the last
-// round is smaller, 128 x 128 where it fills pairs of rounds: within 3 % of the best of the four at 146 sizes of K = 64 to 14336, one round
-// of a short K aside. 1018 rows of the 1B shape: o and down two rounds of 64 x 64, q/k/v three, gate / up four of 128 x 128. Before this
+// round is smaller, 128 x 128 where it fills pairs of rounds: within 3 % of the best of the four at 146 sizes of K = 64 to 14336, one and
+// two rounds of the latter aside. 1018 rows of the 1B shape: o and down two rounds of 64 x 64, q/k/v three, gate / up four of 128 x 128. Before this
 // was measured for the present kernels 64 x 64 was priced 21 + 36 r: 800 rows by 2048 columns took 90 us where two rounds take 72, 1400
 // rows 144 where three take 107, 700 rows by 16384 columns 498 (128 x 128) where eleven take 384.
 template <class Epi>
@@ -409,11 +411,12 @@ static bool launch_f32_product(const float *A, int64_t lda, const FMap &map, con
     auto rounds = [&](int b) { return ((M + b - 1) / b * ((N + b - 1) / b) + cus - 1) / cus; };
     if ((M + 31) / 32 * ((N + 31) / 32) > (1ll << 30)) return false;
     const int64_t r64 = rounds(64), r128 = rounds(128);
-    const double c32 = 10 + 11.6 * (double)rounds(32), c64 = r64 == 1 ? (K < 1024 ? 57 : 47) : 2 + 35 * (double)r64, c128 = r128 == 1 ? 147 : 126 * (double)(r128 + r128 % 2);
+    const double c32 = 10 + 11.6 * (double)rounds(32), c128 = r128 == 1 ? 147 : 126 * (double)(r128 + r128 % 2);
+    const double c64 = (r64 == 1 ? 47 : 2 + 35 * (double)r64) + (r64 <= 2 && (Epi::pairs || K < 1024) ? 10 : 0);
     if (c128 <= c64 && c128 <= c32) return launch_f32mfma<128, 128, 64, 64, 2, 1, 1>(A, lda, map, epi, M, (int)N, K, st);
     if (c64 <= c32)
         return (r64 == 2 || r64 == 4) && K % 64 == 0 ? launch_f32mfma<64, 64, 32, 32, 2, 2, 2>(A, lda, map, epi, M, (int)N, K, st)
-                                                : launch_f32mfma<64, 64, 32, 32, 3, 1, 2>(A, lda, map, epi, M, (int)N, K, st);
+                                                     : launch_f32mfma<64, 64, 32, 32, 3, 1, 2>(A, lda, map, epi, M, (int)N, K, st);
     const int tm = (int)((M + 31) / 32), tn = (int)((N + 31) / 32);
     hipLaunchKernelGGL(k_gemm_f32small<Epi>, dim3((tm * tn + 7) / 8 * 8), dim3(256), F32SMALL_STAGES * 64 * 128, st, A, lda, map, epi, M, (int)N, K, tm, tn);
     return true;

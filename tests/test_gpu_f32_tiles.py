@@ -40,10 +40,12 @@ def test_rows_do_not_depend_on_the_call(shape):
     assert bool(((outs[0][2].double() - ref).abs() <= bound).all())
 
 
-def _tile(rows, cols, k, cus):
-    """The library's rule: the tile that a product takes, "64/2" and "64/1" being the 64 x 64 one with two slices of K per barrier and one."""
+def _tile(rows, cols, k, cus, pairs=False):
+    """The library's rule: the tile that a product takes, "64/2" and "64/1" being the 64 x 64 one with two slices of K per barrier
+    and one; pairs: rotary or SiLU * up at its end."""
     r32, r64, r128 = (-(-(-(-rows // b) * -(-cols // b)) // cus) for b in (32, 64, 128))
-    c32, c64, c128 = 10 + 11.6 * r32, (57 if k < 1024 else 47) if r64 == 1 else 2 + 35 * r64, 147 if r128 == 1 else 126 * (r128 + r128 % 2)
+    c32, c64, c128 = 10 + 11.6 * r32, 47 if r64 == 1 else 2 + 35 * r64, 147 if r128 == 1 else 126 * (r128 + r128 % 2)
+    c64 += 10 if r64 <= 2 and (pairs or k < 1024) else 0
     if c128 <= c64 and c128 <= c32:
         return "128"
     if c64 > c32:
@@ -61,10 +63,10 @@ def _tile(rows, cols, k, cus):
 def test_every_tile_gives_the_small_calls_bits(shape, T, tiles):
     n, few, cus = 2, 30, torch.cuda.get_device_properties(0).multi_processor_count
     d, nq, nkv, ff = shape.d_model, shape.n_q_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim, shape.d_ff
-    maps = ((nq + 2 * nkv, d), (2 * ff, d), (d, nq), (d, ff))
+    maps = ((nq + 2 * nkv, d, cus, True), (2 * ff, d, cus, True), (d, nq, cus), (d, ff, cus))
     if cus == 256:                                    # (other dies have other rounds)
-        assert tuple(_tile(n * T, *m, cus) for m in maps) == tiles
-        assert all(_tile(few, *m, cus) == "32" for m in maps)
+        assert tuple(_tile(n * T, *m) for m in maps) == tiles
+        assert all(_tile(few, *m) == "32" for m in maps)
     weights = synth.layer_weights(shape, 31, std=0.05)
     w = {k: torch.from_numpy(np.ascontiguousarray(a)).cuda() for k, a in weights.items()}
     g = torch.Generator(device="cuda").manual_seed(8)
