@@ -686,12 +686,13 @@ k_gemm_mfma(const bf16_t *__restrict__ X, BMap bmap, int64_t m_first, int64_t M,
 // Bound: a CU's rate of L2 misses. 64 x 64 tiles take 0.18 us per slice of 16 KB (90 GB/s), 128 x 64 0.3, 128 x 128 0.5,
 // whatever U and G are from (2, 4) to (1, 10); from the L2 alone the loads would reach 130 GB/s.
 // 128 x 64 and 128 x 128 tiles have eight waves, two per SIMD, so that one's instructions cover the other's barrier and reads. Four
-// waves (32 x 64, 64 x 64) -> eight, us: down of the 1B shape, 600 rows 36.1 -> 34.8, 1300 57.1 -> 52.2; of the 8B shape, 280 rows
-// 62.5 -> 59.3, 700 111.7 -> 105.6; o 8B 700 33.0 -> 31.4; q/k/v 1B 400 rows 12.6 -> 11.8, 700 19.4 -> 17.9. With six or five
+// waves (32 x 64, 64 x 64) -> eight, us: down of the 1B shape, 600 rows 35.6 -> 34.6, 1300 56.9 -> 52.7; of the 8B shape, 260 rows
+// 62.5 -> 60.2, 700 111.8 -> 106.4; o 8B 700 32.7 -> 31.0; q/k/v 1B 400 rows 12.5 -> 11.8, 700 19.3 -> 17.8. With six or five
 // slices in flight, or groups of two: no better, or worse. Heads of 128 in 128 x 128 tiles: level, four waves there.
 // Against the kernel before this one (32x32x16 instructions, eight waves, 4-byte stores, requests past the end), us: q/k/v of the 1B
-// shape 96 rows 14.2 -> 9.0, 333 rows 16.5 -> 11.8, of the 8B shape 36.5 -> 21.6 and 41.3 -> 32.3; down 1B 25.5 -> 23.1 (140 rows) and
-// 42.6 -> 39.6 (1024), 8B 61.4 -> 59.3 (280); 1B o, 1100 to 1300 rows, the one map that is not faster: 17.5 -> 17.8.
+// shape 70 rows 14.1 -> 9.0, 400 rows 16.4 -> 11.8, of the 8B shape 36.0 -> 21.3 and 41.8 -> 32.9; down 1B 24.9 -> 22.8 (140 rows) and
+// 42.7 -> 40.4 (1024), 8B 62.9 -> 60.2 (260); 1B o at 512, 1200 and 1300 rows, the one map that is not faster: 9.2 -> 9.3, 17.9 -> 18.1,
+// 18.5 -> 18.6.
 // The sums are k_gemm_mfma's (the same instructions over k), so the tile does not show in the results.
 // ------------------------------------------------------------------------------------------------
 template <int BT, int BW, int WT, int WW, int U, int G, class Epi>
