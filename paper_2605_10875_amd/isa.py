@@ -15,8 +15,9 @@ VALU_TO_MFMA = 2       # wait states from a vector write to a matrix instruction
 
 def objdump():
     """Path of llvm-objdump, None if there is none."""
-    rocm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
-    return rocm if os.path.exists(rocm) else shutil.which("llvm-objdump")
+    roots = [r for r in (os.environ.get("ROCM_PATH"), "/opt/rocm") if r]
+    here = [os.path.join(r, "llvm", "bin", "llvm-objdump") for r in roots]
+    return next((p for p in here if os.path.exists(p)), None) or shutil.which("llvm-objdump")
 
 
 def device_code(path):
